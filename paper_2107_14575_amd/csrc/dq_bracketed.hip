@@ -85,14 +85,9 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
 
     float4 x[TILES][2];
     int32_t seg[TILES];
+    qp_load<TILES>(g, tid, n_elems, x);
 #pragma unroll
-    for (int it = 0; it < TILES; ++it) {
-        uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
-        e = e < n_elems ? e : n_elems - QP_PER_LANE; // clamped: always in bounds, result unused
-        x[it][0] = *reinterpret_cast<const float4*>(g + e);
-        x[it][1] = *reinterpret_cast<const float4*>(g + e + 4);
-        seg[it] = gseg[e >> 7];
-    }
+    for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES>(tid, it, n_elems)];
 
     const int32_t seg_first = gseg[0];
     const int32_t seg_last = gseg[(n_elems - 1) >> 7];
@@ -122,14 +117,16 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
     const bool any_whole = lds_any_whole != 0;
 
     // partial sums of squares (or maxima) of the chunk's tensors
-    int valid[TILES], local[TILES];
+    int valid[TILES], local[TILES], granule[TILES];
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
-        const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+        dq_arrange_wave_tile(x[it][0], x[it][1]);
+        const uint32_t e = qp_elem<TILES>(tid, it);
+        granule[it] = static_cast<int>(e >> 7);
         local[it] = seg[it] - seg_first;
         valid[it] = e < n_elems ? lds_valid_end[local[it]] - static_cast<int32_t>(e) : 0;
     }
-    const int n_scan = dq_chunk_granule_sums<LINF>(x, valid, local, static_cast<int>(tid), lds_gsum, lds_glocal,
+    const int n_scan = dq_chunk_granule_sums<LINF>(x, valid, local, granule, static_cast<int>(tid), lds_gsum, lds_glocal,
                                                    seg_first == seg_last, static_cast<int>(n_elems >> 7));
     __syncthreads();
     if (tid < DQ_CHUNK_GRANULES)
@@ -160,7 +157,7 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
 
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
-        const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+        const uint32_t e = qp_elem<TILES>(tid, it);
         if (e < n_elems) {
             const uint32_t quad = quad_lo0 + (e >> 2);
             // levels at the low end of the bracket: the largest any norm inside it can give
@@ -188,8 +185,8 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
                     }
                 }
             }
-            lds_sign[it * QP_THREADS + tid] = static_cast<uint8_t>(sign);
-            stage_bytes<B>(&lds_level[(it * QP_THREADS + tid) * B], level);
+            lds_sign[e >> 3] = static_cast<uint8_t>(sign);
+            stage_bytes<B>(&lds_level[(e >> 3) * B], level);
         }
     }
     __syncthreads();
@@ -253,14 +250,9 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed_v(
 
     float4 x[TILES][2];
     int32_t seg[TILES];
+    qp_load<TILES>(g, tid, n_elems, x);
 #pragma unroll
-    for (int it = 0; it < TILES; ++it) {
-        uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
-        e = e < n_elems ? e : n_elems - QP_PER_LANE;
-        x[it][0] = *reinterpret_cast<const float4*>(g + e);
-        x[it][1] = *reinterpret_cast<const float4*>(g + e + 4);
-        seg[it] = gseg[e >> 7];
-    }
+    for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES>(tid, it, n_elems)];
 
     const int32_t seg_first = gseg[0];
     const int32_t seg_last = gseg[(n_elems - 1) >> 7];
@@ -294,14 +286,16 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed_v(
     const int skip = __syncthreads_or(unusable);
     const bool any_whole = lds_any_whole != 0;
 
-    int valid[TILES], local[TILES];
+    int valid[TILES], local[TILES], granule[TILES];
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
-        const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+        dq_arrange_wave_tile(x[it][0], x[it][1]);
+        const uint32_t e = qp_elem<TILES>(tid, it);
+        granule[it] = static_cast<int>(e >> 7);
         local[it] = seg[it] - seg_first;
         valid[it] = e < n_elems ? lds_valid_end[local[it]] - static_cast<int32_t>(e) : 0;
     }
-    const int n_scan = dq_chunk_granule_sums<LINF>(x, valid, local, static_cast<int>(tid), lds_gsum, lds_glocal,
+    const int n_scan = dq_chunk_granule_sums<LINF>(x, valid, local, granule, static_cast<int>(tid), lds_gsum, lds_glocal,
                                                    seg_first == seg_last, static_cast<int>(n_elems >> 7));
     __syncthreads();
     if (tid < DQ_CHUNK_GRANULES)
@@ -332,7 +326,7 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed_v(
 
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
-        const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+        const uint32_t e = qp_elem<TILES>(tid, it);
         if (e < n_elems) {
             const float S = lds_levels[local[it]];
             const int b = lds_b[local[it]];
@@ -362,18 +356,8 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed_v(
                     }
                 }
             }
-            lds_sign[it * QP_THREADS + tid] = static_cast<uint8_t>(sign);
-            uint8_t* dst = &lds_level[lds_level_base[local[it]] + static_cast<int32_t>(e >> 3) * b];
-            switch (b) {
-            case 1: stage_bytes<1>(dst, level); break;
-            case 2: stage_bytes<2>(dst, level); break;
-            case 3: stage_bytes<3>(dst, level); break;
-            case 4: stage_bytes<4>(dst, level); break;
-            case 5: stage_bytes<5>(dst, level); break;
-            case 6: stage_bytes<6>(dst, level); break;
-            case 7: stage_bytes<7>(dst, level); break;
-            default: stage_bytes<8>(dst, level); break;
-            }
+            lds_sign[e >> 3] = static_cast<uint8_t>(sign);
+            stage_bytes_v(&lds_level[lds_level_base[local[it]] + static_cast<int32_t>(e >> 3) * b], level, b);
         }
     }
     __syncthreads();

@@ -3,8 +3,8 @@
 // that way).  Used by the norm kernel for such plans and by the quantize kernel that computes
 // the norms itself, so that the gradient is read once.
 //
-// A workgroup of 256 lanes owns the chunk; lane t holds elements [8t, 8t+8) of each of its two
-// 2048-element tiles.  Squares are summed in binary64 (exact products) in a fixed order: the
+// A workgroup of 256 lanes owns the chunk; a lane holds eight consecutive elements of each of its
+// wavefront's two 512-element tiles.  Squares are summed in binary64 (exact products) in a fixed order: the
 // lane's eight, the 16 lanes of a 128-element granule by four rotate-and-add steps inside the
 // 16-lane DPP row (the granule's first lane keeps the result), then the granules of a tensor by a
 // segmented scan over the chunk's 32 granules.  The max norm takes the same route with maxima.
@@ -35,7 +35,8 @@ __device__ __forceinline__ double dq_row_ror(double v)
 
 // Step 1 (every lane): x[it][h] are the lane's float4 halves of tile it; valid[it] says how many
 // of the lane's eight elements of tile `it` belong to their tensor (<= 0: none, >= 8: all);
-// local[it] is the index of that tensor among the chunk's tensors.  Leaves the sum (or maximum)
+// local[it] is the index of that tensor among the chunk's tensors and granule[it] the lane's granule
+// (the same for the 16 lanes of a DPP row).  Leaves the sum (or maximum)
 // of every 128-element granule in lds_gsum[32] and the granule's tensor index in lds_glocal[32].
 // The caller puts a barrier between the two steps.
 //
@@ -44,8 +45,9 @@ __device__ __forceinline__ double dq_row_ror(double v)
 // granule totals, all of tensor 0.  Returns the number of entries step 2 has to scan.
 template <bool LINF>
 __device__ __forceinline__ int dq_chunk_granule_sums(const float4 (&x)[2][2], const int (&valid)[2],
-                                                     const int (&local)[2], int tid, double* lds_gsum,
-                                                     int32_t* lds_glocal, bool single, int n_granules)
+                                                     const int (&local)[2], const int (&granule)[2], int tid,
+                                                     double* lds_gsum, int32_t* lds_glocal, bool single,
+                                                     int n_granules)
 {
     if (single) {
         double row;
@@ -103,7 +105,7 @@ __device__ __forceinline__ int dq_chunk_granule_sums(const float4 (&x)[2][2], co
     for (int it = 0; it < 2; ++it) {
         const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w,
                              x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
-        double granule;
+        double sum;
         if constexpr (LINF) { // maxima are exact in binary32
             float m = 0.0f;
 #pragma unroll
@@ -116,7 +118,7 @@ __device__ __forceinline__ int dq_chunk_granule_sums(const float4 (&x)[2][2], co
             o = dq_row_ror<4>(m); m = o > m ? o : m;
             o = dq_row_ror<2>(m); m = o > m ? o : m;
             o = dq_row_ror<1>(m); m = o > m ? o : m;
-            granule = static_cast<double>(m);
+            sum = static_cast<double>(m);
         } else {
             double acc = 0.0;
             if (valid[it] >= 8) { // all eight belong to the tensor (almost every lane): no masking
@@ -136,11 +138,11 @@ __device__ __forceinline__ int dq_chunk_granule_sums(const float4 (&x)[2][2], co
             acc += dq_row_ror<4>(acc);
             acc += dq_row_ror<2>(acc);
             acc += dq_row_ror<1>(acc);
-            granule = acc; // every lane of the row now has all sixteen terms; the first lane's order is the one used
+            sum = acc; // every lane of the row now has all sixteen terms; the first lane's order is the one used
         }
         if ((tid & 15) == 0) {
-            lds_gsum[it * 16 + (tid >> 4)] = granule;
-            lds_glocal[it * 16 + (tid >> 4)] = local[it];
+            lds_gsum[granule[it]] = sum;
+            lds_glocal[granule[it]] = local[it];
         }
     }
     return n_granules;

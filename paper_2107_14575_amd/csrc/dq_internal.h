@@ -157,6 +157,49 @@ __device__ __forceinline__ uint2 dq_load_stream(const uint2* src)
 }
 __device__ __forceinline__ uint32_t dq_load_stream(const uint32_t* src) { return __builtin_nontemporal_load(src); }
 
+// What the wavefront's lanes wrote to LDS becomes visible to its other lanes (no other wavefront takes
+// part, so no workgroup barrier).
+__device__ __forceinline__ void dq_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A wavefront's tile of 512 consecutive elements, lane l receiving elements [8l, 8l + 8) in lo, hi.
+// Two 16-byte loads per lane of eight consecutive elements each would use half of every cache line
+// per instruction, so that the line has to be kept for the second one: the streaming hint then costs
+// 4 %.  Instead each instruction covers 1 KiB in full -- the first one elements [0, 256) of the tile:
+// lanes 0..31 the first four elements of lanes 0..31's eight, lanes 32..63 the last four; the second
+// one [256, 512) the same way for lanes 32..63 -- with the streaming hint, and four swaps between the
+// halves of the wavefront put every lane's own elements in place.
+//   base       the tile's first element, relative to g
+//   n_elems    elements of g that exist (a multiple of 128, at least 128): a 16-byte load past them is
+//              taken from the last four instead (in bounds, and only lanes past the end receive it)
+__device__ __forceinline__ void dq_load_wave_tile(const float* __restrict__ g, uint32_t base, uint32_t lane,
+                                                  uint32_t n_elems, float4& lo, float4& hi)
+{
+    uint32_t e0 = base + (lane & 31u) * 8u + (lane >> 5) * 4u, e1 = e0 + 256u;
+    e0 = e0 < n_elems ? e0 : n_elems - 4u;
+    e1 = e1 < n_elems ? e1 : n_elems - 4u;
+    lo = dq_load_stream(reinterpret_cast<const float4*>(g + e0));
+    hi = dq_load_stream(reinterpret_cast<const float4*>(g + e1));
+}
+__device__ __forceinline__ void dq_swap_halves(float& a, float& b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+// the second half of the load: call it where the values are first used
+__device__ __forceinline__ void dq_arrange_wave_tile(float4& lo, float4& hi)
+{
+    dq_swap_halves(lo.x, hi.x);
+    dq_swap_halves(lo.y, hi.y);
+    dq_swap_halves(lo.z, hi.z);
+    dq_swap_halves(lo.w, hi.w);
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two 32x32->64 multiplies, key
 // bumped by the Weyl constants between rounds.  The three-input XOR is one v_bitop3_b32.
 __device__ __forceinline__ uint32_t dq_xor3(uint32_t a, uint32_t b, uint32_t c)

@@ -230,15 +230,15 @@ __global__ __launch_bounds__(256) void k_norm_chunk(const float* __restrict__ gr
     const float* g = grads + static_cast<int64_t>(w) * worker_stride + chunk0;
     const int32_t* gseg = granule_cseg + (chunk0 >> 7);
 
+    // wavefront v owns elements [1024 v, 1024 v + 1024) in two tiles of 512
     float4 x[2][2];
     int32_t seg[2];
+    uint32_t elem[2];
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
-        uint32_t e = it * 2048 + tid * 8;
-        e = e < n_elems ? e : n_elems - 8; // clamped: always in bounds, masked out below
-        x[it][0] = dq_load_stream(reinterpret_cast<const float4*>(g + e));
-        x[it][1] = dq_load_stream(reinterpret_cast<const float4*>(g + e + 4));
-        seg[it] = gseg[e >> 7];
+        elem[it] = (tid >> 6) * 1024 + it * 512 + (tid & 63) * 8;
+        dq_load_wave_tile(g, (tid >> 6) * 1024 + it * 512, tid & 63, n_elems, x[it][0], x[it][1]);
+        seg[it] = gseg[(elem[it] < n_elems ? elem[it] : n_elems - 8) >> 7]; // clamped: in bounds, masked out below
     }
     const int32_t seg_first = gseg[0];
     const int n_local = gseg[(n_elems - 1) >> 7] - seg_first + 1;
@@ -247,14 +247,15 @@ __global__ __launch_bounds__(256) void k_norm_chunk(const float* __restrict__ gr
         lds_valid_end[tid] = rel < DQ_CHUNK ? static_cast<int32_t>(rel) : DQ_CHUNK;
     }
     __syncthreads();
-    int valid[2], local[2];
+    int valid[2], local[2], granule[2];
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
-        const uint32_t e = it * 2048 + tid * 8;
+        dq_arrange_wave_tile(x[it][0], x[it][1]);
+        granule[it] = elem[it] >> 7;
         local[it] = seg[it] - seg_first;
-        valid[it] = e < n_elems ? lds_valid_end[local[it]] - static_cast<int32_t>(e) : 0;
+        valid[it] = elem[it] < n_elems ? lds_valid_end[local[it]] - static_cast<int32_t>(elem[it]) : 0;
     }
-    const int n_scan = dq_chunk_granule_sums<LINF>(x, valid, local, tid, lds_gsum, lds_glocal, n_local == 1,
+    const int n_scan = dq_chunk_granule_sums<LINF>(x, valid, local, granule, tid, lds_gsum, lds_glocal, n_local == 1,
                                                    static_cast<int>(n_elems >> 7));
     __syncthreads();
     if (tid < DQ_CHUNK_GRANULES)

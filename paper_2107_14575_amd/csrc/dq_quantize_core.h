@@ -12,7 +12,8 @@ namespace {
 
 constexpr int QP_THREADS = 256;
 constexpr int QP_PER_LANE = 8;
-constexpr int QP_TILE = QP_THREADS * QP_PER_LANE; // 2048 elements
+constexpr int QP_TILE = QP_THREADS * QP_PER_LANE;      // 2048 elements: one tile of every wavefront
+constexpr int QP_WAVE_TILE = 64 * QP_PER_LANE;         // 512 elements: a wavefront's tile
 
 // Writes the low B bytes of v at dst (LDS, byte offset a multiple of B) with naturally aligned
 // stores only.
@@ -29,6 +30,21 @@ __device__ __forceinline__ void stage_bytes(uint8_t* dst, uint64_t v)
     } else {
 #pragma unroll
         for (int k = 0; k < B; ++k) dst[k] = static_cast<uint8_t>(v >> (8 * k));
+    }
+}
+
+// The same for a width that is a value.
+__device__ __forceinline__ void stage_bytes_v(uint8_t* dst, uint64_t v, int b)
+{
+    switch (b) {
+    case 1: stage_bytes<1>(dst, v); break;
+    case 2: stage_bytes<2>(dst, v); break;
+    case 3: stage_bytes<3>(dst, v); break;
+    case 4: stage_bytes<4>(dst, v); break;
+    case 5: stage_bytes<5>(dst, v); break;
+    case 6: stage_bytes<6>(dst, v); break;
+    case 7: stage_bytes<7>(dst, v); break;
+    default: stage_bytes<8>(dst, v); break;
     }
 }
 
@@ -91,6 +107,42 @@ __device__ __forceinline__ void quantize8(const float4 x_lo, const float4 x_hi, 
     level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * b));
 }
 
+// First element (inside the chunk) of a lane's eight of tile `it`.  Each wavefront owns TILES
+// consecutive tiles of 512 elements, i.e. one stretch of every plane: it stages and stores its own
+// bytes, with no workgroup barrier between the two.
+template <int TILES>
+__device__ __forceinline__ uint32_t qp_elem(uint32_t tid, int it)
+{
+    return (tid >> 6) * (QP_WAVE_TILE * TILES) + it * QP_WAVE_TILE + (tid & 63u) * QP_PER_LANE;
+}
+
+// The lane's inputs of every tile, in flight together (dq_arrange_wave_tile completes them).  Lanes
+// past the end of a ragged last chunk re-read its last elements (always in bounds); what they
+// compute is never stored.
+template <int TILES>
+__device__ __forceinline__ void qp_load(const float* __restrict__ g, uint32_t tid, uint32_t n_elems, float4 (&x)[TILES][2])
+{
+#pragma unroll
+    for (int it = 0; it < TILES; ++it)
+        dq_load_wave_tile(g, (tid >> 6) * (QP_WAVE_TILE * TILES) + it * QP_WAVE_TILE, tid & 63u, n_elems, x[it][0], x[it][1]);
+}
+
+// The granule (128 elements) of a lane's eight of tile `it`, clamped to the chunk's last one.
+template <int TILES>
+__device__ __forceinline__ uint32_t qp_granule(uint32_t tid, int it, uint32_t n_elems)
+{
+    const uint32_t e = qp_elem<TILES>(tid, it);
+    return (e < n_elems ? e : n_elems - QP_PER_LANE) >> 7;
+}
+
+// A wavefront's staged bytes [0, bytes) (a multiple of 16) leave as 16-byte streaming stores.
+__device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t lane)
+{
+    uint4* d = reinterpret_cast<uint4*>(dst);
+    const uint4* f = reinterpret_cast<const uint4*>(src);
+    for (uint32_t i = lane; i < bytes / 16; i += 64) dq_store_stream(d + i, f[i]);
+}
+
 // NORM = 0: the norms are an input.  NORM = 1 (l2) or 2 (max): chunk-local plans only; the kernel
 // computes the norms of its chunk's tensors itself, writes them to norms_out and quantizes from
 // the registers it already holds -- one read of the gradient instead of two.
@@ -121,18 +173,11 @@ __device__ __forceinline__ void quantize_pack_chunk(
     const int32_t* gseg = granule_cseg + (chunk0 >> 7);
 
     // This lane's inputs first, so the loads are in flight while the segment table is built.
-    // Lanes past the end of a ragged last chunk re-read its last eight elements (always in
-    // bounds); what they compute is never stored.
     float4 x[TILES][2];
     int32_t seg[TILES];
+    qp_load<TILES>(g, tid, n_elems, x);
 #pragma unroll
-    for (int it = 0; it < TILES; ++it) {
-        uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
-        e = e < n_elems ? e : n_elems - QP_PER_LANE;
-        x[it][0] = *reinterpret_cast<const float4*>(g + e);
-        x[it][1] = *reinterpret_cast<const float4*>(g + e + 4);
-        seg[it] = gseg[e >> 7];
-    }
+    for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES>(tid, it, n_elems)];
 
     // compact segment indices grow by at most one per granule, so the chunk's segments fit the table
     const int32_t seg_first = gseg[0];
@@ -145,6 +190,8 @@ __device__ __forceinline__ void quantize_pack_chunk(
             lds_valid_end[tid] = rel < CHUNK ? static_cast<int32_t>(rel) : CHUNK;
         }
         __syncthreads();
+#pragma unroll
+        for (int it = 0; it < TILES; ++it) dq_arrange_wave_tile(x[it][0], x[it][1]);
     } else {
         __shared__ double lds_gsum[DQ_CHUNK_GRANULES];
         __shared__ int32_t lds_glocal[DQ_CHUNK_GRANULES];
@@ -153,15 +200,18 @@ __device__ __forceinline__ void quantize_pack_chunk(
             lds_valid_end[tid] = rel < CHUNK ? static_cast<int32_t>(rel) : CHUNK;
         }
         __syncthreads();
-        int valid[TILES], local[TILES];
+        int valid[TILES], local[TILES], granule[TILES];
 #pragma unroll
         for (int it = 0; it < TILES; ++it) {
-            const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+            dq_arrange_wave_tile(x[it][0], x[it][1]);
+            const uint32_t e = qp_elem<TILES>(tid, it);
+            granule[it] = static_cast<int>(e >> 7);
             local[it] = seg[it] - seg_first;
             valid[it] = e < n_elems ? lds_valid_end[local[it]] - static_cast<int32_t>(e) : 0;
         }
-        const int n_scan = dq_chunk_granule_sums<NORM == 2>(x, valid, local, static_cast<int>(tid), lds_gsum, lds_glocal,
-                                                            seg_first == seg_last, static_cast<int>(n_elems >> 7));
+        const int n_scan = dq_chunk_granule_sums<NORM == 2>(x, valid, local, granule, static_cast<int>(tid), lds_gsum,
+                                                            lds_glocal, seg_first == seg_last,
+                                                            static_cast<int>(n_elems >> 7));
         __syncthreads();
         if (tid < DQ_CHUNK_GRANULES)
             dq_chunk_tensor_norms<NORM == 2>(static_cast<int>(tid), n_scan, lds_gsum, lds_glocal,
@@ -180,7 +230,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
 
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
-        const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+        const uint32_t e = qp_elem<TILES>(tid, it);
         if (e < n_elems) {
             const int local = seg[it] - seg_first;
             const float scale = lds_scale[local];
@@ -196,30 +246,27 @@ __device__ __forceinline__ void quantize_pack_chunk(
                 sign &= (1u << nv) - 1u;
                 level &= (static_cast<uint64_t>(1) << (nv * B)) - 1u;
             }
-            lds_sign[it * QP_THREADS + tid] = static_cast<uint8_t>(sign);
-            stage_bytes<B>(&lds_level[(it * QP_THREADS + tid) * B], level);
+            lds_sign[e >> 3] = static_cast<uint8_t>(sign);
+            stage_bytes<B>(&lds_level[(e >> 3) * B], level);
         }
     }
-    __syncthreads();
+    dq_wave_sync();
 
-    // 16-byte stores; every plane of a chunk is a whole number of 16-byte pieces because the
-    // chunk holds a multiple of 128 elements
-    uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
-    {
-        uint4* dst = reinterpret_cast<uint4*>(msg + (chunk0 >> 3));
-        const uint4* src = reinterpret_cast<const uint4*>(lds_sign);
-        for (uint32_t i = tid; i < n_elems / 128; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
-    }
-    {
-        uint4* dst = reinterpret_cast<uint4*>(msg + (padded_elems >> 3) + (chunk0 >> 3) * B);
-        const uint4* src = reinterpret_cast<const uint4*>(lds_level);
-        for (uint32_t i = tid; i < n_elems / 128 * B; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
+    // 16-byte stores of this wavefront's stretch; every plane of it is a whole number of 16-byte
+    // pieces because it holds a multiple of 128 elements
+    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
+    if (wave0 < n_elems) {
+        const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * TILES ? n_elems - wave0 : QP_WAVE_TILE * TILES;
+        uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
+        qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], n_wave >> 3, tid & 63u);
+        qp_store_wave(msg + (padded_elems >> 3) + ((chunk0 + wave0) >> 3) * B, &lds_level[(wave0 >> 3) * B],
+                      (n_wave >> 3) * B, tid & 63u);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 // Per-tensor widths.  Same work split; b, the level count and the place of the level bytes come
-// from the widths table per segment instead of the template argument.  A chunk's level bytes are
+// from the widths table per segment instead of the template argument.  A wavefront's level bytes are
 // still one contiguous stretch of the message (every segment's stretch is a whole number of
 // 16-byte pieces per granule), so they are staged and stored the same way.
 // ---------------------------------------------------------------------------------------------
@@ -256,14 +303,9 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
 
     float4 x[TILES][2];
     int32_t seg[TILES];
+    qp_load<TILES>(g, tid, n_elems, x);
 #pragma unroll
-    for (int it = 0; it < TILES; ++it) {
-        uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
-        e = e < n_elems ? e : n_elems - QP_PER_LANE;
-        x[it][0] = *reinterpret_cast<const float4*>(g + e);
-        x[it][1] = *reinterpret_cast<const float4*>(g + e + 4);
-        seg[it] = gseg[e >> 7];
-    }
+    for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES>(tid, it, n_elems)];
 
     const int32_t seg_first = gseg[0];
     const int32_t seg_last = gseg[(n_elems - 1) >> 7];
@@ -285,18 +327,22 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
         lds_valid_end[tid] = rel < CHUNK ? static_cast<int32_t>(rel) : CHUNK;
     }
     __syncthreads();
+#pragma unroll
+    for (int it = 0; it < TILES; ++it) dq_arrange_wave_tile(x[it][0], x[it][1]);
     if constexpr (NORM != 0) {
         __shared__ double lds_gsum[DQ_CHUNK_GRANULES];
         __shared__ int32_t lds_glocal[DQ_CHUNK_GRANULES];
-        int valid[TILES], local[TILES];
+        int valid[TILES], local[TILES], granule[TILES];
 #pragma unroll
         for (int it = 0; it < TILES; ++it) {
-            const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+            const uint32_t e = qp_elem<TILES>(tid, it);
+            granule[it] = static_cast<int>(e >> 7);
             local[it] = seg[it] - seg_first;
             valid[it] = e < n_elems ? lds_valid_end[local[it]] - static_cast<int32_t>(e) : 0;
         }
-        const int n_scan = dq_chunk_granule_sums<NORM == 2>(x, valid, local, static_cast<int>(tid), lds_gsum, lds_glocal,
-                                                            seg_first == seg_last, static_cast<int>(n_elems >> 7));
+        const int n_scan = dq_chunk_granule_sums<NORM == 2>(x, valid, local, granule, static_cast<int>(tid), lds_gsum,
+                                                            lds_glocal, seg_first == seg_last,
+                                                            static_cast<int>(n_elems >> 7));
         __syncthreads();
         if (tid < DQ_CHUNK_GRANULES)
             dq_chunk_tensor_norms<NORM == 2>(static_cast<int>(tid), n_scan, lds_gsum, lds_glocal,
@@ -313,7 +359,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
 
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
-        const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+        const uint32_t e = qp_elem<TILES>(tid, it);
         if (e < n_elems) {
             const int local = seg[it] - seg_first;
             const float scale = lds_scale[local];
@@ -330,36 +376,25 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
                 sign &= (1u << nv) - 1u;
                 level &= (static_cast<uint64_t>(1) << (nv * b)) - 1u;
             }
-            lds_sign[it * QP_THREADS + tid] = static_cast<uint8_t>(sign);
+            lds_sign[e >> 3] = static_cast<uint8_t>(sign);
             // b bytes at an offset that is a multiple of b past a 16-byte boundary (every tensor's
             // stretch of a chunk starts on one), so the naturally aligned stores of stage_bytes apply
-            uint8_t* dst = &lds_level[lds_level_base[local] + static_cast<int32_t>(e >> 3) * b];
-            switch (b) {
-            case 1: stage_bytes<1>(dst, level); break;
-            case 2: stage_bytes<2>(dst, level); break;
-            case 3: stage_bytes<3>(dst, level); break;
-            case 4: stage_bytes<4>(dst, level); break;
-            case 5: stage_bytes<5>(dst, level); break;
-            case 6: stage_bytes<6>(dst, level); break;
-            case 7: stage_bytes<7>(dst, level); break;
-            default: stage_bytes<8>(dst, level); break;
-            }
+            stage_bytes_v(&lds_level[lds_level_base[local] + static_cast<int32_t>(e >> 3) * b], level, b);
         }
     }
-    __syncthreads();
+    dq_wave_sync();
 
-    uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
-    {
-        uint4* dst = reinterpret_cast<uint4*>(msg + (chunk0 >> 3));
-        const uint4* src = reinterpret_cast<const uint4*>(lds_sign);
-        for (uint32_t i = tid; i < n_elems / 128; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
-    }
-    {
-        const int last = seg_last - seg_first;
-        const uint32_t level_bytes = static_cast<uint32_t>(lds_level_base[last]) + (n_elems >> 3) * lds_b[last];
-        uint4* dst = reinterpret_cast<uint4*>(msg + (padded_elems >> 3) + chunk_level0);
-        const uint4* src = reinterpret_cast<const uint4*>(lds_level);
-        for (uint32_t i = tid; i < level_bytes / 16; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
+    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
+    if (wave0 < n_elems) {
+        const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * TILES ? n_elems - wave0 : QP_WAVE_TILE * TILES;
+        uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
+        qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], n_wave >> 3, tid & 63u);
+        // level bytes of the wavefront's first element up to those of its last granule
+        const int a = gseg[wave0 >> 7] - seg_first, z = gseg[(wave0 + n_wave - 1) >> 7] - seg_first;
+        const int32_t from = lds_level_base[a] + static_cast<int32_t>(wave0 >> 3) * lds_b[a];
+        const int32_t to = lds_level_base[z] + static_cast<int32_t>((wave0 + n_wave) >> 3) * lds_b[z];
+        qp_store_wave(msg + (padded_elems >> 3) + chunk_level0 + from, &lds_level[from], static_cast<uint32_t>(to - from),
+                      tid & 63u);
     }
 }
 

@@ -68,17 +68,13 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
 
     float4 x[SP_TILES][2];
     int64_t valid_end[SP_TILES];
+    qp_load<SP_TILES>(g, tid, n_elems, x);
+#pragma unroll
+    for (int it = 0; it < SP_TILES; ++it) valid_end[it] = cseg_valid_end[gseg[qp_granule<SP_TILES>(tid, it, n_elems)]];
 #pragma unroll
     for (int it = 0; it < SP_TILES; ++it) {
-        uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
-        e = e < n_elems ? e : n_elems - QP_PER_LANE; // clamped: always in bounds, result unused
-        x[it][0] = *reinterpret_cast<const float4*>(g + e);
-        x[it][1] = *reinterpret_cast<const float4*>(g + e + 4);
-        valid_end[it] = cseg_valid_end[gseg[e >> 7]];
-    }
-#pragma unroll
-    for (int it = 0; it < SP_TILES; ++it) {
-        const uint32_t e = it * QP_TILE + tid * QP_PER_LANE;
+        dq_arrange_wave_tile(x[it][0], x[it][1]);
+        const uint32_t e = qp_elem<SP_TILES>(tid, it);
         if (e < n_elems) {
             const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w,
                                  x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
@@ -87,13 +83,16 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
             for (int k = 7; k >= 0; --k) sign = __builtin_amdgcn_alignbit(sign, __float_as_uint(v[k]), 31);
             const int64_t n_valid = valid_end[it] - (chunk0 + e);
             if (n_valid < QP_PER_LANE) sign &= (1u << (n_valid > 0 ? static_cast<int>(n_valid) : 0)) - 1u;
-            lds_sign[it * QP_THREADS + tid] = static_cast<uint8_t>(sign);
+            lds_sign[e >> 3] = static_cast<uint8_t>(sign);
         }
     }
-    __syncthreads();
-    uint4* dst = reinterpret_cast<uint4*>(packed + static_cast<int64_t>(w) * packed_stride + (chunk0 >> 3));
-    const uint4* src = reinterpret_cast<const uint4*>(lds_sign);
-    for (uint32_t i = tid; i < n_elems / 128; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
+    dq_wave_sync();
+    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * SP_TILES);
+    if (wave0 < n_elems) {
+        const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * SP_TILES ? n_elems - wave0 : QP_WAVE_TILE * SP_TILES;
+        qp_store_wave(packed + static_cast<int64_t>(w) * packed_stride + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3],
+                      n_wave >> 3, tid & 63u);
+    }
 }
 
 template <int B, int NORM>
