@@ -561,8 +561,8 @@ constexpr int64_t SETTLE_WIDE_MAX = 1 << 16;
 template <int B>
 __global__ __launch_bounds__(QP_THREADS) void k_bracket_redo(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
-    const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
-    const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, uint32_t key0, uint32_t key1, uint32_t step,
+    const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
+    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, uint32_t key0, uint32_t key1, uint32_t step,
     uint32_t worker_base, uint8_t* __restrict__ packed, int64_t packed_stride,
     const unsigned long long* __restrict__ redo_map, int64_t n_words, const dq_cseg_width* __restrict__ widths_table,
     int32_t widths_worker_stride)
@@ -580,11 +580,11 @@ __global__ __launch_bounds__(QP_THREADS) void k_bracket_redo(
             bits &= bits - 1;
             const uint32_t chunk = static_cast<uint32_t>((word0 + k) * 64 + bit);
             if constexpr (B == 0)
-                quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, granule_cseg, cseg_seg, cseg_valid_end,
+                quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                             widths_table, widths_worker_stride, padded_elems, key0, key1, step,
                                             worker_base, packed, packed_stride, nullptr, chunk);
             else
-                quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, granule_cseg, cseg_seg, cseg_valid_end,
+                quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                              padded_elems, key0, key1, step, worker_base, packed, packed_stride, nullptr,
                                              chunk);
             __syncthreads(); // the chunk's staging in LDS is reused by the next one
@@ -598,8 +598,8 @@ __global__ __launch_bounds__(QP_THREADS) void k_bracket_redo(
 template <int B>
 __global__ __launch_bounds__(QP_THREADS) void k_bracket_redo_direct(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
-    const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
-    const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, uint32_t key0, uint32_t key1, uint32_t step,
+    const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
+    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, uint32_t key0, uint32_t key1, uint32_t step,
     uint32_t worker_base, uint8_t* __restrict__ packed, int64_t packed_stride,
     const unsigned long long* __restrict__ redo_map, int64_t n_words, const dq_cseg_width* __restrict__ widths_table,
     int32_t widths_worker_stride)
@@ -607,11 +607,11 @@ __global__ __launch_bounds__(QP_THREADS) void k_bracket_redo_direct(
     const unsigned long long word = redo_map[static_cast<int64_t>(blockIdx.y) * n_words + (blockIdx.x >> 6)];
     if (((word >> (blockIdx.x & 63)) & 1ull) == 0) return; // uniform: one address for the whole workgroup
     if constexpr (B == 0)
-        quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, granule_cseg, cseg_seg, cseg_valid_end, widths_table,
+        quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end, widths_table,
                                     widths_worker_stride, padded_elems, key0, key1, step, worker_base, packed,
                                     packed_stride, nullptr, blockIdx.x);
     else
-        quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, granule_cseg, cseg_seg, cseg_valid_end,
+        quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                      padded_elems, key0, key1, step, worker_base, packed, packed_stride, nullptr,
                                      blockIdx.x);
 }
@@ -701,11 +701,11 @@ int launch_bracketed(const dq_plan* plan, const float* grads, int64_t worker_str
     }
     if (static_cast<int64_t>(M) * L.n_chunks <= SETTLE_WIDE_MAX)
         hipLaunchKernelGGL(k_bracket_redo_direct<B>, grid, block, 0, stream, grads, worker_stride, norms, plan->n_seg,
-                           plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, key0, key1,
+                           plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, key0, key1,
                            step, worker_base, packed, packed_stride, redo_map, L.n_words, widths_table, widths_row);
     else
         hipLaunchKernelGGL(k_bracket_redo<B>, dim3(static_cast<unsigned>((L.n_words + REDO_WORDS - 1) / REDO_WORDS), M),
-                           block, 0, stream, grads, worker_stride, norms, plan->n_seg, plan->d_granule_cseg,
+                           block, 0, stream, grads, worker_stride, norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,
                            plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, key0, key1, step, worker_base,
                            packed, packed_stride, redo_map, L.n_words, widths_table, widths_row);
     if (stats) {

@@ -15,6 +15,22 @@ struct dq_norm_item {
 
 constexpr int DQ_NORM_CHUNK = 4096; // elements per norm item (one workgroup, 4 float4 per lane)
 
+// Which tensor a 4096-element chunk of the padded index space belongs to: cseg (compact index, see
+// below) and seg when all of its elements are there and are data of that one tensor; otherwise cseg = -1
+// and seg is the tensor of its first element.
+// Almost every chunk of a gradient of large tensors is of the first kind, and a kernel then gets by
+// with two scalar loads in place of the granule table (32 entries per chunk and worker).
+struct __align__(8) dq_chunk_tensor {
+    int32_t cseg;
+    int32_t seg;
+};
+// both words in one scalar load (k is the same for the whole workgroup)
+__device__ __forceinline__ dq_chunk_tensor dq_load_chunk_tensor(const dq_chunk_tensor* __restrict__ table, int64_t k)
+{
+    const uint64_t v = reinterpret_cast<const uint64_t*>(table)[k];
+    return dq_chunk_tensor{ static_cast<int32_t>(static_cast<uint32_t>(v)), static_cast<int32_t>(v >> 32) };
+}
+
 struct dq_plan {
     int32_t n_seg;
     int64_t padded_elems; // D'
@@ -26,6 +42,7 @@ struct dq_plan {
     bool chunk_local;     // no segment crosses a multiple of 4096 in the padded index space
     // device tables.  Kernels address segments through a compact index c that counts only the
     // non-empty ones, so consecutive granules differ by at most one in c.
+    dq_chunk_tensor* d_chunk_tensor; // [ceil(D'/4096)]
     int32_t* d_granule_cseg;       // [D'/128]  compact segment index of each 128-element granule
     int32_t* d_cseg_seg;           // [n_nonempty] segment l of compact index c
     int64_t* d_cseg_valid_end;     // [n_nonempty] P_l + len_l: first padded index past the data
@@ -182,8 +199,10 @@ __device__ __forceinline__ void dq_load_wave_tile(const float* __restrict__ g, u
     uint32_t e0 = base + (lane & 31u) * 8u + (lane >> 5) * 4u, e1 = e0 + 256u;
     e0 = e0 < n_elems ? e0 : n_elems - 4u;
     e1 = e1 < n_elems ? e1 : n_elems - 4u;
-    lo = dq_load_stream(reinterpret_cast<const float4*>(g + e0));
-    hi = dq_load_stream(reinterpret_cast<const float4*>(g + e1));
+    // 32-bit byte offsets from the uniform base: no 64-bit address arithmetic per lane
+    const char* at = reinterpret_cast<const char*>(g);
+    lo = dq_load_stream(reinterpret_cast<const float4*>(at + e0 * 4u));
+    hi = dq_load_stream(reinterpret_cast<const float4*>(at + e1 * 4u));
 }
 __device__ __forceinline__ void dq_swap_halves(float& a, float& b)
 {

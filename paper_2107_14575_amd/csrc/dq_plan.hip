@@ -26,6 +26,8 @@ bool upload(T** dst, const std::vector<T>& src)
 
 void free_device_tables(dq_plan* p)
 {
+    if (p->d_chunk_tensor) (void)hipFree(p->d_chunk_tensor);
+    p->d_chunk_tensor = nullptr;
     if (p->d_granule_cseg) (void)hipFree(p->d_granule_cseg);
     if (p->d_cseg_seg) (void)hipFree(p->d_cseg_seg);
     if (p->d_cseg_valid_end) (void)hipFree(p->d_cseg_valid_end);
@@ -102,12 +104,14 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
     std::vector<int32_t> span_cseg;
     std::vector<int32_t> cseg_seg;
     std::vector<int32_t> granule_cseg;
+    std::vector<dq_chunk_tensor> chunk_tensor;
     std::vector<dq_norm_item> items;
     std::vector<int32_t> item_begin;
     std::vector<int32_t> finish_seg;
     try {
         // every allocation of the host tables happens in here: std::bad_alloc never leaves the call
         granule_cseg.resize(static_cast<size_t>(total / DQ_GRANULE));
+        chunk_tensor.resize(static_cast<size_t>((total + 4095) / 4096));
         item_begin.resize(static_cast<size_t>(n_seg) + 1);
         items.reserve(static_cast<size_t>(n_items));
         for (int32_t l = 0; l < n_seg; ++l) {
@@ -117,6 +121,10 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
                 cseg_valid_end.push_back(p->seg_start[l] + p->seg_len[l]);
                 cseg_start.push_back(p->seg_start[l]);
                 if (p->seg_start[l] / 4096 != (p->seg_start[l] + p->seg_len[l] - 1) / 4096) span_cseg.push_back(c);
+                // the chunks that begin inside this tensor (padding included: tensors begin at multiples of 128)
+                for (int64_t k = (p->seg_start[l] + 4095) / 4096; k * 4096 < p->seg_start[l + 1]; ++k)
+                    chunk_tensor[static_cast<size_t>(k)] =
+                        dq_chunk_tensor{ (k + 1) * 4096 <= p->seg_start[l] + p->seg_len[l] ? c : -1, l };
                 for (int64_t g = p->seg_start[l] / DQ_GRANULE; g < p->seg_start[l + 1] / DQ_GRANULE; ++g)
                     granule_cseg[static_cast<size_t>(g)] = c;
             }
@@ -138,7 +146,7 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
         return DQ_ERR_ALLOC;
     }
 
-    const bool ok = upload(&p->d_granule_cseg, granule_cseg) && upload(&p->d_cseg_seg, cseg_seg) &&
+    const bool ok = upload(&p->d_chunk_tensor, chunk_tensor) && upload(&p->d_granule_cseg, granule_cseg) && upload(&p->d_cseg_seg, cseg_seg) &&
                     upload(&p->d_cseg_valid_end, cseg_valid_end) && upload(&p->d_cseg_start, cseg_start) && upload(&p->d_span_cseg, span_cseg) &&
                     upload(&p->d_items, items) && upload(&p->d_seg_item_begin, item_begin) &&
                     upload(&p->d_finish_seg, finish_seg);

@@ -62,29 +62,31 @@ __device__ __forceinline__ void stage_bytes_v(uint8_t* dst, uint64_t v, int b)
 // S, b: the level count and bits of the tensor (template argument B > 0 fixes them at compile time).
 // r[h][k] receives the random word of element 4h + k unless the all-zero route was taken (then no
 // caller needs it: every level is zero).
+// quantize_quads leaves the two groups of four apart (their Philox blocks are quad0 and quad1): sign
+// nibbles and 4*B level bits each.
 template <int B>
-__device__ __forceinline__ void quantize8(const float4 x_lo, const float4 x_hi, const float scale, const float S_arg,
-                                          const int b_arg, const uint32_t quad, const uint32_t quad_hi,
-                                          const uint32_t worker, const uint32_t step, const uint32_t key0,
-                                          const uint32_t key1, uint32_t& sign, uint64_t& level, uint32_t (&r)[2][4])
+__device__ __forceinline__ void quantize_quads(const float4 x0, const float4 x1, const float scale, const float S_arg,
+                                               const int b_arg, const uint32_t quad0, const uint32_t quad1,
+                                               const uint32_t quad_hi, const uint32_t worker, const uint32_t step,
+                                               const uint32_t key0, const uint32_t key1, uint32_t (&sign)[2],
+                                               uint32_t (&lv)[2], uint32_t (&r)[2][4])
 {
     const float S = B > 0 ? static_cast<float>((1 << (B > 0 ? B : 1)) - 1) : S_arg;
     const int b = B > 0 ? B : b_arg;
-    const float v[8] = { x_lo.x, x_lo.y, x_lo.z, x_lo.w, x_hi.x, x_hi.y, x_hi.z, x_hi.w };
+    const float v[8] = { x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w };
     float a[8];
-    sign = 0;
+    sign[0] = sign[1] = 0;
 #pragma unroll
     for (int k = 7; k >= 0; --k) {
-        sign = __builtin_amdgcn_alignbit(sign, __float_as_uint(v[k]), 31); // element 0 ends in bit 0
-        a[k] = fabsf(v[k]) * scale;                                         // s|g|/N, one rounding
+        sign[k >> 2] = __builtin_amdgcn_alignbit(sign[k >> 2], __float_as_uint(v[k]), 31); // element 4h ends in bit 0
+        a[k] = fabsf(v[k]) * scale;                                                         // s|g|/N, one rounding
     }
     const float top = fmaxf(fmaxf(__builtin_fmaxf(__builtin_fmaxf(a[0], a[1]), a[2]), __builtin_fmaxf(__builtin_fmaxf(a[3], a[4]), a[5])),
                             __builtin_fmaxf(a[6], a[7]));
-    level = 0;
+    lv[0] = lv[1] = 0u;
     if (__all(top == 0.0f)) return;
-    dq_philox4x32_10(quad, quad_hi, worker, step, key0, key1, r[0]);
-    dq_philox4x32_10(quad + 1u, quad_hi, worker, step, key0, key1, r[1]);
-    uint32_t lv[2] = { 0u, 0u };
+    dq_philox4x32_10(quad0, quad_hi, worker, step, key0, key1, r[0]);
+    dq_philox4x32_10(quad1, quad_hi, worker, step, key0, key1, r[1]);
     if (__all(top < 1.0f)) {
 #pragma unroll
         for (int h = 1; h >= 0; --h)
@@ -104,7 +106,36 @@ __device__ __forceinline__ void quantize8(const float4 x_lo, const float4 x_hi, 
                 lv[h] = (lv[h] << b) + static_cast<uint32_t>(c) + (u < p ? 1u : 0u);
             }
     }
-    level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * b));
+}
+
+template <int B>
+__device__ __forceinline__ void quantize8(const float4 x_lo, const float4 x_hi, const float scale, const float S_arg,
+                                          const int b_arg, const uint32_t quad, const uint32_t quad_hi,
+                                          const uint32_t worker, const uint32_t step, const uint32_t key0,
+                                          const uint32_t key1, uint32_t& sign, uint64_t& level, uint32_t (&r)[2][4])
+{
+    uint32_t sg[2], lv[2];
+    quantize_quads<B>(x_lo, x_hi, scale, S_arg, b_arg, quad, quad + 1u, quad_hi, worker, step, key0, key1, sg, lv, r);
+    sign = sg[0] | (sg[1] << 4);
+    level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * (B > 0 ? B : b_arg)));
+}
+
+// The same for a wavefront's tile as dq_load_wave_tile loaded it (not arranged) when one scale serves
+// the whole tile: every lane quantizes the two quads it loaded, and the codes change places instead of
+// the values -- two swaps in place of eight.  quad_tile: the tile's first quad.
+template <int B>
+__device__ __forceinline__ void quantize_wave_tile(const float4 lo, const float4 hi, const float scale, const float S_arg,
+                                                   const int b_arg, const uint32_t quad_tile, const uint32_t lane,
+                                                   const uint32_t quad_hi, const uint32_t worker, const uint32_t step,
+                                                   const uint32_t key0, const uint32_t key1, uint32_t& sign, uint64_t& level)
+{
+    uint32_t sg[2], lv[2], r[2][4];
+    const uint32_t quad = quad_tile + (lane & 31u) * 2u + (lane >> 5);
+    quantize_quads<B>(lo, hi, scale, S_arg, b_arg, quad, quad + 64u, quad_hi, worker, step, key0, key1, sg, lv, r);
+    const auto s = __builtin_amdgcn_permlane32_swap(sg[0], sg[1], false, false);
+    const auto l = __builtin_amdgcn_permlane32_swap(lv[0], lv[1], false, false);
+    sign = s[0] | (s[1] << 4);
+    level = static_cast<uint64_t>(l[0]) | (static_cast<uint64_t>(l[1]) << (4 * (B > 0 ? B : b_arg)));
 }
 
 // First element (inside the chunk) of a lane's eight of tile `it`.  Each wavefront owns TILES
@@ -143,14 +174,22 @@ __device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const u
     for (uint32_t i = lane; i < bytes / 16; i += 64) dq_store_stream(d + i, f[i]);
 }
 
+// What bounds it: the memory system's rate at 4 bytes read to (B+1)/8 written (about 6.1-6.2 TB/s, what a
+// kernel with the same accesses and no arithmetic reaches), with the vector ALU at 80 % beside it.  A chunk
+// that lies in one tensor (nearly all of a gradient of large tensors) takes the first route: two scalar
+// loads and one division per wavefront in place of the granule table, LDS and a barrier, and the codes
+// change places between the lanes instead of the values.  Measured at D = 2^28, M = 16 against the table
+// route alone: b = 2 3.36 -> 3.06 ms (6.1 TB/s), b = 4 3.39 -> 3.28 ms; ResNet-18 shape, M = 8, b = 2
+// 74.9 -> 66.9 us.  Chunks that hold a tensor's end or several tensors take the table.
+//
 // NORM = 0: the norms are an input.  NORM = 1 (l2) or 2 (max): chunk-local plans only; the kernel
 // computes the norms of its chunk's tensors itself, writes them to norms_out and quantizes from
 // the registers it already holds -- one read of the gradient instead of two.
 template <int B, int TILES, int NORM>
 __device__ __forceinline__ void quantize_pack_chunk(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
-    const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
-    const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
+    const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
+    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
     int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index)
 {
@@ -174,8 +213,40 @@ __device__ __forceinline__ void quantize_pack_chunk(
 
     // This lane's inputs first, so the loads are in flight while the segment table is built.
     float4 x[TILES][2];
-    int32_t seg[TILES];
     qp_load<TILES>(g, tid, n_elems, x);
+
+    // Philox counter words: quad index P>>2 (low word varies per lane, high word is uniform because
+    // a chunk never straddles a multiple of 2^34 elements), worker, step
+    const uint32_t quad_lo0 = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 2);
+    const uint32_t quad_hi = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 34);
+    const uint32_t worker = worker_base + w;
+    uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
+    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
+
+    if constexpr (NORM == 0) {
+        const dq_chunk_tensor whole = dq_load_chunk_tensor(chunk_tensor, chunk0 / DQ_CHUNK);
+        const float N = norms[static_cast<int64_t>(w) * n_seg + whole.seg]; // issued whatever cseg is: one wait less
+        if (whole.cseg >= 0) { // 4096 elements of one tensor: one scale, nothing to mask, no table, no barrier
+            const float scale = N >= DQ_MIN_NORM ? S / N : 0.0f;
+#pragma unroll
+            for (int it = 0; it < TILES; ++it) {
+                uint32_t sign;
+                uint64_t level;
+                const uint32_t tile0 = wave0 + it * QP_WAVE_TILE, at = (tile0 >> 3) + (tid & 63u);
+                quantize_wave_tile<B>(x[it][0], x[it][1], scale, 0.0f, 0, quad_lo0 + (tile0 >> 2), tid & 63u, quad_hi,
+                                      worker, step, key0, key1, sign, level);
+                lds_sign[at] = static_cast<uint8_t>(sign);
+                stage_bytes<B>(&lds_level[at * B], level);
+            }
+            dq_wave_sync();
+            qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], QP_WAVE_TILE * TILES / 8, tid & 63u);
+            qp_store_wave(msg + (padded_elems >> 3) + ((chunk0 + wave0) >> 3) * B, &lds_level[(wave0 >> 3) * B],
+                          QP_WAVE_TILE * TILES / 8 * B, tid & 63u);
+            return;
+        }
+    }
+
+    int32_t seg[TILES];
 #pragma unroll
     for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES>(tid, it, n_elems)];
 
@@ -222,12 +293,6 @@ __device__ __forceinline__ void quantize_pack_chunk(
         __syncthreads();
     }
 
-    // Philox counter words: quad index P>>2 (low word varies per lane, high word is uniform because
-    // a chunk never straddles a multiple of 2^34 elements), worker, step
-    const uint32_t quad_lo0 = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 2);
-    const uint32_t quad_hi = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 34);
-    const uint32_t worker = worker_base + w;
-
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
         const uint32_t e = qp_elem<TILES>(tid, it);
@@ -254,10 +319,8 @@ __device__ __forceinline__ void quantize_pack_chunk(
 
     // 16-byte stores of this wavefront's stretch; every plane of it is a whole number of 16-byte
     // pieces because it holds a multiple of 128 elements
-    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
     if (wave0 < n_elems) {
         const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * TILES ? n_elems - wave0 : QP_WAVE_TILE * TILES;
-        uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
         qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], n_wave >> 3, tid & 63u);
         qp_store_wave(msg + (padded_elems >> 3) + ((chunk0 + wave0) >> 3) * B, &lds_level[(wave0 >> 3) * B],
                       (n_wave >> 3) * B, tid & 63u);
@@ -273,9 +336,9 @@ __device__ __forceinline__ void quantize_pack_chunk(
 template <int TILES, int NORM> // NORM as in quantize_pack_chunk
 __device__ __forceinline__ void quantize_pack_chunk_v(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
-    const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
-    const int64_t* __restrict__ cseg_valid_end, const dq_cseg_width* __restrict__ widths_table,
-    int32_t widths_worker_stride, int64_t padded_elems,
+    const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
+    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
+    const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
     int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index)
 {
@@ -302,8 +365,40 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     const int32_t* gseg = granule_cseg + (chunk0 >> 7);
 
     float4 x[TILES][2];
-    int32_t seg[TILES];
     qp_load<TILES>(g, tid, n_elems, x);
+
+    const uint32_t quad_lo0 = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 2);
+    const uint32_t quad_hi = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 34);
+    const uint32_t worker = worker_base + w;
+    uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
+    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
+
+    if constexpr (NORM == 0) { // one tensor: as in quantize_pack_chunk, its width from one (scalar) table entry
+        const dq_chunk_tensor whole = dq_load_chunk_tensor(chunk_tensor, chunk0 / DQ_CHUNK);
+        const float N = norms[static_cast<int64_t>(w) * n_seg + whole.seg];
+        if (whole.cseg >= 0) {
+            const dq_cseg_width e = widths[whole.cseg];
+            const float S = static_cast<float>((1 << e.b) - 1);
+            const float scale = N >= DQ_MIN_NORM ? S / N : 0.0f;
+#pragma unroll
+            for (int it = 0; it < TILES; ++it) {
+                uint32_t sign;
+                uint64_t level;
+                const uint32_t tile0 = wave0 + it * QP_WAVE_TILE, at = (tile0 >> 3) + (tid & 63u);
+                quantize_wave_tile<0>(x[it][0], x[it][1], scale, S, e.b, quad_lo0 + (tile0 >> 2), tid & 63u, quad_hi,
+                                      worker, step, key0, key1, sign, level);
+                lds_sign[at] = static_cast<uint8_t>(sign);
+                stage_bytes_v(&lds_level[at * e.b], level, e.b);
+            }
+            dq_wave_sync();
+            qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], QP_WAVE_TILE * TILES / 8, tid & 63u);
+            qp_store_wave(msg + (padded_elems >> 3) + e.level_start + ((chunk0 + wave0 - e.seg_start) >> 3) * e.b,
+                          &lds_level[(wave0 >> 3) * e.b], QP_WAVE_TILE * TILES / 8 * e.b, tid & 63u);
+            return;
+        }
+    }
+
+    int32_t seg[TILES];
 #pragma unroll
     for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES>(tid, it, n_elems)];
 
@@ -353,10 +448,6 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
         __syncthreads();
     }
 
-    const uint32_t quad_lo0 = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 2);
-    const uint32_t quad_hi = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 34);
-    const uint32_t worker = worker_base + w;
-
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
         const uint32_t e = qp_elem<TILES>(tid, it);
@@ -384,10 +475,8 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     }
     dq_wave_sync();
 
-    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
     if (wave0 < n_elems) {
         const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * TILES ? n_elems - wave0 : QP_WAVE_TILE * TILES;
-        uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
         qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], n_wave >> 3, tid & 63u);
         // level bytes of the wavefront's first element up to those of its last granule
         const int a = gseg[wave0 >> 7] - seg_first, z = gseg[(wave0 + n_wave - 1) >> 7] - seg_first;

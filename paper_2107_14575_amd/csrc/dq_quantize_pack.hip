@@ -19,12 +19,13 @@ namespace {
 template <int B, int TILES, int NORM>
 __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
-    const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
-    const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
+    const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
+    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
+    int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
     int64_t packed_stride, float* __restrict__ norms_out)
 {
-    quantize_pack_chunk<B, TILES, NORM>(grads, worker_stride, norms, n_seg, granule_cseg, cseg_seg, cseg_valid_end,
+    quantize_pack_chunk<B, TILES, NORM>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                         padded_elems, key0, key1, step, worker_base, packed, packed_stride, norms_out,
                                         blockIdx.x);
 }
@@ -32,13 +33,14 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack(
 template <int TILES, int NORM> // NORM as in k_quantize_pack
 __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
-    const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
-    const int64_t* __restrict__ cseg_valid_end, const dq_cseg_width* __restrict__ widths_table,
+    const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
+    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
+    const dq_cseg_width* __restrict__ widths_table,
     int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
     int64_t packed_stride, float* __restrict__ norms_out)
 {
-    quantize_pack_chunk_v<TILES, NORM>(grads, worker_stride, norms, n_seg, granule_cseg, cseg_seg, cseg_valid_end,
+    quantize_pack_chunk_v<TILES, NORM>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                        widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
                                        packed, packed_stride, norms_out, blockIdx.x);
 }
@@ -100,12 +102,12 @@ int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M
            uint64_t seed, uint32_t step, uint32_t worker_base, uint8_t* packed, int64_t packed_stride,
            float* norms_out, hipStream_t stream)
 {
-    constexpr int TILES = DQ_QP_TILES;
+    constexpr int TILES = NORM == 0 ? DQ_QP_TILES : 2;
     constexpr int CHUNK = QP_TILE * TILES;
     const int64_t n_chunks = (plan->padded_elems + CHUNK - 1) / CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     hipLaunchKernelGGL((k_quantize_pack<B, TILES, NORM>), dim3(static_cast<unsigned>(n_chunks), M), dim3(QP_THREADS),
-                       0, stream, grads, worker_stride, norms, plan->n_seg, plan->d_granule_cseg,
+                       0, stream, grads, worker_stride, norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,
                        plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, static_cast<uint32_t>(seed),
                        static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out);
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
@@ -176,14 +178,14 @@ int quantize_v_entry(int norm_mode, const dq_plan_t* plan, const dq_widths_t* wi
         if (zrc != DQ_OK) return zrc;
     }
     if (plan->padded_elems == 0) return DQ_OK;
-    constexpr int TILES = DQ_QP_TILES;
-    constexpr int CHUNK = QP_TILE * TILES;
+    const int TILES = norm_mode == 0 ? DQ_QP_TILES : 2;
+    const int64_t CHUNK = QP_TILE * TILES;
     const int64_t n_chunks = (plan->padded_elems + CHUNK - 1) / CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
 #define DQ_LAUNCH_QV(NORM)                                                                                        \
-    hipLaunchKernelGGL((k_quantize_pack_v<TILES, NORM>), grid, block, 0, stream, grads_dev, worker_stride_elems,  \
-                       norms_in, plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end,     \
+    hipLaunchKernelGGL((k_quantize_pack_v<(NORM == 0 ? DQ_QP_TILES : 2), NORM>), grid, block, 0, stream, grads_dev, worker_stride_elems,  \
+                       norms_in, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end,     \
                        widths->d_table, row_stride, plan->padded_elems, static_cast<uint32_t>(seed),              \
                        static_cast<uint32_t>(seed >> 32), step, worker_base, packed_dev, packed_worker_stride_bytes, \
                        norms_out)
