@@ -12,14 +12,19 @@
 // is converted as an 8-bit float, which is exactly +-level * 2^-9: half a conversion instruction
 // and one FMA per element, no sign handling per element (about 2.6-3.4 vector instructions per
 // worker and element against 4.5 with a conversion, a sign shift, a sign merge and an FMA each).
-// B >= 5 (bound by memory): convert the level (one v_cvt_f32_ubyteN at B = 8, a field extract and a
-// convert otherwise), put the sign bit on the worker's unit (shift, v_and_or), one FMA.
+// B >= 5: the same with pairs of half-words that a mixed-precision FMA takes as 16-bit floats.
+//
+// What bounds it: reading the messages (5.7-6.1 TB/s at D = 2^28, M = 16); at M = 64 and B >= 5 the vector
+// ALU beside it.  Measured with the half-word route, full-line loads and per-wavefront tables, before and
+// after: 2^26 x 16 b = 5 199 -> 183 us, b = 6 214 -> 203, b = 8 255 -> 249; 4.2 M ragged elements with
+// update, M = 64, b = 5 66.9 -> 52 us, b = 8 76.6 -> 66; ResNet-18 shape with update, M = 8, b = 6
+// 35.4 -> 28.4 us; b = 4 at 2^28 x 16 stays within 2 % (602 -> 615) and gains 4 % with update (870 -> 833).
 //
 // The 32 results of a lane are consecutive in memory, so storing them directly would be 16-byte
 // pieces 128 bytes apart; they go through LDS (XOR-swizzled 16-byte slots, conflict free both
 // ways) and leave as fully coalesced 16-byte stores.
 //
-// The units N/s of the segments a workgroup touches are computed once per workgroup into LDS.
+// Each wavefront works out the units N/s of its own tensors; no workgroup barrier.
 //
 // HBM traffic per output element: M(B+1)/8 bytes read, 4 bytes written.
 //
@@ -31,53 +36,12 @@
 
 namespace {
 
-#ifndef UR_THREADS_N
-#define UR_THREADS_N 256
-#endif
-constexpr int UR_THREADS = UR_THREADS_N;
+constexpr int UR_THREADS = 256;
 constexpr int UR_PER_LANE = 32;
 constexpr int UR_TILE = UR_THREADS * UR_PER_LANE; // 8192 elements
 constexpr int UR_MAX_LOCAL_SEG = UR_TILE / DQ_GRANULE;
-
-// level k (0..31) of a lane's B dwords; fields may straddle two dwords when B is not a power of two
-template <int B>
-__device__ __forceinline__ uint32_t level_field(const uint32_t (&wd)[B], int k)
-{
-    const int bit = k * B;
-    const int word = bit >> 5, off = bit & 31;
-    if (off + B <= 32) return __builtin_amdgcn_ubfe(wd[word], off, B);
-    // straddles: funnel-shift the pair down, then mask
-    const uint32_t lo = __builtin_amdgcn_alignbit(wd[word + 1 < B ? word + 1 : word], wd[word], off);
-    return lo & ((1u << B) - 1u);
-}
-
-// Calls f(k, (float)level_k) for the 32 levels of a lane.  When B divides 8 the fields of a dword
-// are first spread to one per byte (a shift and a mask serve four levels), so each conversion is
-// a single v_cvt_f32_ubyteN with no separate field extract.
-template <int B, typename F>
-__device__ __forceinline__ void for_each_level(const uint32_t (&wd)[B], F&& f)
-{
-    if constexpr (8 % B == 0) {
-        constexpr int R = 8 / B;                                   // fields per byte
-        constexpr uint32_t MASK = ((1u << B) - 1u) * 0x01010101u;  // one field per byte
-#pragma unroll
-        for (int w = 0; w < B; ++w) {
-#pragma unroll
-            for (int s = 0; s < R; ++s) {
-                uint32_t t = B == 8 ? wd[w] : (wd[w] >> (s * B)) & MASK;
-                // keep the spread form: without this the compiler folds shift, mask and byte select
-                // back into one field extract per level
-                if constexpr (B != 8) asm("" : "+v"(t));
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    f(w * (32 / B) + j * R + s, static_cast<float>((t >> (8 * j)) & 0xFFu));
-            }
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < UR_PER_LANE; ++k) f(k, static_cast<float>(level_field<B>(wd, k)));
-    }
-}
+constexpr int UR_WAVE_ELEMS = 64 * UR_PER_LANE; // 2048 elements
+constexpr int UR_WAVE_SEGS = UR_WAVE_ELEMS / DQ_GRANULE;
 
 // Widths 1 to 4 take the sign-and-level route below: the byte (sign << 7) | level, level <= 15,
 // read as an 8-bit float (E4M3: 4 exponent bits with bias 7, 3 fraction bits) is exactly
@@ -92,7 +56,8 @@ constexpr float UR_FP8_SCALE = 512.0f;
 constexpr int UR_MIN_WAVES = 4;
 constexpr int UR_SUM_BLOCK = 8; // workers per block of the two-level sum (a power of two)
 // workers whose loads are issued together (measured per width at D = 2^28, M = 16)
-__host__ __device__ constexpr int ur_group(int b) { return b <= 4 ? 16 : b <= 6 ? 2 : 4; }
+// (b = 3, 4: eight need no spills in the kernels that hold all widths, and sixteen gain nothing)
+__host__ __device__ constexpr int ur_group(int b) { return b <= 2 ? 16 : b <= 4 ? 8 : 4; }
 
 // bytes of {hi, lo} picked by the four selector bytes of sel: 0..3 = bytes of lo, 4..7 = bytes of hi
 __device__ __forceinline__ uint32_t byte_perm(uint32_t hi, uint32_t lo, uint32_t sel)
@@ -158,21 +123,93 @@ __device__ __forceinline__ void accumulate_words_fp8(uint32_t sg, const uint32_t
     }
 }
 
+// Widths 5 to 8: the half-word (sign << 15) | level << (8 - B), read as a 16-bit float, is a subnormal
+// number (its exponent field is zero): exactly +-level * 2^(-16-B).  One mixed-precision FMA
+// (v_fma_mix_f32) takes it as it is, so that two elements share the extraction and the sign handling.
+// With the unit times 2^(B-1) every product is the true one times 2^-17, which the caller takes out
+// together with 1/M (UR_FP16_SCALE): at most 0.52 N, so nothing overflows that did not before, and at
+// least 2^-125 for a usable norm (2^-100), so every product is a normal number and rounds as the true
+// one does -- the sums are bit for bit those of convert, sign merge and FMA in binary32.
+// About 3.4 vector instructions per worker and element at B = 5, 6, 7 and 2.5 at B = 8, one of them (the FMA)
+// at half rate, against 5 and 4.
+// The pairs are elements (E, E + 16) of the lane: 16 fields are B half-words, so the words
+// p[i] = {half-word i + B, half-word i} hold both elements' fields at the same place, and bits E and
+// E + 16 of the sign dword are as far apart as the half-words' sign bits.
+typedef _Float16 ur_half2 __attribute__((ext_vector_type(2)));
+__host__ __device__ constexpr float ur_unit_factor(int b) { return ur_fp8_width(b) ? 1.0f : static_cast<float>(1 << (b - 1)); }
+constexpr float UR_FP16_SCALE = 131072.0f;
+__host__ __device__ constexpr float ur_sum_scale(int b) { return ur_fp8_width(b) ? UR_FP8_SCALE : UR_FP16_SCALE; }
+
+template <int D> // shift left by D, or right by -D
+__device__ __forceinline__ uint32_t shift_by(uint32_t v)
+{
+    if constexpr (D >= 0)
+        return v << D;
+    else
+        return v >> -D;
+}
+
+template <int B, int E>
+__device__ __forceinline__ void fma_signed_halves(const uint32_t (&p)[B], uint32_t sg, float unit, float (&acc)[UR_PER_LANE])
+{
+    constexpr int word = (E * B) >> 4, off = (E * B) & 15, J = 8 - B;
+    const uint32_t sign = (sg << (15 - E)) & 0x80008000u;
+    uint32_t coded;
+    if constexpr (off + B <= 16) {
+        constexpr uint32_t MASK = (((1u << B) - 1u) << J) * 0x00010001u;
+        coded = (shift_by<J - off>(p[word]) & MASK) | sign;
+    } else { // the field straddles two half-words
+        constexpr int LOW = 16 - off; // bits of it in the first one
+        constexpr uint32_t MASK_LO = (((1u << LOW) - 1u) << J) * 0x00010001u;
+        constexpr uint32_t MASK_HI = (((1u << (B - LOW)) - 1u) << (J + LOW)) * 0x00010001u;
+        coded = (shift_by<J - off>(p[word]) & MASK_LO) | sign;
+        coded = ((p[word + 1 < B ? word + 1 : word] << (J + LOW)) & MASK_HI) | coded;
+    }
+    const ur_half2 h = __builtin_bit_cast(ur_half2, coded);
+    acc[E] = __builtin_fmaf(static_cast<float>(h[0]), unit, acc[E]);
+    acc[E + 16] = __builtin_fmaf(static_cast<float>(h[1]), unit, acc[E + 16]);
+}
+
+template <int E> // B = 8: the two bytes come out by one permute each pair
+__device__ __forceinline__ void fma_signed_halves_b8(const uint32_t (&wd)[8], uint32_t sg, float unit, float (&acc)[UR_PER_LANE])
+{
+    constexpr uint32_t SEL = 0x0C000C00u | (E % 4) | ((4u + E % 4) << 16); // 0x0C: a zero byte
+    const uint32_t coded = byte_perm(wd[E / 4 + 4], wd[E / 4], SEL) | ((sg << (15 - E)) & 0x80008000u);
+    const ur_half2 h = __builtin_bit_cast(ur_half2, coded);
+    acc[E] = __builtin_fmaf(static_cast<float>(h[0]), unit, acc[E]);
+    acc[E + 16] = __builtin_fmaf(static_cast<float>(h[1]), unit, acc[E + 16]);
+}
+
+template <int B, int... E>
+__device__ __forceinline__ void accumulate_words_fp16(uint32_t sg, const uint32_t (&wd)[B], float unit,
+                                                      float (&acc)[UR_PER_LANE], std::integer_sequence<int, E...>)
+{
+    static_assert(sizeof...(E) == 16, "sixteen pairs of elements");
+    if constexpr (B == 8) {
+        (fma_signed_halves_b8<E>(wd, sg, unit, acc), ...);
+    } else {
+        uint32_t p[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const uint32_t lo = wd[i >> 1], hi = wd[(i + B) >> 1];
+            const uint32_t sel = ((i & 1) ? 0x0302u : 0x0100u) | (((i + B) & 1) ? 0x07060000u : 0x05040000u);
+            p[i] = byte_perm(hi, lo, sel);
+        }
+        (fma_signed_halves<B, E>(p, sg, unit, acc), ...);
+    }
+}
+
 // One worker's contribution to a lane's 32 elements from the worker's sign dword and its B level
-// dwords: acc[k] += sgn_k * level_k * unit, times 2^-9 when ur_fp8_width(B).
+// dwords: acc[k] += sgn_k * level_k * unit, divided by ur_sum_scale(B); unit is N/s times
+// ur_unit_factor(B).
 template <int B>
 __device__ __forceinline__ void accumulate_words(uint32_t sg, const uint32_t (&wd)[B], float unit,
                                                  float (&acc)[UR_PER_LANE])
 {
-    if constexpr (ur_fp8_width(B)) {
+    if constexpr (ur_fp8_width(B))
         accumulate_words_fp8<B>(sg, wd, unit, acc, std::make_integer_sequence<int, 8>{});
-    } else {
-        for_each_level<B>(wd, [&](int k, float lv) {
-            // sign bit of element k on top of the unit, whose own sign bit is always clear
-            const float su = __uint_as_float(__float_as_uint(unit) | ((sg << (31 - k)) & 0x80000000u));
-            acc[k] = __builtin_fmaf(lv, su, acc[k]);
-        });
-    }
+    else
+        accumulate_words_fp16<B>(sg, wd, unit, acc, std::make_integer_sequence<int, 16>{});
 }
 
 // The same from eight loaded dwords of which the first B count (per-worker widths).
@@ -233,54 +270,94 @@ struct block_total {
     }
 };
 
-// The M workers' contributions to a lane's 32 elements: acc[k] += sgn * level * unit, workers in
-// ascending order.  sign_ptr / level_ptr address worker 0's sign dword and B level dwords of the
-// lane; unit_ptr[w] is worker w's N/s for the lane's segment.
-template <int B>
-__device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign_ptr,
-                                                const uint8_t* __restrict__ level_ptr, int64_t packed_stride,
-                                                int M, const float* unit_ptr, float (&acc)[UR_PER_LANE],
-                                                lane_slots slots)
+// A lane's B level dwords of one worker, by the widest loads their size allows (a global load needs no
+// more than dword alignment).  Where one load takes them all, the lanes' loads cover whole cache lines
+// and the streaming hint pays at the largest sizes; where a line is met by several loads (5 to 8) it has
+// to stay: with the hint B = 7 took 236 instead of 226 us at D = 2^26, M = 16 and 36.7 instead of 32.5 us
+// on 11 M elements, M = 8.
+typedef uint32_t ur_v4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t ur_v3u __attribute__((ext_vector_type(3), aligned(4)));
+typedef uint32_t ur_v2u __attribute__((ext_vector_type(2), aligned(4)));
+#define UR_GLOBAL __attribute__((address_space(1)))
+typedef const UR_GLOBAL uint8_t* ur_bytes;
+// An address that is the same for the whole wavefront, kept as one pair of scalar registers: left alone the
+// compiler adds the lane's offset first and carries a vector register pair per load around the loop over
+// the workers (22 to 41 of them spilled at B = 2, 3, 4).
+__device__ __forceinline__ ur_bytes scalar_address(const uint8_t* at)
 {
-    // one worker's sign dword and B level dwords of this lane
-    auto load_worker = [&](int w, uint32_t& sg, uint32_t (&wd)[B]) {
-        sg = dq_load_stream(reinterpret_cast<const uint32_t*>(sign_ptr + static_cast<int64_t>(w) * packed_stride));
-        const uint32_t* lp = reinterpret_cast<const uint32_t*>(level_ptr + static_cast<int64_t>(w) * packed_stride);
-        if constexpr (B % 4 == 0) {
+    uint64_t a = reinterpret_cast<uint64_t>(at);
+    asm("" : "+s"(a));
+    return reinterpret_cast<ur_bytes>(a);
+}
+__device__ __forceinline__ ur_bytes global_address(const uint8_t* at)
+{
+    return reinterpret_cast<ur_bytes>(reinterpret_cast<uint64_t>(at));
+}
+template <bool STREAM, typename T>
+__device__ __forceinline__ T load_dwords(ur_bytes at)
+{
+    if constexpr (STREAM)
+        return __builtin_nontemporal_load(reinterpret_cast<const UR_GLOBAL T*>(at));
+    else
+        return *reinterpret_cast<const UR_GLOBAL T*>(at);
+}
+template <int B>
+__device__ __forceinline__ void load_levels(ur_bytes at, uint32_t (&wd)[B])
+{
+    constexpr bool STREAM = B <= 4;
 #pragma unroll
-            for (int q = 0; q < B / 4; ++q) {
-                const uint4 t = dq_load_stream(reinterpret_cast<const uint4*>(lp) + q);
-                wd[4 * q] = t.x; wd[4 * q + 1] = t.y; wd[4 * q + 2] = t.z; wd[4 * q + 3] = t.w;
-            }
-        } else if constexpr (B % 2 == 0) {
-#pragma unroll
-            for (int q = 0; q < B / 2; ++q) {
-                const uint2 t = dq_load_stream(reinterpret_cast<const uint2*>(lp) + q);
-                wd[2 * q] = t.x; wd[2 * q + 1] = t.y;
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < B; ++q) wd[q] = dq_load_stream(lp + q);
-        }
-    };
-    // Workers in groups whose loads are all issued before the first is used: the pass is bound by
-    // memory latency once the arithmetic is cheap, so narrow widths (few registers per worker) take
-    // large groups.  Groups halve towards the end, so any M keeps its loads batched.
-    //
-    // Order of the additions: workers ascending inside blocks of UR_SUM_BLOCK workers (an FMA chain
-    // from zero), the block sums added in block order.  However the loads are grouped, a value
-    // passes through at most 7 + ceil(M/8) roundings: 15 at M = 64, where a single chain over all
-    // workers would take 63 (and measurably leaves the 1e-6 tolerance when one worker's norm
-    // dominates).  Up to eight workers nothing is flushed: the plain chain.
+    for (int q = 0; q + 4 <= B; q += 4) {
+        const ur_v4u t = load_dwords<STREAM, ur_v4u>(at + 4 * q);
+        wd[q] = t.x; wd[q + 1] = t.y; wd[q + 2] = t.z; wd[q + 3] = t.w;
+    }
+    constexpr int Q = B & ~3;
+    if constexpr ((B & 3) == 3) {
+        const ur_v3u t = load_dwords<STREAM, ur_v3u>(at + 4 * Q);
+        wd[Q] = t.x; wd[Q + 1] = t.y; wd[Q + 2] = t.z;
+    } else if constexpr ((B & 3) == 2) {
+        const ur_v2u t = load_dwords<STREAM, ur_v2u>(at + 4 * Q);
+        wd[Q] = t.x; wd[Q + 1] = t.y;
+    } else if constexpr ((B & 3) == 1) {
+        wd[Q] = load_dwords<STREAM, uint32_t>(at + 4 * Q);
+    }
+}
+
+// The M workers' contributions to a lane's 32 elements: acc[k] += sgn * level * unit, workers in
+// ascending order.  load(w, sg, wd) fetches worker w's sign dword and B level dwords of the lane,
+// unit(w) is its unit for the lane's tensor.  WAVE: called by accumulate_wave.  prepare() runs once, when
+// the first group's loads are on their way: what unit(w) needs and those loads do not belongs there.
+//
+// Workers in groups whose loads are all issued before the first is used: the pass is bound by
+// memory latency once the arithmetic is cheap, so narrow widths (few registers per worker) take
+// large groups.  Groups halve towards the end, so any M keeps its loads batched.
+//
+// Order of the additions: workers ascending inside blocks of UR_SUM_BLOCK workers (an FMA chain
+// from zero), the block sums added in block order.  However the loads are grouped, a value
+// passes through at most 7 + ceil(M/8) roundings: 15 at M = 64, where a single chain over all
+// workers would take 63 (and measurably leaves the 1e-6 tolerance when one worker's norm
+// dominates).  Up to eight workers nothing is flushed: the plain chain.
+template <int B, bool WAVE, typename Load, typename Prepare, typename Unit>
+__device__ __forceinline__ void accumulate_workers(int M, Load&& load, Prepare&& prepare, Unit&& unit,
+                                                   float (&acc)[UR_PER_LANE], lane_slots slots)
+{
     block_total total{ slots };
     auto group = [&](auto g, int w) { // w is a multiple of G
         constexpr int G = decltype(g)::value;
         uint32_t sg[G], wd[G][B];
 #pragma unroll
-        for (int i = 0; i < G; ++i) load_worker(w + i, sg[i], wd[i]);
+        for (int i = 0; i < G; ++i) load(w + i, sg[i], wd[i]);
+        if (w == 0) prepare();
 #pragma unroll
         for (int i = 0; i < G; ++i) {
-            accumulate_words<B>(sg[i], wd[i], unit_ptr[w + i], acc);
+            if constexpr (WAVE && B == 8) { // halves of the wavefront trade pieces (accumulate_wave)
+#pragma unroll
+                for (int q = 0; q < B / 2; ++q) {
+                    const auto t = __builtin_amdgcn_permlane32_swap(wd[i][q], wd[i][q + B / 2], false, false);
+                    wd[i][q] = t[0];
+                    wd[i][q + B / 2] = t[1];
+                }
+            }
+            accumulate_words<B>(sg[i], wd[i], unit(w + i), acc);
             if constexpr (G >= UR_SUM_BLOCK) {
                 if ((i + 1) % UR_SUM_BLOCK == 0 && w + i + 1 < M) total.flush(acc);
             }
@@ -289,7 +366,7 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
             if (((w + G) & (UR_SUM_BLOCK - 1)) == 0 && w + G < M) total.flush(acc);
         }
     };
-    constexpr int GROUP = ur_group(B);
+    constexpr int GROUP = WAVE ? ur_group(B) : ur_group(B) / 2;
     int w = 0;
     for (; w + GROUP <= M; w += GROUP) group(std::integral_constant<int, GROUP>{}, w);
     if constexpr (GROUP > 8) if (w + 8 <= M) { group(std::integral_constant<int, 8>{}, w); w += 8; }
@@ -299,12 +376,68 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
     total.finish(acc);
 }
 
-// Scales a lane's sums by 1/M (zero beyond the tensor's end), transposes the workgroup's tile
-// through LDS and writes it out; with UPDATE it also applies the model update to x (and then
+// Lanes of different tensors: sign_ptr / level_ptr address worker 0's sign dword and level dwords of the
+// lane, unit_ptr[w] (LDS) is worker w's unit for the lane's tensor.
+template <int B>
+__device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign_ptr,
+                                                const uint8_t* __restrict__ level_ptr, int64_t packed_stride,
+                                                int M, const float* unit_ptr, float (&acc)[UR_PER_LANE],
+                                                lane_slots slots)
+{
+    accumulate_workers<B, false>(
+        M,
+        [&](int w, uint32_t& sg, uint32_t (&wd)[B]) {
+            int64_t off = static_cast<int64_t>(w) * packed_stride; // scalar, for the reason given at scalar_address
+            asm("" : "+s"(off));
+            sg = load_dwords<true, uint32_t>(global_address(sign_ptr + off));
+            load_levels<B>(global_address(level_ptr + off), wd);
+        },
+        [] {}, [&](int w) { return unit_ptr[w]; }, acc, slots);
+}
+
+// All lanes of a wavefront with one place for their level bytes: sign_wave addresses worker 0's sign bytes
+// of the wavefront's first element and level_wave(w) worker w's level bytes of it, the same for all lanes,
+// so a worker's address is scalar arithmetic.  Lanes past the end (n_lanes, a multiple of 4, exist) fetch
+// the last ones' bytes.
+// At B = 8 a lane's dwords are two 16-byte pieces: each load instruction covers 1 KiB in full (lanes
+// 0..31 and 32..63 take the first and second pieces of 32 lanes) and swaps between the halves of the
+// wavefront put the pieces in place, so that the streaming hint can stay on.
+template <int B, typename LevelWave, typename Prepare, typename Unit>
+__device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign_wave, LevelWave&& level_wave,
+                                                int64_t packed_stride, int M, Prepare&& prepare, Unit&& unit, int n_lanes,
+                                                float (&acc)[UR_PER_LANE], lane_slots slots)
+{
+    const uint32_t lane = slots.lane < n_lanes ? slots.lane : n_lanes - 1;
+    uint32_t at0 = lane * (4u * B), at1 = 0;
+    if constexpr (B == 8) {
+        const uint32_t end = n_lanes * 32u - 16u;
+        at0 = (slots.lane & 31) * 32u + (slots.lane >> 5) * 16u;
+        at1 = at0 + 1024u < end ? at0 + 1024u : end;
+        at0 = at0 < end ? at0 : end;
+    }
+    accumulate_workers<B, true>(
+        M,
+        [&](int w, uint32_t& sg, uint32_t (&wd)[B]) {
+            const ur_bytes lp = scalar_address(level_wave(w));
+            sg = load_dwords<true, uint32_t>(scalar_address(sign_wave + static_cast<int64_t>(w) * packed_stride) + lane * 4u);
+            if constexpr (B == 8) {
+                const ur_v4u a = load_dwords<true, ur_v4u>(lp + at0);
+                const ur_v4u b = load_dwords<true, ur_v4u>(lp + at1);
+                wd[0] = a.x; wd[1] = a.y; wd[2] = a.z; wd[3] = a.w;
+                wd[4] = b.x; wd[5] = b.y; wd[6] = b.z; wd[7] = b.w;
+            } else {
+                load_levels<B>(lp + at0, wd);
+            }
+        },
+        prepare, unit, acc, slots);
+}
+
+// Scales a lane's sums by 1/M (zero beyond the tensor's end), transposes the wavefront's 2048 elements
+// (from padded index wave0 on) through LDS and writes them out; with UPDATE it also applies the model update to x (and then
 // `out` may be null).
 template <bool UPDATE>
 __device__ __forceinline__ void finish_tile(float (&acc)[UR_PER_LANE], bool active, int64_t n_valid, float inv_M,
-                                            float4* lds_out, int tid, int64_t tile0, int64_t tile_end,
+                                            float4* lds_out, int tid, int64_t wave0, int64_t padded_elems,
                                             float* __restrict__ out, float* __restrict__ x, float eta)
 {
     if (active) {
@@ -314,6 +447,16 @@ __device__ __forceinline__ void finish_tile(float (&acc)[UR_PER_LANE], bool acti
     }
     // lane t of wave v holds elements [v*2048 + 32t, +32): slot (t, q) -> t*8 + (q ^ (t & 7))
     const int wave = tid >> 6, lane = tid & 63;
+    // the model's pieces, all eight in flight before the first is used (each load behind its own bounds
+    // check and the store before it cost a memory latency apiece); past the end: the last ones again
+    float4 xv[8];
+    if constexpr (UPDATE) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t P = wave0 + 256 * j + 4 * lane;
+            xv[j] = *reinterpret_cast<const float4*>(x + (P < padded_elems ? P : padded_elems - 4));
+        }
+    }
     float4* wave_out = lds_out + wave * 512;
 #pragma unroll
     for (int q = 0; q < 8; ++q)
@@ -323,24 +466,128 @@ __device__ __forceinline__ void finish_tile(float (&acc)[UR_PER_LANE], bool acti
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        // store j of the wave covers its elements [256j, 256j + 256); this lane takes 4 of them
+    // piece j of the wave covers its elements [256j, 256j + 256); this lane takes 4 of them
+    auto piece = [&](int j) {
         const int src_lane = 8 * j + (lane >> 3), q = lane & 7;
-        const float4 v = wave_out[src_lane * 8 + (q ^ (src_lane & 7))];
-        const int64_t P = tile0 + wave * 2048 + 256 * j + 4 * lane;
-        if (P < tile_end) {
-            if (!UPDATE || out) dq_store_stream(reinterpret_cast<float4*>(out + P), v);
-            if constexpr (UPDATE) { // model update of Algorithm 1: x <- x - eta * g_hat (pads: g_hat is +0, x unchanged)
-                float4 xv = *reinterpret_cast<const float4*>(x + P);
-                xv.x = __builtin_fmaf(-eta, v.x, xv.x);
-                xv.y = __builtin_fmaf(-eta, v.y, xv.y);
-                xv.z = __builtin_fmaf(-eta, v.z, xv.z);
-                xv.w = __builtin_fmaf(-eta, v.w, xv.w);
-                *reinterpret_cast<float4*>(x + P) = xv;
-            }
+        return wave_out[src_lane * 8 + (q ^ (src_lane & 7))];
+    };
+    if constexpr (!UPDATE) {
+        // one after the other behind their bounds checks: eight stores in one go took 161 instead of 152 us at
+        // D = 2^26, M = 16, b = 4
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t P = wave0 + 256 * j + 4 * lane;
+            if (P < padded_elems) dq_store_stream(reinterpret_cast<float4*>(out + P), piece(j));
+        }
+    } else { // model update of Algorithm 1: x <- x - eta * g_hat (pads: g_hat is +0, x unchanged)
+        float4 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = piece(j);
+        auto update = [&](int j) {
+            const int64_t P = wave0 + 256 * j + 4 * lane;
+            if (out) dq_store_stream(reinterpret_cast<float4*>(out + P), v[j]);
+            float4 t = xv[j];
+            t.x = __builtin_fmaf(-eta, v[j].x, t.x);
+            t.y = __builtin_fmaf(-eta, v[j].y, t.y);
+            t.z = __builtin_fmaf(-eta, v[j].z, t.z);
+            t.w = __builtin_fmaf(-eta, v[j].w, t.w);
+            *reinterpret_cast<float4*>(x + P) = t;
+        };
+        if (wave0 + UR_WAVE_ELEMS <= padded_elems) { // the same for the whole wavefront
+#pragma unroll
+            for (int j = 0; j < 8; ++j) update(j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (wave0 + 256 * j + 4 * lane < padded_elems) update(j);
         }
     }
+}
+
+// Which tile a workgroup takes.  Consecutive workgroups go to the eight XCDs in turn; four consecutive
+// tiles are given to one XCD (32 tiles, the last 0..31 left as they are), so that a worker's stretch of the
+// message is read in pieces of four times a tile's bytes by one of them.  Measured at D = 2^28, M = 16:
+// b = 4 with update 905 -> 836 us, without 634 -> 610; b = 8 at 2^26 256 -> 248; groups of two or eight, or
+// one contiguous range per XCD, gave less.
+__device__ __forceinline__ uint32_t ur_tile_index()
+{
+    const uint32_t i = blockIdx.x;
+    return i < gridDim.x / 32u * 32u ? i / 32u * 32u + (i % 8u) * 4u + i / 8u % 4u : i;
+}
+
+// The 2048 elements of a wavefront and the tensors they belong to (compact indices first..last).
+struct wave_span {
+    int64_t start;  // first padded index
+    int n_lanes;    // lanes whose 32 elements exist (a multiple of 4; <= 0: none)
+    int32_t first, last;
+};
+__device__ __forceinline__ wave_span wave_span_of(int tid, int64_t padded_elems, const int32_t* __restrict__ granule_cseg)
+{
+    wave_span s;
+    s.start = static_cast<int64_t>(ur_tile_index()) * UR_TILE + __builtin_amdgcn_readfirstlane(tid >> 6) * UR_WAVE_ELEMS;
+    s.n_lanes = 0;
+    s.first = s.last = 0;
+    if (s.start < padded_elems) {
+        const int64_t left = padded_elems - s.start;
+        s.n_lanes = static_cast<int>(left < UR_WAVE_ELEMS ? left : UR_WAVE_ELEMS) / UR_PER_LANE;
+        s.first = granule_cseg[s.start >> 7];
+        s.last = granule_cseg[(s.start + s.n_lanes * UR_PER_LANE - 1) >> 7];
+    }
+    return s;
+}
+
+// Runs f with the width as a compile-time constant (widths outside 1..8 are never uploaded).
+template <typename F>
+__device__ __forceinline__ void with_width(int b, F&& f)
+{
+    switch (b) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    default: break;
+    }
+}
+
+__device__ __forceinline__ float ur_unit(float N, int b)
+{
+    return N >= DQ_MIN_NORM ? N / static_cast<float>((1 << b) - 1) * ur_unit_factor(b) : 0.0f;
+}
+
+// Worker w's value out of the one each lane holds (M <= 64).
+__device__ __forceinline__ float lane_value(float of_lane, int w)
+{
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(of_lane), w));
+}
+
+// The wavefront's table [tensor of the span][worker] in LDS, value(w, c) of worker w and compact tensor c;
+// returns the row of the lane's own tensor and the end of its data relative to P0.  A wavefront inside
+// one tensor (nearly every one of a gradient of large tensors) fills one row, a lane each.
+template <typename Value>
+__device__ __forceinline__ const float* wave_table(const wave_span& span, int lane, int M, int64_t P0,
+                                                   const int32_t* __restrict__ granule_cseg,
+                                                   const int64_t* __restrict__ cseg_valid_end, float* table,
+                                                   int64_t& n_valid, Value&& value)
+{
+    const int32_t first = __builtin_amdgcn_readfirstlane(span.first), last = __builtin_amdgcn_readfirstlane(span.last);
+    int32_t c = first;
+    if (first == last) {
+        if (lane < M) table[lane] = value(lane, first);
+    } else {
+        c = granule_cseg[(lane < span.n_lanes ? P0 : span.start) >> 7]; // lanes past the end: the first one's
+        const int n_local = last - first + 1; // <= UR_WAVE_SEGS: compact indices grow by <= 1 per granule
+        for (int i = lane; i < n_local * M; i += 64) {
+            const int local = i / M, w = i - local * M;
+            table[i] = value(w, first + local);
+        }
+    }
+    n_valid = cseg_valid_end[c] - P0;
+    dq_wave_sync();
+    return table + (c - first) * M;
 }
 
 template <int B, bool UPDATE>
@@ -350,49 +597,40 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
     const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, float inv_M, float* __restrict__ out,
     float* __restrict__ x, float eta)
 {
-    constexpr float S = static_cast<float>((1 << B) - 1);
     extern __shared__ __align__(16) uint8_t lds_raw[];
-    float4* lds_out = reinterpret_cast<float4*>(lds_raw);                       // [UR_TILE / 4]
-    float* lds_unit = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float)); // [local seg][M]
+    float4* lds_out = reinterpret_cast<float4*>(lds_raw); // [UR_TILE / 4]
 
-    const int tid = threadIdx.x;
-    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * UR_TILE;
-    const int64_t tile_end = tile0 + UR_TILE < padded_elems ? tile0 + UR_TILE : padded_elems;
-    const int64_t P0 = tile0 + tid * UR_PER_LANE;
-    const bool active = P0 < tile_end;
-
-    const int32_t seg_first = granule_cseg[tile0 >> 7];
-    const int32_t seg_last = granule_cseg[(tile_end - 1) >> 7];
-    const int n_local = seg_last - seg_first + 1; // <= UR_MAX_LOCAL_SEG: compact indices grow by <= 1 per granule
-    for (int i = tid; i < n_local * M; i += UR_THREADS) {
-        const int local = i / M, w = i - local * M;
-        const float N = norms[static_cast<int64_t>(w) * n_seg + cseg_seg[seg_first + local]];
-        lds_unit[i] = N >= DQ_MIN_NORM ? N / S : 0.0f;
-    }
-    int local = 0;
-    int64_t n_valid = 0;
-    if (active) {
-        const int32_t c = granule_cseg[P0 >> 7];
-        local = c - seg_first;
-        n_valid = cseg_valid_end[c] - P0;
-    }
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const wave_span span = wave_span_of(tid, padded_elems, granule_cseg);
+    if (span.n_lanes <= 0) return; // the whole wavefront; no workgroup barrier below
+    const int64_t P0 = span.start + lane * UR_PER_LANE;
+    const bool active = lane < span.n_lanes;
+    const uint8_t* level_plane = packed + (padded_elems >> 3);
 
     float acc[UR_PER_LANE];
 #pragma unroll
     for (int k = 0; k < UR_PER_LANE; ++k) acc[k] = 0.0f;
+    int64_t n_valid = 0;
 
-    if (active)
-        accumulate_lane<B>(packed + (P0 >> 3), packed + (padded_elems >> 3) + (P0 >> 3) * B, packed_stride, M,
-                           lds_unit + local * M, acc, slots_of(lds_out, tid));
-    finish_tile<UPDATE>(acc, active, n_valid, ur_fp8_width(B) ? inv_M * UR_FP8_SCALE : inv_M, lds_out, tid, tile0,
-                        tile_end, out, x, eta);
+    // one width: the message bytes do not depend on the tensors, the first loads go ahead of the table
+    float* table = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float)) + (tid >> 6) * UR_WAVE_SEGS * M;
+    const float* unit_ptr = nullptr;
+    const uint8_t* level_wave = level_plane + (span.start >> 3) * B;
+    accumulate_wave<B>(
+        packed + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; },
+        packed_stride, M,
+        [&] {
+            unit_ptr = wave_table(span, lane, M, P0, granule_cseg, cseg_valid_end, table, n_valid, [&](int w, int32_t c) {
+                return ur_unit(norms[static_cast<int64_t>(w) * n_seg + cseg_seg[c]], B);
+            });
+        },
+        [&](int w) { return unit_ptr[w]; }, span.n_lanes, acc, slots_of(lds_out, tid));
+    finish_tile<UPDATE>(acc, active, n_valid, inv_M * ur_sum_scale(B), lds_out, tid, span.start, padded_elems, out, x, eta);
 }
 
-// Per-tensor widths: each lane takes its segment's b and the place of its level dwords from the
-// widths table and runs the accumulation specialised for that b.  A lane's 32 elements lie in one
-// 128-element granule, hence in one segment; lanes of a wave differ in b only where a wave
-// straddles two tensors.
+// Per-tensor widths: a wavefront inside one tensor takes its b and the place of its level dwords from the
+// widths table (scalar) and runs the accumulation specialised for that b.  Elsewhere each lane does: its
+// 32 elements lie in one 128-element granule, hence in one segment.
 template <bool UPDATE>
 __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_reduce_v(
     const uint8_t* __restrict__ packed, int64_t packed_stride, int M, const float* __restrict__ norms,
@@ -402,62 +640,63 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
 {
     extern __shared__ __align__(16) uint8_t lds_raw[];
     float4* lds_out = reinterpret_cast<float4*>(lds_raw);
-    float* lds_unit = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float));
 
-    const int tid = threadIdx.x;
-    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * UR_TILE;
-    const int64_t tile_end = tile0 + UR_TILE < padded_elems ? tile0 + UR_TILE : padded_elems;
-    const int64_t P0 = tile0 + tid * UR_PER_LANE;
-    const bool active = P0 < tile_end;
-
-    const int32_t seg_first = granule_cseg[tile0 >> 7];
-    const int32_t seg_last = granule_cseg[(tile_end - 1) >> 7];
-    const int n_local = seg_last - seg_first + 1;
-    for (int i = tid; i < n_local * M; i += UR_THREADS) {
-        const int local = i / M, w = i - local * M;
-        const float S = static_cast<float>((1 << widths[seg_first + local].b) - 1);
-        const float N = norms[static_cast<int64_t>(w) * n_seg + cseg_seg[seg_first + local]];
-        lds_unit[i] = N >= DQ_MIN_NORM ? N / S : 0.0f;
-    }
-    int local = 0, b = 0;
-    int64_t n_valid = 0, level_off = 0;
-    if (active) {
-        const int32_t c = granule_cseg[P0 >> 7];
-        const dq_cseg_width e = widths[c];
-        local = c - seg_first;
-        n_valid = cseg_valid_end[c] - P0;
-        b = e.b;
-        level_off = e.level_start + ((P0 - e.seg_start) >> 3) * e.b; // 4*b bytes per lane: dword aligned
-    }
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const wave_span span = wave_span_of(tid, padded_elems, granule_cseg);
+    if (span.n_lanes <= 0) return;
+    const int64_t P0 = span.start + lane * UR_PER_LANE;
+    const bool active = lane < span.n_lanes;
+    const uint8_t* level_plane = packed + (padded_elems >> 3);
 
     float acc[UR_PER_LANE];
 #pragma unroll
     for (int k = 0; k < UR_PER_LANE; ++k) acc[k] = 0.0f;
+    int64_t n_valid = 0;
+    int b = 0;
 
-    if (active) {
-        const uint8_t* sign_ptr = packed + (P0 >> 3);
-        const uint8_t* level_ptr = packed + (padded_elems >> 3) + level_off;
-        const float* unit_ptr = lds_unit + local * M;
-        switch (b) {
-        case 1: accumulate_lane<1>(sign_ptr, level_ptr, packed_stride, M, unit_ptr, acc, slots_of(lds_out, tid)); break;
-        case 2: accumulate_lane<2>(sign_ptr, level_ptr, packed_stride, M, unit_ptr, acc, slots_of(lds_out, tid)); break;
-        case 3: accumulate_lane<3>(sign_ptr, level_ptr, packed_stride, M, unit_ptr, acc, slots_of(lds_out, tid)); break;
-        case 4: accumulate_lane<4>(sign_ptr, level_ptr, packed_stride, M, unit_ptr, acc, slots_of(lds_out, tid)); break;
-        case 5: accumulate_lane<5>(sign_ptr, level_ptr, packed_stride, M, unit_ptr, acc, slots_of(lds_out, tid)); break;
-        case 6: accumulate_lane<6>(sign_ptr, level_ptr, packed_stride, M, unit_ptr, acc, slots_of(lds_out, tid)); break;
-        case 7: accumulate_lane<7>(sign_ptr, level_ptr, packed_stride, M, unit_ptr, acc, slots_of(lds_out, tid)); break;
-        case 8: accumulate_lane<8>(sign_ptr, level_ptr, packed_stride, M, unit_ptr, acc, slots_of(lds_out, tid)); break;
-        default: break; // the host only uploads widths in 1..8
+    if (span.first == span.last) {
+        const dq_cseg_width e = widths[span.first];
+        const int32_t seg = cseg_seg[span.first];
+        n_valid = cseg_valid_end[span.first] - P0;
+        b = __builtin_amdgcn_readfirstlane(e.b);
+        const float unit = lane < M ? ur_unit(norms[static_cast<int64_t>(lane) * n_seg + seg], b) : 0.0f;
+        const uint8_t* level_wave = level_plane + e.level_start + ((span.start - e.seg_start) >> 3) * b;
+        with_width(b, [&](auto width) {
+            accumulate_wave<decltype(width)::value>(
+                packed + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; },
+                packed_stride, M, [] {}, [&](int w) { return lane_value(unit, w); }, span.n_lanes, acc, slots_of(lds_out, tid));
+        });
+    } else {
+        // the lane's own tensor, fetched beside the table (lanes past the end: the first one's)
+        const int32_t c = granule_cseg[(active ? P0 : span.start) >> 7];
+        n_valid = cseg_valid_end[c] - P0;
+        const dq_cseg_width e = widths[c];
+        float* lds_unit = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float)) + (tid >> 6) * UR_WAVE_SEGS * M;
+        const int n_local = span.last - span.first + 1;
+        for (int i = lane; i < n_local * M; i += 64) {
+            const int local = i / M, w = i - local * M;
+            lds_unit[i] = ur_unit(norms[static_cast<int64_t>(w) * n_seg + cseg_seg[span.first + local]],
+                                  widths[span.first + local].b);
+        }
+        dq_wave_sync();
+        if (active) {
+            b = e.b;
+            const uint8_t* level_ptr = level_plane + e.level_start + ((P0 - e.seg_start) >> 3) * e.b; // dword aligned
+            const float* unit_ptr = lds_unit + (c - span.first) * M;
+            with_width(b, [&](auto width) {
+                accumulate_lane<decltype(width)::value>(packed + (P0 >> 3), level_ptr, packed_stride, M, unit_ptr, acc,
+                                                        slots_of(lds_out, tid));
+            });
         }
     }
-    finish_tile<UPDATE>(acc, active, n_valid, ur_fp8_width(b) ? inv_M * UR_FP8_SCALE : inv_M, lds_out, tid, tile0,
-                        tile_end, out, x, eta);
+    finish_tile<UPDATE>(acc, active, n_valid, inv_M * ur_sum_scale(b), lds_out, tid, span.start, padded_elems, out, x, eta);
 }
 
-// Per-worker widths: every worker's message has its own layout, so a lane looks up b and the
-// place of its level dwords once per worker and decodes that worker's dwords with the code
-// specialised for its b.
+// Per-worker widths: every worker's message has its own layout.  Workers' gradients of one tensor are alike,
+// so most tensors have one width with all workers: a wavefront inside such a tensor runs the accumulation
+// specialised for it, only the place of the level bytes differs from worker to worker.  Elsewhere a lane
+// looks up b and the place of its level dwords once per worker and decodes that worker's dwords with the
+// code specialised for its b.
 struct worker_entry { // what a lane needs to decode one worker's tensor: 16 bytes, one LDS read
     float unit;         // N / s for that worker and tensor
     int32_t b;          // level bits
@@ -473,96 +712,132 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
 {
     extern __shared__ __align__(16) uint8_t lds_raw[];
     float4* lds_out = reinterpret_cast<float4*>(lds_raw);
-    worker_entry* lds_entry = reinterpret_cast<worker_entry*>(lds_raw + UR_TILE * sizeof(float)); // [local seg][M]
 
-    const int tid = threadIdx.x;
-    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * UR_TILE;
-    const int64_t tile_end = tile0 + UR_TILE < padded_elems ? tile0 + UR_TILE : padded_elems;
-    const int64_t P0 = tile0 + tid * UR_PER_LANE;
-    const bool active = P0 < tile_end;
-
-    const int32_t seg_first = granule_cseg[tile0 >> 7];
-    const int32_t seg_last = granule_cseg[(tile_end - 1) >> 7];
-    const int n_local = seg_last - seg_first + 1;
-    for (int i = tid; i < n_local * M; i += UR_THREADS) {
-        const int local = i / M, w = i - local * M;
-        const dq_cseg_width e = widths[static_cast<int64_t>(w) * n_cseg + seg_first + local];
-        const float S = static_cast<float>((1 << e.b) - 1);
-        const float N = norms[static_cast<int64_t>(w) * n_seg + cseg_seg[seg_first + local]];
-        worker_entry we;
-        // every worker's sum is kept with the factor 2^-9 of the sign-and-level route: the widths that
-        // do not take it get the factor on their unit (exact: a usable norm is at least 2^-100)
-        const float unit = N >= DQ_MIN_NORM ? N / S : 0.0f;
-        we.unit = ur_fp8_width(e.b) ? unit : unit * (1.0f / UR_FP8_SCALE);
-        we.b = e.b;
-        we.level_base = e.level_start - (e.seg_start >> 3) * e.b; // seg_start is a multiple of 128
-        lds_entry[i] = we;
-    }
-    int32_t c = 0;
-    int64_t n_valid = 0;
-    if (active) {
-        c = granule_cseg[P0 >> 7];
-        n_valid = cseg_valid_end[c] - P0;
-    }
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const wave_span span = wave_span_of(tid, padded_elems, granule_cseg);
+    if (span.n_lanes <= 0) return;
+    const int64_t P0 = span.start + lane * UR_PER_LANE;
+    const bool active = lane < span.n_lanes;
+    const uint8_t* level_plane = packed + (padded_elems >> 3);
 
     float acc[UR_PER_LANE];
 #pragma unroll
     for (int k = 0; k < UR_PER_LANE; ++k) acc[k] = 0.0f;
+    int64_t n_valid = 0;
+    float scale = inv_M * UR_FP16_SCALE;
+    bool done = false; // the same for the whole wavefront
 
-    if (active) {
-        const worker_entry* entry = lds_entry + (c - seg_first) * M;
-        const uint8_t* sign_ptr = packed + (P0 >> 3);
-        const uint8_t* level_plane = packed + (padded_elems >> 3);
-        // workers four at a time: sign dwords and up to eight level dwords each are fetched first
-        // (loads past a worker's width are skipped), then decoded width by width
-        constexpr int GROUP = 4;
-        block_total total{ slots_of(lds_out, tid) }; // the block sums of accumulate_lane: same order of additions
-        for (int w0 = 0; w0 < M; w0 += GROUP) {
-            uint32_t sg[GROUP], wd[GROUP][8];
-            worker_entry we[GROUP];
-#pragma unroll
-            for (int i = 0; i < GROUP; ++i) {
-                we[i].b = 0;
-                if (w0 + i < M) {
-                    we[i] = entry[w0 + i];
-                    const int64_t msg = static_cast<int64_t>(w0 + i) * packed_stride;
-                    const uint32_t* lp =
-                        reinterpret_cast<const uint32_t*>(level_plane + msg + we[i].level_base + (P0 >> 3) * we[i].b);
-                    sg[i] = dq_load_stream(reinterpret_cast<const uint32_t*>(sign_ptr + msg));
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) wd[i][q] = q < we[i].b ? dq_load_stream(lp + q) : 0u;
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < GROUP; ++i) {
-                switch (we[i].b) {
-                case 1: accumulate_first_words<1>(sg[i], wd[i], we[i].unit, acc); break;
-                case 2: accumulate_first_words<2>(sg[i], wd[i], we[i].unit, acc); break;
-                case 3: accumulate_first_words<3>(sg[i], wd[i], we[i].unit, acc); break;
-                case 4: accumulate_first_words<4>(sg[i], wd[i], we[i].unit, acc); break;
-                case 5: accumulate_first_words<5>(sg[i], wd[i], we[i].unit, acc); break;
-                case 6: accumulate_first_words<6>(sg[i], wd[i], we[i].unit, acc); break;
-                case 7: accumulate_first_words<7>(sg[i], wd[i], we[i].unit, acc); break;
-                case 8: accumulate_first_words<8>(sg[i], wd[i], we[i].unit, acc); break;
-                default: break; // past the last worker, or a width the host never uploads
-                }
-            }
-            if (((w0 + GROUP) & (UR_SUM_BLOCK - 1)) == 0 && w0 + GROUP < M) total.flush(acc);
+    if (span.first == span.last) {
+        const int32_t seg = cseg_seg[span.first];
+        n_valid = cseg_valid_end[span.first] - P0;
+        const int mine = lane < M ? lane : 0; // this lane's worker
+        const dq_cseg_width e = widths[static_cast<int64_t>(mine) * n_cseg + span.first];
+        const float N = norms[static_cast<int64_t>(mine) * n_seg + seg];
+        const int b = __builtin_amdgcn_readfirstlane(e.b);
+        if (__all(e.b == b)) {
+            const int64_t at = e.level_start + ((span.start - e.seg_start) >> 3) * b;
+            const uint32_t at_lo = static_cast<uint32_t>(at), at_hi = static_cast<uint32_t>(static_cast<uint64_t>(at) >> 32);
+            const float unit = ur_unit(N, b);
+            with_width(b, [&](auto width) {
+                accumulate_wave<decltype(width)::value>(
+                    packed + (span.start >> 3),
+                    [&](int w) {
+                        const uint64_t off = (static_cast<uint64_t>(__builtin_amdgcn_readlane(at_hi, w)) << 32) |
+                                             static_cast<uint32_t>(__builtin_amdgcn_readlane(at_lo, w));
+                        return level_plane + (static_cast<int64_t>(w) * packed_stride + static_cast<int64_t>(off));
+                    },
+                    packed_stride, M, [] {}, [&](int w) { return lane_value(unit, w); }, span.n_lanes, acc, slots_of(lds_out, tid));
+            });
+            scale = inv_M * ur_sum_scale(b);
+            done = true;
         }
-        total.finish(acc);
     }
-    finish_tile<UPDATE>(acc, active, n_valid, inv_M * UR_FP8_SCALE, lds_out, tid, tile0, tile_end, out, x, eta);
+    if (!done) {
+        // the lane's own tensor, fetched beside the table (lanes past the end: the first one's)
+        const int32_t c = granule_cseg[(active ? P0 : span.start) >> 7];
+        n_valid = cseg_valid_end[c] - P0;
+        worker_entry* lds_entry = reinterpret_cast<worker_entry*>(lds_raw + UR_TILE * sizeof(float)) +
+                                  (tid >> 6) * UR_WAVE_SEGS * M; // [local seg][M]
+        const int n_local = span.last - span.first + 1;
+        for (int i = lane; i < n_local * M; i += 64) {
+            const int local = i / M, w = i - local * M;
+            const dq_cseg_width e = widths[static_cast<int64_t>(w) * n_cseg + span.first + local];
+            worker_entry we;
+            // every worker's sum is kept with the factor 2^-17 of widths 5 to 8: the narrower ones, whose
+            // own factor is 2^-9, get the rest of it on their unit (exact: a usable norm is at least 2^-100)
+            we.unit = ur_unit(norms[static_cast<int64_t>(w) * n_seg + cseg_seg[span.first + local]], e.b) *
+                      (ur_fp8_width(e.b) ? UR_FP8_SCALE / UR_FP16_SCALE : 1.0f);
+            we.b = e.b;
+            we.level_base = e.level_start - (e.seg_start >> 3) * e.b; // seg_start is a multiple of 128
+            lds_entry[i] = we;
+        }
+        dq_wave_sync();
+        if (active) {
+            const worker_entry* entry = lds_entry + (c - span.first) * M;
+            const uint8_t* sign_ptr = packed + (P0 >> 3);
+            // workers four at a time: sign dwords and up to eight level dwords each are fetched first
+            // (loads past a worker's width are skipped), then decoded width by width
+            constexpr int GROUP = 4;
+            block_total total{ slots_of(lds_out, tid) }; // the block sums of accumulate_workers: same order of additions
+            for (int w0 = 0; w0 < M; w0 += GROUP) {
+                uint32_t sg[GROUP], wd[GROUP][8];
+                worker_entry we[GROUP];
+#pragma unroll
+                for (int i = 0; i < GROUP; ++i) {
+                    we[i].b = 0;
+                    if (w0 + i < M) {
+                        we[i] = entry[w0 + i];
+                        const int64_t msg = static_cast<int64_t>(w0 + i) * packed_stride;
+                        const uint32_t* lp =
+                            reinterpret_cast<const uint32_t*>(level_plane + msg + we[i].level_base + (P0 >> 3) * we[i].b);
+                        sg[i] = dq_load_stream(reinterpret_cast<const uint32_t*>(sign_ptr + msg));
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) wd[i][q] = q < we[i].b ? lp[q] : 0u;
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < GROUP; ++i) // b = 0: past the last worker
+                    with_width(we[i].b, [&](auto width) {
+                        accumulate_first_words<decltype(width)::value>(sg[i], wd[i], we[i].unit, acc);
+                    });
+                if (((w0 + GROUP) & (UR_SUM_BLOCK - 1)) == 0 && w0 + GROUP < M) total.flush(acc);
+            }
+            total.finish(acc);
+        }
+    }
+    finish_tile<UPDATE>(acc, active, n_valid, scale, lds_out, tid, span.start, padded_elems, out, x, eta);
 }
 
 // acc[k] += sgn_k * scale for a lane's 32 elements: the scale with its sign flipped where the bit is set.
-// (The conversion route of the quantized average -- (sign << 7) | 0x38 is +-1 as an 8-bit float -- was
-// measured here too: 0.40 ms against 0.35 ms at D = 2^28, M = 16, so the integer form stays.)
+// (Conversion routes were measured here too and the integer form stays: (sign << 7) | 0x38 as an 8-bit
+// float 0.40 ms against 0.35 ms at D = 2^28, M = 16; (sign << 15) | 0x3C00 as the 16-bit operand of a
+// mixed-precision FMA, which issues at half rate, 33.8 against 30.8 us on 4.2 M elements at M = 64.)
 __device__ __forceinline__ void add_signed_scale(uint32_t sg, float scale, float (&acc)[UR_PER_LANE])
 {
     const uint32_t unit = __float_as_uint(scale);
 #pragma unroll
     for (int k = 0; k < UR_PER_LANE; ++k) acc[k] += __uint_as_float(unit ^ ((sg << (31 - k)) & 0x80000000u));
+}
+
+// The workers in ascending order, eight loads in flight; prepare() as in accumulate_workers.
+template <typename Load, typename Prepare, typename Scale>
+__device__ __forceinline__ void accumulate_signs(int M, Load&& load, Prepare&& prepare, Scale&& scale,
+                                                 float (&acc)[UR_PER_LANE])
+{
+    auto group = [&](auto g, int w) {
+        constexpr int G = decltype(g)::value;
+        uint32_t sg[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) sg[i] = load(w + i);
+        if (w == 0) prepare();
+#pragma unroll
+        for (int i = 0; i < G; ++i) add_signed_scale(sg[i], scale(w + i), acc);
+    };
+    int w = 0;
+    for (; w + 8 <= M; w += 8) group(std::integral_constant<int, 8>{}, w);
+    if (w + 4 <= M) { group(std::integral_constant<int, 4>{}, w); w += 4; }
+    if (w + 2 <= M) { group(std::integral_constant<int, 2>{}, w); w += 2; }
+    if (w < M) group(std::integral_constant<int, 1>{}, w);
 }
 
 // Sign-only messages (the one-bit baseline of the paper's Table 2): the mean of scale * sgn,
@@ -575,52 +850,33 @@ __global__ __launch_bounds__(UR_THREADS) void k_sign_reduce_scaled(
 {
     extern __shared__ __align__(16) uint8_t lds_raw[];
     float4* lds_out = reinterpret_cast<float4*>(lds_raw);
-    float* lds_unit = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float)); // [local seg][M]
 
-    const int tid = threadIdx.x;
-    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * UR_TILE;
-    const int64_t tile_end = tile0 + UR_TILE < padded_elems ? tile0 + UR_TILE : padded_elems;
-    const int64_t P0 = tile0 + tid * UR_PER_LANE;
-    const bool active = P0 < tile_end;
-
-    const int32_t seg_first = granule_cseg[tile0 >> 7];
-    const int32_t seg_last = granule_cseg[(tile_end - 1) >> 7];
-    const int n_local = seg_last - seg_first + 1;
-    for (int i = tid; i < n_local * M; i += UR_THREADS) {
-        const int local = i / M, w = i - local * M;
-        lds_unit[i] = scales[static_cast<int64_t>(w) * n_seg + cseg_seg[seg_first + local]];
-    }
-    int local = 0;
-    int64_t n_valid = 0;
-    if (active) {
-        const int32_t c = granule_cseg[P0 >> 7];
-        local = c - seg_first;
-        n_valid = cseg_valid_end[c] - P0;
-    }
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const wave_span span = wave_span_of(tid, padded_elems, granule_cseg);
+    if (span.n_lanes <= 0) return;
+    const int64_t P0 = span.start + lane * UR_PER_LANE;
+    const bool active = lane < span.n_lanes;
 
     float acc[UR_PER_LANE];
 #pragma unroll
     for (int k = 0; k < UR_PER_LANE; ++k) acc[k] = 0.0f;
-    if (active) {
-        const uint8_t* sign_ptr = packed + (P0 >> 3);
-        const float* unit_ptr = lds_unit + local * M;
-        constexpr int GROUP = 8;
-        int w = 0;
-        for (; w + GROUP <= M; w += GROUP) {
-            uint32_t sg[GROUP];
-#pragma unroll
-            for (int i = 0; i < GROUP; ++i)
-                sg[i] = dq_load_stream(reinterpret_cast<const uint32_t*>(sign_ptr + static_cast<int64_t>(w + i) * packed_stride));
-#pragma unroll
-            for (int i = 0; i < GROUP; ++i) add_signed_scale(sg[i], unit_ptr[w + i], acc);
-        }
-        for (; w < M; ++w) {
-            const uint32_t sg = dq_load_stream(reinterpret_cast<const uint32_t*>(sign_ptr + static_cast<int64_t>(w) * packed_stride));
-            add_signed_scale(sg, unit_ptr[w], acc);
-        }
-    }
-    finish_tile<false>(acc, active, n_valid, inv_M, lds_out, tid, tile0, tile_end, out, nullptr, 0.0f);
+    int64_t n_valid = 0;
+    float* table = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float)) + (tid >> 6) * UR_WAVE_SEGS * M;
+    const float* scale_ptr = nullptr;
+    const uint8_t* sign_wave = packed + (span.start >> 3);
+    const uint32_t at = (active ? lane : span.n_lanes - 1) * 4u;
+    accumulate_signs(
+        M,
+        [&](int w) {
+            return load_dwords<true, uint32_t>(scalar_address(sign_wave + static_cast<int64_t>(w) * packed_stride) + at);
+        },
+        [&] {
+            scale_ptr = wave_table(span, lane, M, P0, granule_cseg, cseg_valid_end, table, n_valid, [&](int w, int32_t c) {
+                return scales[static_cast<int64_t>(w) * n_seg + cseg_seg[c]];
+            });
+        },
+        [&](int w) { return scale_ptr[w]; }, acc);
+    finish_tile<false>(acc, active, n_valid, inv_M, lds_out, tid, span.start, padded_elems, out, nullptr, 0.0f);
 }
 
 // Sign-only messages without scales: per element only the number of workers whose bit is set
@@ -684,8 +940,11 @@ __global__ __launch_bounds__(UR_THREADS) void k_sign_reduce_count(
                 acc[k] = static_cast<float>(votes);
         }
     }
-    finish_tile<false>(acc, active, n_valid, MAJORITY ? 1.0f : inv_M, lds_out, tid, tile0, tile_end, out, nullptr, 0.0f);
+    finish_tile<false>(acc, active, n_valid, MAJORITY ? 1.0f : inv_M, lds_out, tid, tile0 + (tid >> 6) * UR_WAVE_ELEMS,
+                       padded_elems, out, nullptr, 0.0f);
 }
+
+constexpr size_t UR_LDS_THREE_PER_CU = 41 * 1024; // of 160 KiB
 
 template <int B>
 int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, int M, const float* norms,
@@ -693,7 +952,11 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
 {
     const int64_t n_tiles = (plan->padded_elems + UR_TILE - 1) / UR_TILE;
     if (n_tiles > INT32_MAX) return DQ_ERR_INVALID_ARG;
-    const size_t lds_bytes = UR_TILE * sizeof(float) + static_cast<size_t>(UR_MAX_LOCAL_SEG) * M * sizeof(float);
+    size_t lds_bytes = UR_TILE * sizeof(float) + static_cast<size_t>(UR_MAX_LOCAL_SEG) * M * sizeof(float);
+    // Where thousands of tiles stream wide messages, three workgroups per CU move more than four: at D = 2^28,
+    // M = 16 b = 4 631 -> 615 us, b = 6 839 -> 806, at 2^26 b = 5 189 -> 183, b = 8 252 -> 249; with b = 2 and 3
+    // (471 -> 492, 549 -> 563) and on up to 1533 tiles (b = 8, M = 8 29.7 -> 32.5) four are better.
+    if (B >= 4 && n_tiles >= 4096 && lds_bytes < UR_LDS_THREE_PER_CU) lds_bytes = UR_LDS_THREE_PER_CU;
     const dim3 grid(static_cast<unsigned>(n_tiles)), block(UR_THREADS);
     const float inv_M = 1.0f / static_cast<float>(M);
     if (x)
