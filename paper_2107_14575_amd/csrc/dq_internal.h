@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "dq.h"
 
 // One piece of a segment handed to one workgroup of the norm kernel: `count` valid elements
@@ -173,6 +175,23 @@ __device__ __forceinline__ uint2 dq_load_stream(const uint2* src)
     return make_uint2(t.x, t.y);
 }
 __device__ __forceinline__ uint32_t dq_load_stream(const uint32_t* src) { return __builtin_nontemporal_load(src); }
+
+// Runs f with a width as a compile-time constant (widths outside 1..8 are never uploaded).
+template <typename F>
+__device__ __forceinline__ void dq_with_width(int b, F&& f)
+{
+    switch (b) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    default: break;
+    }
+}
 
 // What the wavefront's lanes wrote to LDS becomes visible to its other lanes (no other wavefront takes
 // part, so no workgroup barrier).

@@ -536,23 +536,6 @@ __device__ __forceinline__ wave_span wave_span_of(int tid, int64_t padded_elems,
     return s;
 }
 
-// Runs f with the width as a compile-time constant (widths outside 1..8 are never uploaded).
-template <typename F>
-__device__ __forceinline__ void with_width(int b, F&& f)
-{
-    switch (b) {
-    case 1: f(std::integral_constant<int, 1>{}); break;
-    case 2: f(std::integral_constant<int, 2>{}); break;
-    case 3: f(std::integral_constant<int, 3>{}); break;
-    case 4: f(std::integral_constant<int, 4>{}); break;
-    case 5: f(std::integral_constant<int, 5>{}); break;
-    case 6: f(std::integral_constant<int, 6>{}); break;
-    case 7: f(std::integral_constant<int, 7>{}); break;
-    case 8: f(std::integral_constant<int, 8>{}); break;
-    default: break;
-    }
-}
-
 __device__ __forceinline__ float ur_unit(float N, int b)
 {
     return N >= DQ_MIN_NORM ? N / static_cast<float>((1 << b) - 1) * ur_unit_factor(b) : 0.0f;
@@ -661,7 +644,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
         b = __builtin_amdgcn_readfirstlane(e.b);
         const float unit = lane < M ? ur_unit(norms[static_cast<int64_t>(lane) * n_seg + seg], b) : 0.0f;
         const uint8_t* level_wave = level_plane + e.level_start + ((span.start - e.seg_start) >> 3) * b;
-        with_width(b, [&](auto width) {
+        dq_with_width(b, [&](auto width) {
             accumulate_wave<decltype(width)::value>(
                 packed + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; },
                 packed_stride, M, [] {}, [&](int w) { return lane_value(unit, w); }, span.n_lanes, acc, slots_of(lds_out, tid));
@@ -683,7 +666,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
             b = e.b;
             const uint8_t* level_ptr = level_plane + e.level_start + ((P0 - e.seg_start) >> 3) * e.b; // dword aligned
             const float* unit_ptr = lds_unit + (c - span.first) * M;
-            with_width(b, [&](auto width) {
+            dq_with_width(b, [&](auto width) {
                 accumulate_lane<decltype(width)::value>(packed + (P0 >> 3), level_ptr, packed_stride, M, unit_ptr, acc,
                                                         slots_of(lds_out, tid));
             });
@@ -738,7 +721,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
             const int64_t at = e.level_start + ((span.start - e.seg_start) >> 3) * b;
             const uint32_t at_lo = static_cast<uint32_t>(at), at_hi = static_cast<uint32_t>(static_cast<uint64_t>(at) >> 32);
             const float unit = ur_unit(N, b);
-            with_width(b, [&](auto width) {
+            dq_with_width(b, [&](auto width) {
                 accumulate_wave<decltype(width)::value>(
                     packed + (span.start >> 3),
                     [&](int w) {
@@ -797,7 +780,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
                 }
 #pragma unroll
                 for (int i = 0; i < GROUP; ++i) // b = 0: past the last worker
-                    with_width(we[i].b, [&](auto width) {
+                    dq_with_width(we[i].b, [&](auto width) {
                         accumulate_first_words<decltype(width)::value>(sg[i], wd[i], we[i].unit, acc);
                     });
                 if (((w0 + GROUP) & (UR_SUM_BLOCK - 1)) == 0 && w0 + GROUP < M) total.flush(acc);
