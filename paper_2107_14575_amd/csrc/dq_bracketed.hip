@@ -17,13 +17,14 @@
 //       (index and value) in the chunk's block of the workspace.
 //   k_bracket_norm_finish      for the tensors that cross a chunk boundary: adds the partial sums in
 //       a fixed order: the norms, and whether each came out inside its bracket.
-//   k_bracket_settle[_wide]    one lane per chunk (large plans) or one wavefront per chunk with a
-//       lane per record (up to 2^16 chunks): quantizes the chunk's recorded elements with the
+//   k_bracket_settle           one lane per chunk: quantizes the chunk's recorded elements with the
 //       true norm and ORs their levels into the zero fields; a chunk with too many records, with
 //       no usable bracket, or with a norm outside its bracket gets a bit in the redo map instead.
 //   k_bracket_redo             quantizes the chunks of the redo map again in full from the
 //       gradient (the only case that reads it twice); a few thousand workgroups walk the map, so
 //       an empty map costs next to nothing.
+//   k_bracket_settle_redo      both in one launch for up to 2^16 (worker, chunk) pairs: one wavefront per
+//       chunk and a lane per record; a chunk to be quantized again is taken by its workgroup.
 // The messages are exactly those of dq_quantize_pack for the norms this path computes.
 #include "dq_quantize_core.h"
 
@@ -641,42 +642,55 @@ __device__ __forceinline__ bool chunk_needs_redo(uint32_t count, uint32_t flags,
     return again;
 }
 
-// grid (ceil(n_chunks / 4), M), one wavefront per chunk and one lane per record: for plans of
-// moderate size, where a launch of that many wavefronts is cheap and a chunk may hold dozens of
-// records.
+// grid (ceil(n_chunks / 4), M), one wavefront per chunk and one lane per record, and the workgroup itself
+// quantizes those of its four chunks again that need it: for plans of moderate size, where a launch of
+// that many workgroups is cheap and a chunk may hold dozens of records.  One launch where clearing the redo
+// map, settling and walking the map were three: the lagged iteration of the ResNet-18 shape, M = 8, b = 3
+// takes 131.5 us instead of 135.5.
 template <int B>
-__global__ __launch_bounds__(256) void k_bracket_settle_wide(
-    const float* __restrict__ norms, int32_t n_seg, int32_t n_cseg, const int32_t* __restrict__ granule_cseg,
-    const int32_t* __restrict__ cseg_seg, int64_t padded_elems, uint32_t key0, uint32_t key1, uint32_t step,
-    uint32_t worker_base, uint8_t* __restrict__ packed, int64_t packed_stride, dq_bracket_block* __restrict__ blocks,
-    int64_t n_chunks, const uint8_t* __restrict__ inside, unsigned long long* __restrict__ redo_map, int64_t n_words,
+__global__ __launch_bounds__(QP_THREADS) void k_bracket_settle_redo(
+    const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
+    int32_t n_cseg, const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
+    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, uint32_t key0,
+    uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed, int64_t packed_stride,
+    dq_bracket_block* __restrict__ blocks, int64_t n_chunks, const uint8_t* __restrict__ inside,
     const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride)
 {
+    __shared__ int lds_again[QP_THREADS / 64];
     const dq_cseg_width* __restrict__ widths = widths_table + static_cast<int64_t>(blockIdx.y) * widths_worker_stride;
     const uint32_t w = blockIdx.y;
-    const uint32_t lane = threadIdx.x & 63;
-    const int64_t chunk = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (chunk >= n_chunks) return; // the whole wavefront
-    dq_bracket_block* blk = blocks + static_cast<int64_t>(w) * n_chunks + chunk;
-    const uint32_t count = blk->count, flags = blk->flags;
-    const int64_t chunk0 = chunk * DQ_CHUNK;
-    const bool again = chunk_needs_redo(count, flags, chunk0, padded_elems, w, n_cseg, granule_cseg, inside);
-    if (again) {
-        if (lane == 0) {
-            blk->flags = flags | 2u;
-            atomicOr(redo_map + static_cast<int64_t>(w) * n_words + (chunk >> 6), 1ull << (chunk & 63));
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t chunk_first = static_cast<int64_t>(blockIdx.x) * (QP_THREADS / 64), chunk = chunk_first + wave;
+    bool again = false;
+    if (chunk < n_chunks) { // the same for the whole wavefront
+        dq_bracket_block* blk = blocks + static_cast<int64_t>(w) * n_chunks + chunk;
+        const uint32_t count = blk->count, flags = blk->flags;
+        const uint2 rec = blk->rec[lane < DQ_BRACKET_CAP ? lane : 0]; // fetched beside the count: used only below it
+        const int64_t chunk0 = chunk * DQ_CHUNK;
+        again = chunk_needs_redo(count, flags, chunk0, padded_elems, w, n_cseg, granule_cseg, inside);
+        if (again) {
+            if (lane == 0) blk->flags = flags | 2u;
+        } else if (lane < count) {
+            uint32_t* plane = reinterpret_cast<uint32_t*>(packed + static_cast<int64_t>(w) * packed_stride + (padded_elems >> 3));
+            settle_record<B>(rec, chunk0, w, norms, n_seg, granule_cseg, cseg_seg, key0, key1, step, worker_base + w, plane,
+                             widths);
         }
-    } else if (lane < count) {
-        uint32_t* plane = reinterpret_cast<uint32_t*>(packed + static_cast<int64_t>(w) * packed_stride + (padded_elems >> 3));
-        settle_record<B>(blk->rec[lane], chunk0, w, norms, n_seg, granule_cseg, cseg_seg, key0, key1, step,
-                         worker_base + w, plane, widths);
     }
-}
-
-__global__ __launch_bounds__(256) void k_zero_words(unsigned long long* __restrict__ dst, int64_t n)
-{
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i < n) dst[i] = 0;
+    if (lane == 0) lds_again[wave] = again ? 1 : 0;
+    __syncthreads();
+    for (int k = 0; k < QP_THREADS / 64; ++k) {
+        if (__builtin_amdgcn_readfirstlane(lds_again[k]) == 0) continue; // the same for the whole workgroup
+        const uint32_t c = static_cast<uint32_t>(chunk_first) + k;
+        if constexpr (B == 0)
+            quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
+                                        widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
+                                        packed, packed_stride, nullptr, c);
+        else
+            quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg,
+                                         cseg_valid_end, padded_elems, key0, key1, step, worker_base, packed, packed_stride,
+                                         nullptr, c);
+        __syncthreads(); // the chunk's staging in LDS is reused by the next one
+    }
 }
 
 // grid (ceil(n_chunks / 256), M), one lane per chunk: for large plans with few records per chunk.
@@ -716,8 +730,7 @@ __global__ __launch_bounds__(256) void k_bracket_settle(
 // grid (ceil(n_words / REDO_WORDS), M): each workgroup walks REDO_WORDS words of the redo map and
 // quantizes the chunks whose bit is set.
 constexpr int REDO_WORDS = 8;
-// up to this many (worker, chunk) pairs the settle kernel runs one wavefront per chunk and the
-// redo kernel one workgroup per chunk
+// up to this many (worker, chunk) pairs one kernel settles and quantizes again, a wavefront per chunk
 constexpr int64_t SETTLE_WIDE_MAX = 1 << 16;
 
 template <int B>
@@ -752,30 +765,6 @@ __global__ __launch_bounds__(QP_THREADS) void k_bracket_redo(
             __syncthreads(); // the chunk's staging in LDS is reused by the next one
         }
     }
-}
-
-// grid (n_chunks, M): the same with one workgroup per chunk that looks up its own bit -- for plans of
-// moderate size, where that many workgroups start in a few microseconds and flagged chunks that
-// sit next to each other are then quantized side by side instead of one after the other.
-template <int B>
-__global__ __launch_bounds__(QP_THREADS) void k_bracket_redo_direct(
-    const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
-    const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
-    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, uint32_t key0, uint32_t key1, uint32_t step,
-    uint32_t worker_base, uint8_t* __restrict__ packed, int64_t packed_stride,
-    const unsigned long long* __restrict__ redo_map, int64_t n_words, const dq_cseg_width* __restrict__ widths_table,
-    int32_t widths_worker_stride)
-{
-    const unsigned long long word = redo_map[static_cast<int64_t>(blockIdx.y) * n_words + (blockIdx.x >> 6)];
-    if (((word >> (blockIdx.x & 63)) & 1ull) == 0) return; // uniform: one address for the whole workgroup
-    if constexpr (B == 0)
-        quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end, widths_table,
-                                    widths_worker_stride, padded_elems, key0, key1, step, worker_base, packed,
-                                    packed_stride, nullptr, blockIdx.x);
-    else
-        quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
-                                     padded_elems, key0, key1, step, worker_base, packed, packed_stride, nullptr,
-                                     blockIdx.x);
 }
 
 // Statistics of one call, from the blocks: elements settled afterwards and chunks quantized again.
@@ -848,28 +837,20 @@ int launch_bracketed(const dq_plan* plan, const float* grads, int64_t worker_str
                            plan->d_cseg_start, plan->d_cseg_valid_end, plan->d_cseg_seg, plan->d_span_cseg, plan->n_seg,
                            plan->n_cseg, norm_lo, norm_hi, norms, inside);
     if (static_cast<int64_t>(M) * L.n_chunks <= SETTLE_WIDE_MAX) {
-        const int64_t words = static_cast<int64_t>(M) * L.n_words;
-        hipLaunchKernelGGL(k_zero_words, dim3(static_cast<unsigned>((words + 255) / 256)), dim3(256), 0, stream,
-                           redo_map, words);
-        hipLaunchKernelGGL(k_bracket_settle_wide<B>, dim3(static_cast<unsigned>((L.n_chunks + 3) / 4), M), dim3(256), 0,
-                           stream, norms, plan->n_seg, plan->n_cseg, plan->d_granule_cseg, plan->d_cseg_seg,
-                           plan->padded_elems, key0, key1, step, worker_base, packed, packed_stride, blocks, L.n_chunks,
-                           inside, redo_map, L.n_words, widths_table, widths_row);
+        hipLaunchKernelGGL(k_bracket_settle_redo<B>, dim3(static_cast<unsigned>((L.n_chunks + 3) / 4), M), block, 0, stream,
+                           grads, worker_stride, norms, plan->n_seg, plan->n_cseg, plan->d_chunk_tensor,
+                           plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, key0, key1,
+                           step, worker_base, packed, packed_stride, blocks, L.n_chunks, inside, widths_table, widths_row);
     } else {
         hipLaunchKernelGGL(k_bracket_settle<B>, dim3(static_cast<unsigned>((L.n_chunks + 255) / 256), M), dim3(256), 0,
                            stream, norms, plan->n_seg, plan->n_cseg, plan->d_granule_cseg, plan->d_cseg_seg,
                            plan->padded_elems, key0, key1, step, worker_base, packed, packed_stride, blocks, L.n_chunks,
                            inside, redo_map, L.n_words, widths_table, widths_row);
-    }
-    if (static_cast<int64_t>(M) * L.n_chunks <= SETTLE_WIDE_MAX)
-        hipLaunchKernelGGL(k_bracket_redo_direct<B>, grid, block, 0, stream, grads, worker_stride, norms, plan->n_seg,
-                           plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, key0, key1,
-                           step, worker_base, packed, packed_stride, redo_map, L.n_words, widths_table, widths_row);
-    else
         hipLaunchKernelGGL(k_bracket_redo<B>, dim3(static_cast<unsigned>((L.n_words + REDO_WORDS - 1) / REDO_WORDS), M),
                            block, 0, stream, grads, worker_stride, norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,
                            plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, key0, key1, step, worker_base,
                            packed, packed_stride, redo_map, L.n_words, widths_table, widths_row);
+    }
     if (stats) {
         const int64_t n_blocks = static_cast<int64_t>(M) * L.n_chunks;
         const int64_t wgs = (n_blocks + 256 * BS_PER_LANE - 1) / (256 * BS_PER_LANE);
