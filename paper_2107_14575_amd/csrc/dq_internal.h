@@ -42,6 +42,7 @@ struct dq_plan {
     int device;           // HIP device the tables live on, -1 if none
     int32_t n_cseg;       // number of non-empty segments
     bool chunk_local;     // no segment crosses a multiple of 4096 in the padded index space
+    void* d_tables;       // the one device allocation that holds all of the tables below
     // device tables.  Kernels address segments through a compact index c that counts only the
     // non-empty ones, so consecutive granules differ by at most one in c.
     dq_chunk_tensor* d_chunk_tensor; // [ceil(D'/4096)]

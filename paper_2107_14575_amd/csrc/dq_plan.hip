@@ -12,38 +12,24 @@ namespace {
 
 int64_t padded_len(int64_t len) { return (len + DQ_GRANULE - 1) / DQ_GRANULE * DQ_GRANULE; }
 
-template <typename T>
-bool upload(T** dst, const std::vector<T>& src)
-{
-    *dst = nullptr;
-    const size_t bytes = (src.empty() ? 1 : src.size()) * sizeof(T);
-    if (hipMalloc(reinterpret_cast<void**>(dst), bytes) != hipSuccess) return false;
-    if (!src.empty() &&
-        hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
-        return false;
-    return true;
-}
+// The tables one after the other, each on a multiple of 256 bytes, for one allocation and one copy (nine of
+// each took most of a small plan's set-up).
+struct table_stage {
+    std::vector<unsigned char> bytes;
+    template <typename T>
+    size_t add(const std::vector<T>& src) // the table's offset; may throw std::bad_alloc
+    {
+        const size_t at = (bytes.size() + 255) / 256 * 256, n = src.size() * sizeof(T);
+        bytes.resize(at + (n ? n : sizeof(T)));
+        if (n) memcpy(bytes.data() + at, src.data(), n);
+        return at;
+    }
+};
 
 void free_device_tables(dq_plan* p)
 {
-    if (p->d_chunk_tensor) (void)hipFree(p->d_chunk_tensor);
-    p->d_chunk_tensor = nullptr;
-    if (p->d_granule_cseg) (void)hipFree(p->d_granule_cseg);
-    if (p->d_cseg_seg) (void)hipFree(p->d_cseg_seg);
-    if (p->d_cseg_valid_end) (void)hipFree(p->d_cseg_valid_end);
-    if (p->d_cseg_start) (void)hipFree(p->d_cseg_start);
-    if (p->d_span_cseg) (void)hipFree(p->d_span_cseg);
-    if (p->d_items) (void)hipFree(p->d_items);
-    if (p->d_seg_item_begin) (void)hipFree(p->d_seg_item_begin);
-    if (p->d_finish_seg) (void)hipFree(p->d_finish_seg);
-    p->d_finish_seg = nullptr;
-    p->d_granule_cseg = nullptr;
-    p->d_cseg_seg = nullptr;
-    p->d_cseg_valid_end = nullptr;
-    p->d_cseg_start = nullptr;
-    p->d_span_cseg = nullptr;
-    p->d_items = nullptr;
-    p->d_seg_item_begin = nullptr;
+    if (p->d_tables) (void)hipFree(p->d_tables);
+    p->d_tables = nullptr;
 }
 
 } // namespace
@@ -108,6 +94,8 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
     std::vector<dq_norm_item> items;
     std::vector<int32_t> item_begin;
     std::vector<int32_t> finish_seg;
+    table_stage stage;
+    size_t at[9] = {};
     try {
         // every allocation of the host tables happens in here: std::bad_alloc never leaves the call
         granule_cseg.resize(static_cast<size_t>(total / DQ_GRANULE));
@@ -141,21 +129,42 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
         item_begin[n_seg] = static_cast<int32_t>(items.size());
         for (int32_t l = 0; l < n_seg; ++l)
             if (item_begin[l + 1] - item_begin[l] != 1) finish_seg.push_back(l);
+        at[0] = stage.add(chunk_tensor);
+        at[1] = stage.add(granule_cseg);
+        at[2] = stage.add(cseg_seg);
+        at[3] = stage.add(cseg_valid_end);
+        at[4] = stage.add(cseg_start);
+        at[5] = stage.add(span_cseg);
+        at[6] = stage.add(items);
+        at[7] = stage.add(item_begin);
+        at[8] = stage.add(finish_seg);
     } catch (const std::bad_alloc&) {
         dq_plan_destroy(p);
         return DQ_ERR_ALLOC;
     }
 
-    const bool ok = upload(&p->d_chunk_tensor, chunk_tensor) && upload(&p->d_granule_cseg, granule_cseg) && upload(&p->d_cseg_seg, cseg_seg) &&
-                    upload(&p->d_cseg_valid_end, cseg_valid_end) && upload(&p->d_cseg_start, cseg_start) && upload(&p->d_span_cseg, span_cseg) &&
-                    upload(&p->d_items, items) && upload(&p->d_seg_item_begin, item_begin) &&
-                    upload(&p->d_finish_seg, finish_seg);
-    if (!ok) {
+    unsigned char* base = nullptr;
+    if (hipMalloc(reinterpret_cast<void**>(&base), stage.bytes.size()) != hipSuccess) {
+        (void)hipGetLastError();
+        dq_plan_destroy(p);
+        return DQ_ERR_ALLOC;
+    }
+    p->d_tables = base;
+    if (hipMemcpy(base, stage.bytes.data(), stage.bytes.size(), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipGetLastError();
         free_device_tables(p);
         dq_plan_destroy(p);
         return DQ_ERR_ALLOC;
     }
+    p->d_chunk_tensor = reinterpret_cast<dq_chunk_tensor*>(base + at[0]);
+    p->d_granule_cseg = reinterpret_cast<int32_t*>(base + at[1]);
+    p->d_cseg_seg = reinterpret_cast<int32_t*>(base + at[2]);
+    p->d_cseg_valid_end = reinterpret_cast<int64_t*>(base + at[3]);
+    p->d_cseg_start = reinterpret_cast<int64_t*>(base + at[4]);
+    p->d_span_cseg = reinterpret_cast<int32_t*>(base + at[5]);
+    p->d_items = reinterpret_cast<dq_norm_item*>(base + at[6]);
+    p->d_seg_item_begin = reinterpret_cast<int32_t*>(base + at[7]);
+    p->d_finish_seg = reinterpret_cast<int32_t*>(base + at[8]);
     p->device = dev;
     dq_norm_static_scratch_prepare(dev); // set-up time: the allocation-free entry point then only launches
     p->n_cseg = static_cast<int32_t>(cseg_seg.size());
