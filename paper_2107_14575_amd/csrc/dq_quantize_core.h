@@ -6,14 +6,13 @@
 
 namespace {
 
-#ifndef DQ_QP_TILES
-#define DQ_QP_TILES 2 // tiles of 2048 elements per workgroup
-#endif
-
 constexpr int QP_THREADS = 256;
 constexpr int QP_PER_LANE = 8;
 constexpr int QP_TILE = QP_THREADS * QP_PER_LANE;      // 2048 elements: one tile of every wavefront
 constexpr int QP_WAVE_TILE = 64 * QP_PER_LANE;         // 512 elements: a wavefront's tile
+// Tiles per workgroup: its chunk is the 4096 elements of one entry of the plan's chunk table (one scale for
+// all of it) and of the chunk norms.
+constexpr int QP_TILES = DQ_CHUNK / QP_TILE;
 
 // Writes the low B bytes of v at dst (LDS, byte offset a multiple of B) with naturally aligned
 // stores only.
@@ -196,7 +195,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
     constexpr float S = static_cast<float>((1 << B) - 1);
-    static_assert(NORM == 0 || CHUNK == DQ_CHUNK, "the fused norm works on 4096-element chunks");
+    static_assert(CHUNK == DQ_CHUNK, "the chunk table and the fused norm work on 4096-element chunks");
 
     __shared__ float lds_scale[MAX_LOCAL_SEG];
     __shared__ int32_t lds_valid_end[MAX_LOCAL_SEG]; // relative to the chunk, clamped to CHUNK
@@ -344,7 +343,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
-    static_assert(NORM == 0 || CHUNK == DQ_CHUNK, "the fused norm works on 4096-element chunks");
+    static_assert(CHUNK == DQ_CHUNK, "the chunk table and the fused norm work on 4096-element chunks");
     // this worker's row of the table (stride 0: the workers share one row)
     const dq_cseg_width* __restrict__ widths = widths_table + static_cast<int64_t>(blockIdx.y) * widths_worker_stride;
 

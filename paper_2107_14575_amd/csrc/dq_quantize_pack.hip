@@ -102,11 +102,9 @@ int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M
            uint64_t seed, uint32_t step, uint32_t worker_base, uint8_t* packed, int64_t packed_stride,
            float* norms_out, hipStream_t stream)
 {
-    constexpr int TILES = NORM == 0 ? DQ_QP_TILES : 2;
-    constexpr int CHUNK = QP_TILE * TILES;
-    const int64_t n_chunks = (plan->padded_elems + CHUNK - 1) / CHUNK;
+    const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
-    hipLaunchKernelGGL((k_quantize_pack<B, TILES, NORM>), dim3(static_cast<unsigned>(n_chunks), M), dim3(QP_THREADS),
+    hipLaunchKernelGGL((k_quantize_pack<B, QP_TILES, NORM>), dim3(static_cast<unsigned>(n_chunks), M), dim3(QP_THREADS),
                        0, stream, grads, worker_stride, norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,
                        plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, static_cast<uint32_t>(seed),
                        static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out);
@@ -178,15 +176,13 @@ int quantize_v_entry(int norm_mode, const dq_plan_t* plan, const dq_widths_t* wi
         if (zrc != DQ_OK) return zrc;
     }
     if (plan->padded_elems == 0) return DQ_OK;
-    const int TILES = norm_mode == 0 ? DQ_QP_TILES : 2;
-    const int64_t CHUNK = QP_TILE * TILES;
-    const int64_t n_chunks = (plan->padded_elems + CHUNK - 1) / CHUNK;
+    const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
 #define DQ_LAUNCH_QV(NORM)                                                                                        \
-    hipLaunchKernelGGL((k_quantize_pack_v<(NORM == 0 ? DQ_QP_TILES : 2), NORM>), grid, block, 0, stream, grads_dev, worker_stride_elems,  \
-                       norms_in, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end,     \
-                       widths->d_table, row_stride, plan->padded_elems, static_cast<uint32_t>(seed),              \
+    hipLaunchKernelGGL((k_quantize_pack_v<QP_TILES, NORM>), grid, block, 0, stream, grads_dev, worker_stride_elems, \
+                       norms_in, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,       \
+                       plan->d_cseg_valid_end, widths->d_table, row_stride, plan->padded_elems, static_cast<uint32_t>(seed), \
                        static_cast<uint32_t>(seed >> 32), step, worker_base, packed_dev, packed_worker_stride_bytes, \
                        norms_out)
     if (norm_mode == 0)
