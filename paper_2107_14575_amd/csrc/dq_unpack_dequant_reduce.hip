@@ -18,13 +18,15 @@
 // ALU beside it.  Measured with the half-word route, full-line loads and per-wavefront tables, before and
 // after: 2^26 x 16 b = 5 199 -> 183 us, b = 6 214 -> 203, b = 8 255 -> 249; 4.2 M ragged elements with
 // update, M = 64, b = 5 66.9 -> 52 us, b = 8 76.6 -> 66; ResNet-18 shape with update, M = 8, b = 6
-// 35.4 -> 28.4 us; b = 4 at 2^28 x 16 stays within 2 % (602 -> 615) and gains 4 % with update (870 -> 833).
+// 35.4 -> 28.4 us.  Narrow widths are where they were before those changes or below: 2^28 x 16 b = 1 402 -> 380,
+// b = 2 466 -> 447, b = 3 538 -> 532, b = 4 594 -> 588 and with update 875 -> 820; ResNet-18 shape, M = 8, b = 1, 2, 3
+// 15.0, 15.4, 16.9 -> 14.6, 15.3, 16.7 (see ur_table_first).
 //
 // The 32 results of a lane are consecutive in memory, so storing them directly would be 16-byte
 // pieces 128 bytes apart; they go through LDS (XOR-swizzled 16-byte slots, conflict free both
 // ways) and leave as fully coalesced 16-byte stores.
 //
-// Each wavefront works out the units N/s of its own tensors; no workgroup barrier.
+// Each wavefront works out the units N/s of its own tensors.
 //
 // HBM traffic per output element: M(B+1)/8 bytes read, 4 bytes written.
 //
@@ -56,8 +58,20 @@ constexpr float UR_FP8_SCALE = 512.0f;
 constexpr int UR_MIN_WAVES = 4;
 constexpr int UR_SUM_BLOCK = 8; // workers per block of the two-level sum (a power of two)
 // workers whose loads are issued together (measured per width at D = 2^28, M = 16)
-// (b = 3, 4: eight need no spills in the kernels that hold all widths, and sixteen gain nothing)
+// (b = 3, 4: with eight the kernel of per-tensor widths, which holds all of them, needs no spills)
 __host__ __device__ constexpr int ur_group(int b) { return b <= 2 ? 16 : b <= 4 ? 8 : 4; }
+// The same in the kernel of one width, where sixteen fit at b = 4 too: 2^28 x 16 607 -> 587 us (b = 3: 524 -> 520
+// there, but 17.2 -> 18.0 us on the ResNet-18 shape, M = 8, so it stays at eight).
+__host__ __device__ constexpr int ur_group_one_width(int b) { return b == 4 ? 16 : ur_group(b); }
+// Whether the wavefront's table of units comes before the first group's loads.  One width: the message bytes do
+// not depend on the tensors, so those loads can go ahead, and at b >= 5 they do.  But loads return in order, and
+// the table's own then wait for the whole group, which costs more than it hides where a worker's bytes are few:
+// at b <= 4 the table comes first, and a barrier after it lets the workgroup's wavefronts start on their
+// neighbouring bytes together.  Measured against the loads first, in us: 2^28 x 16 b = 1 397 -> 381, b = 2
+// 455 -> 444; 2^26 x 16 b = 1 110.6 -> 99.2; ResNet-18 shape, M = 8, b = 1, 2, 3 17.4, 18.3, 18.9 -> 14.2, 15.3,
+// 17.2 (without the barrier 15.0, 15.7, 17.2).  At b = 8 it is the other way round: that shape with update
+// 29.3 -> 31.8.
+__host__ __device__ constexpr bool ur_table_first(int b) { return b <= 4; }
 
 // bytes of {hi, lo} picked by the four selector bytes of sel: 0..3 = bytes of lo, 4..7 = bytes of hi
 __device__ __forceinline__ uint32_t byte_perm(uint32_t hi, uint32_t lo, uint32_t sel)
@@ -336,7 +350,7 @@ __device__ __forceinline__ void load_levels(ur_bytes at, uint32_t (&wd)[B])
 // passes through at most 7 + ceil(M/8) roundings: 15 at M = 64, where a single chain over all
 // workers would take 63 (and measurably leaves the 1e-6 tolerance when one worker's norm
 // dominates).  Up to eight workers nothing is flushed: the plain chain.
-template <int B, bool WAVE, typename Load, typename Prepare, typename Unit>
+template <int B, bool WAVE, int GROUP, typename Load, typename Prepare, typename Unit>
 __device__ __forceinline__ void accumulate_workers(int M, Load&& load, Prepare&& prepare, Unit&& unit,
                                                    float (&acc)[UR_PER_LANE], lane_slots slots)
 {
@@ -345,7 +359,14 @@ __device__ __forceinline__ void accumulate_workers(int M, Load&& load, Prepare&&
         constexpr int G = decltype(g)::value;
         uint32_t sg[G], wd[G][B];
 #pragma unroll
-        for (int i = 0; i < G; ++i) load(w + i, sg[i], wd[i]);
+        for (int i = 0; i < G; ++i) {
+            load(w + i, sg[i], wd[i]);
+            // Narrow fields: the loads in the order of their use.  Left to itself the compiler puts most sign
+            // dwords behind the levels, and the second worker waits for six loads: b = 1 at 2^28 x 16 380 -> 374
+            // us, b = 2 and 3 on 2^24 values in tensors of 512, M = 8 23.1 -> 22.4 and 25.1 -> 24.5.  With
+            // wider ones its order is the better one (2^28 x 16: b = 4 586 against 629 us, b = 7 877 against 957).
+            if constexpr (B <= 3) __builtin_amdgcn_sched_barrier(0);
+        }
         if (w == 0) prepare();
 #pragma unroll
         for (int i = 0; i < G; ++i) {
@@ -366,7 +387,6 @@ __device__ __forceinline__ void accumulate_workers(int M, Load&& load, Prepare&&
             if (((w + G) & (UR_SUM_BLOCK - 1)) == 0 && w + G < M) total.flush(acc);
         }
     };
-    constexpr int GROUP = WAVE ? ur_group(B) : ur_group(B) / 2;
     int w = 0;
     for (; w + GROUP <= M; w += GROUP) group(std::integral_constant<int, GROUP>{}, w);
     if constexpr (GROUP > 8) if (w + 8 <= M) { group(std::integral_constant<int, 8>{}, w); w += 8; }
@@ -384,7 +404,7 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
                                                 int M, const float* unit_ptr, float (&acc)[UR_PER_LANE],
                                                 lane_slots slots)
 {
-    accumulate_workers<B, false>(
+    accumulate_workers<B, false, ur_group(B) / 2>(
         M,
         [&](int w, uint32_t& sg, uint32_t (&wd)[B]) {
             int64_t off = static_cast<int64_t>(w) * packed_stride; // scalar, for the reason given at scalar_address
@@ -402,7 +422,7 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
 // At B = 8 a lane's dwords are two 16-byte pieces: each load instruction covers 1 KiB in full (lanes
 // 0..31 and 32..63 take the first and second pieces of 32 lanes) and swaps between the halves of the
 // wavefront put the pieces in place, so that the streaming hint can stay on.
-template <int B, typename LevelWave, typename Prepare, typename Unit>
+template <int B, int GROUP, typename LevelWave, typename Prepare, typename Unit>
 __device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign_wave, LevelWave&& level_wave,
                                                 int64_t packed_stride, int M, Prepare&& prepare, Unit&& unit, int n_lanes,
                                                 float (&acc)[UR_PER_LANE], lane_slots slots)
@@ -415,7 +435,7 @@ __device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign
         at1 = at0 + 1024u < end ? at0 + 1024u : end;
         at0 = at0 < end ? at0 : end;
     }
-    accumulate_workers<B, true>(
+    accumulate_workers<B, true, GROUP>(
         M,
         [&](int w, uint32_t& sg, uint32_t (&wd)[B]) {
             const ur_bytes lp = scalar_address(level_wave(w));
@@ -585,27 +605,37 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
 
     const int tid = threadIdx.x, lane = tid & 63;
     const wave_span span = wave_span_of(tid, padded_elems, granule_cseg);
-    if (span.n_lanes <= 0) return; // the whole wavefront; no workgroup barrier below
     const int64_t P0 = span.start + lane * UR_PER_LANE;
     const bool active = lane < span.n_lanes;
     const uint8_t* level_plane = packed + (padded_elems >> 3);
 
+    int64_t n_valid = 0;
+    float* table = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float)) + (tid >> 6) * UR_WAVE_SEGS * M;
+    const float* unit_ptr = nullptr;
+    auto make_table = [&] { // the row of the lane's tensor
+        unit_ptr = wave_table(span, lane, M, P0, granule_cseg, cseg_valid_end, table, n_valid, [&](int w, int32_t c) {
+            return ur_unit(norms[static_cast<int64_t>(w) * n_seg + cseg_seg[c]], B);
+        });
+    };
+    if constexpr (ur_table_first(B)) {
+        // past the layout's end too (the row of tensor 0, not used): behind a condition the load of n_valid would
+        // be waited for ahead of the barrier (ResNet-18 shape, M = 8, b = 2 15.1 -> 15.9 us)
+        make_table();
+        // ... except that b = 3, with its 12-byte loads, is better off waiting: 17.5 -> 16.6 us there
+        if constexpr (B == 3) asm volatile("" ::"v"(static_cast<uint32_t>(n_valid)));
+        __syncthreads();
+    }
+    if (span.n_lanes <= 0) return; // the whole wavefront; there is no workgroup barrier below
+
     float acc[UR_PER_LANE];
 #pragma unroll
     for (int k = 0; k < UR_PER_LANE; ++k) acc[k] = 0.0f;
-    int64_t n_valid = 0;
-
-    // one width: the message bytes do not depend on the tensors, the first loads go ahead of the table
-    float* table = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float)) + (tid >> 6) * UR_WAVE_SEGS * M;
-    const float* unit_ptr = nullptr;
     const uint8_t* level_wave = level_plane + (span.start >> 3) * B;
-    accumulate_wave<B>(
+    accumulate_wave<B, ur_group_one_width(B)>(
         packed + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; },
         packed_stride, M,
         [&] {
-            unit_ptr = wave_table(span, lane, M, P0, granule_cseg, cseg_valid_end, table, n_valid, [&](int w, int32_t c) {
-                return ur_unit(norms[static_cast<int64_t>(w) * n_seg + cseg_seg[c]], B);
-            });
+            if constexpr (!ur_table_first(B)) make_table();
         },
         [&](int w) { return unit_ptr[w]; }, span.n_lanes, acc, slots_of(lds_out, tid));
     finish_tile<UPDATE>(acc, active, n_valid, inv_M * ur_sum_scale(B), lds_out, tid, span.start, padded_elems, out, x, eta);
@@ -645,7 +675,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
         const float unit = lane < M ? ur_unit(norms[static_cast<int64_t>(lane) * n_seg + seg], b) : 0.0f;
         const uint8_t* level_wave = level_plane + e.level_start + ((span.start - e.seg_start) >> 3) * b;
         dq_with_width(b, [&](auto width) {
-            accumulate_wave<decltype(width)::value>(
+            accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value)>(
                 packed + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; },
                 packed_stride, M, [] {}, [&](int w) { return lane_value(unit, w); }, span.n_lanes, acc, slots_of(lds_out, tid));
         });
@@ -722,7 +752,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
             const uint32_t at_lo = static_cast<uint32_t>(at), at_hi = static_cast<uint32_t>(static_cast<uint64_t>(at) >> 32);
             const float unit = ur_unit(N, b);
             dq_with_width(b, [&](auto width) {
-                accumulate_wave<decltype(width)::value>(
+                accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value)>(
                     packed + (span.start >> 3),
                     [&](int w) {
                         const uint64_t off = (static_cast<uint64_t>(__builtin_amdgcn_readlane(at_hi, w)) << 32) |

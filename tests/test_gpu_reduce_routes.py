@@ -131,3 +131,21 @@ def test_workers_of_mixed_widths(dq, oracle, M):
     _check(out.cpu().numpy(), mean, mag)
     table.close()
     plan.close()
+
+
+@pytest.mark.parametrize("b", [1, 2, 3, 4])
+@pytest.mark.parametrize("M", [15, 16, 17, 31, 64])
+def test_groups_of_workers(dq, oracle, b, M):
+    """Widths 1 to 4 take up to sixteen workers' loads at once: full groups, and what is left of the next one,
+    on workgroups all of whose wavefronts hold data and on ones whose last wavefronts hold none."""
+    for seg_len in ([8192 + 2048 + 1], [300, 2048, 129, 8192 * 2]):
+        rng = np.random.default_rng(1000 * b + M)
+        plan = dq.Plan(seg_len)
+        starts, sign, level = _codes(seg_len, M, lambda i, l: b, rng)
+        norms = (10.0 ** rng.uniform(-2, 1, (M, len(seg_len)))).astype(np.float32)
+        packed = torch.from_numpy(np.stack([oracle.pack(sign[i], level[i], b) for i in range(M)])).cuda()
+        mean, mag = _reference(seg_len, starts, sign, level, norms, lambda i, l: b)
+        out = torch.full((plan.padded_elems,), float("nan"), device="cuda")
+        dq.unpack_dequant_reduce(plan, packed, torch.from_numpy(norms).cuda(), b, out)
+        _check(out.cpu().numpy(), mean, mag)
+        plan.close()
