@@ -285,10 +285,11 @@ struct block_total {
 };
 
 // A lane's B level dwords of one worker, by the widest loads their size allows (a global load needs no
-// more than dword alignment).  Where one load takes them all, the lanes' loads cover whole cache lines
-// and the streaming hint pays at the largest sizes; where a line is met by several loads (5 to 8) it has
-// to stay: with the hint B = 7 took 236 instead of 226 us at D = 2^26, M = 16 and 36.7 instead of 32.5 us
-// on 11 M elements, M = 8.
+// more than dword alignment).  Where one load takes them all (b <= 4), the lanes' loads cover whole cache lines
+// and the streaming hint pays at the largest sizes.  Where a line is met by several loads (5 to 7) it has to
+// stay when messages are all that is read: with the hint b = 7 took 236 instead of 226 us at D = 2^26, M = 16 and
+// 36.7 instead of 32.5 us on 11 M elements, M = 8.  With the model update it is the other way round (STREAM; see
+// UR_LAST_LEVEL_CACHE).
 typedef uint32_t ur_v4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t ur_v3u __attribute__((ext_vector_type(3), aligned(4)));
 typedef uint32_t ur_v2u __attribute__((ext_vector_type(2), aligned(4)));
@@ -315,10 +316,9 @@ __device__ __forceinline__ T load_dwords(ur_bytes at)
     else
         return *reinterpret_cast<const UR_GLOBAL T*>(at);
 }
-template <int B>
+template <int B, bool STREAM>
 __device__ __forceinline__ void load_levels(ur_bytes at, uint32_t (&wd)[B])
 {
-    constexpr bool STREAM = B <= 4;
 #pragma unroll
     for (int q = 0; q + 4 <= B; q += 4) {
         const ur_v4u t = load_dwords<STREAM, ur_v4u>(at + 4 * q);
@@ -410,7 +410,7 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
             int64_t off = static_cast<int64_t>(w) * packed_stride; // scalar, for the reason given at scalar_address
             asm("" : "+s"(off));
             sg = load_dwords<true, uint32_t>(global_address(sign_ptr + off));
-            load_levels<B>(global_address(level_ptr + off), wd);
+            load_levels<B, B <= 4>(global_address(level_ptr + off), wd);
         },
         [] {}, [&](int w) { return unit_ptr[w]; }, acc, slots);
 }
@@ -422,7 +422,7 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
 // At B = 8 a lane's dwords are two 16-byte pieces: each load instruction covers 1 KiB in full (lanes
 // 0..31 and 32..63 take the first and second pieces of 32 lanes) and swaps between the halves of the
 // wavefront put the pieces in place, so that the streaming hint can stay on.
-template <int B, int GROUP, typename LevelWave, typename Prepare, typename Unit>
+template <int B, int GROUP, bool STREAM, typename LevelWave, typename Prepare, typename Unit>
 __device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign_wave, LevelWave&& level_wave,
                                                 int64_t packed_stride, int M, Prepare&& prepare, Unit&& unit, int n_lanes,
                                                 float (&acc)[UR_PER_LANE], lane_slots slots)
@@ -446,7 +446,7 @@ __device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign
                 wd[0] = a.x; wd[1] = a.y; wd[2] = a.z; wd[3] = a.w;
                 wd[4] = b.x; wd[5] = b.y; wd[6] = b.z; wd[7] = b.w;
             } else {
-                load_levels<B>(lp + at0, wd);
+                load_levels<B, STREAM || B <= 4>(lp + at0, wd);
             }
         },
         prepare, unit, acc, slots);
@@ -593,7 +593,7 @@ __device__ __forceinline__ const float* wave_table(const wave_span& span, int la
     return table + (c - first) * M;
 }
 
-template <int B, bool UPDATE>
+template <int B, bool UPDATE, bool STREAM = false> // STREAM: the hint on level loads that would not have it
 __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_reduce(
     const uint8_t* __restrict__ packed, int64_t packed_stride, int M, const float* __restrict__ norms,
     int32_t n_seg, const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
 #pragma unroll
     for (int k = 0; k < UR_PER_LANE; ++k) acc[k] = 0.0f;
     const uint8_t* level_wave = level_plane + (span.start >> 3) * B;
-    accumulate_wave<B, ur_group_one_width(B)>(
+    accumulate_wave<B, ur_group_one_width(B), STREAM>(
         packed + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; },
         packed_stride, M,
         [&] {
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
         const float unit = lane < M ? ur_unit(norms[static_cast<int64_t>(lane) * n_seg + seg], b) : 0.0f;
         const uint8_t* level_wave = level_plane + e.level_start + ((span.start - e.seg_start) >> 3) * b;
         dq_with_width(b, [&](auto width) {
-            accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value)>(
+            accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value), false>(
                 packed + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; },
                 packed_stride, M, [] {}, [&](int w) { return lane_value(unit, w); }, span.n_lanes, acc, slots_of(lds_out, tid));
         });
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
             const uint32_t at_lo = static_cast<uint32_t>(at), at_hi = static_cast<uint32_t>(static_cast<uint64_t>(at) >> 32);
             const float unit = ur_unit(N, b);
             dq_with_width(b, [&](auto width) {
-                accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value)>(
+                accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value), false>(
                     packed + (span.start >> 3),
                     [&](int w) {
                         const uint64_t off = (static_cast<uint64_t>(__builtin_amdgcn_readlane(at_hi, w)) << 32) |
@@ -964,6 +964,17 @@ __global__ __launch_bounds__(UR_THREADS) void k_sign_reduce_count(
 
 constexpr size_t UR_LDS_THREE_PER_CU = 41 * 1024; // of 160 KiB
 
+// With the model update, messages and model that do not fit the last-level cache together: the level loads of
+// widths 5 to 7 carry the streaming hint too, so that the messages do not push the model out.  Measured without
+// and with it, in us (inputs in no cache): 2^26 elements, M = 8 b = 6 183 -> 153, M = 16 b = 5 244 -> 214, M = 32 b = 7 499 -> 488;
+// 2^24, M = 16 b = 7 80 -> 68 (all of them 3 to 12 % above what they took when every load had the hint, and below it
+// now).  Smaller inputs that were just written are still in the cache, as in an iteration that simulates all workers,
+// and are better off without: 12.5 M elements, M = 16 b = 6 42.6 -> 48.4, ResNet-18 shape, M = 8 28.8 -> 30.1; from
+// elsewhere they would gain (54.0 -> 48.9, 34.0 -> 31.4).  Beyond 32 workers (three workgroups per CU, the vector ALU as
+// much as the loads) it gives nothing: 4.2 M ragged elements, M = 64 b = 5 55.6 -> 62.0.
+constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20;
+constexpr bool ur_may_stream(int b) { return b >= 5 && b <= 7; }
+
 template <int B>
 int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, int M, const float* norms,
            float* out, float* x, float eta, hipStream_t stream)
@@ -977,7 +988,12 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
     if (B >= 4 && n_tiles >= 4096 && lds_bytes < UR_LDS_THREE_PER_CU) lds_bytes = UR_LDS_THREE_PER_CU;
     const dim3 grid(static_cast<unsigned>(n_tiles)), block(UR_THREADS);
     const float inv_M = 1.0f / static_cast<float>(M);
-    if (x)
+    const bool fits_cache = plan->padded_elems * (M * (B + 1) + 32) / 8 <= UR_LAST_LEVEL_CACHE; // messages and model
+    if (x && ur_may_stream(B) && !fits_cache && M <= 32)
+        hipLaunchKernelGGL((k_unpack_dequant_reduce<B, true, ur_may_stream(B)>), grid, block, lds_bytes, stream, packed,
+                           packed_stride, M, norms, plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg,
+                           plan->d_cseg_valid_end, plan->padded_elems, inv_M, out, x, eta);
+    else if (x)
         hipLaunchKernelGGL((k_unpack_dequant_reduce<B, true>), grid, block, lds_bytes, stream, packed, packed_stride, M,
                            norms, plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end,
                            plan->padded_elems, inv_M, out, x, eta);

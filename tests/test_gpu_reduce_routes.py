@@ -149,3 +149,24 @@ def test_groups_of_workers(dq, oracle, b, M):
         dq.unpack_dequant_reduce(plan, packed, torch.from_numpy(norms).cuda(), b, out)
         _check(out.cpu().numpy(), mean, mag)
         plan.close()
+
+
+@pytest.mark.parametrize("b", [5, 6, 7])
+def test_update_with_more_than_the_last_level_cache_holds(dq, b):
+    """Messages and model of more than 256 MB take other loads with the update: the average has the bits of the
+    kernel without update, and the model is one FMA of it."""
+    M, seg_len = 16, [(1 << 24) + 3 * 2048 + 77, 300, (1 << 20) + 1]
+    gen = torch.Generator(device="cuda").manual_seed(b)
+    plan = dq.Plan(seg_len)
+    assert plan.padded_elems * (M * (b + 1) + 32) // 8 > 256 << 20
+    packed = torch.empty((M, plan.packed_bytes(b) // 8), dtype=torch.int64, device="cuda").random_(generator=gen).view(torch.uint8)
+    norms = torch.rand((M, len(seg_len)), generator=gen, device="cuda") + 0.5
+    out = torch.full((plan.padded_elems,), float("nan"), device="cuda")
+    dq.unpack_dequant_reduce(plan, packed, norms, b, out)
+    x0 = torch.randn(plan.padded_elems, generator=gen, device="cuda")
+    x, ghat = x0.clone(), torch.full_like(out, float("nan"))
+    dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.5, x, ghat=ghat)
+    assert torch.equal(ghat, out)
+    # 0.5 * out is exact, so the FMA is the rounded sum of two binary32 numbers
+    assert torch.equal(x, x0 - 0.5 * out)
+    plan.close()
