@@ -982,10 +982,15 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
     const int64_t n_tiles = (plan->padded_elems + UR_TILE - 1) / UR_TILE;
     if (n_tiles > INT32_MAX) return DQ_ERR_INVALID_ARG;
     size_t lds_bytes = UR_TILE * sizeof(float) + static_cast<size_t>(UR_MAX_LOCAL_SEG) * M * sizeof(float);
-    // Where thousands of tiles stream wide messages, three workgroups per CU move more than four: at D = 2^28,
-    // M = 16 b = 4 631 -> 615 us, b = 6 839 -> 806, at 2^26 b = 5 189 -> 183, b = 8 252 -> 249; with b = 2 and 3
-    // (471 -> 492, 549 -> 563) and on up to 1533 tiles (b = 8, M = 8 29.7 -> 32.5) four are better.
-    if (B >= 4 && n_tiles >= 4096 && lds_bytes < UR_LDS_THREE_PER_CU) lds_bytes = UR_LDS_THREE_PER_CU;
+    // Where thousands of tiles stream wide messages, three workgroups per CU move more than four.  Measured for
+    // M = 1..32, 2048..16384 tiles, b = 4..8, inputs in no cache and inputs read before, as a factor on the time:
+    // M = 16 b = 4..8 0.98, 0.98, 0.97, 0.98, 0.99 at 4096 tiles and 0.95, 0.94, 0.95, 0.97, 0.99 at 16384; M = 8 0.98..1.0 at
+    // 4096, 0.97..0.99 at 8192; M = 32 0.96..0.99 at 8192.  Below 4096 tiles or eight workers four are as good or better (M = 16
+    // at 3072 tiles 0.98..1.02, at 2048 1.0..1.03; M = 4 b = 5 1.03..1.1, M = 1 1.01..1.16).  With update b = 5 to 7 lose 1 to
+    // 4 % at any size, and 4 and 8 gain from 8192 tiles on (1.0, 16384 tiles 0.97..0.99).  b = 2 and 3 lose (471 -> 492 us, 549 ->
+    // 563 at 2^28 x 16).
+    const bool three = B >= 4 && M >= 8 && (x ? !ur_may_stream(B) && n_tiles >= 8192 : n_tiles >= 4096);
+    if (three && lds_bytes < UR_LDS_THREE_PER_CU) lds_bytes = UR_LDS_THREE_PER_CU;
     const dim3 grid(static_cast<unsigned>(n_tiles)), block(UR_THREADS);
     const float inv_M = 1.0f / static_cast<float>(M);
     const bool fits_cache = plan->padded_elems * (M * (B + 1) + 32) / 8 <= UR_LAST_LEVEL_CACHE; // messages and model
