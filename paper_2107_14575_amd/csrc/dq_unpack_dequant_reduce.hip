@@ -58,7 +58,7 @@ constexpr float UR_FP8_SCALE = 512.0f;
 constexpr int UR_MIN_WAVES = 4;
 constexpr int UR_SUM_BLOCK = 8; // workers per block of the two-level sum (a power of two)
 // workers whose loads are issued together (measured per width at D = 2^28, M = 16)
-// (b = 3, 4: with eight the kernel of per-tensor widths, which holds all of them, needs no spills)
+// (b = 3, 4: with eight the kernels that hold all widths need no spills)
 __host__ __device__ constexpr int ur_group(int b) { return b <= 2 ? 16 : b <= 4 ? 8 : 4; }
 // The same in the kernel of one width, where sixteen fit at b = 4 too: 2^28 x 16 607 -> 587 us (b = 3: 524 -> 520
 // there, but 17.2 -> 18.0 us on the ResNet-18 shape, M = 8, so it stays at eight).
@@ -737,8 +737,6 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
 #pragma unroll
     for (int k = 0; k < UR_PER_LANE; ++k) acc[k] = 0.0f;
     int64_t n_valid = 0;
-    float scale = inv_M * UR_FP16_SCALE;
-    bool done = false; // the same for the whole wavefront
 
     if (span.first == span.last) {
         const int32_t seg = cseg_seg[span.first];
@@ -761,64 +759,67 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
                     },
                     packed_stride, M, [] {}, [&](int w) { return lane_value(unit, w); }, span.n_lanes, acc, slots_of(lds_out, tid));
             });
-            scale = inv_M * ur_sum_scale(b);
-            done = true;
+            // This route ends here.  Joined with the general one ahead of finish_tile, the kernel spilled 18 registers,
+            // and the general one paid: widths mixed, 4.2 M ragged elements, M = 64 152 us before there were two routes,
+            // 206 joined, 137 now; one width in buckets of 512, M = 8, b = 2 33, 42, 31; this route, ResNet-18 shape, M = 8, b = 4
+            // 24.0 joined, 21.2 now.
+            finish_tile<UPDATE>(acc, active, n_valid, inv_M * ur_sum_scale(b), lds_out, tid, span.start, padded_elems, out, x, eta);
+            return;
         }
     }
-    if (!done) {
-        // the lane's own tensor, fetched beside the table (lanes past the end: the first one's)
-        const int32_t c = granule_cseg[(active ? P0 : span.start) >> 7];
-        n_valid = cseg_valid_end[c] - P0;
-        worker_entry* lds_entry = reinterpret_cast<worker_entry*>(lds_raw + UR_TILE * sizeof(float)) +
-                                  (tid >> 6) * UR_WAVE_SEGS * M; // [local seg][M]
-        const int n_local = span.last - span.first + 1;
-        for (int i = lane; i < n_local * M; i += 64) {
-            const int local = i / M, w = i - local * M;
-            const dq_cseg_width e = widths[static_cast<int64_t>(w) * n_cseg + span.first + local];
-            worker_entry we;
-            // every worker's sum is kept with the factor 2^-17 of widths 5 to 8: the narrower ones, whose
-            // own factor is 2^-9, get the rest of it on their unit (exact: a usable norm is at least 2^-100)
-            we.unit = ur_unit(norms[static_cast<int64_t>(w) * n_seg + cseg_seg[span.first + local]], e.b) *
-                      (ur_fp8_width(e.b) ? UR_FP8_SCALE / UR_FP16_SCALE : 1.0f);
-            we.b = e.b;
-            we.level_base = e.level_start - (e.seg_start >> 3) * e.b; // seg_start is a multiple of 128
-            lds_entry[i] = we;
-        }
-        dq_wave_sync();
-        if (active) {
-            const worker_entry* entry = lds_entry + (c - span.first) * M;
-            const uint8_t* sign_ptr = packed + (P0 >> 3);
-            // workers four at a time: sign dwords and up to eight level dwords each are fetched first
-            // (loads past a worker's width are skipped), then decoded width by width
-            constexpr int GROUP = 4;
-            block_total total{ slots_of(lds_out, tid) }; // the block sums of accumulate_workers: same order of additions
-            for (int w0 = 0; w0 < M; w0 += GROUP) {
-                uint32_t sg[GROUP], wd[GROUP][8];
-                worker_entry we[GROUP];
+
+    // the lane's own tensor, fetched beside the table (lanes past the end: the first one's)
+    const int32_t c = granule_cseg[(active ? P0 : span.start) >> 7];
+    n_valid = cseg_valid_end[c] - P0;
+    worker_entry* lds_entry = reinterpret_cast<worker_entry*>(lds_raw + UR_TILE * sizeof(float)) +
+                              (tid >> 6) * UR_WAVE_SEGS * M; // [local seg][M]
+    const int n_local = span.last - span.first + 1;
+    for (int i = lane; i < n_local * M; i += 64) {
+        const int local = i / M, w = i - local * M;
+        const dq_cseg_width e = widths[static_cast<int64_t>(w) * n_cseg + span.first + local];
+        worker_entry we;
+        // every worker's sum is kept with the factor 2^-17 of widths 5 to 8: the narrower ones, whose
+        // own factor is 2^-9, get the rest of it on their unit (exact: a usable norm is at least 2^-100)
+        we.unit = ur_unit(norms[static_cast<int64_t>(w) * n_seg + cseg_seg[span.first + local]], e.b) *
+                  (ur_fp8_width(e.b) ? UR_FP8_SCALE / UR_FP16_SCALE : 1.0f);
+        we.b = e.b;
+        we.level_base = e.level_start - (e.seg_start >> 3) * e.b; // seg_start is a multiple of 128
+        lds_entry[i] = we;
+    }
+    dq_wave_sync();
+    if (active) {
+        const worker_entry* entry = lds_entry + (c - span.first) * M;
+        const uint8_t* sign_ptr = packed + (P0 >> 3);
+        // workers four at a time: sign dwords and up to eight level dwords each are fetched first
+        // (loads past a worker's width are skipped), then decoded width by width
+        constexpr int GROUP = 4;
+        block_total total{ slots_of(lds_out, tid) }; // the block sums of accumulate_workers: same order of additions
+        for (int w0 = 0; w0 < M; w0 += GROUP) {
+            uint32_t sg[GROUP], wd[GROUP][8];
+            worker_entry we[GROUP];
 #pragma unroll
-                for (int i = 0; i < GROUP; ++i) {
-                    we[i].b = 0;
-                    if (w0 + i < M) {
-                        we[i] = entry[w0 + i];
-                        const int64_t msg = static_cast<int64_t>(w0 + i) * packed_stride;
-                        const uint32_t* lp =
-                            reinterpret_cast<const uint32_t*>(level_plane + msg + we[i].level_base + (P0 >> 3) * we[i].b);
-                        sg[i] = dq_load_stream(reinterpret_cast<const uint32_t*>(sign_ptr + msg));
+            for (int i = 0; i < GROUP; ++i) {
+                we[i].b = 0;
+                if (w0 + i < M) {
+                    we[i] = entry[w0 + i];
+                    const int64_t msg = static_cast<int64_t>(w0 + i) * packed_stride;
+                    const uint32_t* lp =
+                        reinterpret_cast<const uint32_t*>(level_plane + msg + we[i].level_base + (P0 >> 3) * we[i].b);
+                    sg[i] = dq_load_stream(reinterpret_cast<const uint32_t*>(sign_ptr + msg));
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) wd[i][q] = q < we[i].b ? lp[q] : 0u;
-                    }
+                    for (int q = 0; q < 8; ++q) wd[i][q] = q < we[i].b ? lp[q] : 0u;
                 }
-#pragma unroll
-                for (int i = 0; i < GROUP; ++i) // b = 0: past the last worker
-                    dq_with_width(we[i].b, [&](auto width) {
-                        accumulate_first_words<decltype(width)::value>(sg[i], wd[i], we[i].unit, acc);
-                    });
-                if (((w0 + GROUP) & (UR_SUM_BLOCK - 1)) == 0 && w0 + GROUP < M) total.flush(acc);
             }
-            total.finish(acc);
+#pragma unroll
+            for (int i = 0; i < GROUP; ++i) // b = 0: past the last worker
+                dq_with_width(we[i].b, [&](auto width) {
+                    accumulate_first_words<decltype(width)::value>(sg[i], wd[i], we[i].unit, acc);
+                });
+            if (((w0 + GROUP) & (UR_SUM_BLOCK - 1)) == 0 && w0 + GROUP < M) total.flush(acc);
         }
+        total.finish(acc);
     }
-    finish_tile<UPDATE>(acc, active, n_valid, scale, lds_out, tid, span.start, padded_elems, out, x, eta);
+    finish_tile<UPDATE>(acc, active, n_valid, inv_M * UR_FP16_SCALE, lds_out, tid, span.start, padded_elems, out, x, eta);
 }
 
 // acc[k] += sgn_k * scale for a lane's 32 elements: the scale with its sign flipped where the bit is set.
