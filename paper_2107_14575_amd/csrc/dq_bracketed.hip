@@ -887,6 +887,7 @@ extern "C" int dq_norm_bracket(const float* norms_dev, int64_t n, float margin, 
         (reinterpret_cast<uintptr_t>(norm_hi_dev) & 3u))
         return DQ_ERR_INVALID_ARG;
     if (n == 0) return DQ_OK;
+    dq_forget_earlier_errors();
     hipLaunchKernelGGL(k_norm_bracket, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0,
                        static_cast<hipStream_t>(hip_stream), norms_dev, n, 1.0f - margin, 1.0f + margin, norm_lo_dev,
                        norm_hi_dev);

@@ -142,6 +142,11 @@ int dq_zero_floats(float* dst_dev, int64_t n, hipStream_t stream);
 // and makes that GPU current.
 int dq_plan_check_device(const dq_plan* plan);
 
+// Launches are checked through the thread's last runtime error.  One that an earlier call of the program left there
+// (hipErrorInvalidDevice was seen where torch had just allocated new blocks) is not this call's: it is dropped
+// before the first launch, and dq_plan_check_device does so.
+inline void dq_forget_earlier_errors() { (void)hipGetLastError(); }
+
 // Streaming accesses: data that passes through once (a message being written or read, the averaged
 // gradient) is stored and loaded with the non-temporal hint, so it does not displace what the caches
 // could keep.  Measured at D = 2^28, M = 16, b = 4: quantize+pack 3.67 -> 3.48 ms with such stores,

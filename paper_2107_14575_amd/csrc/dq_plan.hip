@@ -222,6 +222,7 @@ int dq_plan_check_device(const dq_plan* plan)
     int cur = -1;
     if (hipGetDevice(&cur) != hipSuccess) return DQ_ERR_HIP;
     if (cur != plan->device && hipSetDevice(plan->device) != hipSuccess) return DQ_ERR_HIP;
+    dq_forget_earlier_errors();
     return DQ_OK;
 }
 
