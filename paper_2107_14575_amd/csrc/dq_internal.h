@@ -42,6 +42,10 @@ struct dq_plan {
     int device;           // HIP device the tables live on, -1 if none
     int32_t n_cseg;       // number of non-empty segments
     bool chunk_local;     // no segment crosses a multiple of 4096 in the padded index space
+    // At least a quarter of the chunks are of one tensor: the quantize kernels then look for them (see
+    // quantize_pack_chunk).  Against the form that does not, b = 1, 4, 6 take 1.02, 1.0, 1.04 of its time with no such
+    // chunk (tensors of 3000), 0.98, 0.96, 1.03 at 13 % (4700), 0.95, 0.94, 0.99 at 32 % (6000).
+    bool many_whole;
     void* d_tables;       // the one device allocation that holds all of the tables below
     // device tables.  Kernels address segments through a compact index c that counts only the
     // non-empty ones, so consecutive granules differ by at most one in c.

@@ -140,9 +140,11 @@ __device__ __forceinline__ void quantize_wave_tile(const float4 lo, const float4
 // First element (inside the chunk) of a lane's eight of tile `it`.  Each wavefront owns TILES
 // consecutive tiles of 512 elements, i.e. one stretch of every plane: it stages and stores its own
 // bytes, with no workgroup barrier between the two.
-template <int TILES>
+// BLOCK: the workgroup's lanes side by side in each of its tiles of 2048 elements instead (see qp_load_block).
+template <int TILES, bool BLOCK = false>
 __device__ __forceinline__ uint32_t qp_elem(uint32_t tid, int it)
 {
+    if constexpr (BLOCK) return it * QP_TILE + tid * QP_PER_LANE;
     return (tid >> 6) * (QP_WAVE_TILE * TILES) + it * QP_WAVE_TILE + (tid & 63u) * QP_PER_LANE;
 }
 
@@ -157,11 +159,26 @@ __device__ __forceinline__ void qp_load(const float* __restrict__ g, uint32_t ti
         dq_load_wave_tile(g, (tid >> 6) * (QP_WAVE_TILE * TILES) + it * QP_WAVE_TILE, tid & 63u, n_elems, x[it][0], x[it][1]);
 }
 
-// The granule (128 elements) of a lane's eight of tile `it`, clamped to the chunk's last one.
+// The same for layouts whose chunks hold several tensors: each lane loads its own eight elements, so that
+// nothing has to change places before they are used, and the workgroup stores its bytes together after a
+// barrier.
 template <int TILES>
+__device__ __forceinline__ void qp_load_block(const float* __restrict__ g, uint32_t tid, uint32_t n_elems, float4 (&x)[TILES][2])
+{
+#pragma unroll
+    for (int it = 0; it < TILES; ++it) {
+        uint32_t e = qp_elem<TILES, true>(tid, it);
+        e = e < n_elems ? e : n_elems - QP_PER_LANE;
+        x[it][0] = *reinterpret_cast<const float4*>(g + e);
+        x[it][1] = *reinterpret_cast<const float4*>(g + e + 4);
+    }
+}
+
+// The granule (128 elements) of a lane's eight of tile `it`, clamped to the chunk's last one.
+template <int TILES, bool BLOCK = false>
 __device__ __forceinline__ uint32_t qp_granule(uint32_t tid, int it, uint32_t n_elems)
 {
-    const uint32_t e = qp_elem<TILES>(tid, it);
+    const uint32_t e = qp_elem<TILES, BLOCK>(tid, it);
     return (e < n_elems ? e : n_elems - QP_PER_LANE) >> 7;
 }
 
@@ -173,6 +190,14 @@ __device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const u
     for (uint32_t i = lane; i < bytes / 16; i += 64) dq_store_stream(d + i, f[i]);
 }
 
+// The workgroup's staged bytes [0, bytes) (a multiple of 16), after a barrier.
+__device__ __forceinline__ void qp_store_block(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t tid)
+{
+    uint4* d = reinterpret_cast<uint4*>(dst);
+    const uint4* f = reinterpret_cast<const uint4*>(src);
+    for (uint32_t i = tid; i < bytes / 16; i += QP_THREADS) dq_store_stream(d + i, f[i]);
+}
+
 // What bounds it: the memory system's rate at 4 bytes read to (B+1)/8 written (about 6.1-6.2 TB/s, what a
 // kernel with the same accesses and no arithmetic reaches), with the vector ALU at 80 % beside it.  A chunk
 // that lies in one tensor (nearly all of a gradient of large tensors) takes the first route: two scalar
@@ -180,11 +205,15 @@ __device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const u
 // change places between the lanes instead of the values.  Measured at D = 2^28, M = 16 against the table
 // route alone: b = 2 3.36 -> 3.06 ms (6.1 TB/s), b = 4 3.39 -> 3.28 ms; ResNet-18 shape, M = 8, b = 2
 // 74.9 -> 66.9 us.  Chunks that hold a tensor's end or several tensors take the table.
+// WHOLE = false (NORM = 0 only): no such route, and the lanes' elements as qp_load_block has them, for layouts with
+// few chunks of one tensor (dq_plan::many_whole).  Measured there against the form with the route, in us: 5.4 M
+// values in tensors of 128, M = 8 b = 4 38.0 -> 36.6, 16.8 M in tensors of 512, M = 8 b = 6 121.8 -> 114.8 and, with a
+// widths table, b = 7 130.9 -> 122.4; 30.7 M in tensors of 1000, M = 4 b = 6 112.0 -> 104.5.
 //
 // NORM = 0: the norms are an input.  NORM = 1 (l2) or 2 (max): chunk-local plans only; the kernel
 // computes the norms of its chunk's tensors itself, writes them to norms_out and quantizes from
 // the registers it already holds -- one read of the gradient instead of two.
-template <int B, int TILES, int NORM>
+template <int B, int TILES, int NORM, bool WHOLE = true>
 __device__ __forceinline__ void quantize_pack_chunk(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
@@ -196,6 +225,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
     constexpr float S = static_cast<float>((1 << B) - 1);
     static_assert(CHUNK == DQ_CHUNK, "the chunk table and the fused norm work on 4096-element chunks");
+    constexpr bool BLOCK = NORM == 0 && !WHOLE;
 
     __shared__ float lds_scale[MAX_LOCAL_SEG];
     __shared__ int32_t lds_valid_end[MAX_LOCAL_SEG]; // relative to the chunk, clamped to CHUNK
@@ -212,7 +242,10 @@ __device__ __forceinline__ void quantize_pack_chunk(
 
     // This lane's inputs first, so the loads are in flight while the segment table is built.
     float4 x[TILES][2];
-    qp_load<TILES>(g, tid, n_elems, x);
+    if constexpr (BLOCK)
+        qp_load_block<TILES>(g, tid, n_elems, x);
+    else
+        qp_load<TILES>(g, tid, n_elems, x);
 
     // Philox counter words: quad index P>>2 (low word varies per lane, high word is uniform because
     // a chunk never straddles a multiple of 2^34 elements), worker, step
@@ -222,7 +255,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
     uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
     const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
 
-    if constexpr (NORM == 0) {
+    if constexpr (NORM == 0 && WHOLE) {
         const dq_chunk_tensor whole = dq_load_chunk_tensor(chunk_tensor, chunk0 / DQ_CHUNK);
         const float N = norms[static_cast<int64_t>(w) * n_seg + whole.seg]; // issued whatever cseg is: one wait less
         if (whole.cseg >= 0) { // 4096 elements of one tensor: one scale, nothing to mask, no table, no barrier
@@ -247,7 +280,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
 
     int32_t seg[TILES];
 #pragma unroll
-    for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES>(tid, it, n_elems)];
+    for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES, BLOCK>(tid, it, n_elems)];
 
     // compact segment indices grow by at most one per granule, so the chunk's segments fit the table
     const int32_t seg_first = gseg[0];
@@ -260,8 +293,10 @@ __device__ __forceinline__ void quantize_pack_chunk(
             lds_valid_end[tid] = rel < CHUNK ? static_cast<int32_t>(rel) : CHUNK;
         }
         __syncthreads();
+        if constexpr (!BLOCK) {
 #pragma unroll
-        for (int it = 0; it < TILES; ++it) dq_arrange_wave_tile(x[it][0], x[it][1]);
+            for (int it = 0; it < TILES; ++it) dq_arrange_wave_tile(x[it][0], x[it][1]);
+        }
     } else {
         __shared__ double lds_gsum[DQ_CHUNK_GRANULES];
         __shared__ int32_t lds_glocal[DQ_CHUNK_GRANULES];
@@ -274,7 +309,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
 #pragma unroll
         for (int it = 0; it < TILES; ++it) {
             dq_arrange_wave_tile(x[it][0], x[it][1]);
-            const uint32_t e = qp_elem<TILES>(tid, it);
+            const uint32_t e = qp_elem<TILES, BLOCK>(tid, it);
             granule[it] = static_cast<int>(e >> 7);
             local[it] = seg[it] - seg_first;
             valid[it] = e < n_elems ? lds_valid_end[local[it]] - static_cast<int32_t>(e) : 0;
@@ -294,7 +329,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
 
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
-        const uint32_t e = qp_elem<TILES>(tid, it);
+        const uint32_t e = qp_elem<TILES, BLOCK>(tid, it);
         if (e < n_elems) {
             const int local = seg[it] - seg_first;
             const float scale = lds_scale[local];
@@ -314,6 +349,12 @@ __device__ __forceinline__ void quantize_pack_chunk(
             stage_bytes<B>(&lds_level[(e >> 3) * B], level);
         }
     }
+    if constexpr (BLOCK) {
+        __syncthreads();
+        qp_store_block(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid);
+        qp_store_block(msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_level, (n_elems >> 3) * B, tid);
+        return;
+    }
     dq_wave_sync();
 
     // 16-byte stores of this wavefront's stretch; every plane of it is a whole number of 16-byte
@@ -332,7 +373,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
 // still one contiguous stretch of the message (every segment's stretch is a whole number of
 // 16-byte pieces per granule), so they are staged and stored the same way.
 // ---------------------------------------------------------------------------------------------
-template <int TILES, int NORM> // NORM as in quantize_pack_chunk
+template <int TILES, int NORM, bool WHOLE = true> // as in quantize_pack_chunk
 __device__ __forceinline__ void quantize_pack_chunk_v(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
@@ -344,6 +385,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
     static_assert(CHUNK == DQ_CHUNK, "the chunk table and the fused norm work on 4096-element chunks");
+    constexpr bool BLOCK = NORM == 0 && !WHOLE;
     // this worker's row of the table (stride 0: the workers share one row)
     const dq_cseg_width* __restrict__ widths = widths_table + static_cast<int64_t>(blockIdx.y) * widths_worker_stride;
 
@@ -364,7 +406,10 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     const int32_t* gseg = granule_cseg + (chunk0 >> 7);
 
     float4 x[TILES][2];
-    qp_load<TILES>(g, tid, n_elems, x);
+    if constexpr (BLOCK)
+        qp_load_block<TILES>(g, tid, n_elems, x);
+    else
+        qp_load<TILES>(g, tid, n_elems, x);
 
     const uint32_t quad_lo0 = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 2);
     const uint32_t quad_hi = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 34);
@@ -372,7 +417,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
     const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
 
-    if constexpr (NORM == 0) { // one tensor: as in quantize_pack_chunk, its width from one (scalar) table entry
+    if constexpr (NORM == 0 && WHOLE) { // one tensor: as in quantize_pack_chunk, its width from one (scalar) table entry
         const dq_chunk_tensor whole = dq_load_chunk_tensor(chunk_tensor, chunk0 / DQ_CHUNK);
         const float N = norms[static_cast<int64_t>(w) * n_seg + whole.seg];
         if (whole.cseg >= 0) {
@@ -399,7 +444,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
 
     int32_t seg[TILES];
 #pragma unroll
-    for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES>(tid, it, n_elems)];
+    for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES, BLOCK>(tid, it, n_elems)];
 
     const int32_t seg_first = gseg[0];
     const int32_t seg_last = gseg[(n_elems - 1) >> 7];
@@ -421,15 +466,17 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
         lds_valid_end[tid] = rel < CHUNK ? static_cast<int32_t>(rel) : CHUNK;
     }
     __syncthreads();
+    if constexpr (!BLOCK) {
 #pragma unroll
-    for (int it = 0; it < TILES; ++it) dq_arrange_wave_tile(x[it][0], x[it][1]);
+        for (int it = 0; it < TILES; ++it) dq_arrange_wave_tile(x[it][0], x[it][1]);
+    }
     if constexpr (NORM != 0) {
         __shared__ double lds_gsum[DQ_CHUNK_GRANULES];
         __shared__ int32_t lds_glocal[DQ_CHUNK_GRANULES];
         int valid[TILES], local[TILES], granule[TILES];
 #pragma unroll
         for (int it = 0; it < TILES; ++it) {
-            const uint32_t e = qp_elem<TILES>(tid, it);
+            const uint32_t e = qp_elem<TILES, BLOCK>(tid, it);
             granule[it] = static_cast<int>(e >> 7);
             local[it] = seg[it] - seg_first;
             valid[it] = e < n_elems ? lds_valid_end[local[it]] - static_cast<int32_t>(e) : 0;
@@ -449,7 +496,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
 
 #pragma unroll
     for (int it = 0; it < TILES; ++it) {
-        const uint32_t e = qp_elem<TILES>(tid, it);
+        const uint32_t e = qp_elem<TILES, BLOCK>(tid, it);
         if (e < n_elems) {
             const int local = seg[it] - seg_first;
             const float scale = lds_scale[local];
@@ -471,6 +518,14 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
             // stretch of a chunk starts on one), so the naturally aligned stores of stage_bytes apply
             stage_bytes_v(&lds_level[lds_level_base[local] + static_cast<int32_t>(e >> 3) * b], level, b);
         }
+    }
+    if constexpr (BLOCK) {
+        __syncthreads();
+        const int last = seg_last - seg_first;
+        qp_store_block(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid);
+        qp_store_block(msg + (padded_elems >> 3) + chunk_level0, lds_level,
+                       static_cast<uint32_t>(lds_level_base[last]) + (n_elems >> 3) * lds_b[last], tid);
+        return;
     }
     dq_wave_sync();
 

@@ -16,7 +16,7 @@
 
 namespace {
 
-template <int B, int TILES, int NORM>
+template <int B, int TILES, int NORM, bool WHOLE>
 __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
@@ -25,12 +25,12 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack(
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
     int64_t packed_stride, float* __restrict__ norms_out)
 {
-    quantize_pack_chunk<B, TILES, NORM>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
+    quantize_pack_chunk<B, TILES, NORM, WHOLE>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                         padded_elems, key0, key1, step, worker_base, packed, packed_stride, norms_out,
                                         blockIdx.x);
 }
 
-template <int TILES, int NORM> // NORM as in k_quantize_pack
+template <int TILES, int NORM, bool WHOLE> // as in k_quantize_pack
 __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
     int64_t packed_stride, float* __restrict__ norms_out)
 {
-    quantize_pack_chunk_v<TILES, NORM>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
+    quantize_pack_chunk_v<TILES, NORM, WHOLE>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                        widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
                                        packed, packed_stride, norms_out, blockIdx.x);
 }
@@ -104,10 +104,17 @@ int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M
 {
     const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
-    hipLaunchKernelGGL((k_quantize_pack<B, QP_TILES, NORM>), dim3(static_cast<unsigned>(n_chunks), M), dim3(QP_THREADS),
-                       0, stream, grads, worker_stride, norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,
-                       plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, static_cast<uint32_t>(seed),
-                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out);
+    const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
+#define DQ_LAUNCH_Q(WHOLE)                                                                                        \
+    hipLaunchKernelGGL((k_quantize_pack<B, QP_TILES, NORM, WHOLE>), grid, block, 0, stream, grads, worker_stride, \
+                       norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,          \
+                       plan->d_cseg_valid_end, plan->padded_elems, static_cast<uint32_t>(seed),                   \
+                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out)
+    if (NORM != 0 || plan->many_whole)
+        DQ_LAUNCH_Q(true);
+    else
+        DQ_LAUNCH_Q(NORM != 0); // false; a kernel that works out the norms has the one form only
+#undef DQ_LAUNCH_Q
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
 
@@ -179,18 +186,20 @@ int quantize_v_entry(int norm_mode, const dq_plan_t* plan, const dq_widths_t* wi
     const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
-#define DQ_LAUNCH_QV(NORM)                                                                                        \
-    hipLaunchKernelGGL((k_quantize_pack_v<QP_TILES, NORM>), grid, block, 0, stream, grads_dev, worker_stride_elems, \
-                       norms_in, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,       \
-                       plan->d_cseg_valid_end, widths->d_table, row_stride, plan->padded_elems, static_cast<uint32_t>(seed), \
-                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed_dev, packed_worker_stride_bytes, \
-                       norms_out)
-    if (norm_mode == 0)
-        DQ_LAUNCH_QV(0);
+#define DQ_LAUNCH_QV(NORM, WHOLE)                                                                                 \
+    hipLaunchKernelGGL((k_quantize_pack_v<QP_TILES, NORM, WHOLE>), grid, block, 0, stream, grads_dev,             \
+                       worker_stride_elems, norms_in, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,    \
+                       plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, row_stride, plan->padded_elems, \
+                       static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), step, worker_base,         \
+                       packed_dev, packed_worker_stride_bytes, norms_out)
+    if (norm_mode == 0 && plan->many_whole)
+        DQ_LAUNCH_QV(0, true);
+    else if (norm_mode == 0)
+        DQ_LAUNCH_QV(0, false);
     else if (norm_mode == 1)
-        DQ_LAUNCH_QV(1);
+        DQ_LAUNCH_QV(1, true);
     else
-        DQ_LAUNCH_QV(2);
+        DQ_LAUNCH_QV(2, true);
 #undef DQ_LAUNCH_QV
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
