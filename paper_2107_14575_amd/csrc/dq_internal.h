@@ -151,13 +151,13 @@ int dq_plan_check_device(const dq_plan* plan);
 // before the first launch, and dq_plan_check_device does so.
 inline void dq_forget_earlier_errors() { (void)hipGetLastError(); }
 
-// Streaming accesses: data that passes through once (a message being written or read, the averaged
-// gradient) is stored and loaded with the non-temporal hint, so it does not displace what the caches
-// could keep.  Measured at D = 2^28, M = 16, b = 4: quantize+pack 3.67 -> 3.48 ms with such stores,
-// the reduce 0.68 -> 0.59 ms with such loads and stores, the norm pass 2.69 -> 2.57 ms with such loads
-// (in quantize+pack non-temporal loads of the gradients cost 4 % instead: they stay plain there).
+// Streaming accesses: data that passes through once (a gradient or a message being read, a message or the averaged
+// gradient being written) is loaded and stored with the non-temporal hint, so it does not displace what the caches
+// could keep.  Measured at D = 2^28, M = 16, b = 4: quantize+pack 3.67 -> 3.48 ms with such stores, the reduce
+// 0.68 -> 0.59 ms with such loads and stores, the norm pass 2.69 -> 2.57 ms with such loads.  The hint pays where one
+// load instruction covers whole cache lines (dq_load_wave_tile); where a line is met by several it costs instead
+// (quantize+pack with two 16-byte loads per lane 4 %; the level loads of widths 5 to 7 in the reduce).
 typedef uint32_t dq_v4u __attribute__((ext_vector_type(4)));
-typedef uint32_t dq_v2u __attribute__((ext_vector_type(2)));
 typedef float dq_v4f __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void dq_store_stream(uint4* dst, const uint4& v)
 {
@@ -173,16 +173,6 @@ __device__ __forceinline__ float4 dq_load_stream(const float4* src)
 {
     const dq_v4f t = __builtin_nontemporal_load(reinterpret_cast<const dq_v4f*>(src));
     return make_float4(t.x, t.y, t.z, t.w);
-}
-__device__ __forceinline__ uint4 dq_load_stream(const uint4* src)
-{
-    const dq_v4u t = __builtin_nontemporal_load(reinterpret_cast<const dq_v4u*>(src));
-    return make_uint4(t.x, t.y, t.z, t.w);
-}
-__device__ __forceinline__ uint2 dq_load_stream(const uint2* src)
-{
-    const dq_v2u t = __builtin_nontemporal_load(reinterpret_cast<const dq_v2u*>(src));
-    return make_uint2(t.x, t.y);
 }
 __device__ __forceinline__ uint32_t dq_load_stream(const uint32_t* src) { return __builtin_nontemporal_load(src); }
 

@@ -1,17 +1,19 @@
 // dq_quantize_pack: the EWU quantizer of Eq. (5)-(6) fused with the packing of the message whose
 // size Eq. (7) counts.
 //
-// Work split.  One workgroup (256 lanes) owns TILES consecutive tiles of 2048 padded elements of
-// one worker; a lane owns 8 consecutive elements of each tile (two 16-byte loads, two Philox
-// blocks), so its output is exactly one sign byte and B level bytes.  Those bytes are staged in
-// LDS and leave the workgroup as 16-byte stores that cover each plane's bytes contiguously.
+// Work split.  One workgroup (256 lanes) owns a chunk of 4096 consecutive padded elements of one worker, each of its
+// four wavefronts two tiles of 512; a lane's eight elements of a tile (two Philox blocks) give exactly one sign byte
+// and B level bytes.  A tile is loaded by two instructions of 1 KiB each, which hand a lane two quads of elements
+// from different places (dq_load_wave_tile).  The bytes are staged in LDS and leave the wavefront as 16-byte stores
+// that cover each plane's bytes contiguously.
 //
-// Per-segment state.  The scale s/N and the end of the valid range of every segment the
-// workgroup touches (at most one per 128-element granule) are put in LDS once per workgroup, so
-// the one binary32 division per (worker, segment) is never on a lane's critical path.
+// A chunk inside one tensor (nearly every one of a gradient of large tensors): the plan's chunk table names the
+// tensor, so one scalar load of 8 bytes, one of the norm and one binary32 division per wavefront give the scale;
+// the lanes quantize the quads as loaded and the codes change places.  Other chunks: the granule table (4 bytes per
+// 128 elements) names their tensors, whose scales s/N and ends are put in LDS once per workgroup, and the values
+// change places.  Layouts with few chunks of the first kind have a form of their own (qp_load_block).
 //
-// HBM traffic per element: 4 bytes read, (B+1)/8 bytes written, plus 4 bytes per 128 elements for
-// the granule table.
+// HBM traffic per element: 4 bytes read, (B+1)/8 bytes written, plus the tables.
 #include "dq_quantize_core.h"
 
 namespace {

@@ -1,7 +1,9 @@
 """The server average where its kernels change route: wavefronts of 2048 elements inside one tensor, shared
 by several, and cut short by the layout's end; tile counts around the multiples of 32 in which workgroups
 are assigned; widths 5 to 8 (levels as 16-bit floats) at both ends of the usable norms; one width for all
-workers of a tensor and mixed ones.  Messages are random bits, the reference is the oracle's average.
+workers of a tensor and mixed ones.  Messages are random codes packed by the oracle.  The reference is the mean of the
+same binary32 terms in binary64, worked out here; the oracle's average (rounded to binary32) is compared where the norms
+are moderate.
 
 Tolerance: that of test_gpu_average_worst_case, 1e-6 of the mean magnitude of the terms."""
 import numpy as np
@@ -65,6 +67,7 @@ def test_one_width(dq, oracle, seg_len, b):
     out = torch.full((plan.padded_elems,), float("nan"), device="cuda")
     dq.unpack_dequant_reduce(plan, packed, norms_dev, b, out)
     _check(out.cpu().numpy(), mean, mag)
+    _check(out.cpu().numpy(), oracle.unpack_dequant_reduce(seg_len, packed.cpu().numpy(), norms, b).astype(np.float64), mag)
     # with update: the average beside it has the same bits, x is one FMA of it
     x0 = rng.standard_normal(plan.padded_elems).astype(np.float32)
     x, ghat = torch.from_numpy(x0).cuda(), torch.full_like(out, float("nan"))
@@ -129,6 +132,7 @@ def test_workers_of_mixed_widths(dq, oracle, M):
     out = torch.full((plan.padded_elems,), float("nan"), device="cuda")
     dq.unpack_dequant_reduce_v(plan, table, torch.from_numpy(packed).cuda(), torch.from_numpy(norms).cuda(), out)
     _check(out.cpu().numpy(), mean, mag)
+    _check(out.cpu().numpy(), oracle.unpack_dequant_reduce_w(seg_len, packed, norms, widths).astype(np.float64), mag)
     table.close()
     plan.close()
 
