@@ -50,6 +50,32 @@ __device__ __forceinline__ uint32_t level_of_s(float v, float scale, float S, ui
     return static_cast<uint32_t>(a) + (u < p ? 1u : 0u);
 }
 
+// A quad's elements whose level the bracket leaves open: `open` holds their fields of b bits, and those fields of lv are
+// cleared for the settle kernel.  e: the quad's first element in the chunk.  Few lanes have any, and seldom more than
+// one: a lane takes one per turn and picks its value from the registers.  With code of its own for each of a lane's
+// eight elements the kernels needed 85 to 88 registers for the random numbers kept across the second look (five wavefronts
+// per SIMD); so they need 70 to 72 (seven): 2^24 values, M = 16, b = 2 254 -> 245 us, ResNet-18 shape, M = 8, b = 3
+// 105 -> 97.
+__device__ __forceinline__ void record_open(uint32_t open, const float4 x, const int b, const uint32_t e, uint32_t* count,
+                                            dq_bracket_block* __restrict__ blk, uint32_t& lv)
+{
+    const uint32_t field = (1u << b) - 1u;
+    open &= static_cast<uint32_t>((static_cast<uint64_t>(1) << (4 * b)) - 1u); // each turn clears one of four fields: at most four turns
+    while (open != 0) {
+        const int bit = __builtin_ctz(open);
+        const uint32_t k = (bit >= b ? 1u : 0u) + (bit >= 2 * b ? 1u : 0u) + (bit >= 3 * b ? 1u : 0u);
+        const uint32_t keep = ~(field << (k * b));
+        const float lo = (k & 1u) ? x.y : x.x, hi = (k & 1u) ? x.w : x.z;
+        const uint32_t slot = atomicAdd(count, 1u);
+        if (slot < DQ_BRACKET_CAP) { // a 32-bit offset from the uniform block: no 64-bit address in registers
+            const uint32_t at = static_cast<uint32_t>(offsetof(dq_bracket_block, rec)) + slot * static_cast<uint32_t>(sizeof(uint2));
+            *reinterpret_cast<uint2*>(reinterpret_cast<char*>(blk) + at) = make_uint2(e + k, __float_as_uint((k & 2u) ? hi : lo));
+        }
+        open &= keep;
+        lv &= keep;
+    }
+}
+
 // A chunk that lies in one tensor which goes on beyond it -- nearly every chunk of a gradient of large
 // tensors: one bracket for all of it (two scalar loads and two divisions), nothing to mask.  The squares
 // are added from the values as they were loaded, the lanes quantize the two quads they loaded and the
@@ -74,7 +100,6 @@ __device__ __forceinline__ void bracketed_one_tensor(const float4 (&x)[2][2], fl
                                                      double* __restrict__ partial)
 {
     constexpr float S = static_cast<float>((1 << B) - 1);
-    constexpr uint32_t FIELD = (1u << B) - 1u;
     const uint32_t lane = tid & 63u;
 
     double row;
@@ -126,30 +151,22 @@ __device__ __forceinline__ void bracketed_one_tensor(const float4 (&x)[2][2], fl
             const uint32_t tile0 = wave0 + it * QP_WAVE_TILE;
             const uint32_t e0 = tile0 + (lane & 31u) * 8u + (lane >> 5) * 4u; // elements e0.. and e0 + 256..
             const uint32_t quad = quad_lo0 + (e0 >> 2);
-            uint32_t sg[2], lv[2], r[2][4];
+            uint32_t sg[2], lv[2], sign;
+            uint64_t level;
+            float t[8];
             // levels at the low end of the bracket: the largest any norm inside it can give
-            quantize_quads<B>(x[it][0], x[it][1], scale_hi, 0.0f, 0, quad, quad + 64u, quad_hi, worker, step, key0, key1,
-                              sg, lv, r);
-            if ((lv[0] | lv[1]) != 0) { // a zero at the low end is a zero everywhere in the bracket
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const float v[4] = { x[it][h].x, x[it][h].y, x[it][h].z, x[it][h].w };
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const uint32_t top = (lv[h] >> (k * B)) & FIELD;
-                        if (top != 0 && level_of<B>(v[k], scale_lo, r[h][k]) != top) {
-                            const uint32_t slot = atomicAdd(&state->count, 1u);
-                            if (slot < DQ_BRACKET_CAP) blk->rec[slot] = make_uint2(e0 + h * 256 + k, __float_as_uint(v[k]));
-                            lv[h] &= ~(FIELD << (k * B)); // left zero for the settle kernel
-                        }
-                    }
-                }
+            const qp_range range = quantize_quads<B>(x[it][0], x[it][1], scale_hi, 0.0f, 0, quad, quad + 64u, quad_hi, worker,
+                                                     step, key0, key1, sg, lv, t);
+            if (__any((lv[0] | lv[1]) != 0)) { // a zero at the low end is a zero everywhere in the bracket
+                uint32_t lv_lo[2];
+                quantize_again<B>(range, x[it][0], x[it][1], scale_lo, 0.0f, 0, t, lv_lo);
+                record_open(lv[0] ^ lv_lo[0], x[it][0], B, e0, &state->count, blk, lv[0]);
+                record_open(lv[1] ^ lv_lo[1], x[it][1], B, e0 + 256, &state->count, blk, lv[1]);
             }
-            const auto s = __builtin_amdgcn_permlane32_swap(sg[0], sg[1], false, false);
-            const auto l = __builtin_amdgcn_permlane32_swap(lv[0], lv[1], false, false);
+            quantize_exchange<B>(sg, lv, 0, sign, level);
             const uint32_t at = (tile0 >> 3) + lane;
-            lds_sign[at] = static_cast<uint8_t>(s[0] | (s[1] << 4));
-            stage_bytes<B>(&lds_level[at * B], static_cast<uint64_t>(l[0]) | (static_cast<uint64_t>(l[1]) << (4 * B)));
+            lds_sign[at] = static_cast<uint8_t>(sign);
+            stage_bytes<B>(&lds_level[at * B], level);
         }
         dq_wave_sync();
         qp_store_wave(sign_chunk + (wave0 >> 3), &lds_sign[wave0 >> 3], QP_WAVE_TILE * 2 / 8, lane);
@@ -194,7 +211,7 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
     constexpr int TILES = 2;
     constexpr int CHUNK = DQ_CHUNK;
     constexpr float S = static_cast<float>((1 << B) - 1);
-    constexpr uint64_t FIELD = (static_cast<uint64_t>(1) << B) - 1u;
+    constexpr uint32_t quad_fields = static_cast<uint32_t>((static_cast<uint64_t>(1) << (4 * B)) - 1u);
 
     __shared__ float lds_scale_hi[DQ_CHUNK_GRANULES]; // s / lo: the larger scale
     __shared__ float lds_scale_lo[DQ_CHUNK_GRANULES]; // s / hi
@@ -306,30 +323,27 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
         if (e < n_elems) {
             const uint32_t quad = quad_lo0 + (e >> 2);
             // levels at the low end of the bracket: the largest any norm inside it can give
-            uint32_t sign, rr[2][4];
-            uint64_t level;
-            quantize8<B>(x[it][0], x[it][1], lds_scale_hi[local[it]], 0.0f, 0, quad, quad_hi, worker, step, key0, key1,
-                         sign, level, rr);
+            uint32_t sg[2], lv[2];
+            float t[8];
+            const qp_range range = quantize_quads<B>(x[it][0], x[it][1], lds_scale_hi[local[it]], 0.0f, 0, quad, quad + 1u,
+                                                     quad_hi, worker, step, key0, key1, sg, lv, t);
             const int nv = valid[it] >= QP_PER_LANE ? QP_PER_LANE : (valid[it] > 0 ? valid[it] : 0);
-            if (nv < QP_PER_LANE) {
+            uint32_t sign = quantize_sign_byte(sg[0], sg[1]);
+            if (nv < QP_PER_LANE) { // the tensor ends inside (or before) this lane's eight elements
                 sign &= (1u << nv) - 1u;
-                level &= (static_cast<uint64_t>(1) << (nv * B)) - 1u;
+                const uint64_t fields = (static_cast<uint64_t>(1) << (nv * B)) - 1u;
+                lv[0] &= static_cast<uint32_t>(fields) & quad_fields;
+                lv[1] &= static_cast<uint32_t>(fields >> (4 * B));
             }
-            if (level != 0) { // a zero at the low end is a zero everywhere in the bracket
-                const float scale_lo = lds_scale_lo[local[it]];
-                const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w,
-                                     x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
-                const uint32_t r[8] = { rr[0][0], rr[0][1], rr[0][2], rr[0][3], rr[1][0], rr[1][1], rr[1][2], rr[1][3] };
-#pragma unroll
-                for (int k = 0; k < QP_PER_LANE; ++k) {
-                    const uint32_t top = static_cast<uint32_t>(level >> (k * B)) & static_cast<uint32_t>(FIELD);
-                    if (top != 0 && level_of<B>(v[k], scale_lo, r[k]) != top) {
-                        const uint32_t slot = atomicAdd(&lds_count, 1u);
-                        if (slot < DQ_BRACKET_CAP) blk->rec[slot] = make_uint2(e + k, __float_as_uint(v[k]));
-                        level &= ~(FIELD << (k * B)); // left zero for the settle kernel
-                    }
-                }
+            if ((lv[0] | lv[1]) != 0) { // a zero at the low end is a zero everywhere in the bracket
+                uint32_t lv_lo[2];
+                quantize_again<B>(range, x[it][0], x[it][1], lds_scale_lo[local[it]], 0.0f, 0, t, lv_lo);
+                // (lv is zero past the tensor's end, so is what lv_lo has there once masked)
+                const uint64_t fields = nv < QP_PER_LANE ? (static_cast<uint64_t>(1) << (nv * B)) - 1u : ~static_cast<uint64_t>(0);
+                record_open(lv[0] ^ (lv_lo[0] & static_cast<uint32_t>(fields) & quad_fields), x[it][0], B, e, &lds_count, blk, lv[0]);
+                record_open(lv[1] ^ (lv_lo[1] & static_cast<uint32_t>(fields >> (4 * B))), x[it][1], B, e + 4u, &lds_count, blk, lv[1]);
             }
+            const uint64_t level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * B));
             lds_sign[e >> 3] = static_cast<uint8_t>(sign);
             stage_bytes<B>(&lds_level[(e >> 3) * B], level);
         }
@@ -356,8 +370,10 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
 // The first kernel with per-tensor widths (dq_widths_t: one row shared by the workers or one row per
 // worker): b, the level count and the place of the level bytes of every tensor the chunk touches
 // come from the widths table, as in quantize_pack_chunk_v; everything else as above.
+// Seven wavefronts per SIMD as there, which the compiler takes 74 registers to miss unless told: 2^26 values, M = 16, b = 4
+// 962 -> 938 us; eight spill (1393).
 template <bool LINF>
-__global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed_v(
+__global__ __launch_bounds__(QP_THREADS, 7) void k_quantize_pack_bracketed_v(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norm_lo,
     const float* __restrict__ norm_hi, int32_t n_seg, const dq_chunk_tensor* __restrict__ chunk_tensor,
     const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_start,
@@ -493,32 +509,30 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed_v(
         if (e < n_elems) {
             const float S = lds_levels[local[it]];
             const int b = lds_b[local[it]];
-            const uint64_t field = (static_cast<uint64_t>(1) << b) - 1u;
+            const uint32_t quad_fields = static_cast<uint32_t>((static_cast<uint64_t>(1) << (4 * b)) - 1u);
             const uint32_t quad = quad_lo0 + (e >> 2);
-            uint32_t sign, rr[2][4];
-            uint64_t level;
-            quantize8<0>(x[it][0], x[it][1], lds_scale_hi[local[it]], S, b, quad, quad_hi, worker, step, key0, key1,
-                         sign, level, rr);
-            const int nv = valid[it] >= QP_PER_LANE ? QP_PER_LANE : (valid[it] > 0 ? valid[it] : 0);
-            if (nv < QP_PER_LANE) {
+            uint32_t sg[2], lv[2];
+            float t[8];
+            const qp_range range = quantize_quads<0>(x[it][0], x[it][1], lds_scale_hi[local[it]], S, b, quad, quad + 1u,
+                                                     quad_hi, worker, step, key0, key1, sg, lv, t);
+            const int left = lds_valid_end[local[it]] - static_cast<int32_t>(e); // read again: seven wavefronts leave no register for it
+            const int nv = left >= QP_PER_LANE ? QP_PER_LANE : (left > 0 ? left : 0);
+            uint32_t sign = quantize_sign_byte(sg[0], sg[1]);
+            if (nv < QP_PER_LANE) { // the tensor ends inside (or before) this lane's eight elements
                 sign &= (1u << nv) - 1u;
-                level &= (static_cast<uint64_t>(1) << (nv * b)) - 1u;
+                const uint64_t fields = (static_cast<uint64_t>(1) << (nv * b)) - 1u;
+                lv[0] &= static_cast<uint32_t>(fields) & quad_fields;
+                lv[1] &= static_cast<uint32_t>(fields >> (4 * b));
             }
-            if (level != 0) {
-                const float scale_lo = lds_scale_lo[local[it]];
-                const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w,
-                                     x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
-                const uint32_t r[8] = { rr[0][0], rr[0][1], rr[0][2], rr[0][3], rr[1][0], rr[1][1], rr[1][2], rr[1][3] };
-#pragma unroll
-                for (int k = 0; k < QP_PER_LANE; ++k) {
-                    const uint32_t top = static_cast<uint32_t>(level >> (k * b)) & static_cast<uint32_t>(field);
-                    if (top != 0 && level_of_s(v[k], scale_lo, S, r[k]) != top) {
-                        const uint32_t slot = atomicAdd(&lds_count, 1u);
-                        if (slot < DQ_BRACKET_CAP) blk->rec[slot] = make_uint2(e + k, __float_as_uint(v[k]));
-                        level &= ~(field << (k * b));
-                    }
-                }
+            if ((lv[0] | lv[1]) != 0) { // a zero at the low end is a zero everywhere in the bracket
+                uint32_t lv_lo[2];
+                quantize_again<0>(range, x[it][0], x[it][1], lds_scale_lo[local[it]], S, b, t, lv_lo);
+                // (lv is zero past the tensor's end, so is what lv_lo has there once masked)
+                const uint64_t fields = nv < QP_PER_LANE ? (static_cast<uint64_t>(1) << (nv * b)) - 1u : ~static_cast<uint64_t>(0);
+                record_open(lv[0] ^ (lv_lo[0] & static_cast<uint32_t>(fields) & quad_fields), x[it][0], b, e, &lds_count, blk, lv[0]);
+                record_open(lv[1] ^ (lv_lo[1] & static_cast<uint32_t>(fields >> (4 * b))), x[it][1], b, e + 4u, &lds_count, blk, lv[1]);
             }
+            const uint64_t level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * b));
             lds_sign[e >> 3] = static_cast<uint8_t>(sign);
             stage_bytes_v(&lds_level[lds_level_base[local[it]] + static_cast<int32_t>(e >> 3) * b], level, b);
         }

@@ -19,7 +19,7 @@ template <int N>
 __device__ __forceinline__ float dq_row_ror(float v)
 {
     return __uint_as_float(static_cast<uint32_t>(
-        __builtin_amdgcn_update_dpp(0, static_cast<int>(__float_as_uint(v)), 0x120 + N, 0xF, 0xF, false)));
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(__float_as_uint(v)), 0x120 + N, 0xF, 0xF, true)));
 }
 
 template <int N>
@@ -27,9 +27,9 @@ __device__ __forceinline__ double dq_row_ror(double v)
 {
     const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(v));
     const uint32_t lo = static_cast<uint32_t>(
-        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(bits)), 0x120 + N, 0xF, 0xF, false));
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(bits)), 0x120 + N, 0xF, 0xF, true));
     const uint32_t hi = static_cast<uint32_t>(
-        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(bits >> 32)), 0x120 + N, 0xF, 0xF, false));
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(bits >> 32)), 0x120 + N, 0xF, 0xF, true));
     return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
 }
 

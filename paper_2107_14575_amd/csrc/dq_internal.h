@@ -209,19 +209,26 @@ __device__ __forceinline__ void dq_wave_sync()
 // lanes 0..31 the first four elements of lanes 0..31's eight, lanes 32..63 the last four; the second
 // one [256, 512) the same way for lanes 32..63 -- with the streaming hint, and four swaps between the
 // halves of the wavefront put every lane's own elements in place.
-//   base       the tile's first element, relative to g
-//   n_elems    elements of g that exist (a multiple of 128, at least 128): a 16-byte load past them is
-//              taken from the last four instead (in bounds, and only lanes past the end receive it)
-__device__ __forceinline__ void dq_load_wave_tile(const float* __restrict__ g, uint32_t base, uint32_t lane,
-                                                  uint32_t n_elems, float4& lo, float4& hi)
+// The loads are buffer loads over the workgroup's n_elems elements: one address register serves all of a lane's tiles
+// (the rest is the instruction's immediate offset), and what lies past the end reads as zero.  As global loads with
+// clamped offsets a lane's four loads took fourteen instructions more.
+//   base       the tile's first element, relative to the buffer
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t dq_elems_buffer(const float* g, uint32_t n_elems)
 {
-    uint32_t e0 = base + (lane & 31u) * 8u + (lane >> 5) * 4u, e1 = e0 + 256u;
-    e0 = e0 < n_elems ? e0 : n_elems - 4u;
-    e1 = e1 < n_elems ? e1 : n_elems - 4u;
-    // 32-bit byte offsets from the uniform base: no 64-bit address arithmetic per lane
-    const char* at = reinterpret_cast<const char*>(g);
-    lo = dq_load_stream(reinterpret_cast<const float4*>(at + e0 * 4u));
-    hi = dq_load_stream(reinterpret_cast<const float4*>(at + e1 * 4u));
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g), 0, static_cast<int>(n_elems * 4u), 0x00020000);
+}
+__device__ __forceinline__ float4 dq_load_stream(const __amdgpu_buffer_rsrc_t buffer, uint32_t byte)
+{
+    constexpr int STREAM = 2; // the non-temporal bit
+    const dq_v4u t = __builtin_amdgcn_raw_buffer_load_b128(buffer, static_cast<int>(byte), 0, STREAM);
+    return make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
+}
+__device__ __forceinline__ void dq_load_wave_tile(const __amdgpu_buffer_rsrc_t buffer, uint32_t base, uint32_t lane,
+                                                  float4& lo, float4& hi)
+{
+    const uint32_t at = (base + (lane & 31u) * 8u + (lane >> 5) * 4u) * 4u;
+    lo = dq_load_stream(buffer, at);
+    hi = dq_load_stream(buffer, at + 1024u);
 }
 __device__ __forceinline__ void dq_swap_halves(float& a, float& b)
 {

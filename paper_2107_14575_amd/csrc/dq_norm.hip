@@ -231,13 +231,14 @@ __global__ __launch_bounds__(256) void k_norm_chunk(const float* __restrict__ gr
     const int32_t* gseg = granule_cseg + (chunk0 >> 7);
 
     // wavefront v owns elements [1024 v, 1024 v + 1024) in two tiles of 512
+    const __amdgpu_buffer_rsrc_t buffer = dq_elems_buffer(g, n_elems);
     float4 x[2][2];
     int32_t seg[2];
     uint32_t elem[2];
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
         elem[it] = (tid >> 6) * 1024 + it * 512 + (tid & 63) * 8;
-        dq_load_wave_tile(g, (tid >> 6) * 1024 + it * 512, tid & 63, n_elems, x[it][0], x[it][1]);
+        dq_load_wave_tile(buffer, (tid >> 6) * 1024 + it * 512, tid & 63, x[it][0], x[it][1]);
         seg[it] = gseg[(elem[it] < n_elems ? elem[it] : n_elems - 8) >> 7]; // clamped: in bounds, masked out below
     }
     const int32_t seg_first = gseg[0];

@@ -14,22 +14,24 @@ constexpr int QP_WAVE_TILE = 64 * QP_PER_LANE;         // 512 elements: a wavefr
 // all of it) and of the chunk norms.
 constexpr int QP_TILES = DQ_CHUNK / QP_TILE;
 
-// Writes the low B bytes of v at dst (LDS, byte offset a multiple of B) with naturally aligned
-// stores only.
+// Writes the low B bytes of v at dst (LDS, byte offset a multiple of B): pieces of 8, 4, 2 and 1 bytes, which LDS takes
+// at any byte address (the compiler checks that the target does).
 template <int B>
 __device__ __forceinline__ void stage_bytes(uint8_t* dst, uint64_t v)
 {
-    if constexpr (B == 8) {
-        *reinterpret_cast<uint64_t*>(dst) = v;
-    } else if constexpr (B == 4) {
-        *reinterpret_cast<uint32_t*>(dst) = static_cast<uint32_t>(v);
-    } else if constexpr (B % 2 == 0) {
-#pragma unroll
-        for (int k = 0; k < B / 2; ++k) reinterpret_cast<uint16_t*>(dst)[k] = static_cast<uint16_t>(v >> (16 * k));
-    } else {
-#pragma unroll
-        for (int k = 0; k < B; ++k) dst[k] = static_cast<uint8_t>(v >> (8 * k));
+    if constexpr ((B & 8) != 0) {
+        __builtin_memcpy(dst, &v, 8);
+        return;
     }
+    if constexpr ((B & 4) != 0) {
+        const uint32_t piece = static_cast<uint32_t>(v);
+        __builtin_memcpy(dst, &piece, 4);
+    }
+    if constexpr ((B & 2) != 0) {
+        const uint16_t piece = static_cast<uint16_t>(v >> (8 * (B & 4)));
+        __builtin_memcpy(dst + (B & 4), &piece, 2);
+    }
+    if constexpr ((B & 1) != 0) dst[B - 1] = static_cast<uint8_t>(v >> (8 * (B - 1)));
 }
 
 // The same for a width that is a value.
@@ -47,94 +49,248 @@ __device__ __forceinline__ void stage_bytes_v(uint8_t* dst, uint64_t v, int b)
     }
 }
 
-// A lane's eight consecutive elements (two Philox blocks with counters quad, quad + 1): the sign
-// byte (element 0 in bit 0) and the 8*B level bits (element 0 in the low B bits).  Per element, with
-// a = min(|g| * scale, s) in binary32 and u = (word >> 8) * 2^-24: level = floor(a) + [u < a - floor(a)]
-// (Eq. (5)-(6)).  Three routes, chosen per wavefront, all giving exactly those bits:
-//   * every lane's eight products |g| * scale are zero (exact-zero stretches of a gradient, or a
-//     tensor whose norm is unusable): every level is 0 whatever the random numbers, none are drawn;
-//   * every product is below 1 (the usual case for a tensor of many elements: |g|/N ~ 1/sqrt(d)):
-//     then a = min(a, s) = a, floor(a) = 0 and a - floor(a) = a, so the level is [u < a] -- no clamp,
-//     no fract, no float-to-integer conversion;
-//   * otherwise the general form: clamp, v_fract, convert, compare, add with carry.
-// The wavefront-wide test costs a maximum over the eight products and two votes.
-// S, b: the level count and bits of the tensor (template argument B > 0 fixes them at compile time).
-// r[h][k] receives the random word of element 4h + k unless the all-zero route was taken (then no
-// caller needs it: every level is zero).
-// quantize_quads leaves the two groups of four apart (their Philox blocks are quad0 and quad1): sign
-// nibbles and 4*B level bits each.
+// ---------------------------------------------------------------------------------------------
+// Two quads (four consecutive elements each, one Philox block) of a lane.  Per element, with
+// a = min(|g| * scale, s) in binary32 and u = (word >> 8) * 2^-24, the level of Eq. (5)-(6) is
+// floor(a) + [u < a - floor(a)], which is the integer ceil(a - u): inside an integer interval of a the
+// difference is above floor(a) exactly when u < a - floor(a), and never above floor(a) + 1 or at most floor(a) - 1.
+// Rounding towards +infinity keeps the ceiling of a difference that binary32 cannot hold (no integer lies between
+// the exact value and its rounding), and adding 1.5 * 2^23 in that mode takes the ceiling itself.  So with the
+// mode set, fma(-(word >> 8), 2^-24, a) and one addition per element give the level in the low bits of a sum that
+// also holds the levels packed before it (times 2^b by one exact fma).
+//
+// What bounds it: vector issue, where the norms are computed in the same pass; the plain pass is bound by memory.  Per
+// element and beside the 9.3 instructions of Philox, 7.4 are issued: multiply, half a max3, shift, convert, fma, fma and
+// addition (a quad's first needs no fma), sign; with minimum (and the canonicalising maximum ahead of it), v_fract, two
+// conversions, compare, add with carry and shift they were 12.5, and 8.5 in a form for wavefronts whose products are all
+// below 1.  Fma and addition also issue twice as fast as those (2.4 against 4.3 cycles by themselves, less of a
+// difference in a mixture).  Norms and messages in one pass, 16.8 M values in buckets of 512, M = 8: b = 4 137 -> 120 us,
+// b = 8 141 -> 123, b = 2 (products below 1) 125 -> 120.
+// ---------------------------------------------------------------------------------------------
+
+// s|g|/N of the lane's eight elements, one rounding each, and what the wavefront can conclude from the largest:
+enum qp_range {
+    QP_ALL_ZERO, // every product of the wavefront is +0 (exact-zero stretches, unusable norm): every level is 0
+                 // whatever the random numbers, and none are drawn
+    QP_BELOW_S,  // none above s: min(a, s) = a
+    QP_CLAMP     // something above s, or a NaN
+};
 template <int B>
-__device__ __forceinline__ void quantize_quads(const float4 x0, const float4 x1, const float scale, const float S_arg,
-                                               const int b_arg, const uint32_t quad0, const uint32_t quad1,
-                                               const uint32_t quad_hi, const uint32_t worker, const uint32_t step,
-                                               const uint32_t key0, const uint32_t key1, uint32_t (&sign)[2],
-                                               uint32_t (&lv)[2], uint32_t (&r)[2][4])
+__device__ __forceinline__ qp_range quantize_products(const float4 x0, const float4 x1, const float scale, const float S_arg,
+                                                      float (&a)[8])
 {
     const float S = B > 0 ? static_cast<float>((1 << (B > 0 ? B : 1)) - 1) : S_arg;
-    const int b = B > 0 ? B : b_arg;
     const float v[8] = { x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w };
-    float a[8];
-    sign[0] = sign[1] = 0;
+    uint32_t n[8];
 #pragma unroll
-    for (int k = 7; k >= 0; --k) {
-        sign[k >> 2] = __builtin_amdgcn_alignbit(sign[k >> 2], __float_as_uint(v[k]), 31); // element 4h ends in bit 0
-        a[k] = fabsf(v[k]) * scale;                                                         // s|g|/N, one rounding
+    for (int k = 0; k < 8; ++k) {
+        a[k] = fabsf(v[k]) * scale;
+        n[k] = __float_as_uint(a[k]); // never negative, so the patterns are in the values' order, a NaN above all
     }
-    const float top = fmaxf(fmaxf(__builtin_fmaxf(__builtin_fmaxf(a[0], a[1]), a[2]), __builtin_fmaxf(__builtin_fmaxf(a[3], a[4]), a[5])),
-                            __builtin_fmaxf(a[6], a[7]));
-    lv[0] = lv[1] = 0u;
-    if (__all(top == 0.0f)) return;
+    const uint32_t top = max(max(max(max(n[0], n[1]), n[2]), max(max(n[3], n[4]), n[5])), max(n[6], n[7]));
+    if (__all(top == 0u)) return QP_ALL_ZERO;
+    return __all(top <= __float_as_uint(S)) ? QP_BELOW_S : QP_CLAMP;
+}
+
+// min(a, s): a caller's norm may be too small, and |g|/N may round above 1.  A NaN goes to s, and an unusable norm
+// (scale 0) to 0 whatever the elements are.
+template <int B>
+__device__ __forceinline__ void quantize_clamp(float (&a)[8], const float scale, const float S_arg)
+{
+    const float S = B > 0 ? static_cast<float>((1 << (B > 0 ? B : 1)) - 1) : S_arg;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a[k] = scale > 0.0f ? fminf(a[k], S) : 0.0f;
+}
+
+// word >> 8 of the two quads' random words, as binary32 (exact).
+__device__ __forceinline__ void quantize_random(const uint32_t quad0, const uint32_t quad1, const uint32_t quad_hi,
+                                                const uint32_t worker, const uint32_t step, const uint32_t key0,
+                                                const uint32_t key1, float (&t)[8])
+{
+    uint32_t r[2][4];
     dq_philox4x32_10(quad0, quad_hi, worker, step, key0, key1, r[0]);
     dq_philox4x32_10(quad1, quad_hi, worker, step, key0, key1, r[1]);
-    if (__all(top < 1.0f)) {
 #pragma unroll
-        for (int h = 1; h >= 0; --h)
+    for (int k = 0; k < 8; ++k) t[k] = static_cast<float>(r[k >> 2][k & 3] >> 8);
+}
+
+// The two quads' levels, four fields of b bits each in lv[h], from the clamped products and the random numbers.
+// The rounding mode is set and put back inside the one asm statement, so no other operation runs under it.
+// b <= 5: a quad's 20 bits fit the sum's 22; above, pairs are summed and joined.  b: the width, where B = 0.
+template <int B>
+__device__ __forceinline__ void quantize_levels(const float (&a)[8], const float (&t)[8], const int b, uint32_t (&lv)[2])
+{
+    constexpr uint32_t MAGIC = 0x4B400000u; // 1.5 * 2^23: sums from here on are whole numbers, and the pattern counts them
+    float c[8];
 #pragma unroll
-            for (int k = 3; k >= 0; --k) {
-                const float u = static_cast<float>(r[h][k] >> 8) * 0x1p-24f; // exact, in [0,1)
-                lv[h] = (lv[h] << b) + (u < a[4 * h + k] ? 1u : 0u);
-            }
+    for (int k = 0; k < 8; ++k) c[k] = a[k];
+    const float pw = B > 0 ? static_cast<float>(1 << B) : __uint_as_float(static_cast<uint32_t>(127 + b) << 23);
+    const float back = 0x1.8p23f - 0x1.8p23f * pw; // y -> y * pw + back keeps 1.5 * 2^23 and multiplies the rest; exact
+    if constexpr (B >= 1 && B <= 5) {
+        asm("s_nop 1\n\t"
+            "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 1\n\t"
+            "v_fma_f32 %3, -%11, %16, %3\n\t"
+            "v_fma_f32 %7, -%15, %16, %7\n\t"
+            "v_fma_f32 %2, -%10, %16, %2\n\t"
+            "v_fma_f32 %6, -%14, %16, %6\n\t"
+            "v_add_f32 %3, %17, %3\n\t"
+            "v_add_f32 %7, %17, %7\n\t"
+            "v_fma_f32 %1, -%9, %16, %1\n\t"
+            "v_fma_f32 %5, -%13, %16, %5\n\t"
+            "v_fma_f32 %3, %3, %18, %19\n\t"
+            "v_fma_f32 %7, %7, %18, %19\n\t"
+            "v_fma_f32 %0, -%8, %16, %0\n\t"
+            "v_fma_f32 %4, -%12, %16, %4\n\t"
+            "v_add_f32 %3, %3, %2\n\t"
+            "v_add_f32 %7, %7, %6\n\t"
+            "v_fma_f32 %3, %3, %18, %19\n\t"
+            "v_fma_f32 %7, %7, %18, %19\n\t"
+            "v_add_f32 %3, %3, %1\n\t"
+            "v_add_f32 %7, %7, %5\n\t"
+            "v_fma_f32 %3, %3, %18, %19\n\t"
+            "v_fma_f32 %7, %7, %18, %19\n\t"
+            "v_add_f32 %3, %3, %0\n\t"
+            "v_add_f32 %7, %7, %4\n\t"
+            "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
+            : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]), "+v"(c[7])
+            : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "s"(0x1p-24f),
+              "s"(0x1.8p23f), "s"(pw), "v"(back));
+        lv[0] = __float_as_uint(c[3]) - MAGIC;
+        lv[1] = __float_as_uint(c[7]) - MAGIC;
     } else {
-#pragma unroll
-        for (int h = 1; h >= 0; --h)
-#pragma unroll
-            for (int k = 3; k >= 0; --k) {
-                const float c = fminf(a[4 * h + k], S);                      // clamped
-                const float p = __builtin_amdgcn_fractf(c);                  // c - floor(c), exact
-                const float u = static_cast<float>(r[h][k] >> 8) * 0x1p-24f;
-                lv[h] = (lv[h] << b) + static_cast<uint32_t>(c) + (u < p ? 1u : 0u);
-            }
+        asm("s_nop 1\n\t"
+            "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 1\n\t"
+            "v_fma_f32 %1, -%9, %16, %1\n\t"
+            "v_fma_f32 %3, -%11, %16, %3\n\t"
+            "v_fma_f32 %5, -%13, %16, %5\n\t"
+            "v_fma_f32 %7, -%15, %16, %7\n\t"
+            "v_fma_f32 %0, -%8, %16, %0\n\t"
+            "v_fma_f32 %2, -%10, %16, %2\n\t"
+            "v_fma_f32 %4, -%12, %16, %4\n\t"
+            "v_fma_f32 %6, -%14, %16, %6\n\t"
+            "v_add_f32 %1, %17, %1\n\t"
+            "v_add_f32 %3, %17, %3\n\t"
+            "v_add_f32 %5, %17, %5\n\t"
+            "v_add_f32 %7, %17, %7\n\t"
+            "v_fma_f32 %1, %1, %18, %19\n\t"
+            "v_fma_f32 %3, %3, %18, %19\n\t"
+            "v_fma_f32 %5, %5, %18, %19\n\t"
+            "v_fma_f32 %7, %7, %18, %19\n\t"
+            "v_add_f32 %1, %1, %0\n\t"
+            "v_add_f32 %3, %3, %2\n\t"
+            "v_add_f32 %5, %5, %4\n\t"
+            "v_add_f32 %7, %7, %6\n\t"
+            "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
+            : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]), "+v"(c[7])
+            : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "s"(0x1p-24f),
+              "s"(0x1.8p23f), "v"(pw), "v"(back));
+        // (hi << 2b) + lo, less what the two patterns carry
+        const int two = 2 * (B > 0 ? B : b);
+        const uint32_t excess = (MAGIC << two) + MAGIC;
+        lv[0] = (__float_as_uint(c[3]) << two) + __float_as_uint(c[1]) - excess;
+        lv[1] = (__float_as_uint(c[7]) << two) + __float_as_uint(c[5]) - excess;
     }
 }
 
-template <int B>
-__device__ __forceinline__ void quantize8(const float4 x_lo, const float4 x_hi, const float scale, const float S_arg,
-                                          const int b_arg, const uint32_t quad, const uint32_t quad_hi,
-                                          const uint32_t worker, const uint32_t step, const uint32_t key0,
-                                          const uint32_t key1, uint32_t& sign, uint64_t& level, uint32_t (&r)[2][4])
+// The sign bits of a quad in bits 28..31 (element 0 in bit 28); the bits below are not cleared.
+__device__ __forceinline__ uint32_t quantize_signs(const float4 x)
 {
-    uint32_t sg[2], lv[2];
-    quantize_quads<B>(x_lo, x_hi, scale, S_arg, b_arg, quad, quad + 1u, quad_hi, worker, step, key0, key1, sg, lv, r);
-    sign = sg[0] | (sg[1] << 4);
-    level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * (B > 0 ? B : b_arg)));
+    // bitop3 0xCA: a ? b : c, bit by bit
+    const uint32_t hi = __builtin_amdgcn_bitop3_b32(0x80000000u, __float_as_uint(x.w), __float_as_uint(x.z) >> 1, 0xCA);
+    const uint32_t lo = __builtin_amdgcn_bitop3_b32(0x80000000u, __float_as_uint(x.y), __float_as_uint(x.x) >> 1, 0xCA);
+    return __builtin_amdgcn_bitop3_b32(0xC0000000u, hi, lo >> 2, 0xCA);
+}
+// the sign byte of eight elements from the words of their two quads (bits 28..31 count)
+__device__ __forceinline__ uint32_t quantize_sign_byte(const uint32_t sg0, const uint32_t sg1)
+{
+    return (sg0 >> 28) | ((sg1 >> 24) & 0xF0u);
 }
 
-// The same for a wavefront's tile as dq_load_wave_tile loaded it (not arranged) when one scale serves
-// the whole tile: every lane quantizes the two quads it loaded, and the codes change places instead of
-// the values -- two swaps in place of eight.  quad_tile: the tile's first quad.
+// Both quads: the words of quantize_signs and the levels.  The random numbers are left in t for a caller that
+// quantizes the same elements again (QP_ALL_ZERO: none were drawn, every level is 0 for any smaller scale too).
 template <int B>
-__device__ __forceinline__ void quantize_wave_tile(const float4 lo, const float4 hi, const float scale, const float S_arg,
-                                                   const int b_arg, const uint32_t quad_tile, const uint32_t lane,
+__device__ __forceinline__ qp_range quantize_quads(const float4 x0, const float4 x1, const float scale, const float S,
+                                                   const int b, const uint32_t quad0, const uint32_t quad1,
+                                                   const uint32_t quad_hi, const uint32_t worker, const uint32_t step,
+                                                   const uint32_t key0, const uint32_t key1, uint32_t (&sign)[2],
+                                                   uint32_t (&lv)[2], float (&t)[8])
+{
+    float a[8];
+    sign[0] = quantize_signs(x0);
+    sign[1] = quantize_signs(x1);
+    lv[0] = lv[1] = 0u;
+    const qp_range range = quantize_products<B>(x0, x1, scale, S, a);
+    if (range != QP_ALL_ZERO) {
+        quantize_random(quad0, quad1, quad_hi, worker, step, key0, key1, t);
+        if (range == QP_CLAMP) quantize_clamp<B>(a, scale, S);
+        quantize_levels<B>(a, t, b, lv);
+    }
+    return range;
+}
+
+// The same elements' levels with a smaller scale, for the random numbers and the range quantize_quads gave.
+template <int B>
+__device__ __forceinline__ void quantize_again(const qp_range range, const float4 x0, const float4 x1, const float scale,
+                                               const float S, const int b, const float (&t)[8], uint32_t (&lv)[2])
+{
+    float a[8] = { fabsf(x0.x) * scale, fabsf(x0.y) * scale, fabsf(x0.z) * scale, fabsf(x0.w) * scale,
+                   fabsf(x1.x) * scale, fabsf(x1.y) * scale, fabsf(x1.z) * scale, fabsf(x1.w) * scale };
+    if (range == QP_CLAMP) quantize_clamp<B>(a, scale, S);
+    quantize_levels<B>(a, t, b, lv);
+}
+
+// A lane's eight consecutive elements (Philox counters quad, quad + 1): the sign byte (element 0 in bit 0)
+// and the 8*B level bits (element 0 in the low B bits).
+// S, b: the level count and bits of the tensor (template argument B > 0 fixes them at compile time).
+template <int B>
+__device__ __forceinline__ qp_range quantize8(const float4 x_lo, const float4 x_hi, const float scale, const float S,
+                                              const int b, const uint32_t quad, const uint32_t quad_hi,
+                                              const uint32_t worker, const uint32_t step, const uint32_t key0,
+                                              const uint32_t key1, uint32_t& sign, uint64_t& level, float (&t)[8])
+{
+    uint32_t sg[2], lv[2];
+    const qp_range range = quantize_quads<B>(x_lo, x_hi, scale, S, b, quad, quad + 1u, quad_hi, worker, step, key0, key1,
+                                             sg, lv, t);
+    sign = quantize_sign_byte(sg[0], sg[1]);
+    level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * (B > 0 ? B : b)));
+    return range;
+}
+
+// The codes of the two quads a lane loaded (dq_load_wave_tile, not arranged) change places between the halves of
+// the wavefront, so that the lane has its eight consecutive elements' sign byte and level bits.  Up to seven bits
+// the signs travel in the top four bits of the levels' words.
+template <int B>
+__device__ __forceinline__ void quantize_exchange(const uint32_t (&sg)[2], const uint32_t (&lv)[2], const int b,
+                                                  uint32_t& sign, uint64_t& level)
+{
+    if constexpr (B >= 1 && B <= 7) {
+        constexpr uint32_t FIELDS = (1u << (4 * (B >= 1 && B <= 7 ? B : 1))) - 1u;
+        const auto w = __builtin_amdgcn_permlane32_swap(__builtin_amdgcn_bitop3_b32(0xF0000000u, sg[0], lv[0], 0xCA),
+                                                        __builtin_amdgcn_bitop3_b32(0xF0000000u, sg[1], lv[1], 0xCA), false, false);
+        sign = quantize_sign_byte(w[0], w[1]);
+        level = static_cast<uint64_t>(w[0] & FIELDS) | (static_cast<uint64_t>(w[1] & FIELDS) << (4 * B));
+    } else {
+        const auto s = __builtin_amdgcn_permlane32_swap(sg[0], sg[1], false, false);
+        const auto l = __builtin_amdgcn_permlane32_swap(lv[0], lv[1], false, false);
+        sign = quantize_sign_byte(s[0], s[1]);
+        level = static_cast<uint64_t>(l[0]) | (static_cast<uint64_t>(l[1]) << (4 * (B > 0 ? B : b)));
+    }
+}
+
+// quantize8 for a wavefront's tile as dq_load_wave_tile loaded it (not arranged) when one scale serves
+// the whole tile: every lane quantizes the two quads it loaded, and the codes change places instead of
+// the values -- one or two swaps in place of eight.  quad_tile: the tile's first quad.
+template <int B>
+__device__ __forceinline__ void quantize_wave_tile(const float4 lo, const float4 hi, const float scale, const float S,
+                                                   const int b, const uint32_t quad_tile, const uint32_t lane,
                                                    const uint32_t quad_hi, const uint32_t worker, const uint32_t step,
                                                    const uint32_t key0, const uint32_t key1, uint32_t& sign, uint64_t& level)
 {
-    uint32_t sg[2], lv[2], r[2][4];
+    uint32_t sg[2], lv[2];
+    float t[8];
     const uint32_t quad = quad_tile + (lane & 31u) * 2u + (lane >> 5);
-    quantize_quads<B>(lo, hi, scale, S_arg, b_arg, quad, quad + 64u, quad_hi, worker, step, key0, key1, sg, lv, r);
-    const auto s = __builtin_amdgcn_permlane32_swap(sg[0], sg[1], false, false);
-    const auto l = __builtin_amdgcn_permlane32_swap(lv[0], lv[1], false, false);
-    sign = s[0] | (s[1] << 4);
-    level = static_cast<uint64_t>(l[0]) | (static_cast<uint64_t>(l[1]) << (4 * (B > 0 ? B : b_arg)));
+    quantize_quads<B>(lo, hi, scale, S, b, quad, quad + 64u, quad_hi, worker, step, key0, key1, sg, lv, t);
+    quantize_exchange<B>(sg, lv, b, sign, level);
 }
 
 // First element (inside the chunk) of a lane's eight of tile `it`.  Each wavefront owns TILES
@@ -149,14 +305,14 @@ __device__ __forceinline__ uint32_t qp_elem(uint32_t tid, int it)
 }
 
 // The lane's inputs of every tile, in flight together (dq_arrange_wave_tile completes them).  Lanes
-// past the end of a ragged last chunk re-read its last elements (always in bounds); what they
-// compute is never stored.
+// past the end of a ragged last chunk get zeros; what they compute is never stored.
 template <int TILES>
 __device__ __forceinline__ void qp_load(const float* __restrict__ g, uint32_t tid, uint32_t n_elems, float4 (&x)[TILES][2])
 {
+    const __amdgpu_buffer_rsrc_t buffer = dq_elems_buffer(g, n_elems);
 #pragma unroll
     for (int it = 0; it < TILES; ++it)
-        dq_load_wave_tile(g, (tid >> 6) * (QP_WAVE_TILE * TILES) + it * QP_WAVE_TILE, tid & 63u, n_elems, x[it][0], x[it][1]);
+        dq_load_wave_tile(buffer, (tid >> 6) * (QP_WAVE_TILE * TILES) + it * QP_WAVE_TILE, tid & 63u, x[it][0], x[it][1]);
 }
 
 // The same for layouts whose chunks hold several tensors: each lane loads its own eight elements, so that
@@ -300,8 +456,10 @@ __device__ __forceinline__ void quantize_pack_chunk(
     } else {
         __shared__ double lds_gsum[DQ_CHUNK_GRANULES];
         __shared__ int32_t lds_glocal[DQ_CHUNK_GRANULES];
+        __shared__ int32_t lds_seg[MAX_LOCAL_SEG]; // fetched with the tables: a load where the norm is written is waited for
         if (static_cast<int32_t>(tid) <= seg_last - seg_first) {
             const int64_t rel = cseg_valid_end[seg_first + tid] - chunk0;
+            lds_seg[tid] = cseg_seg[seg_first + tid];
             lds_valid_end[tid] = rel < CHUNK ? static_cast<int32_t>(rel) : CHUNK;
         }
         __syncthreads();
@@ -321,8 +479,8 @@ __device__ __forceinline__ void quantize_pack_chunk(
         if (tid < DQ_CHUNK_GRANULES)
             dq_chunk_tensor_norms<NORM == 2>(static_cast<int>(tid), n_scan, lds_gsum, lds_glocal,
                                              [&](int j, float N) {
-                                                 norms_out[static_cast<int64_t>(w) * n_seg + cseg_seg[seg_first + j]] = N;
                                                  lds_scale[j] = N >= DQ_MIN_NORM ? S / N : 0.0f;
+                                                 norms_out[static_cast<int64_t>(w) * n_seg + lds_seg[j]] = N;
                                              });
         __syncthreads();
     }
@@ -338,8 +496,8 @@ __device__ __forceinline__ void quantize_pack_chunk(
             const uint32_t quad = quad_lo0 + (e >> 2); // even; quad + 1 cannot carry
             uint32_t sign;
             uint64_t level;
-            uint32_t r[2][4];
-            quantize8<B>(x[it][0], x[it][1], scale, 0.0f, 0, quad, quad_hi, worker, step, key0, key1, sign, level, r);
+            float t[8];
+            quantize8<B>(x[it][0], x[it][1], scale, 0.0f, 0, quad, quad_hi, worker, step, key0, key1, sign, level, t);
             if (n_valid < QP_PER_LANE) { // the tensor ends inside (or before) this lane's eight elements
                 const int nv = n_valid > 0 ? n_valid : 0;
                 sign &= (1u << nv) - 1u;
@@ -392,6 +550,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     __shared__ float lds_scale[MAX_LOCAL_SEG];
     __shared__ float lds_levels[MAX_LOCAL_SEG];      // s = 2^b - 1 of the segment
     __shared__ int32_t lds_b[MAX_LOCAL_SEG];
+    __shared__ int32_t lds_seg[NORM == 0 ? 1 : MAX_LOCAL_SEG]; // as in quantize_pack_chunk
     __shared__ int32_t lds_level_base[MAX_LOCAL_SEG]; // byte offset, in the chunk's level bytes, the
                                                       // segment's fields would have at chunk element 0
     __shared__ int32_t lds_valid_end[MAX_LOCAL_SEG];
@@ -454,9 +613,12 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     if (static_cast<int32_t>(tid) <= seg_last - seg_first) {
         const dq_cseg_width e = widths[seg_first + tid];
         const float S = static_cast<float>((1 << e.b) - 1);
+        const int32_t own_seg = cseg_seg[seg_first + tid];
         if constexpr (NORM == 0) {
-            const float N = norms[static_cast<int64_t>(w) * n_seg + cseg_seg[seg_first + tid]];
+            const float N = norms[static_cast<int64_t>(w) * n_seg + own_seg];
             lds_scale[tid] = N >= DQ_MIN_NORM ? S / N : 0.0f;
+        } else {
+            lds_seg[tid] = own_seg;
         }
         lds_levels[tid] = S;
         lds_b[tid] = e.b;
@@ -488,8 +650,8 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
         if (tid < DQ_CHUNK_GRANULES)
             dq_chunk_tensor_norms<NORM == 2>(static_cast<int>(tid), n_scan, lds_gsum, lds_glocal,
                                              [&](int j, float N) {
-                                                 norms_out[static_cast<int64_t>(w) * n_seg + cseg_seg[seg_first + j]] = N;
                                                  lds_scale[j] = N >= DQ_MIN_NORM ? lds_levels[j] / N : 0.0f;
+                                                 norms_out[static_cast<int64_t>(w) * n_seg + lds_seg[j]] = N;
                                              });
         __syncthreads();
     }
@@ -505,9 +667,10 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
             const int32_t n_valid = lds_valid_end[local] - static_cast<int32_t>(e);
 
             const uint32_t quad = quad_lo0 + (e >> 2);
-            uint32_t sign, r[2][4];
+            uint32_t sign;
             uint64_t level;
-            quantize8<0>(x[it][0], x[it][1], scale, S, b, quad, quad_hi, worker, step, key0, key1, sign, level, r);
+            float t[8];
+            quantize8<0>(x[it][0], x[it][1], scale, S, b, quad, quad_hi, worker, step, key0, key1, sign, level, t);
             if (n_valid < QP_PER_LANE) {
                 const int nv = n_valid > 0 ? n_valid : 0;
                 sign &= (1u << nv) - 1u;
