@@ -604,20 +604,15 @@ __global__ __launch_bounds__(256) void k_bracket_norm_finish(
     }
 }
 
-// One recorded element: its level for the true norm, ORed into the zero field the first kernel left.
+// One recorded element of tensor c with norm N: its level, ORed into the zero field the first kernel left.
 // B = 0: per-tensor widths, b and the place of the tensor's level fields come from `widths` (this
 // worker's row of the table).
 template <int B>
-__device__ __forceinline__ void settle_record(uint2 rec, int64_t chunk0, uint32_t w, const float* __restrict__ norms,
-                                              int32_t n_seg, const int32_t* __restrict__ granule_cseg,
-                                              const int32_t* __restrict__ cseg_seg, uint32_t key0, uint32_t key1,
-                                              uint32_t step, uint32_t worker, uint32_t* __restrict__ plane,
-                                              const dq_cseg_width* __restrict__ widths)
+__device__ __forceinline__ void settle_element(uint2 rec, int64_t chunk0, int32_t c, float N, uint32_t key0, uint32_t key1,
+                                               uint32_t step, uint32_t worker, uint32_t* __restrict__ plane,
+                                               const dq_cseg_width* __restrict__ widths)
 {
-    const uint32_t e = rec.x; // < 4096 and inside the layout: written by the first kernel for this chunk
-    const int32_t c = granule_cseg[(chunk0 >> 7) + (e >> 7)];
-    const float N = norms[static_cast<int64_t>(w) * n_seg + cseg_seg[c]];
-    const uint64_t P = static_cast<uint64_t>(chunk0) + e;
+    const uint64_t P = static_cast<uint64_t>(chunk0) + rec.x;
     uint32_t r[4];
     dq_philox4x32_10(static_cast<uint32_t>(P >> 2), static_cast<uint32_t>(P >> 34), worker, step, key0, key1, r);
     const uint32_t word = (P & 2u) ? ((P & 1u) ? r[3] : r[2]) : ((P & 1u) ? r[1] : r[0]);
@@ -644,6 +639,19 @@ __device__ __forceinline__ void settle_record(uint2 rec, int64_t chunk0, uint32_
     }
 }
 
+// The same, with the element's tensor looked up first.
+template <int B>
+__device__ __forceinline__ void settle_record(uint2 rec, int64_t chunk0, uint32_t w, const float* __restrict__ norms,
+                                              int32_t n_seg, const int32_t* __restrict__ granule_cseg,
+                                              const int32_t* __restrict__ cseg_seg, uint32_t key0, uint32_t key1,
+                                              uint32_t step, uint32_t worker, uint32_t* __restrict__ plane,
+                                              const dq_cseg_width* __restrict__ widths)
+{
+    const uint32_t e = rec.x; // < 4096 and inside the layout: written by the first kernel for this chunk
+    const int32_t c = granule_cseg[(chunk0 >> 7) + (e >> 7)];
+    settle_element<B>(rec, chunk0, c, norms[static_cast<int64_t>(w) * n_seg + cseg_seg[c]], key0, key1, step, worker, plane, widths);
+}
+
 // What the settle kernels decide per chunk: true if the chunk has to be quantized again.
 __device__ __forceinline__ bool chunk_needs_redo(uint32_t count, uint32_t flags, int64_t chunk0, int64_t padded_elems,
                                                  uint32_t w, int32_t n_cseg, const int32_t* __restrict__ granule_cseg,
@@ -666,6 +674,10 @@ __device__ __forceinline__ bool chunk_needs_redo(uint32_t count, uint32_t flags,
 // inside their brackets 119 -> 109, all outside 188 -> 172, one worker's outside 130 -> 116; b = 6 at +-12.5 % (a fifth of
 // the chunks again) 156 -> 146; transformer shape, M = 16, b = 8 (two fifths) 319 -> 293; 2^20 elements of one worker inside
 // 17.8 -> 12.6, all outside 18.7 -> 17.1.
+// What bounds it: memory latency.  A chunk of one tensor (nearly all) gets norm and bracket test from the chunk table beside
+// its block instead of by granule, record and tensor in turn, and the quantizer's lane arithmetic stays inside the loop
+// (66 to 72 registers, were 82 to 98): ResNet-18 shape, M = 8, b = 2 18.9 -> 14.7 us, b = 3 20.4 -> 15.4, b = 5 30.3 -> 25.1.
+// Two chunks to a wavefront: 12.1, 14.7, but 32.6 where a fifth are taken again (a workgroup takes its chunks in turn).
 template <int B>
 __global__ __launch_bounds__(QP_THREADS) void k_bracket_settle_redo(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
@@ -678,21 +690,33 @@ __global__ __launch_bounds__(QP_THREADS) void k_bracket_settle_redo(
     __shared__ int lds_again[QP_THREADS / 64];
     const dq_cseg_width* __restrict__ widths = widths_table + static_cast<int64_t>(blockIdx.y) * widths_worker_stride;
     const uint32_t w = blockIdx.y;
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t chunk_first = static_cast<int64_t>(blockIdx.x) * (QP_THREADS / 64), chunk = chunk_first + wave;
+    // all that the wavefront needs, in flight together; past the last chunk it is the last one's, and not used
+    const int64_t own = chunk < n_chunks ? chunk : n_chunks - 1;
+    dq_bracket_block* blk = blocks + static_cast<int64_t>(w) * n_chunks + own;
+    const dq_chunk_tensor owner = dq_load_chunk_tensor(chunk_tensor, own);
+    const uint2 rec = blk->rec[lane < DQ_BRACKET_CAP ? lane : 0];
+    const uint32_t count = blk->count, flags = blk->flags;
+    // the chunk's only tensor, if it has one: its norm, and whether that lies inside its bracket
+    const float N = norms[static_cast<int64_t>(w) * n_seg + owner.seg];
+    const uint32_t in = inside[static_cast<int64_t>(w) * n_cseg + (owner.cseg >= 0 ? owner.cseg : 0)];
+    const int64_t chunk0 = chunk * DQ_CHUNK;
     bool again = false;
     if (chunk < n_chunks) { // the same for the whole wavefront
-        dq_bracket_block* blk = blocks + static_cast<int64_t>(w) * n_chunks + chunk;
-        const uint32_t count = blk->count, flags = blk->flags;
-        const uint2 rec = blk->rec[lane < DQ_BRACKET_CAP ? lane : 0]; // fetched beside the count: used only below it
-        const int64_t chunk0 = chunk * DQ_CHUNK;
-        again = chunk_needs_redo(count, flags, chunk0, padded_elems, w, n_cseg, granule_cseg, inside);
+        if (owner.cseg >= 0)
+            again = flags != 0 || count > DQ_BRACKET_CAP || in == 0;
+        else
+            again = chunk_needs_redo(count, flags, chunk0, padded_elems, w, n_cseg, granule_cseg, inside);
         if (again) {
             if (lane == 0) blk->flags = flags | 2u;
         } else if (lane < count) {
             uint32_t* plane = reinterpret_cast<uint32_t*>(packed + static_cast<int64_t>(w) * packed_stride + (padded_elems >> 3));
-            settle_record<B>(rec, chunk0, w, norms, n_seg, granule_cseg, cseg_seg, key0, key1, step, worker_base + w, plane,
-                             widths);
+            if (owner.cseg >= 0)
+                settle_element<B>(rec, chunk0, owner.cseg, N, key0, key1, step, worker_base + w, plane, widths);
+            else
+                settle_record<B>(rec, chunk0, w, norms, n_seg, granule_cseg, cseg_seg, key0, key1, step, worker_base + w, plane,
+                                 widths);
         }
     }
     if (lane == 0) lds_again[wave] = again ? 1 : 0;
@@ -703,11 +727,11 @@ __global__ __launch_bounds__(QP_THREADS) void k_bracket_settle_redo(
         if constexpr (B == 0)
             quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                         widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
-                                        packed, packed_stride, nullptr, c);
+                                        packed, packed_stride, nullptr, c, qp_tid_in_loop());
         else
             quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg,
                                          cseg_valid_end, padded_elems, key0, key1, step, worker_base, packed, packed_stride,
-                                         nullptr, c);
+                                         nullptr, c, qp_tid_in_loop());
         __syncthreads(); // the chunk's staging in LDS is reused by the next one
     }
 }
@@ -779,11 +803,11 @@ __global__ __launch_bounds__(QP_THREADS) void k_bracket_redo(
             if constexpr (B == 0)
                 quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                             widths_table, widths_worker_stride, padded_elems, key0, key1, step,
-                                            worker_base, packed, packed_stride, nullptr, chunk);
+                                            worker_base, packed, packed_stride, nullptr, chunk, qp_tid_in_loop());
             else
                 quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                              padded_elems, key0, key1, step, worker_base, packed, packed_stride, nullptr,
-                                             chunk);
+                                             chunk, qp_tid_in_loop());
             __syncthreads(); // the chunk's staging in LDS is reused by the next one
         }
     }

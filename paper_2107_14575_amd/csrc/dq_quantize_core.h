@@ -293,6 +293,15 @@ __device__ __forceinline__ void quantize_wave_tile(const float4 lo, const float4
     quantize_exchange<B>(sg, lv, b, sign, level);
 }
 
+// threadIdx.x for the body of a loop over chunks: what follows from it is not worked out ahead of the loop and held in
+// registers (k_bracket_settle_redo 82 to 98 -> 66 to 72).
+__device__ __forceinline__ uint32_t qp_tid_in_loop()
+{
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
 // First element (inside the chunk) of a lane's eight of tile `it`.  Each wavefront owns TILES
 // consecutive tiles of 512 elements, i.e. one stretch of every plane: it stages and stores its own
 // bytes, with no workgroup barrier between the two.
@@ -366,6 +375,7 @@ __device__ __forceinline__ void qp_store_block(uint8_t* __restrict__ dst, const 
 // values in tensors of 128, M = 8 b = 4 38.0 -> 36.6, 16.8 M in tensors of 512, M = 8 b = 6 121.8 -> 114.8 and, with a
 // widths table, b = 7 130.9 -> 122.4; 30.7 M in tensors of 1000, M = 4 b = 6 112.0 -> 104.5.
 //
+// tid: threadIdx.x, or qp_tid_in_loop() where a workgroup takes several chunks.
 // NORM = 0: the norms are an input.  NORM = 1 (l2) or 2 (max): chunk-local plans only; the kernel
 // computes the norms of its chunk's tensors itself, writes them to norms_out and quantizes from
 // the registers it already holds -- one read of the gradient instead of two.
@@ -375,7 +385,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid)
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -388,7 +398,6 @@ __device__ __forceinline__ void quantize_pack_chunk(
     __shared__ __align__(16) uint8_t lds_sign[TILES * QP_THREADS];
     __shared__ __align__(16) uint8_t lds_level[TILES * QP_THREADS * B];
 
-    const uint32_t tid = threadIdx.x;
     const uint32_t w = blockIdx.y;
     const int64_t chunk0 = static_cast<int64_t>(chunk_index) * CHUNK;
     // elements of this chunk that exist (a multiple of 128, at least 128)
@@ -538,7 +547,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
     const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid)
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -557,7 +566,6 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     __shared__ __align__(16) uint8_t lds_sign[TILES * QP_THREADS];
     __shared__ __align__(16) uint8_t lds_level[TILES * QP_THREADS * 8];
 
-    const uint32_t tid = threadIdx.x;
     const uint32_t w = blockIdx.y;
     const int64_t chunk0 = static_cast<int64_t>(chunk_index) * CHUNK;
     const uint32_t n_elems = static_cast<uint32_t>(padded_elems - chunk0 < CHUNK ? padded_elems - chunk0 : CHUNK);

@@ -29,7 +29,7 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack(
 {
     quantize_pack_chunk<B, TILES, NORM, WHOLE>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                         padded_elems, key0, key1, step, worker_base, packed, packed_stride, norms_out,
-                                        blockIdx.x);
+                                        blockIdx.x, threadIdx.x);
 }
 
 template <int TILES, int NORM, bool WHOLE> // as in k_quantize_pack
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
 {
     quantize_pack_chunk_v<TILES, NORM, WHOLE>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                        widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
-                                       packed, packed_stride, norms_out, blockIdx.x);
+                                       packed, packed_stride, norms_out, blockIdx.x, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------
