@@ -350,7 +350,8 @@ __device__ __forceinline__ void load_levels(ur_bytes at, uint32_t (&wd)[B])
 // passes through at most 7 + ceil(M/8) roundings: 15 at M = 64, where a single chain over all
 // workers would take 63 (and measurably leaves the 1e-6 tolerance when one worker's norm
 // dominates).  Up to eight workers nothing is flushed: the plain chain.
-template <int B, bool WAVE, int GROUP, typename Load, typename Prepare, typename Unit>
+// JOIN: the last block joins the total; otherwise the flushed blocks' total stays in the slots and the last block in acc.
+template <int B, bool WAVE, int GROUP, bool JOIN = true, typename Load, typename Prepare, typename Unit>
 __device__ __forceinline__ void accumulate_workers(int M, Load&& load, Prepare&& prepare, Unit&& unit,
                                                    float (&acc)[UR_PER_LANE], lane_slots slots)
 {
@@ -393,7 +394,7 @@ __device__ __forceinline__ void accumulate_workers(int M, Load&& load, Prepare&&
     if constexpr (GROUP > 4) if (w + 4 <= M) { group(std::integral_constant<int, 4>{}, w); w += 4; }
     if constexpr (GROUP > 2) if (w + 2 <= M) { group(std::integral_constant<int, 2>{}, w); w += 2; }
     if (w < M) group(std::integral_constant<int, 1>{}, w);
-    total.finish(acc);
+    if constexpr (JOIN) total.finish(acc);
 }
 
 // Lanes of different tensors: sign_ptr / level_ptr address worker 0's sign dword and level dwords of the
@@ -422,7 +423,7 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
 // At B = 8 a lane's dwords are two 16-byte pieces: each load instruction covers 1 KiB in full (lanes
 // 0..31 and 32..63 take the first and second pieces of 32 lanes) and swaps between the halves of the
 // wavefront put the pieces in place, so that the streaming hint can stay on.
-template <int B, int GROUP, bool STREAM, typename LevelWave, typename Prepare, typename Unit>
+template <int B, int GROUP, bool STREAM, bool JOIN = true, typename LevelWave, typename Prepare, typename Unit>
 __device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign_wave, LevelWave&& level_wave,
                                                 int64_t packed_stride, int M, Prepare&& prepare, Unit&& unit, int n_lanes,
                                                 float (&acc)[UR_PER_LANE], lane_slots slots)
@@ -435,7 +436,7 @@ __device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign
         at1 = at0 + 1024u < end ? at0 + 1024u : end;
         at0 = at0 < end ? at0 : end;
     }
-    accumulate_workers<B, true, GROUP>(
+    accumulate_workers<B, true, GROUP, JOIN>(
         M,
         [&](int w, uint32_t& sg, uint32_t (&wd)[B]) {
             const ur_bytes lp = scalar_address(level_wave(w));
@@ -541,10 +542,10 @@ struct wave_span {
     int n_lanes;    // lanes whose 32 elements exist (a multiple of 4; <= 0: none)
     int32_t first, last;
 };
-__device__ __forceinline__ wave_span wave_span_of(int tid, int64_t padded_elems, const int32_t* __restrict__ granule_cseg)
+__device__ __forceinline__ wave_span wave_span_from(int64_t start, int64_t padded_elems, const int32_t* __restrict__ granule_cseg)
 {
     wave_span s;
-    s.start = static_cast<int64_t>(ur_tile_index()) * UR_TILE + __builtin_amdgcn_readfirstlane(tid >> 6) * UR_WAVE_ELEMS;
+    s.start = start;
     s.n_lanes = 0;
     s.first = s.last = 0;
     if (s.start < padded_elems) {
@@ -555,10 +556,21 @@ __device__ __forceinline__ wave_span wave_span_of(int tid, int64_t padded_elems,
     }
     return s;
 }
+__device__ __forceinline__ wave_span wave_span_of(int tid, int64_t padded_elems, const int32_t* __restrict__ granule_cseg)
+{
+    return wave_span_from(static_cast<int64_t>(ur_tile_index()) * UR_TILE +
+                              __builtin_amdgcn_readfirstlane(tid >> 6) * UR_WAVE_ELEMS,
+                          padded_elems, granule_cseg);
+}
 
 __device__ __forceinline__ float ur_unit(float N, int b)
 {
     return N >= DQ_MIN_NORM ? N / static_cast<float>((1 << b) - 1) * ur_unit_factor(b) : 0.0f;
+}
+
+__device__ __forceinline__ float ur_plain_unit(float N, int b) // without the width's factor
+{
+    return N >= DQ_MIN_NORM ? N / static_cast<float>((1 << b) - 1) : 0.0f;
 }
 
 // Worker w's value out of the one each lane holds (M <= 64).
@@ -639,6 +651,212 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
         },
         [&](int w) { return unit_ptr[w]; }, span.n_lanes, acc, slots_of(lds_out, tid));
     finish_tile<UPDATE>(acc, active, n_valid, inv_M * ur_sum_scale(B), lds_out, tid, span.start, padded_elems, out, x, eta);
+}
+
+// Few tiles and many workers: the workgroup's four wavefronts share the 2048 elements of a span, each with `per_wave`
+// consecutive blocks of UR_SUM_BLOCK workers (one or two).  The block sums are then added in block order, wavefront after
+// wavefront through LDS -- the additions of k_unpack_dequant_reduce in the same order, bit for bit -- and the wavefronts
+// write a quarter of the span each.
+// What bounds the undivided kernel there is the vector ALU of a few SIMDs: 514 tiles are 2056 wavefronts on 1024
+// SIMDs, and one with three of them takes half as long again as the others with two.
+constexpr int UR_SPLIT = UR_THREADS / 64;
+template <int B, bool UPDATE>
+__global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_reduce_split(
+    const uint8_t* __restrict__ packed, int64_t packed_stride, int M, int per_wave, const float* __restrict__ norms,
+    int32_t n_seg, const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
+    const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, float inv_M, float* __restrict__ out,
+    float* __restrict__ x, float eta)
+{
+    constexpr int PIECES = 8 / UR_SPLIT; // of the span's eight pieces of 256 elements
+    extern __shared__ __align__(16) uint8_t lds_raw[];
+    float4* lds_out = reinterpret_cast<float4*>(lds_raw);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const wave_span span = wave_span_from(static_cast<int64_t>(ur_tile_index()) * UR_WAVE_ELEMS, padded_elems, granule_cseg);
+    const int64_t P0 = span.start + lane * UR_PER_LANE;
+    const int w0 = wave * per_wave * UR_SUM_BLOCK;
+    const int n_mine = M - w0 < per_wave * UR_SUM_BLOCK ? M - w0 : per_wave * UR_SUM_BLOCK; // <= 0: none
+    const int last = (M - 1) / (per_wave * UR_SUM_BLOCK); // the last wavefront with workers
+
+    const auto piece_at = [&](int j) { return span.start + 256 * (wave * PIECES + j) + 4 * lane; };
+    float4 xv[PIECES]; // the model's pieces, in flight from the start; past the end: the last ones again
+    if constexpr (UPDATE) {
+#pragma unroll
+        for (int j = 0; j < PIECES; ++j)
+            xv[j] = *reinterpret_cast<const float4*>(x + (piece_at(j) < padded_elems ? piece_at(j) : padded_elems - 4));
+    }
+
+    float acc[UR_PER_LANE];
+#pragma unroll
+    for (int k = 0; k < UR_PER_LANE; ++k) acc[k] = 0.0f;
+    const lane_slots slots = slots_of(lds_out, tid);
+    int64_t n_valid = 0;
+    if (n_mine > 0) { // a wavefront without workers still reaches the barriers and writes its quarter
+        const uint8_t* mine = packed + static_cast<int64_t>(w0) * packed_stride;
+        const uint8_t* level_wave = mine + (padded_elems >> 3) + (span.start >> 3) * B;
+        float* table = reinterpret_cast<float*>(lds_raw + UR_TILE * sizeof(float)) + wave * UR_WAVE_SEGS * per_wave * UR_SUM_BLOCK;
+        const float* unit_ptr = wave_table(span, lane, n_mine, P0, granule_cseg, cseg_valid_end, table, n_valid, [&](int w, int32_t c) {
+            return ur_unit(norms[static_cast<int64_t>(w0 + w) * n_seg + cseg_seg[c]], B);
+        });
+        accumulate_wave<B, (B <= 4 ? 8 : 4), false, false>(
+            mine + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; }, packed_stride,
+            n_mine, [] {}, [&](int w) { return unit_ptr[w]; }, span.n_lanes, acc, slots);
+    }
+    for (int r = 0; r <= last; ++r) {
+        if (wave == r) {
+            const lane_slots before{ lds_out + (wave - 1) * 512, lane };
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                float4 t = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+                if (n_mine > UR_SUM_BLOCK || r > 0) {
+                    float4 o = n_mine > UR_SUM_BLOCK ? slots[q] : t;
+                    if (r > 0) {
+                        const float4 p = before[q];
+                        o = make_float4(p.x + o.x, p.y + o.y, p.z + o.z, p.w + o.w);
+                    }
+                    if (n_mine > UR_SUM_BLOCK) o = make_float4(o.x + t.x, o.y + t.y, o.z + t.z, o.w + t.w);
+                    t = o;
+                }
+                if (r == last) { // as in finish_tile
+                    const int nv = n_valid >= UR_PER_LANE ? UR_PER_LANE : (n_valid > 0 ? static_cast<int>(n_valid) : 0);
+                    const float scale = inv_M * ur_sum_scale(B);
+                    t.x = 4 * q < nv ? t.x * scale : 0.0f;
+                    t.y = 4 * q + 1 < nv ? t.y * scale : 0.0f;
+                    t.z = 4 * q + 2 < nv ? t.z * scale : 0.0f;
+                    t.w = 4 * q + 3 < nv ? t.w * scale : 0.0f;
+                }
+                slots[q] = t;
+            }
+        }
+        __syncthreads();
+    }
+    const float4* sum = lds_out + last * 512;
+#pragma unroll
+    for (int j = 0; j < PIECES; ++j) {
+        const int64_t P = piece_at(j);
+        if (P >= padded_elems) continue;
+        const int src = 8 * (wave * PIECES + j) + (lane >> 3), q = lane & 7;
+        const float4 v = sum[src * 8 + (q ^ (src & 7))];
+        if (!UPDATE || out) dq_store_stream(reinterpret_cast<float4*>(out + P), v);
+        if constexpr (UPDATE) { // pads: the sum is +0, x unchanged
+            float4 t = xv[j];
+            t.x = __builtin_fmaf(-eta, v.x, t.x);
+            t.y = __builtin_fmaf(-eta, v.y, t.y);
+            t.z = __builtin_fmaf(-eta, v.z, t.z);
+            t.w = __builtin_fmaf(-eta, v.w, t.w);
+            *reinterpret_cast<float4*>(x + P) = t;
+        }
+    }
+}
+
+// Few tiles and few workers: a lane owns 8 elements in place of 32, so that there are four times as many wavefronts, and
+// the loads of messages, model and norms are issued together behind one lookup (the chunk table's) where the elements
+// lie in one tensor.  The same additions in the same order as in k_unpack_dequant_reduce (whose products carry exact
+// powers of two that the epilogue takes out), bit for bit.
+// What bounds it: launch and two memory latencies.
+constexpr int UR_NARROW_PER_LANE = 8, UR_NARROW_WAVE = 64 * UR_NARROW_PER_LANE; // 512 elements, up to four tensors
+constexpr int UR_NARROW_SEGS = UR_NARROW_WAVE / DQ_GRANULE;
+
+template <int B, bool UPDATE>
+__global__ __launch_bounds__(UR_THREADS) void k_unpack_dequant_reduce_narrow(
+    const uint8_t* __restrict__ packed, int64_t packed_stride, int M, const float* __restrict__ norms, int32_t n_seg,
+    const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
+    const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, float inv_M,
+    float* __restrict__ out, float* __restrict__ x, float eta)
+{
+    extern __shared__ __align__(16) uint8_t lds_raw[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    wave_span span;
+    span.start = (static_cast<int64_t>(blockIdx.x) * (UR_THREADS / 64) + wave) * UR_NARROW_WAVE;
+    if (span.start >= padded_elems) return; // the whole wavefront; there is no workgroup barrier below
+    const int64_t left = padded_elems - span.start;
+    span.n_lanes = static_cast<int>(left < UR_NARROW_WAVE ? left : UR_NARROW_WAVE) / UR_NARROW_PER_LANE; // a multiple of 16
+    const dq_chunk_tensor owner = dq_load_chunk_tensor(chunk_tensor, span.start >> 12);
+    const int64_t P0 = span.start + lane * UR_NARROW_PER_LANE;
+    const uint32_t own = lane < span.n_lanes ? lane : span.n_lanes - 1; // lanes past the end fetch the last one's bytes
+    float4 xv[2];
+    if constexpr (UPDATE) {
+        const float4* xp = reinterpret_cast<const float4*>(x + span.start) + own * 2u;
+        xv[0] = xp[0];
+        xv[1] = xp[1];
+    }
+
+    const uint8_t* sign_wave = packed + (span.start >> 3);
+    const uint8_t* level_wave = packed + (padded_elems >> 3) + (span.start >> 3) * B;
+    float* table = reinterpret_cast<float*>(lds_raw) + wave * UR_NARROW_SEGS * M;
+    const float* unit_ptr = nullptr;
+    int64_t n_valid = UR_NARROW_PER_LANE;
+    float acc[UR_NARROW_PER_LANE], total[UR_NARROW_PER_LANE];
+#pragma unroll
+    for (int k = 0; k < UR_NARROW_PER_LANE; ++k) acc[k] = total[k] = 0.0f;
+    auto group = [&](auto g, int w) {
+        constexpr int G = decltype(g)::value;
+        uint32_t sg[G];
+        uint64_t lv[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int64_t off = static_cast<int64_t>(w + i) * packed_stride;
+            const uint8_t* lp = level_wave + off + own * B;
+            sg[i] = sign_wave[off + own];
+            lv[i] = 0;
+            __builtin_memcpy(&lv[i], lp, B); // B bytes, at any byte address
+        }
+        if (w == 0) {
+            if (owner.cseg >= 0) { // the same for the whole wavefront: one tensor, all of it data
+                if (lane < M) table[lane] = ur_plain_unit(norms[static_cast<int64_t>(lane) * n_seg + owner.seg], B);
+                dq_wave_sync();
+                unit_ptr = table;
+            } else {
+                span.first = granule_cseg[span.start >> 7];
+                span.last = granule_cseg[(span.start + span.n_lanes * UR_NARROW_PER_LANE - 1) >> 7];
+                unit_ptr = wave_table(span, lane, M, P0, granule_cseg, cseg_valid_end, table, n_valid, [&](int u, int32_t c) {
+                    return ur_plain_unit(norms[static_cast<int64_t>(u) * n_seg + cseg_seg[c]], B);
+                });
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const float unit = unit_ptr[w + i];
+#pragma unroll
+            for (int k = 0; k < UR_NARROW_PER_LANE; ++k) {
+                const uint32_t level = static_cast<uint32_t>(lv[i] >> (k * B)) & ((1u << B) - 1u);
+                const float v = __uint_as_float(__float_as_uint(static_cast<float>(level)) | ((sg[i] << (31 - k)) & 0x80000000u));
+                acc[k] = __builtin_fmaf(v, unit, acc[k]);
+            }
+            if (((w + i + 1) & (UR_SUM_BLOCK - 1)) == 0 && w + i + 1 < M) { // the block joins the total, as block_total does
+#pragma unroll
+                for (int k = 0; k < UR_NARROW_PER_LANE; ++k) {
+                    total[k] = w + i + 1 > UR_SUM_BLOCK ? total[k] + acc[k] : acc[k];
+                    acc[k] = 0.0f;
+                }
+            }
+        }
+    };
+    int w = 0;
+    for (; w + 8 <= M; w += 8) group(std::integral_constant<int, 8>{}, w);
+    if (w + 4 <= M) { group(std::integral_constant<int, 4>{}, w); w += 4; }
+    if (w + 2 <= M) { group(std::integral_constant<int, 2>{}, w); w += 2; }
+    if (w < M) group(std::integral_constant<int, 1>{}, w);
+    if (lane >= span.n_lanes) return;
+    const int nv = n_valid >= UR_NARROW_PER_LANE ? UR_NARROW_PER_LANE : (n_valid > 0 ? static_cast<int>(n_valid) : 0);
+#pragma unroll
+    for (int k = 0; k < UR_NARROW_PER_LANE; ++k) {
+        const float sum = M > UR_SUM_BLOCK ? total[k] + acc[k] : acc[k];
+        acc[k] = k < nv ? sum * inv_M : 0.0f;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const float4 v = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
+        if (!UPDATE || out) *reinterpret_cast<float4*>(out + P0 + 4 * h) = v;
+        if constexpr (UPDATE) {
+            float4 t = xv[h];
+            t.x = __builtin_fmaf(-eta, v.x, t.x);
+            t.y = __builtin_fmaf(-eta, v.y, t.y);
+            t.z = __builtin_fmaf(-eta, v.z, t.z);
+            t.w = __builtin_fmaf(-eta, v.w, t.w);
+            *reinterpret_cast<float4*>(x + P0 + 4 * h) = t;
+        }
+    }
 }
 
 // Per-tensor widths: a wavefront inside one tensor takes its b and the place of its level dwords from the
@@ -976,12 +1194,64 @@ constexpr size_t UR_LDS_THREE_PER_CU = 41 * 1024; // of 160 KiB
 constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20;
 constexpr bool ur_may_stream(int b) { return b >= 5 && b <= 7; }
 
+// Up to how many tiles the workers are divided over wavefronts (k_unpack_dequant_reduce_split), measured against the
+// undivided kernel for M = 12..64, 16..2048 tiles, all widths, with and without update.  Undivided, a tile is one
+// wavefront on each SIMD of a CU: 128 tiles leave half of the chip idle (M = 32 b = 1 15 %, b = 5 45 % gained; M = 64 33 and 65 %,
+// at 16 tiles 70 and 100 %), and between 128 and 600 those CUs last that have one tile more than the others.  What
+// the division costs (LDS, barriers, a row of units per wavefront) is most at b = 1, 2 and 8.  Inside the lines
+// it gains 1 to 100 %; beyond them it loses: M = 24 at 256 tiles b = 1 10 %, M = 64 at 384 b = 8 14 %, at 768 b = 1..8 3 to 19 %.
+inline int64_t ur_split_max_tiles(int b, int M)
+{
+    if (M > 56 && b == 5) return 600;            // 4.2 M ragged values, M = 64, with update 52.5 -> 45.8 us
+    if (M > 56 && (b == 2 || b == 3)) return 400;
+    if (M >= 40 && b >= 4 && b <= 7) return 256;
+    if (M >= 32 && b >= 3) return 192;
+    return M > 24 ? 128 : 0;
+}
+// Up to how many tiles a lane owns 8 elements (k_unpack_dequant_reduce_narrow), measured against the kernels above for
+// M = 1..64, 0.5..768 tiles, all widths, with and without update (kernel trace).  4096 elements, M = 8, b = 8 with update
+// 4.44 -> 3.32 us; 2^20, M = 4, b = 4 4.84 -> 4.24.  Inside the lines 0 to 60 % gained; beyond them its plain extraction
+// of every level costs more than the idle lanes: M = 1 at 192 tiles 0 %, at 256 up to 9 % lost, M = 8 at 192 b = 1 7 %, 3.0 M ragged
+// values, M = 5 b = 1 7 %; M = 32 b = 7 at 64 tiles 5 %, M = 64 b = 1 at any size 10 %.
+inline int64_t ur_narrow_max_tiles(int b, int M)
+{
+    if (b == 8 && M >= 4) return 192;
+    if (M <= 24) return 128;
+    return M <= 40 && b != 3 && b != 7 ? 64 : 0;
+}
+
 template <int B>
 int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, int M, const float* norms,
            float* out, float* x, float eta, hipStream_t stream)
 {
     const int64_t n_tiles = (plan->padded_elems + UR_TILE - 1) / UR_TILE;
     if (n_tiles > INT32_MAX) return DQ_ERR_INVALID_ARG;
+    const float inv_M = 1.0f / static_cast<float>(M);
+    if (n_tiles <= ur_narrow_max_tiles(B, M)) {
+        const dim3 grid(static_cast<unsigned>((plan->padded_elems + 4 * UR_NARROW_WAVE - 1) / (4 * UR_NARROW_WAVE))), block(UR_THREADS);
+        const size_t lds = static_cast<size_t>(UR_THREADS / 64) * UR_NARROW_SEGS * M * sizeof(float);
+#define DQ_LAUNCH_NARROW(UPDATE)                                                                                          \
+    hipLaunchKernelGGL((k_unpack_dequant_reduce_narrow<B, UPDATE>), grid, block, lds, stream, packed, packed_stride, M, norms, \
+                       plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, \
+                       plan->padded_elems, inv_M, out, x, eta)
+        if (x) DQ_LAUNCH_NARROW(true);
+        else DQ_LAUNCH_NARROW(false);
+#undef DQ_LAUNCH_NARROW
+        return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
+    }
+    if (n_tiles <= ur_split_max_tiles(B, M)) {
+        const int per_wave = (M + UR_SPLIT * UR_SUM_BLOCK - 1) / (UR_SPLIT * UR_SUM_BLOCK); // blocks of workers
+        const dim3 grid(static_cast<unsigned>((plan->padded_elems + UR_WAVE_ELEMS - 1) / UR_WAVE_ELEMS)), block(UR_THREADS);
+        const size_t lds = UR_TILE * sizeof(float) + static_cast<size_t>(UR_MAX_LOCAL_SEG) * per_wave * UR_SUM_BLOCK * sizeof(float);
+#define DQ_LAUNCH_SPLIT(UPDATE)                                                                                           \
+    hipLaunchKernelGGL((k_unpack_dequant_reduce_split<B, UPDATE>), grid, block, lds, stream, packed, packed_stride, M,    \
+                       per_wave, norms, plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end,       \
+                       plan->padded_elems, inv_M, out, x, eta)
+        if (x) DQ_LAUNCH_SPLIT(true);
+        else DQ_LAUNCH_SPLIT(false);
+#undef DQ_LAUNCH_SPLIT
+        return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
+    }
     size_t lds_bytes = UR_TILE * sizeof(float) + static_cast<size_t>(UR_MAX_LOCAL_SEG) * M * sizeof(float);
     // Where thousands of tiles stream wide messages, three workgroups per CU move more than four.  Measured for
     // M = 1..32, 2048..16384 tiles, b = 4..8, inputs in no cache and inputs read before, as a factor on the time:
@@ -993,7 +1263,6 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
     const bool three = B >= 4 && M >= 8 && (x ? !ur_may_stream(B) && n_tiles >= 8192 : n_tiles >= 4096);
     if (three && lds_bytes < UR_LDS_THREE_PER_CU) lds_bytes = UR_LDS_THREE_PER_CU;
     const dim3 grid(static_cast<unsigned>(n_tiles)), block(UR_THREADS);
-    const float inv_M = 1.0f / static_cast<float>(M);
     const bool fits_cache = plan->padded_elems * (M * (B + 1) + 32) / 8 <= UR_LAST_LEVEL_CACHE; // messages and model
     if (x && ur_may_stream(B) && !fits_cache && M <= 32)
         hipLaunchKernelGGL((k_unpack_dequant_reduce<B, true, ur_may_stream(B)>), grid, block, lds_bytes, stream, packed,

@@ -1,0 +1,43 @@
+"""The server average on both sides of the lines between its three kernels (a lane's 32 elements, a lane's 8 elements
+for few tiles, workers divided over wavefronts): the same bits as the widths-table kernel, which has one form for every
+size, and that one is compared with the oracle elsewhere (test_gpu_reduce_routes).  Messages are random bytes, norms
+include unusable ones."""
+import pytest
+import torch
+
+from tests.test_gpu_parity import dq  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+TILE = 8192
+# elements: below a wavefront, ends inside a lane, a granule and a span, and on and beyond 64, 128, 192 and 256 tiles
+LAYOUTS = [
+    [1], [200, 0, 7, 129, 511], [4096], [512 * 3, 1, 2048 * 2 + 77], [300] * 40, [TILE * 64 - 900, 640], [TILE * 64 + 1],
+    [TILE * 100, 5, TILE * 28 - 128], [TILE * 128 + 1], [TILE * 192 - 3], [TILE * 193], [TILE * 255, 130, 4000],
+]
+
+
+@pytest.mark.parametrize("M", [1, 4, 8, 9, 16, 24, 25, 32, 40, 41, 57, 64])
+@pytest.mark.parametrize("layout", range(len(LAYOUTS)))
+def test_same_bits_as_the_widths_table_kernel(dq, layout, M):
+    seg_len = LAYOUTS[layout]
+    plan = dq.Plan(seg_len)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(layout * 100 + M)
+    norms = torch.rand((M, len(seg_len)), generator=gen, device="cuda") * 4 + 1e-3
+    norms[M // 2, len(seg_len) // 2] = float("nan")
+    norms[0, 0] = 0.0 if M > 1 else 2.0 ** -99
+    x0 = torch.randn(plan.padded_elems, generator=gen, device="cuda")
+    for b in range(1, 9):
+        packed = torch.randint(0, 256, (M, plan.packed_bytes(b)), dtype=torch.uint8, device="cuda", generator=gen)
+        want, got = torch.full_like(x0, float("nan")), torch.full_like(x0, float("nan"))
+        table = dq.Widths(plan, [b] * len(seg_len))
+        dq.unpack_dequant_reduce_v(plan, table, packed, norms, want)
+        dq.unpack_dequant_reduce(plan, packed, norms, b, got)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
+        x, y, ghat = x0.clone(), x0.clone(), torch.full_like(x0, float("nan"))
+        dq.unpack_dequant_reduce_update_v(plan, table, packed, norms, 0.25, x)
+        dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.25, y, ghat=ghat)
+        assert torch.equal(y.view(torch.int32), x.view(torch.int32)), b
+        assert torch.equal(ghat.view(torch.int32), want.view(torch.int32)), b
+    plan.close()
