@@ -168,9 +168,7 @@ __device__ __forceinline__ void bracketed_one_tensor(const float4 (&x)[2][2], fl
             lds_sign[at] = static_cast<uint8_t>(sign);
             stage_bytes<B>(&lds_level[at * B], level);
         }
-        dq_wave_sync();
-        qp_store_wave(sign_chunk + (wave0 >> 3), &lds_sign[wave0 >> 3], QP_WAVE_TILE * 2 / 8, lane);
-        qp_store_wave(level_chunk + (wave0 >> 3) * B, &lds_level[(wave0 >> 3) * B], QP_WAVE_TILE * 2 / 8 * B, lane);
+        qp_store_chunk(sign_chunk, level_chunk, lds_sign, lds_level, DQ_CHUNK, wave0, B, tid);
     }
 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -351,16 +349,8 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
     __syncthreads();
 
     uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
-    {
-        uint4* dst = reinterpret_cast<uint4*>(msg + (chunk0 >> 3));
-        const uint4* src = reinterpret_cast<const uint4*>(lds_sign);
-        for (uint32_t i = tid; i < n_elems / 128; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
-    }
-    {
-        uint4* dst = reinterpret_cast<uint4*>(msg + (padded_elems >> 3) + (chunk0 >> 3) * B);
-        const uint4* src = reinterpret_cast<const uint4*>(lds_level);
-        for (uint32_t i = tid; i < n_elems / 128 * B; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
-    }
+    qp_store_block(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid);
+    qp_store_block(msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_level, (n_elems >> 3) * B, tid);
     if (tid == 0) {
         blk->count = lds_count;
         blk->flags = 0;
@@ -540,18 +530,10 @@ __global__ __launch_bounds__(QP_THREADS, 7) void k_quantize_pack_bracketed_v(
     __syncthreads();
 
     uint8_t* msg = packed + static_cast<int64_t>(w) * packed_stride;
-    {
-        uint4* dst = reinterpret_cast<uint4*>(msg + (chunk0 >> 3));
-        const uint4* src = reinterpret_cast<const uint4*>(lds_sign);
-        for (uint32_t i = tid; i < n_elems / 128; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
-    }
-    {
-        const int last = seg_last - seg_first;
-        const uint32_t level_bytes = static_cast<uint32_t>(lds_level_base[last]) + (n_elems >> 3) * lds_b[last];
-        uint4* dst = reinterpret_cast<uint4*>(msg + (padded_elems >> 3) + chunk_level0);
-        const uint4* src = reinterpret_cast<const uint4*>(lds_level);
-        for (uint32_t i = tid; i < level_bytes / 16; i += QP_THREADS) dq_store_stream(dst + i, src[i]);
-    }
+    const int last = seg_last - seg_first;
+    qp_store_block(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid);
+    qp_store_block(msg + (padded_elems >> 3) + chunk_level0, lds_level,
+                   static_cast<uint32_t>(lds_level_base[last]) + (n_elems >> 3) * lds_b[last], tid);
     if (tid == 0) {
         blk->count = lds_count;
         blk->flags = 0;

@@ -347,20 +347,68 @@ __device__ __forceinline__ uint32_t qp_granule(uint32_t tid, int it, uint32_t n_
     return (e < n_elems ? e : n_elems - QP_PER_LANE) >> 7;
 }
 
-// A wavefront's staged bytes [0, bytes) (a multiple of 16) leave as 16-byte streaming stores.
-__device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t lane)
+// One 16-byte piece of a message.  KEEP: it may stay in the caches (keep, the same for the whole launch, decides);
+// otherwise it carries the streaming hint.
+template <bool KEEP>
+__device__ __forceinline__ void qp_store_piece(uint4* dst, const uint4& v, bool keep)
 {
-    uint4* d = reinterpret_cast<uint4*>(dst);
-    const uint4* f = reinterpret_cast<const uint4*>(src);
-    for (uint32_t i = lane; i < bytes / 16; i += 64) dq_store_stream(d + i, f[i]);
+    if (KEEP && keep)
+        *dst = v;
+    else
+        dq_store_stream(dst, v);
 }
 
-// The workgroup's staged bytes [0, bytes) (a multiple of 16), after a barrier.
-__device__ __forceinline__ void qp_store_block(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t tid)
+// A wavefront's staged bytes [0, bytes) (a multiple of 16) leave as 16-byte stores.
+template <bool KEEP = false>
+__device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t lane,
+                                              bool keep = false)
 {
     uint4* d = reinterpret_cast<uint4*>(dst);
     const uint4* f = reinterpret_cast<const uint4*>(src);
-    for (uint32_t i = tid; i < bytes / 16; i += QP_THREADS) dq_store_stream(d + i, f[i]);
+    for (uint32_t i = lane; i < bytes / 16; i += 64) qp_store_piece<KEEP>(d + i, f[i], keep);
+}
+
+// The workgroup's staged bytes [0, bytes) (a multiple of 16), after a barrier.  The lanes are counted from the start of
+// the cache line that holds the first byte, so that no line is shared by two store instructions.
+template <bool KEEP = false>
+__device__ __forceinline__ void qp_store_block(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t tid,
+                                               bool keep = false)
+{
+    uint4* d = reinterpret_cast<uint4*>(dst);
+    const uint4* f = reinterpret_cast<const uint4*>(src);
+    const uint32_t skew = (static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst)) & 127u) >> 4;
+    for (uint32_t i = tid; i < bytes / 16 + skew; i += QP_THREADS)
+        if (i >= skew) qp_store_piece<KEEP>(d + (i - skew), f[i - skew], keep);
+}
+
+// Whether a chunk's two stretches of the message start on cache lines; each wavefront's part then does too (its tiles
+// give a multiple of 128 bytes of either plane).  Where they don't -- the planes follow one another at multiples of 16
+// bytes only --, wavefronts that store for themselves write two parts of a line each, and the memory
+// pays for every part: the workgroup stores together there.  2^26 + 12345 values, M = 16, b = 7 950 -> 933 us, 2^28 - 1000,
+// b = 4 3518 -> 3467, bracketed ResNet-18 shape, M = 8, b = 3 92.9 -> 89.8.
+__device__ __forceinline__ bool qp_on_lines(const uint8_t* sign, const uint8_t* level)
+{
+    return ((reinterpret_cast<uintptr_t>(sign) | reinterpret_cast<uintptr_t>(level)) & 127u) == 0;
+}
+
+// The chunk's staged bytes leave: by wavefronts (each after its own staging) or together (see qp_on_lines).
+// n_elems: the chunk's elements; sign and level: where its stretches start; b: its width; keep: see qp_store_piece.
+template <bool KEEP = false>
+__device__ __forceinline__ void qp_store_chunk(uint8_t* sign, uint8_t* level, const uint8_t* lds_sign, const uint8_t* lds_level,
+                                               uint32_t n_elems, uint32_t wave0, uint32_t b, uint32_t tid, bool keep = false)
+{
+    if (qp_on_lines(sign, level)) {
+        dq_wave_sync();
+        if (wave0 < n_elems) {
+            const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * QP_TILES ? n_elems - wave0 : QP_WAVE_TILE * QP_TILES;
+            qp_store_wave<KEEP>(sign + (wave0 >> 3), lds_sign + (wave0 >> 3), n_wave >> 3, tid & 63u, keep);
+            qp_store_wave<KEEP>(level + (wave0 >> 3) * b, lds_level + (wave0 >> 3) * b, (n_wave >> 3) * b, tid & 63u, keep);
+        }
+    } else {
+        __syncthreads();
+        qp_store_block<KEEP>(sign, lds_sign, n_elems >> 3, tid, keep);
+        qp_store_block<KEEP>(level, lds_level, (n_elems >> 3) * b, tid, keep);
+    }
 }
 
 // What bounds it: the memory system's rate at 4 bytes read to (B+1)/8 written (about 6.1-6.2 TB/s, what a
@@ -375,6 +423,7 @@ __device__ __forceinline__ void qp_store_block(uint8_t* __restrict__ dst, const 
 // values in tensors of 128, M = 8 b = 4 38.0 -> 36.6, 16.8 M in tensors of 512, M = 8 b = 6 121.8 -> 114.8 and, with a
 // widths table, b = 7 130.9 -> 122.4; 30.7 M in tensors of 1000, M = 4 b = 6 112.0 -> 104.5.
 //
+// keep: with NORM = 0, whether the message's stores go without the streaming hint (qp_keep_messages).
 // tid: threadIdx.x, or qp_tid_in_loop() where a workgroup takes several chunks.
 // NORM = 0: the norms are an input.  NORM = 1 (l2) or 2 (max): chunk-local plans only; the kernel
 // computes the norms of its chunk's tensors itself, writes them to norms_out and quantizes from
@@ -385,7 +434,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid, bool keep = false)
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -435,10 +484,8 @@ __device__ __forceinline__ void quantize_pack_chunk(
                 lds_sign[at] = static_cast<uint8_t>(sign);
                 stage_bytes<B>(&lds_level[at * B], level);
             }
-            dq_wave_sync();
-            qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], QP_WAVE_TILE * TILES / 8, tid & 63u);
-            qp_store_wave(msg + (padded_elems >> 3) + ((chunk0 + wave0) >> 3) * B, &lds_level[(wave0 >> 3) * B],
-                          QP_WAVE_TILE * TILES / 8 * B, tid & 63u);
+            qp_store_chunk<NORM == 0>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_sign, lds_level, CHUNK, wave0,
+                           B, tid, keep);
             return;
         }
     }
@@ -518,20 +565,14 @@ __device__ __forceinline__ void quantize_pack_chunk(
     }
     if constexpr (BLOCK) {
         __syncthreads();
-        qp_store_block(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid);
-        qp_store_block(msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_level, (n_elems >> 3) * B, tid);
+        qp_store_block<NORM == 0>(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid, keep);
+        qp_store_block<NORM == 0>(msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_level, (n_elems >> 3) * B, tid, keep);
         return;
     }
-    dq_wave_sync();
-
-    // 16-byte stores of this wavefront's stretch; every plane of it is a whole number of 16-byte
-    // pieces because it holds a multiple of 128 elements
-    if (wave0 < n_elems) {
-        const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * TILES ? n_elems - wave0 : QP_WAVE_TILE * TILES;
-        qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], n_wave >> 3, tid & 63u);
-        qp_store_wave(msg + (padded_elems >> 3) + ((chunk0 + wave0) >> 3) * B, &lds_level[(wave0 >> 3) * B],
-                      (n_wave >> 3) * B, tid & 63u);
-    }
+    // 16-byte stores; every plane of a wavefront's stretch is a whole number of 16-byte pieces because it holds a
+    // multiple of 128 elements
+    qp_store_chunk<NORM == 0>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_sign, lds_level, n_elems, wave0,
+                              B, tid, keep);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -547,7 +588,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
     const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid, bool keep = false)
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -601,10 +642,8 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
                 lds_sign[at] = static_cast<uint8_t>(sign);
                 stage_bytes_v(&lds_level[at * e.b], level, e.b);
             }
-            dq_wave_sync();
-            qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], QP_WAVE_TILE * TILES / 8, tid & 63u);
-            qp_store_wave(msg + (padded_elems >> 3) + e.level_start + ((chunk0 + wave0 - e.seg_start) >> 3) * e.b,
-                          &lds_level[(wave0 >> 3) * e.b], QP_WAVE_TILE * TILES / 8 * e.b, tid & 63u);
+            qp_store_chunk<NORM == 0>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + e.level_start + ((chunk0 - e.seg_start) >> 3) * e.b,
+                           lds_sign, lds_level, CHUNK, wave0, e.b, tid, keep);
             return;
         }
     }
@@ -690,29 +729,11 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
             stage_bytes_v(&lds_level[lds_level_base[local] + static_cast<int32_t>(e >> 3) * b], level, b);
         }
     }
-    if constexpr (BLOCK) {
-        __syncthreads();
-        const int last = seg_last - seg_first;
-        qp_store_block(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid);
-        qp_store_block(msg + (padded_elems >> 3) + chunk_level0, lds_level,
-                       static_cast<uint32_t>(lds_level_base[last]) + (n_elems >> 3) * lds_b[last], tid);
-        return;
-    }
-    dq_wave_sync();
-
-    if (wave0 < n_elems) {
-        const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * TILES ? n_elems - wave0 : QP_WAVE_TILE * TILES;
-        qp_store_wave(msg + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3], n_wave >> 3, tid & 63u);
-        // level bytes of the wavefront's first element up to those of its last granule
-        // (their tensors from the wavefront's first and last lane: looked up in the table again, ahead of the stores,
-        // they cost norms and messages in one read 3 to 4 %: 16.4 M values, M = 8, tensors of 4096 126.6 -> 122.4 us)
-        const int a = __builtin_amdgcn_readfirstlane(seg[0]) - seg_first;
-        const int z = __builtin_amdgcn_readlane(seg[TILES - 1], 63) - seg_first;
-        const int32_t from = lds_level_base[a] + static_cast<int32_t>(wave0 >> 3) * lds_b[a];
-        const int32_t to = lds_level_base[z] + static_cast<int32_t>((wave0 + n_wave) >> 3) * lds_b[z];
-        qp_store_wave(msg + (padded_elems >> 3) + chunk_level0 + from, &lds_level[from], static_cast<uint32_t>(to - from),
-                      tid & 63u);
-    }
+    __syncthreads();
+    const int last = seg_last - seg_first;
+    qp_store_block<NORM == 0>(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid, keep);
+    qp_store_block<NORM == 0>(msg + (padded_elems >> 3) + chunk_level0, lds_level,
+                              static_cast<uint32_t>(lds_level_base[last]) + (n_elems >> 3) * lds_b[last], tid, keep);
 }
 
 } // namespace

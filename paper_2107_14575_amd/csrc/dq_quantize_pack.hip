@@ -25,11 +25,11 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack(
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
     int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out)
+    int64_t packed_stride, float* __restrict__ norms_out, bool keep)
 {
     quantize_pack_chunk<B, TILES, NORM, WHOLE>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                         padded_elems, key0, key1, step, worker_base, packed, packed_stride, norms_out,
-                                        blockIdx.x, threadIdx.x);
+                                        blockIdx.x, threadIdx.x, keep);
 }
 
 template <int TILES, int NORM, bool WHOLE> // as in k_quantize_pack
@@ -40,11 +40,11 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
     const dq_cseg_width* __restrict__ widths_table,
     int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out)
+    int64_t packed_stride, float* __restrict__ norms_out, bool keep)
 {
     quantize_pack_chunk_v<TILES, NORM, WHOLE>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
                                        widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
-                                       packed, packed_stride, norms_out, blockIdx.x, threadIdx.x);
+                                       packed, packed_stride, norms_out, blockIdx.x, threadIdx.x, keep);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -110,6 +110,20 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
     }
 }
 
+// Whether the messages are stored without the streaming hint: they are read next, by the same GPU's reduce or by
+// whatever sends them, and a model of moderate size leaves them room in the 256 MB last-level cache.  Whole
+// iterations (norm, quantize, reduce with update), with the hint and without, in us: ResNet-18 shape, M = 8 b = 4 155.1 ->
+// 151.4, b = 6 160.3 -> 156.4, M = 35 b = 4 608.7 -> 591.1; 2^24 values, M = 16 b = 4 409.8 -> 396.1, b = 8 (302 MB of messages)
+// 453.1 -> 435.7; transformer shape, M = 16, one width per tensor 362.0 -> 350.9 (quantizing alone 170.8 -> 153.8).  Larger models
+// lose, with few bytes of messages too: 2^25 values, M = 16 b = 4 843.3 -> 857.5, 2^26, M = 4 b = 1 431.3 -> 453.5, M = 16 b = 4
+// 1687 -> 1922; and narrow widths gain or lose 2 % either way (ResNet-18 shape, M = 8 b = 2 145.1 -> 147.2).
+// bytes: of all messages, at most.
+constexpr int64_t QP_KEEP_ELEMS = 18 << 20, QP_KEEP_BYTES = 320 << 20;
+inline bool qp_keep_messages(const dq_plan* plan, int b, int64_t bytes)
+{
+    return b >= 3 && plan->padded_elems <= QP_KEEP_ELEMS && bytes <= QP_KEEP_BYTES;
+}
+
 template <int B, int NORM>
 int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M, const float* norms,
            uint64_t seed, uint32_t step, uint32_t worker_base, uint8_t* packed, int64_t packed_stride,
@@ -118,11 +132,12 @@ int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M
     const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
+    const bool keep = NORM == 0 && qp_keep_messages(plan, B, M * dq_packed_bytes(plan, B));
 #define DQ_LAUNCH_Q(WHOLE)                                                                                        \
     hipLaunchKernelGGL((k_quantize_pack<B, QP_TILES, NORM, WHOLE>), grid, block, 0, stream, grads, worker_stride, \
                        norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,          \
                        plan->d_cseg_valid_end, plan->padded_elems, static_cast<uint32_t>(seed),                   \
-                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out)
+                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out, keep)
     if (NORM != 0 || plan->many_whole)
         DQ_LAUNCH_Q(true);
     else
@@ -199,12 +214,14 @@ int quantize_v_entry(int norm_mode, const dq_plan_t* plan, const dq_widths_t* wi
     const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
+    // the widths may be known to the GPU only: eight bits everywhere is the most
+    const bool keep = norm_mode == 0 && qp_keep_messages(plan, 8, M * dq_packed_bytes(plan, 8));
 #define DQ_LAUNCH_QV(NORM, WHOLE)                                                                                 \
     hipLaunchKernelGGL((k_quantize_pack_v<QP_TILES, NORM, WHOLE>), grid, block, 0, stream, grads_dev,             \
                        worker_stride_elems, norms_in, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,    \
                        plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, row_stride, plan->padded_elems, \
                        static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), step, worker_base,         \
-                       packed_dev, packed_worker_stride_bytes, norms_out)
+                       packed_dev, packed_worker_stride_bytes, norms_out, keep)
     if (norm_mode == 0 && plan->many_whole)
         DQ_LAUNCH_QV(0, true);
     else if (norm_mode == 0)
