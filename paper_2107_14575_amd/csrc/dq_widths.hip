@@ -13,6 +13,7 @@
 #include <string.h>
 
 #include <new>
+#include <type_traits>
 
 #include "dq_internal.h"
 
@@ -35,89 +36,139 @@ __device__ __forceinline__ int smallest_width(double s_star, int b_min, int b_ma
 // needs no round trip to the host: one workgroup reads the M x n_seg norms, decides the widths,
 // and fills the widths table (b and, by a scan over the tensors, where each tensor's level bytes
 // start).  rule: 0 = Eq. (17) with the l2 norms, 1 = with max norms, 2 = one width per tensor.
-__global__ __launch_bounds__(SB_THREADS) void k_select_bits(
+//
+// What bounds it: latency, of memory and of a worker's chain of additions.  A lane has one tensor, its table entry is
+// fetched beside the norms, and all loads of a sum are in flight ahead of it: rule 2 reads a tensor's sixteen workers at a
+// time, the others stage 64 tensors of all workers in LDS, so that 64 lanes add 64 workers' squares side by side.
+// Before, 256 lanes read the norms one by one where they added them, and the scan took sixteen barriers.  Per launch, one
+// after the other in a graph: one width for 62 tensors of 8 workers 7.9 -> 3.9 us, 102 of 16 12.0 -> 4.6, 400 of 64 43.9 ->
+// 11.3, 1024 of 64 105 -> 21; one width per tensor, 102 of 16 5.9 -> 3.0, 400 of 64 30.6 -> 6.2, 1024 of 64 59 -> 8.7.  A
+// single tensor's 3.1 became 3.4.  Up to 256 tensors a quarter of the lanes start sooner than 1024: one tensor of 16
+// workers 3.4 against 3.8 us, 102 per tensor 3.0 against 4.5.
+constexpr int SEL_FEW = 256, SEL_MANY = 1024; // lanes, and the most tensors each takes; plans of more take the kernels below
+static_assert(DQ_MAX_WORKERS == 64, "one lane of a wavefront per worker");
+
+template <int SEL_THREADS>
+__global__ __launch_bounds__(SEL_THREADS) void k_select_bits(
     const float* __restrict__ norms, int M, int32_t n_seg, int32_t n_cseg, const int32_t* __restrict__ cseg_seg,
     const int64_t* __restrict__ cseg_valid_end, dq_cseg_width* __restrict__ table, int rule, double root_T_eps,
     double weight, int b_min, int b_max, int64_t sign_bytes, int32_t* __restrict__ b_out,
     double* __restrict__ gbar_out, int64_t* __restrict__ packed_bytes_out)
 {
-    __shared__ double worker_sq[DQ_MAX_WORKERS];
-    __shared__ int b_all;
-    __shared__ int64_t scan[SB_THREADS];
-    __shared__ int64_t carry;
-    const int tid = threadIdx.x;
+    constexpr int SEL_TILE = 64; // tensors staged at a time
+    constexpr int SEL_ROWS = SEL_THREADS / SEL_TILE, SEL_LOADS = DQ_MAX_WORKERS / SEL_ROWS;
+    __shared__ double stage[SEL_TILE * (DQ_MAX_WORKERS + 1)]; // squares [tensor][worker]; the odd row keeps both ways off one bank
+    __shared__ int lds_b[SEL_THREADS];
+    __shared__ int64_t wave_total[SEL_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double factor = root_T_eps * weight;
 
-    if (rule != 2) {
-        if (tid < M) {
-            const float* row = norms + static_cast<int64_t>(tid) * n_seg;
-            double acc = 0.0;
-            for (int32_t l = 0; l < n_seg; ++l) {
-                const double sq = static_cast<double>(row[l]) * static_cast<double>(row[l]);
-                if (rule == 1)
-                    acc = sq > acc ? sq : acc;
-                else
-                    acc += sq;
-            }
-            worker_sq[tid] = acc;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            double sum_sq = 0.0;
-            for (int i = 0; i < M; ++i) sum_sq += worker_sq[i];
-            const double gbar = sqrt(sum_sq / static_cast<double>(M));
-            b_all = smallest_width(factor * gbar, b_min, b_max);
-            if (gbar_out) gbar_out[0] = gbar;
-        }
-        __syncthreads();
-        const int b = b_all;
-        if (b_out)
-            for (int32_t l = tid; l < n_seg; l += SB_THREADS) b_out[l] = b;
-        for (int32_t c = tid; c < n_cseg; c += SB_THREADS) table[c].b = b;
-    } else {
-        auto tensor_width = [&](int32_t l, double* nbar_out) {
-            double acc = 0.0;
-            for (int i = 0; i < M; ++i) {
-                const double n = static_cast<double>(norms[static_cast<int64_t>(i) * n_seg + l]);
-                acc += n * n;
-            }
-            const double nbar = sqrt(acc / static_cast<double>(M));
-            if (nbar_out) *nbar_out = nbar;
-            return smallest_width(factor * nbar, b_min, b_max);
-        };
-        if (b_out || gbar_out)
-            for (int32_t l = tid; l < n_seg; l += SB_THREADS) {
-                const int b = tensor_width(l, gbar_out ? gbar_out + l : nullptr);
-                if (b_out) b_out[l] = b;
-            }
-        for (int32_t c = tid; c < n_cseg; c += SB_THREADS) table[c].b = tensor_width(cseg_seg[c], nullptr);
+    int64_t granules = 0;
+    int32_t seg = 0;
+    if (tid < n_cseg) {
+        granules = (cseg_valid_end[tid] - table[tid].seg_start + DQ_GRANULE - 1) / DQ_GRANULE;
+        seg = cseg_seg[tid];
     }
-    if (tid == 0) carry = 0;
-    __syncthreads();
 
-    // exclusive scan of the tensors' level bytes, 256 tensors per round; thread tid reads back the
-    // width it wrote itself
-    for (int32_t base = 0; base < n_cseg; base += SB_THREADS) {
-        const int32_t c = base + tid;
-        int64_t mine = 0;
-        if (c < n_cseg) {
-            const int64_t len = cseg_valid_end[c] - table[c].seg_start;
-            mine = (len + DQ_GRANULE - 1) / DQ_GRANULE * (DQ_GRANULE / 8) * table[c].b;
-        }
-        scan[tid] = mine;
-        __syncthreads();
-        for (int off = 1; off < SB_THREADS; off <<= 1) {
-            const int64_t add = tid >= off ? scan[tid - off] : 0;
+    if (rule != 2) {
+        const int col = tid & (SEL_TILE - 1), row = tid / SEL_TILE;
+        float v[SEL_LOADS];
+        const auto fetch = [&](int32_t first) { // past the last worker or tensor: the last one's, which nothing adds
+            const int32_t l = first + col < n_seg ? first + col : n_seg - 1;
+#pragma unroll
+            for (int k = 0; k < SEL_LOADS; ++k) {
+                if (k * SEL_ROWS >= M) break; // the same for all
+                const int i = row + k * SEL_ROWS < M ? row + k * SEL_ROWS : M - 1;
+                v[k] = norms[i * n_seg + l];
+            }
+        };
+        fetch(0);
+        double acc = 0.0; // of worker `lane`, in the first wavefront
+        for (int32_t first = 0; first < n_seg; first += SEL_TILE) {
+#pragma unroll
+            for (int k = 0; k < SEL_LOADS; ++k) {
+                if (k * SEL_ROWS >= M) break;
+                stage[col * (DQ_MAX_WORKERS + 1) + row + k * SEL_ROWS] = static_cast<double>(v[k]) * static_cast<double>(v[k]);
+            }
             __syncthreads();
-            scan[tid] += add;
-            __syncthreads();
+            if (first + SEL_TILE < n_seg) fetch(first + SEL_TILE);
+            if (wave == 0) {
+                const int here = n_seg - first < SEL_TILE ? n_seg - first : SEL_TILE;
+                const double* mine = stage + lane;
+                const auto add_all = [&](auto linf) {
+                    const auto add = [&](double sq) { acc = decltype(linf)::value ? (sq > acc ? sq : acc) : acc + sq; };
+                    int l = 0;
+                    for (; l + 16 <= here; l += 16) { // sixteen reads in flight, then the additions in index order
+                        double sq[16];
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) sq[k] = mine[(l + k) * (DQ_MAX_WORKERS + 1)];
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) add(sq[k]);
+                    }
+                    for (; l < here; ++l) add(mine[l * (DQ_MAX_WORKERS + 1)]);
+                };
+                if (rule == 1)
+                    add_all(std::true_type{});
+                else
+                    add_all(std::false_type{});
+            }
+            __syncthreads(); // before the next tensors take the place of these
         }
-        if (c < n_cseg) table[c].level_start = carry + scan[tid] - mine;
-        __syncthreads();
-        if (tid == 0) carry += scan[SB_THREADS - 1];
-        __syncthreads();
+        if (wave == 0) {
+            const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(acc));
+            const int lo = static_cast<int>(static_cast<uint32_t>(bits)), hi = static_cast<int>(bits >> 32);
+            double sum_sq = 0.0;
+            for (int i = 0; i < M; ++i) {
+                const uint64_t own = static_cast<uint32_t>(__builtin_amdgcn_readlane(lo, i)) |
+                                     (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(hi, i))) << 32);
+                sum_sq += __longlong_as_double(static_cast<long long>(own));
+            }
+            const double gbar = sqrt(sum_sq / static_cast<double>(M));
+            if (lane == 0) {
+                lds_b[0] = smallest_width(factor * gbar, b_min, b_max);
+                if (gbar_out) gbar_out[0] = gbar;
+            }
+        }
+        seg = 0; // the one width
+    } else if (tid < n_seg) {
+        double acc = 0.0;
+        for (int i0 = 0; i0 < M; i0 += 16) { // sixteen loads in flight, then the additions in index order
+            float n[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) n[k] = norms[(i0 + k < M ? i0 + k : M - 1) * n_seg + tid];
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                if (i0 + k < M) acc += static_cast<double>(n[k]) * static_cast<double>(n[k]);
+        }
+        const double nbar = sqrt(acc / static_cast<double>(M));
+        if (gbar_out) gbar_out[tid] = nbar;
+        lds_b[tid] = smallest_width(factor * nbar, b_min, b_max);
     }
-    if (tid == 0 && packed_bytes_out) *packed_bytes_out = sign_bytes + carry;
+    __syncthreads();
+    if (b_out && tid < n_seg) b_out[tid] = lds_b[rule != 2 ? 0 : tid];
+    const int b = lds_b[seg];
+
+    // exclusive scan of the tensors' level bytes
+    const int64_t mine = granules * (DQ_GRANULE / 8) * b;
+    int64_t upto = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int64_t before = __shfl_up(static_cast<long long>(upto), off, 64);
+        upto += lane >= off ? before : 0;
+    }
+    if (lane == 63) wave_total[wave] = upto;
+    __syncthreads();
+    int64_t total = 0, start = 0;
+#pragma unroll
+    for (int k = 0; k < SEL_THREADS / 64; ++k) {
+        if (k == wave) start = total;
+        total += wave_total[k];
+    }
+    if (tid < n_cseg) {
+        table[tid].level_start = start + upto - mine;
+        table[tid].b = b;
+    }
+    if (tid == 0 && packed_bytes_out) *packed_bytes_out = sign_bytes + total;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -441,10 +492,16 @@ extern "C" int dq_select_bits_device(const dq_plan_t* plan, dq_widths_t* widths,
     const double root_T_eps = sqrt(static_cast<double>(T) / eps_hat_q);
     const double weight = pow(alpha, static_cast<double>(T - 1 - t) / 2.0);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (plan->n_seg <= 1024) {
-        hipLaunchKernelGGL(k_select_bits, dim3(1), dim3(SB_THREADS), 0, stream, norms_dev, M, plan->n_seg, plan->n_cseg,
-                           plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, rule, root_T_eps, weight, b_min,
-                           b_max, plan->padded_elems / 8, b_out_dev, gbar_out_dev, packed_bytes_out_dev);
+    if (plan->n_seg <= SEL_MANY) {
+#define DQ_LAUNCH_SEL(THREADS)                                                                                            \
+    hipLaunchKernelGGL((k_select_bits<THREADS>), dim3(1), dim3(THREADS), 0, stream, norms_dev, M, plan->n_seg, plan->n_cseg, \
+                       plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, rule, root_T_eps, weight, b_min, b_max, \
+                       plan->padded_elems / 8, b_out_dev, gbar_out_dev, packed_bytes_out_dev)
+        if (plan->n_seg <= SEL_FEW)
+            DQ_LAUNCH_SEL(SEL_FEW);
+        else
+            DQ_LAUNCH_SEL(SEL_MANY);
+#undef DQ_LAUNCH_SEL
     } else {
         const double factor = root_T_eps * weight;
         const int32_t widest = plan->n_seg > plan->n_cseg ? plan->n_seg : plan->n_cseg;

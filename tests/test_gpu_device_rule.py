@@ -71,6 +71,28 @@ def test_same_widths_as_the_host_rules_and_the_oracle(dq, oracle, n_seg):
     plan.close()
 
 
+@pytest.mark.parametrize("M", [1, 7, 17, 64])
+@pytest.mark.parametrize("n_seg", [63, 65, 256, 1024])
+def test_one_launch_rule_at_the_edges_of_its_stages(dq, oracle, n_seg, M):
+    """64 tensors are staged at a time, workers are read sixteen at a time, 256 and 1024 tensors are the most that
+    the two sizes of the launch take: widths, means (binary64, the same additions in the same order) and message sizes are equal."""
+    rng = np.random.default_rng(1000 * n_seg + M)
+    seg_len = [int(x) for x in rng.choice([0, 1, 129, 1000], size=n_seg, p=[0.05, 0.35, 0.3, 0.3])]
+    norms = (10 ** rng.uniform(-3, 0.5, size=(M, n_seg))).astype(np.float32)
+    plan = dq.Plan(seg_len)
+    table = dq.Widths(plan)
+    norms_dev = torch.from_numpy(norms).cuda()
+    T, t, alpha, eps = 100, 60, 0.99, 3e-2
+    for rule, host in (("single", oracle.select_bits), ("single_linf", oracle.select_bits_linf),
+                       ("per_tensor", oracle.select_bits_per_tensor)):
+        b_dev, g_dev, nbytes = _device_rule(dq, plan, table, norms_dev, t, T, eps, alpha, 1, 8, rule)
+        want_b, want_g = host(norms, t, T, eps, alpha, 1, 8)
+        assert np.all(b_dev == want_b) and np.all(g_dev == want_g)
+        assert nbytes == dq.packed_bytes_v(plan, np.broadcast_to(np.asarray(want_b, dtype=np.int32), n_seg))
+    table.close()
+    plan.close()
+
+
 @pytest.mark.parametrize("rule", ["single", "per_tensor"])
 def test_table_filled_on_the_device_drives_the_kernels(dq, oracle, rule):
     """norm -> rule on the device -> quantize+pack -> reduce, no host step in between; the
