@@ -1202,7 +1202,7 @@ constexpr bool ur_may_stream(int b) { return b >= 5 && b <= 7; }
 // it gains 1 to 100 %; beyond them it loses: M = 24 at 256 tiles b = 1 10 %, M = 64 at 384 b = 8 14 %, at 768 b = 1..8 3 to 19 %.
 inline int64_t ur_split_max_tiles(int b, int M)
 {
-    if (M > 56 && b == 5) return 600;            // 4.2 M ragged values, M = 64, with update 52.5 -> 45.8 us
+    if (M > 56 && b == 5) return 600;            // 4.2 M ragged values, M = 64, with update 52.5 -> 45.8 us (messages in the cache; fresh ones 56.2 -> 56.1)
     if (M > 56 && (b == 2 || b == 3)) return 400;
     if (M >= 40 && b >= 4 && b <= 7) return 256;
     if (M >= 32 && b >= 3) return 192;
