@@ -434,7 +434,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid, bool keep = false)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x, bool keep = false)
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -588,7 +588,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
     const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid, bool keep = false)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x, bool keep = false)
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
