@@ -568,9 +568,11 @@ __device__ __forceinline__ float ur_unit(float N, int b)
     return N >= DQ_MIN_NORM ? N / static_cast<float>((1 << b) - 1) * ur_unit_factor(b) : 0.0f;
 }
 
-__device__ __forceinline__ float ur_plain_unit(float N, int b) // without the width's factor
+// The unit of levels that are whole numbers: the products carry 1 / ur_sum_scale(b) as everywhere (a power of two), so that
+// a sum passes the largest value where the other kernels' sums do and not M times sooner.
+__device__ __forceinline__ float ur_level_unit(float N, int b)
 {
-    return N >= DQ_MIN_NORM ? N / static_cast<float>((1 << b) - 1) : 0.0f;
+    return N >= DQ_MIN_NORM ? N / static_cast<float>((1 << b) - 1) * (1.0f / ur_sum_scale(b)) : 0.0f;
 }
 
 // Worker w's value out of the one each lane holds (M <= 64).
@@ -751,8 +753,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
 
 // Few tiles and few workers: a lane owns 8 elements in place of 32, so that there are four times as many wavefronts, and
 // the loads of messages, model and norms are issued together behind one lookup (the chunk table's) where the elements
-// lie in one tensor.  The same additions in the same order as in k_unpack_dequant_reduce (whose products carry exact
-// powers of two that the epilogue takes out), bit for bit.
+// lie in one tensor.  The same products and the same additions in the same order as in k_unpack_dequant_reduce, bit for bit.
 // What bounds it: launch and two memory latencies.
 constexpr int UR_NARROW_PER_LANE = 8, UR_NARROW_WAVE = 64 * UR_NARROW_PER_LANE; // 512 elements, up to four tensors
 constexpr int UR_NARROW_SEGS = UR_NARROW_WAVE / DQ_GRANULE;
@@ -803,14 +804,14 @@ __global__ __launch_bounds__(UR_THREADS) void k_unpack_dequant_reduce_narrow(
         }
         if (w == 0) {
             if (owner.cseg >= 0) { // the same for the whole wavefront: one tensor, all of it data
-                if (lane < M) table[lane] = ur_plain_unit(norms[static_cast<int64_t>(lane) * n_seg + owner.seg], B);
+                if (lane < M) table[lane] = ur_level_unit(norms[static_cast<int64_t>(lane) * n_seg + owner.seg], B);
                 dq_wave_sync();
                 unit_ptr = table;
             } else {
                 span.first = granule_cseg[span.start >> 7];
                 span.last = granule_cseg[(span.start + span.n_lanes * UR_NARROW_PER_LANE - 1) >> 7];
                 unit_ptr = wave_table(span, lane, M, P0, granule_cseg, cseg_valid_end, table, n_valid, [&](int u, int32_t c) {
-                    return ur_plain_unit(norms[static_cast<int64_t>(u) * n_seg + cseg_seg[c]], B);
+                    return ur_level_unit(norms[static_cast<int64_t>(u) * n_seg + cseg_seg[c]], B);
                 });
             }
         }
@@ -842,7 +843,7 @@ __global__ __launch_bounds__(UR_THREADS) void k_unpack_dequant_reduce_narrow(
 #pragma unroll
     for (int k = 0; k < UR_NARROW_PER_LANE; ++k) {
         const float sum = M > UR_SUM_BLOCK ? total[k] + acc[k] : acc[k];
-        acc[k] = k < nv ? sum * inv_M : 0.0f;
+        acc[k] = k < nv ? sum * (inv_M * ur_sum_scale(B)) : 0.0f;
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {

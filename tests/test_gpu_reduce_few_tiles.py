@@ -41,3 +41,29 @@ def test_same_bits_as_the_widths_table_kernel(dq, layout, M):
         assert torch.equal(y.view(torch.int32), x.view(torch.int32)), b
         assert torch.equal(ghat.view(torch.int32), want.view(torch.int32)), b
     plan.close()
+
+
+@pytest.mark.parametrize("M", [2, 7, 8, 9, 24, 32, 40, 64])
+@pytest.mark.parametrize("seg_len", [[200, 0, 7, 129, 511], [4096 + 640], [TILE * 64 - 900, 640], [TILE * 100, 5, TILE * 28 - 128]])
+def test_sum_beyond_the_largest_value_with_a_finite_average(dq, seg_len, M):
+    """Every worker at the top level with one sign and a norm near the largest binary32 value: the sum over the workers
+    passes it, the average does not.  The same bits as the widths-table kernel, and N to the sum's rounding: at most
+    7 + ceil(M / 8) roundings of the sum, and three more (N / s, s products, 1 / M), of 2^-24 each."""
+    plan = dq.Plan(seg_len)
+    N = 3.0e38
+    norms = torch.full((M, len(seg_len)), N, device="cuda")
+    bound = (7 + -(-M // 8) + 3) * 2.0 ** -24
+    for b in range(1, 9):
+        packed = torch.full((M, plan.packed_bytes(b)), 255, dtype=torch.uint8, device="cuda")
+        packed[:, :plan.padded_elems // 8] = 0  # the signs
+        want, got = (torch.full((plan.padded_elems,), float("nan"), device="cuda") for _ in range(2))
+        table = dq.Widths(plan, [b] * len(seg_len))
+        dq.unpack_dequant_reduce_v(plan, table, packed, norms, want)
+        dq.unpack_dequant_reduce(plan, packed, norms, b, got)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
+        data = got[got != 0].double()
+        assert data.numel() == sum(seg_len) and torch.all((data / N - 1).abs() <= bound), b
+        x = torch.zeros_like(got)
+        dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.25, x)
+        assert torch.equal(x.view(torch.int32), (-0.25 * got + 0.0).view(torch.int32)), b
+    plan.close()
