@@ -116,6 +116,8 @@ __device__ __forceinline__ void quantize_random(const uint32_t quad0, const uint
 
 // The two quads' levels, four fields of b bits each in lv[h], from the clamped products and the random numbers.
 // The rounding mode is set and put back inside the one asm statement, so no other operation runs under it.
+// Results are marked as written early: without that an operand still to be read may be given the register of a result
+// that has the same value to begin with.
 // b <= 5: a quad's 20 bits fit the sum's 22; above, pairs are summed and joined.  b: the width, where B = 0.
 template <int B>
 __device__ __forceinline__ void quantize_levels(const float (&a)[8], const float (&t)[8], const int b, uint32_t (&lv)[2])
@@ -152,7 +154,7 @@ __device__ __forceinline__ void quantize_levels(const float (&a)[8], const float
             "v_add_f32 %3, %3, %0\n\t"
             "v_add_f32 %7, %7, %4\n\t"
             "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
-            : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]), "+v"(c[7])
+            : "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5]), "+&v"(c[6]), "+&v"(c[7])
             : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "s"(0x1p-24f),
               "s"(0x1.8p23f), "s"(pw), "v"(back));
         lv[0] = __float_as_uint(c[3]) - MAGIC;
@@ -181,7 +183,7 @@ __device__ __forceinline__ void quantize_levels(const float (&a)[8], const float
             "v_add_f32 %5, %5, %4\n\t"
             "v_add_f32 %7, %7, %6\n\t"
             "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
-            : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]), "+v"(c[7])
+            : "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5]), "+&v"(c[6]), "+&v"(c[7])
             : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "s"(0x1p-24f),
               "s"(0x1.8p23f), "v"(pw), "v"(back));
         // (hi << 2b) + lo, less what the two patterns carry
