@@ -110,18 +110,34 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
     }
 }
 
-// Whether the messages are stored without the streaming hint: they are read next, by the same GPU's reduce or by
-// whatever sends them, and a model of moderate size leaves them room in the 256 MB last-level cache.  Whole
-// iterations (norm, quantize, reduce with update), with the hint and without, in us: ResNet-18 shape, M = 8 b = 4 155.1 ->
-// 151.4, b = 6 160.3 -> 156.4, M = 35 b = 4 608.7 -> 591.1; 2^24 values, M = 16 b = 4 409.8 -> 396.1, b = 8 (302 MB of messages)
-// 453.1 -> 435.7; transformer shape, M = 16, one width per tensor 362.0 -> 350.9 (quantizing alone 170.8 -> 153.8).  Larger models
-// lose, with few bytes of messages too: 2^25 values, M = 16 b = 4 843.3 -> 857.5, 2^26, M = 4 b = 1 431.3 -> 453.5, M = 16 b = 4
-// 1687 -> 1922; and narrow widths gain or lose 2 % either way (ResNet-18 shape, M = 8 b = 2 145.1 -> 147.2).
-// bytes: of all messages, at most.
+// Whether the messages are stored without the streaming hint: they are read next, by the same GPU's reduce or by whatever
+// sends them, and a model of moderate size leaves them room in the 256 MB last-level cache.  What quantizing saves the
+// reduce pays back in part (transformer shape, M = 16, widths per worker: 180 -> 159 us against 55 -> 69), so whole iterations
+// decide: norm, quantize, reduce on gradients not seen before, 15500 of them drawn over 4096 to 2^24 values, M = 1..64, one
+// tensor and ragged ones, with and without update, with the hint and without it (time with / time without, on average).
+//   One width, b >= 3, by the messages' bytes: up to 1 MB +3 %, 2 to 4 MB +0.5 %, 4 to 16 MB -2 % (b = 5 to 8; b = 3 and 4 -1 to
+// +2 %), 16 to 20 MB +1.5 %, 24 to 300 MB +2 to 4.5 %, beyond 320 MB -3 %.  2^20 values, M = 16 b = 4 36.1 -> 38.8 us, 2^22, M = 2
+// b = 8 25.6 -> 27.3; 2^24, M = 8 b = 4 221.4 -> 211.8, ResNet-18 shape, M = 16 b = 6 304.6 -> 289.3.  From 12 M values on, where
+// one worker's messages are that small, they gain 1 to 4 % too.  (Why some megabytes lose and fewer do not is not known:
+// the XCDs' own caches hold 32 MB, and lines are in part written back there only when another XCD reads them.)
+// b = 1 and 2 gain or lose 2 to 5 % at either end and keep the hint.
+//   Widths tables (b = 1..8 alike, unknown here): six to eighteen million values of two or more workers -0.3 % shared, -1.1 %
+// per worker, a single worker's +2 %; outside +1 to 3.5 %.  Transformer shape, M = 16 345.8 -> 331.4, per worker 342.9 -> 328.5.
+//   Up to 18 M elements: one width at 21 to 24 M gains or loses 1 to 3 %, 2^25, M = 16 b = 4 810.8 -> 823.4, 2^26, M = 16 b = 4
+// 1687 -> 1922; with a widths table 21 M, M = 16 b = 6 582 -> 633.
 constexpr int64_t QP_KEEP_ELEMS = 18 << 20, QP_KEEP_BYTES = 320 << 20;
-inline bool qp_keep_messages(const dq_plan* plan, int b, int64_t bytes)
+constexpr int64_t QP_KEEP_NOT_FROM = 4 << 20, QP_KEEP_NOT_BELOW = 16 << 20, QP_KEEP_NOT_ELEMS = 12 << 20;
+inline bool qp_keep_messages(const dq_plan* plan, int M, int b)
 {
-    return b >= 3 && plan->padded_elems <= QP_KEEP_ELEMS && bytes <= QP_KEEP_BYTES;
+    const int64_t bytes = M * dq_packed_bytes(plan, b);
+    return b >= 3 && plan->padded_elems <= QP_KEEP_ELEMS && bytes <= QP_KEEP_BYTES &&
+           (bytes < QP_KEEP_NOT_FROM || bytes >= QP_KEEP_NOT_BELOW || plan->padded_elems >= QP_KEEP_NOT_ELEMS);
+}
+// The same where the widths may be known to the GPU only: eight bits everywhere is the most, six stand for the usual.
+inline bool qp_keep_messages_v(const dq_plan* plan, int M)
+{
+    return plan->padded_elems <= QP_KEEP_ELEMS && M * dq_packed_bytes(plan, 8) <= QP_KEEP_BYTES &&
+           (M == 1 || qp_keep_messages(plan, M, 6));
 }
 
 template <int B, int NORM>
@@ -132,7 +148,7 @@ int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M
     const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
-    const bool keep = NORM == 0 && qp_keep_messages(plan, B, M * dq_packed_bytes(plan, B));
+    const bool keep = NORM == 0 && qp_keep_messages(plan, M, B);
 #define DQ_LAUNCH_Q(WHOLE)                                                                                        \
     hipLaunchKernelGGL((k_quantize_pack<B, QP_TILES, NORM, WHOLE>), grid, block, 0, stream, grads, worker_stride, \
                        norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,          \
@@ -214,8 +230,7 @@ int quantize_v_entry(int norm_mode, const dq_plan_t* plan, const dq_widths_t* wi
     const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
-    // the widths may be known to the GPU only: eight bits everywhere is the most
-    const bool keep = norm_mode == 0 && qp_keep_messages(plan, 8, M * dq_packed_bytes(plan, 8));
+    const bool keep = norm_mode == 0 && qp_keep_messages_v(plan, M);
 #define DQ_LAUNCH_QV(NORM, WHOLE)                                                                                 \
     hipLaunchKernelGGL((k_quantize_pack_v<QP_TILES, NORM, WHOLE>), grid, block, 0, stream, grads_dev,             \
                        worker_stride_elems, norms_in, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,    \
