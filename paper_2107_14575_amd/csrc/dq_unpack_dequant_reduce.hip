@@ -659,8 +659,8 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
 // consecutive blocks of UR_SUM_BLOCK workers (one or two).  The block sums are then added in block order, wavefront after
 // wavefront through LDS -- the additions of k_unpack_dequant_reduce in the same order, bit for bit -- and the wavefronts
 // write a quarter of the span each.
-// What bounds the undivided kernel there is the vector ALU of a few SIMDs: 514 tiles are 2056 wavefronts on 1024
-// SIMDs, and one with three of them takes half as long again as the others with two.
+// What bounds the undivided kernel there is the vector ALU of a few SIMDs: 258 tiles are 1032 wavefronts on 1024 SIMDs, and
+// one with two of them takes twice as long as the others with one.
 constexpr int UR_SPLIT = UR_THREADS / 64;
 template <int B, bool UPDATE>
 __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_reduce_split(
@@ -1195,16 +1195,18 @@ constexpr size_t UR_LDS_THREE_PER_CU = 41 * 1024; // of 160 KiB
 constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20;
 constexpr bool ur_may_stream(int b) { return b >= 5 && b <= 7; }
 
-// Up to how many tiles the workers are divided over wavefronts (k_unpack_dequant_reduce_split), measured against the
-// undivided kernel for M = 12..64, 16..2048 tiles, all widths, with and without update.  Undivided, a tile is one
-// wavefront on each SIMD of a CU: 128 tiles leave half of the chip idle (M = 32 b = 1 15 %, b = 5 45 % gained; M = 64 33 and 65 %,
-// at 16 tiles 70 and 100 %), and between 128 and 600 those CUs last that have one tile more than the others.  What
-// the division costs (LDS, barriers, a row of units per wavefront) is most at b = 1, 2 and 8.  Inside the lines
-// it gains 1 to 100 %; beyond them it loses: M = 24 at 256 tiles b = 1 10 %, M = 64 at 384 b = 8 14 %, at 768 b = 1..8 3 to 19 %.
+// Up to how many tiles the workers are divided over wavefronts (k_unpack_dequant_reduce_split), measured with update against
+// the undivided kernel for M = 28..64, 64..600 tiles, all widths, messages in no cache and read before (time undivided / time
+// divided).  Undivided, a tile is one wavefront on each SIMD of a CU: 128 tiles leave half of the chip idle (M = 32 b = 1 +7 % and
+// +17, b = 5 +34 and +41; M = 64 +28 and +33, +52 and +60), and beyond 256 some CUs have two tiles and the others wait for them
+// (M = 64 at 256 and 258 tiles b = 5 33.0 and 41.0 us against 29.2 and 35.5).  What the division costs (LDS, barriers, a row of units per
+// wavefront) is most at b = 1, 4 and 8.  Inside the lines it gains up to 100 %.  Beyond them fresh messages lose, at some sizes all do:
+// M = 28 at 192 tiles b = 1 3 %, M = 32 at 256 b = 7 5 %, M = 48 at 258 b = 4 2 and b = 8 12 %; M = 60 at 361 and 400 b = 2, 3, 5 3 to 4 %
+// gained and 3 to 6 lost, M = 57 at 320 and 400 b = 6, 7 2 to 3 gained and 10 lost; at 514 and 600 b = 5 3 and 7 % lost (read before 9 and 2
+// gained), b = 4 16 and 18.
 inline int64_t ur_split_max_tiles(int b, int M)
 {
-    if (M > 56 && b == 5) return 600;            // 4.2 M ragged values, M = 64, with update 52.5 -> 45.8 us (messages in the cache; fresh ones 56.2 -> 56.1)
-    if (M > 56 && (b == 2 || b == 3)) return 400;
+    if (M > 56 && b != 1 && b != 4 && b != 8) return b <= 5 ? 380 : 320;
     if (M >= 40 && b >= 4 && b <= 7) return 256;
     if (M >= 32 && b >= 3) return 192;
     return M > 24 ? 128 : 0;

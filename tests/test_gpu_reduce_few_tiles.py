@@ -10,7 +10,7 @@ from tests.test_gpu_parity import dq  # noqa: F401  (fixture)
 pytestmark = pytest.mark.gpu
 
 TILE = 8192
-# elements: below a wavefront, ends inside a lane, a granule and a span, and on and beyond 64, 128, 192 and 256 tiles
+# elements: below a wavefront, ends inside a lane, a granule and a span, and on and beyond 64, 128 and 192 tiles, on 256
 LAYOUTS = [
     [1], [200, 0, 7, 129, 511], [4096], [512 * 3, 1, 2048 * 2 + 77], [300] * 40, [TILE * 64 - 900, 640], [TILE * 64 + 1],
     [TILE * 100, 5, TILE * 28 - 128], [TILE * 128 + 1], [TILE * 192 - 3], [TILE * 193], [TILE * 255, 130, 4000],
@@ -40,6 +40,30 @@ def test_same_bits_as_the_widths_table_kernel(dq, layout, M):
         dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.25, y, ghat=ghat)
         assert torch.equal(y.view(torch.int32), x.view(torch.int32)), b
         assert torch.equal(ghat.view(torch.int32), want.view(torch.int32)), b
+    plan.close()
+
+
+@pytest.mark.parametrize("M", [40, 57, 64])
+@pytest.mark.parametrize("seg_len", [[TILE * 256 + 1], [300, TILE * 299 + 4000], [TILE * 320 - 130], [TILE * 320 - 200, 77, 128],
+                                     [TILE * 380 - 5], [TILE * 380 + 1]])
+def test_same_bits_on_both_sides_of_the_farthest_lines(dq, seg_len, M):
+    """Beyond 256 tiles, on and beyond 320 and 380; 1199 spans, which the order of the workgroups does not divide."""
+    plan = dq.Plan(seg_len)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M)
+    norms = torch.rand((M, len(seg_len)), generator=gen, device="cuda") * 4 + 1e-3
+    x0 = torch.randn(plan.padded_elems, generator=gen, device="cuda")
+    for b in range(1, 9):
+        packed = torch.randint(0, 256, (M, plan.packed_bytes(b)), dtype=torch.uint8, device="cuda", generator=gen)
+        want, got = torch.full_like(x0, float("nan")), torch.full_like(x0, float("nan"))
+        table = dq.Widths(plan, [b] * len(seg_len))
+        dq.unpack_dequant_reduce_v(plan, table, packed, norms, want)
+        dq.unpack_dequant_reduce(plan, packed, norms, b, got)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
+        x, y = x0.clone(), x0.clone()
+        dq.unpack_dequant_reduce_update_v(plan, table, packed, norms, 0.25, x)
+        dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.25, y)
+        assert torch.equal(y.view(torch.int32), x.view(torch.int32)), b
     plan.close()
 
 
