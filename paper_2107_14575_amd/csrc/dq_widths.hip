@@ -39,12 +39,14 @@ __device__ __forceinline__ int smallest_width(double s_star, int b_min, int b_ma
 //
 // What bounds it: latency, of memory and of a worker's chain of additions.  A lane has one tensor, its table entry is
 // fetched beside the norms, and all loads of a sum are in flight ahead of it: rule 2 reads a tensor's sixteen workers at a
-// time, the others stage 64 tensors of all workers in LDS, so that 64 lanes add 64 workers' squares side by side.
+// time, the others stage 64 tensors of all workers in LDS, so that 64 lanes add 64 workers' squares side by side (up to twelve
+// tensors a lane reads its worker's norms itself, which of 64 workers takes 3.6 us, staged 13 tensors take 4.3).
 // Before, 256 lanes read the norms one by one where they added them, and the scan took sixteen barriers.  Per launch, one
 // after the other in a graph: one width for 62 tensors of 8 workers 7.9 -> 3.9 us, 102 of 16 12.0 -> 4.6, 400 of 64 43.9 ->
-// 11.3, 1024 of 64 105 -> 21; one width per tensor, 102 of 16 5.9 -> 3.0, 400 of 64 30.6 -> 6.2, 1024 of 64 59 -> 8.7.  A
-// single tensor's 3.1 became 3.4.  Up to 256 tensors a quarter of the lanes start sooner than 1024: one tensor of 16
-// workers 3.4 against 3.8 us, 102 per tensor 3.0 against 4.5.
+// 9.8, 1024 of 64 105 -> 19; one width per tensor, 102 of 16 5.9 -> 3.0, 400 of 64 30.6 -> 6.2, 1024 of 64 59 -> 8.7; a
+// single tensor of 16 and 64 workers 3.1 -> 2.7 and 3.5 -> 3.0.  (The workers' sums out of the lanes one by one, with a
+// lane number that changes, took 40 ns each: 64 workers of one tensor 5.2.)  Up to 256 tensors a quarter of the lanes start
+// sooner than 1024: one tensor of 16 workers 3.4 against 3.8 us, 102 per tensor 3.0 against 4.5.
 constexpr int SEL_FEW = 256, SEL_MANY = 1024; // lanes, and the most tensors each takes; plans of more take the kernels below
 static_assert(DQ_MAX_WORKERS == 64, "one lane of a wavefront per worker");
 
@@ -56,6 +58,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_bits(
     double* __restrict__ gbar_out, int64_t* __restrict__ packed_bytes_out)
 {
     constexpr int SEL_TILE = 64; // tensors staged at a time
+    constexpr int SEL_DIRECT = 12; // tensors up to which staging costs more than it saves
     constexpr int SEL_ROWS = SEL_THREADS / SEL_TILE, SEL_LOADS = DQ_MAX_WORKERS / SEL_ROWS;
     __shared__ double stage[SEL_TILE * (DQ_MAX_WORKERS + 1)]; // squares [tensor][worker]; the odd row keeps both ways off one bank
     __shared__ int lds_b[SEL_THREADS];
@@ -71,57 +74,75 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_bits(
     }
 
     if (rule != 2) {
-        const int col = tid & (SEL_TILE - 1), row = tid / SEL_TILE;
-        float v[SEL_LOADS];
-        const auto fetch = [&](int32_t first) { // past the last worker or tensor: the last one's, which nothing adds
-            const int32_t l = first + col < n_seg ? first + col : n_seg - 1;
-#pragma unroll
-            for (int k = 0; k < SEL_LOADS; ++k) {
-                if (k * SEL_ROWS >= M) break; // the same for all
-                const int i = row + k * SEL_ROWS < M ? row + k * SEL_ROWS : M - 1;
-                v[k] = norms[i * n_seg + l];
-            }
-        };
-        fetch(0);
         double acc = 0.0; // of worker `lane`, in the first wavefront
-        for (int32_t first = 0; first < n_seg; first += SEL_TILE) {
+        if (n_seg <= SEL_DIRECT) { // nothing to stage: a lane reads its worker's norms
+            if (tid < M) {
+                float v[SEL_DIRECT];
 #pragma unroll
-            for (int k = 0; k < SEL_LOADS; ++k) {
-                if (k * SEL_ROWS >= M) break;
-                stage[col * (DQ_MAX_WORKERS + 1) + row + k * SEL_ROWS] = static_cast<double>(v[k]) * static_cast<double>(v[k]);
+                for (int l = 0; l < SEL_DIRECT; ++l) v[l] = norms[tid * n_seg + (l < n_seg ? l : n_seg - 1)];
+#pragma unroll
+                for (int l = 0; l < SEL_DIRECT; ++l) {
+                    if (l >= n_seg) break;
+                    const double sq = static_cast<double>(v[l]) * static_cast<double>(v[l]);
+                    acc = rule == 1 ? (sq > acc ? sq : acc) : acc + sq;
+                }
             }
-            __syncthreads();
-            if (first + SEL_TILE < n_seg) fetch(first + SEL_TILE);
-            if (wave == 0) {
-                const int here = n_seg - first < SEL_TILE ? n_seg - first : SEL_TILE;
-                const double* mine = stage + lane;
-                const auto add_all = [&](auto linf) {
-                    const auto add = [&](double sq) { acc = decltype(linf)::value ? (sq > acc ? sq : acc) : acc + sq; };
-                    int l = 0;
-                    for (; l + 16 <= here; l += 16) { // sixteen reads in flight, then the additions in index order
-                        double sq[16];
+        } else {
+            const int col = tid & (SEL_TILE - 1), row = tid / SEL_TILE;
+            float v[SEL_LOADS];
+            const auto fetch = [&](int32_t first) { // past the last worker or tensor: the last one's, which nothing adds
+                const int32_t l = first + col < n_seg ? first + col : n_seg - 1;
 #pragma unroll
-                        for (int k = 0; k < 16; ++k) sq[k] = mine[(l + k) * (DQ_MAX_WORKERS + 1)];
+                for (int k = 0; k < SEL_LOADS; ++k) {
+                    if (k * SEL_ROWS >= M) break; // the same for all
+                    const int i = row + k * SEL_ROWS < M ? row + k * SEL_ROWS : M - 1;
+                    v[k] = norms[i * n_seg + l];
+                }
+            };
+            fetch(0);
+            for (int32_t first = 0; first < n_seg; first += SEL_TILE) {
 #pragma unroll
-                        for (int k = 0; k < 16; ++k) add(sq[k]);
-                    }
-                    for (; l < here; ++l) add(mine[l * (DQ_MAX_WORKERS + 1)]);
-                };
-                if (rule == 1)
-                    add_all(std::true_type{});
-                else
-                    add_all(std::false_type{});
+                for (int k = 0; k < SEL_LOADS; ++k) {
+                    if (k * SEL_ROWS >= M) break;
+                    stage[col * (DQ_MAX_WORKERS + 1) + row + k * SEL_ROWS] = static_cast<double>(v[k]) * static_cast<double>(v[k]);
+                }
+                __syncthreads();
+                if (first + SEL_TILE < n_seg) fetch(first + SEL_TILE);
+                if (wave == 0) {
+                    const int here = n_seg - first < SEL_TILE ? n_seg - first : SEL_TILE;
+                    const double* mine = stage + lane;
+                    const auto add_all = [&](auto linf) {
+                        const auto add = [&](double sq) { acc = decltype(linf)::value ? (sq > acc ? sq : acc) : acc + sq; };
+                        int l = 0;
+                        for (; l + 16 <= here; l += 16) { // sixteen reads in flight, then the additions in index order
+                            double sq[16];
+#pragma unroll
+                            for (int k = 0; k < 16; ++k) sq[k] = mine[(l + k) * (DQ_MAX_WORKERS + 1)];
+#pragma unroll
+                            for (int k = 0; k < 16; ++k) add(sq[k]);
+                        }
+                        for (; l < here; ++l) add(mine[l * (DQ_MAX_WORKERS + 1)]);
+                    };
+                    if (rule == 1)
+                        add_all(std::true_type{});
+                    else
+                        add_all(std::false_type{});
+                }
+                __syncthreads(); // before the next tensors take the place of these
             }
-            __syncthreads(); // before the next tensors take the place of these
         }
         if (wave == 0) {
-            const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(acc));
-            const int lo = static_cast<int>(static_cast<uint32_t>(bits)), hi = static_cast<int>(bits >> 32);
+            // the workers' sums in index order, eight reads in flight; past the last one zeros, which change no sum of squares
+            stage[lane] = lane < M ? acc : 0.0;
+            dq_wave_sync();
             double sum_sq = 0.0;
-            for (int i = 0; i < M; ++i) {
-                const uint64_t own = static_cast<uint32_t>(__builtin_amdgcn_readlane(lo, i)) |
-                                     (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(hi, i))) << 32);
-                sum_sq += __longlong_as_double(static_cast<long long>(own));
+#pragma unroll 1
+            for (int i0 = 0; i0 < M; i0 += 8) {
+                double sq[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sq[k] = stage[i0 + k];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sum_sq += sq[k];
             }
             const double gbar = sqrt(sum_sq / static_cast<double>(M));
             if (lane == 0) {

@@ -93,6 +93,29 @@ def test_one_launch_rule_at_the_edges_of_its_stages(dq, oracle, n_seg, M):
     plan.close()
 
 
+@pytest.mark.parametrize("M", [1, 8, 9, 33, 64])
+@pytest.mark.parametrize("n_seg", [1, 2, 11, 12, 13])
+def test_few_tensors_without_staging(dq, oracle, n_seg, M):
+    """Up to twelve tensors a lane reads its worker's norms itself; the workers' sums are added eight at a time.  The largest
+    norm belongs to the last tensor of the last worker, and one norm is zero."""
+    rng = np.random.default_rng(100 * n_seg + M)
+    seg_len = [int(x) for x in rng.choice([1, 129, 1000], size=n_seg)]
+    norms = (10 ** rng.uniform(-3, 0.5, size=(M, n_seg))).astype(np.float32)
+    norms[0, 0] = 0.0
+    norms[-1, -1] = 7.5
+    plan = dq.Plan(seg_len)
+    table = dq.Widths(plan)
+    norms_dev = torch.from_numpy(norms).cuda()
+    T, t, alpha, eps = 100, 60, 0.99, 3e-2
+    for rule, host in (("single", oracle.select_bits), ("single_linf", oracle.select_bits_linf)):
+        b_dev, g_dev, nbytes = _device_rule(dq, plan, table, norms_dev, t, T, eps, alpha, 1, 8, rule)
+        want_b, want_g = host(norms, t, T, eps, alpha, 1, 8)
+        assert np.all(b_dev == want_b) and np.all(g_dev == want_g)
+        assert nbytes == dq.packed_bytes_v(plan, np.broadcast_to(np.asarray(want_b, dtype=np.int32), n_seg))
+    table.close()
+    plan.close()
+
+
 @pytest.mark.parametrize("rule", ["single", "per_tensor"])
 def test_table_filled_on_the_device_drives_the_kernels(dq, oracle, rule):
     """norm -> rule on the device -> quantize+pack -> reduce, no host step in between; the
