@@ -14,24 +14,29 @@ constexpr int QP_WAVE_TILE = 64 * QP_PER_LANE;         // 512 elements: a wavefr
 // all of it) and of the chunk norms.
 constexpr int QP_TILES = DQ_CHUNK / QP_TILE;
 
-// Writes the low B bytes of v at dst (LDS, byte offset a multiple of B): pieces of 8, 4, 2 and 1 bytes, which LDS takes
-// at any byte address (the compiler checks that the target does).
+// Writes the low B bytes of v at dst (LDS, byte offset a multiple of B): even widths in pieces of 8, 4 and 2 bytes, which
+// LDS takes at any byte address (the compiler checks that the target does), odd ones byte by byte: their pieces would lie
+// at odd addresses, where a store takes longer than the bytes.  Pieces at odd widths against bytes, norms and messages in one
+// pass, 16.8 M values in buckets of 512, M = 8: b = 3 126.6 -> 120.1 us, b = 7 134.3 -> 128.6; bracketed b = 5 168.4 -> 159.3; 64
+// buckets, M = 2, b = 3 3.98 -> 3.76.  At b = 6 4 + 2 bytes against 2 + 2 + 2 124.2 against 126.6.
 template <int B>
 __device__ __forceinline__ void stage_bytes(uint8_t* dst, uint64_t v)
 {
-    if constexpr ((B & 8) != 0) {
+    if constexpr (B % 2 != 0) {
+#pragma unroll
+        for (int k = 0; k < B; ++k) dst[k] = static_cast<uint8_t>(v >> (8 * k));
+    } else if constexpr (B == 8) {
         __builtin_memcpy(dst, &v, 8);
-        return;
+    } else {
+        if constexpr ((B & 4) != 0) {
+            const uint32_t piece = static_cast<uint32_t>(v);
+            __builtin_memcpy(dst, &piece, 4);
+        }
+        if constexpr ((B & 2) != 0) {
+            const uint16_t piece = static_cast<uint16_t>(v >> (8 * (B & 4)));
+            __builtin_memcpy(dst + (B & 4), &piece, 2);
+        }
     }
-    if constexpr ((B & 4) != 0) {
-        const uint32_t piece = static_cast<uint32_t>(v);
-        __builtin_memcpy(dst, &piece, 4);
-    }
-    if constexpr ((B & 2) != 0) {
-        const uint16_t piece = static_cast<uint16_t>(v >> (8 * (B & 4)));
-        __builtin_memcpy(dst + (B & 4), &piece, 2);
-    }
-    if constexpr ((B & 1) != 0) dst[B - 1] = static_cast<uint8_t>(v >> (8 * (B - 1)));
 }
 
 // The same for a width that is a value.
