@@ -354,12 +354,11 @@ __device__ __forceinline__ uint32_t qp_granule(uint32_t tid, int it, uint32_t n_
     return (e < n_elems ? e : n_elems - QP_PER_LANE) >> 7;
 }
 
-// One 16-byte piece of a message.  KEEP: it may stay in the caches (keep, the same for the whole launch, decides);
-// otherwise it carries the streaming hint.
+// One 16-byte piece of a message.  KEEP: it may stay in the caches; otherwise it carries the streaming hint.
 template <bool KEEP>
-__device__ __forceinline__ void qp_store_piece(uint4* dst, const uint4& v, bool keep)
+__device__ __forceinline__ void qp_store_piece(uint4* dst, const uint4& v)
 {
-    if (KEEP && keep)
+    if constexpr (KEEP)
         *dst = v;
     else
         dq_store_stream(dst, v);
@@ -367,25 +366,23 @@ __device__ __forceinline__ void qp_store_piece(uint4* dst, const uint4& v, bool 
 
 // A wavefront's staged bytes [0, bytes) (a multiple of 16) leave as 16-byte stores.
 template <bool KEEP = false>
-__device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t lane,
-                                              bool keep = false)
+__device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t lane)
 {
     uint4* d = reinterpret_cast<uint4*>(dst);
     const uint4* f = reinterpret_cast<const uint4*>(src);
-    for (uint32_t i = lane; i < bytes / 16; i += 64) qp_store_piece<KEEP>(d + i, f[i], keep);
+    for (uint32_t i = lane; i < bytes / 16; i += 64) qp_store_piece<KEEP>(d + i, f[i]);
 }
 
 // The workgroup's staged bytes [0, bytes) (a multiple of 16), after a barrier.  The lanes are counted from the start of
 // the cache line that holds the first byte, so that no line is shared by two store instructions.
 template <bool KEEP = false>
-__device__ __forceinline__ void qp_store_block(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t tid,
-                                               bool keep = false)
+__device__ __forceinline__ void qp_store_block(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t tid)
 {
     uint4* d = reinterpret_cast<uint4*>(dst);
     const uint4* f = reinterpret_cast<const uint4*>(src);
     const uint32_t skew = (static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst)) & 127u) >> 4;
     for (uint32_t i = tid; i < bytes / 16 + skew; i += QP_THREADS)
-        if (i >= skew) qp_store_piece<KEEP>(d + (i - skew), f[i - skew], keep);
+        if (i >= skew) qp_store_piece<KEEP>(d + (i - skew), f[i - skew]);
 }
 
 // Whether a chunk's two stretches of the message start on cache lines; each wavefront's part then does too (its tiles
@@ -399,22 +396,22 @@ __device__ __forceinline__ bool qp_on_lines(const uint8_t* sign, const uint8_t* 
 }
 
 // The chunk's staged bytes leave: by wavefronts (each after its own staging) or together (see qp_on_lines).
-// n_elems: the chunk's elements; sign and level: where its stretches start; b: its width; keep: see qp_store_piece.
+// n_elems: the chunk's elements; sign and level: where its stretches start; b: its width.
 template <bool KEEP = false>
 __device__ __forceinline__ void qp_store_chunk(uint8_t* sign, uint8_t* level, const uint8_t* lds_sign, const uint8_t* lds_level,
-                                               uint32_t n_elems, uint32_t wave0, uint32_t b, uint32_t tid, bool keep = false)
+                                               uint32_t n_elems, uint32_t wave0, uint32_t b, uint32_t tid)
 {
     if (qp_on_lines(sign, level)) {
         dq_wave_sync();
         if (wave0 < n_elems) {
             const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * QP_TILES ? n_elems - wave0 : QP_WAVE_TILE * QP_TILES;
-            qp_store_wave<KEEP>(sign + (wave0 >> 3), lds_sign + (wave0 >> 3), n_wave >> 3, tid & 63u, keep);
-            qp_store_wave<KEEP>(level + (wave0 >> 3) * b, lds_level + (wave0 >> 3) * b, (n_wave >> 3) * b, tid & 63u, keep);
+            qp_store_wave<KEEP>(sign + (wave0 >> 3), lds_sign + (wave0 >> 3), n_wave >> 3, tid & 63u);
+            qp_store_wave<KEEP>(level + (wave0 >> 3) * b, lds_level + (wave0 >> 3) * b, (n_wave >> 3) * b, tid & 63u);
         }
     } else {
         __syncthreads();
-        qp_store_block<KEEP>(sign, lds_sign, n_elems >> 3, tid, keep);
-        qp_store_block<KEEP>(level, lds_level, (n_elems >> 3) * b, tid, keep);
+        qp_store_block<KEEP>(sign, lds_sign, n_elems >> 3, tid);
+        qp_store_block<KEEP>(level, lds_level, (n_elems >> 3) * b, tid);
     }
 }
 
@@ -430,18 +427,18 @@ __device__ __forceinline__ void qp_store_chunk(uint8_t* sign, uint8_t* level, co
 // values in tensors of 128, M = 8 b = 4 38.0 -> 36.6, 16.8 M in tensors of 512, M = 8 b = 6 121.8 -> 114.8 and, with a
 // widths table, b = 7 130.9 -> 122.4; 30.7 M in tensors of 1000, M = 4 b = 6 112.0 -> 104.5.
 //
-// keep: with NORM = 0, whether the message's stores go without the streaming hint (qp_keep_messages).
+// KEEP: the message's stores go without the streaming hint (qp_keep_messages).
 // tid: threadIdx.x, or qp_tid_in_loop() where a workgroup takes several chunks.
 // NORM = 0: the norms are an input.  NORM = 1 (l2) or 2 (max): chunk-local plans only; the kernel
 // computes the norms of its chunk's tensors itself, writes them to norms_out and quantizes from
 // the registers it already holds -- one read of the gradient instead of two.
-template <int B, int TILES, int NORM, bool WHOLE = true>
+template <int B, int TILES, int NORM, bool WHOLE = true, bool KEEP = false>
 __device__ __forceinline__ void quantize_pack_chunk(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x, bool keep = false)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x)
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -491,8 +488,8 @@ __device__ __forceinline__ void quantize_pack_chunk(
                 lds_sign[at] = static_cast<uint8_t>(sign);
                 stage_bytes<B>(&lds_level[at * B], level);
             }
-            qp_store_chunk<NORM == 0>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_sign, lds_level, CHUNK, wave0,
-                           B, tid, keep);
+            qp_store_chunk<KEEP>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_sign, lds_level, CHUNK, wave0,
+                           B, tid);
             return;
         }
     }
@@ -572,14 +569,14 @@ __device__ __forceinline__ void quantize_pack_chunk(
     }
     if constexpr (BLOCK) {
         __syncthreads();
-        qp_store_block<NORM == 0>(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid, keep);
-        qp_store_block<NORM == 0>(msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_level, (n_elems >> 3) * B, tid, keep);
+        qp_store_block<KEEP>(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid);
+        qp_store_block<KEEP>(msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_level, (n_elems >> 3) * B, tid);
         return;
     }
     // 16-byte stores; every plane of a wavefront's stretch is a whole number of 16-byte pieces because it holds a
     // multiple of 128 elements
-    qp_store_chunk<NORM == 0>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_sign, lds_level, n_elems, wave0,
-                              B, tid, keep);
+    qp_store_chunk<KEEP>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_sign, lds_level, n_elems, wave0,
+                              B, tid);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -588,14 +585,14 @@ __device__ __forceinline__ void quantize_pack_chunk(
 // still one contiguous stretch of the message (every segment's stretch is a whole number of
 // 16-byte pieces per granule), so they are staged and stored the same way.
 // ---------------------------------------------------------------------------------------------
-template <int TILES, int NORM, bool WHOLE = true> // as in quantize_pack_chunk
+template <int TILES, int NORM, bool WHOLE = true, bool KEEP = false> // as in quantize_pack_chunk
 __device__ __forceinline__ void quantize_pack_chunk_v(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
     const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x, bool keep = false)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x)
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -649,8 +646,8 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
                 lds_sign[at] = static_cast<uint8_t>(sign);
                 stage_bytes_v(&lds_level[at * e.b], level, e.b);
             }
-            qp_store_chunk<NORM == 0>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + e.level_start + ((chunk0 - e.seg_start) >> 3) * e.b,
-                           lds_sign, lds_level, CHUNK, wave0, e.b, tid, keep);
+            qp_store_chunk<KEEP>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + e.level_start + ((chunk0 - e.seg_start) >> 3) * e.b,
+                           lds_sign, lds_level, CHUNK, wave0, e.b, tid);
             return;
         }
     }
@@ -738,9 +735,9 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
     }
     __syncthreads();
     const int last = seg_last - seg_first;
-    qp_store_block<NORM == 0>(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid, keep);
-    qp_store_block<NORM == 0>(msg + (padded_elems >> 3) + chunk_level0, lds_level,
-                              static_cast<uint32_t>(lds_level_base[last]) + (n_elems >> 3) * lds_b[last], tid, keep);
+    qp_store_block<KEEP>(msg + (chunk0 >> 3), lds_sign, n_elems >> 3, tid);
+    qp_store_block<KEEP>(msg + (padded_elems >> 3) + chunk_level0, lds_level,
+                              static_cast<uint32_t>(lds_level_base[last]) + (n_elems >> 3) * lds_b[last], tid);
 }
 
 } // namespace

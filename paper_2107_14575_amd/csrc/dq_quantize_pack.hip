@@ -18,21 +18,21 @@
 
 namespace {
 
-template <int B, int TILES, int NORM, bool WHOLE>
+template <int B, int TILES, int NORM, bool WHOLE, bool KEEP>
 __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
     int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, bool keep)
+    int64_t packed_stride, float* __restrict__ norms_out)
 {
-    quantize_pack_chunk<B, TILES, NORM, WHOLE>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
-                                        padded_elems, key0, key1, step, worker_base, packed, packed_stride, norms_out,
-                                        blockIdx.x, threadIdx.x, keep);
+    quantize_pack_chunk<B, TILES, NORM, WHOLE, KEEP>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg,
+                                                     cseg_valid_end, padded_elems, key0, key1, step, worker_base, packed,
+                                                     packed_stride, norms_out, blockIdx.x);
 }
 
-template <int TILES, int NORM, bool WHOLE> // as in k_quantize_pack
+template <int TILES, int NORM, bool WHOLE, bool KEEP> // as in k_quantize_pack
 __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
@@ -40,11 +40,11 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
     const dq_cseg_width* __restrict__ widths_table,
     int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, bool keep)
+    int64_t packed_stride, float* __restrict__ norms_out)
 {
-    quantize_pack_chunk_v<TILES, NORM, WHOLE>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
-                                       widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
-                                       packed, packed_stride, norms_out, blockIdx.x, threadIdx.x, keep);
+    quantize_pack_chunk_v<TILES, NORM, WHOLE, KEEP>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg,
+                                                    cseg_valid_end, widths_table, widths_worker_stride, padded_elems, key0,
+                                                    key1, step, worker_base, packed, packed_stride, norms_out, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -125,12 +125,13 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
 // per worker, a single worker's +2 %; outside +1 to 3.5 %.  Transformer shape, M = 16 345.8 -> 331.4, per worker 342.9 -> 328.5.
 //   Up to 18 M elements: one width at 21 to 24 M gains or loses 1 to 3 %, 2^25, M = 16 b = 4 810.8 -> 823.4, 2^26, M = 16 b = 4
 // 1687 -> 1922; with a widths table 21 M, M = 16 b = 6 582 -> 633.
+constexpr int QP_KEEP_WIDTH = 3;
 constexpr int64_t QP_KEEP_ELEMS = 18 << 20, QP_KEEP_BYTES = 320 << 20;
 constexpr int64_t QP_KEEP_NOT_FROM = 4 << 20, QP_KEEP_NOT_BELOW = 16 << 20, QP_KEEP_NOT_ELEMS = 12 << 20;
 inline bool qp_keep_messages(const dq_plan* plan, int M, int b)
 {
     const int64_t bytes = M * dq_packed_bytes(plan, b);
-    return b >= 3 && plan->padded_elems <= QP_KEEP_ELEMS && bytes <= QP_KEEP_BYTES &&
+    return b >= QP_KEEP_WIDTH && plan->padded_elems <= QP_KEEP_ELEMS && bytes <= QP_KEEP_BYTES &&
            (bytes < QP_KEEP_NOT_FROM || bytes >= QP_KEEP_NOT_BELOW || plan->padded_elems >= QP_KEEP_NOT_ELEMS);
 }
 // The same where the widths may be known to the GPU only: eight bits everywhere is the most, six stand for the usual.
@@ -148,16 +149,24 @@ int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M
     const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
-    const bool keep = NORM == 0 && qp_keep_messages(plan, M, B);
-#define DQ_LAUNCH_Q(WHOLE)                                                                                        \
-    hipLaunchKernelGGL((k_quantize_pack<B, QP_TILES, NORM, WHOLE>), grid, block, 0, stream, grads, worker_stride, \
-                       norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,          \
-                       plan->d_cseg_valid_end, plan->padded_elems, static_cast<uint32_t>(seed),                   \
-                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out, keep)
-    if (NORM != 0 || plan->many_whole)
-        DQ_LAUNCH_Q(true);
-    else
-        DQ_LAUNCH_Q(NORM != 0); // false; a kernel that works out the norms has the one form only
+#define DQ_LAUNCH_Q(WHOLE, KEEP)                                                                                        \
+    hipLaunchKernelGGL((k_quantize_pack<B, QP_TILES, NORM, WHOLE, KEEP>), grid, block, 0, stream, grads, worker_stride, \
+                       norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,                \
+                       plan->d_cseg_valid_end, plan->padded_elems, static_cast<uint32_t>(seed),                         \
+                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out)
+    if constexpr (NORM != 0) { // a kernel that works out the norms has the one form only
+        DQ_LAUNCH_Q(true, false);
+    } else {
+        const bool keep = qp_keep_messages(plan, M, B);
+        if (plan->many_whole && keep)
+            DQ_LAUNCH_Q(true, B >= QP_KEEP_WIDTH);
+        else if (plan->many_whole)
+            DQ_LAUNCH_Q(true, false);
+        else if (keep)
+            DQ_LAUNCH_Q(false, B >= QP_KEEP_WIDTH);
+        else
+            DQ_LAUNCH_Q(false, false);
+    }
 #undef DQ_LAUNCH_Q
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
@@ -230,21 +239,25 @@ int quantize_v_entry(int norm_mode, const dq_plan_t* plan, const dq_widths_t* wi
     const int64_t n_chunks = (plan->padded_elems + DQ_CHUNK - 1) / DQ_CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(n_chunks), M), block(QP_THREADS);
-    const bool keep = norm_mode == 0 && qp_keep_messages_v(plan, M);
-#define DQ_LAUNCH_QV(NORM, WHOLE)                                                                                 \
-    hipLaunchKernelGGL((k_quantize_pack_v<QP_TILES, NORM, WHOLE>), grid, block, 0, stream, grads_dev,             \
+    const bool keep = qp_keep_messages_v(plan, M);
+#define DQ_LAUNCH_QV(NORM, WHOLE, KEEP)                                                                           \
+    hipLaunchKernelGGL((k_quantize_pack_v<QP_TILES, NORM, WHOLE, KEEP>), grid, block, 0, stream, grads_dev,       \
                        worker_stride_elems, norms_in, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg,    \
                        plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, row_stride, plan->padded_elems, \
                        static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), step, worker_base,         \
-                       packed_dev, packed_worker_stride_bytes, norms_out, keep)
-    if (norm_mode == 0 && plan->many_whole)
-        DQ_LAUNCH_QV(0, true);
-    else if (norm_mode == 0)
-        DQ_LAUNCH_QV(0, false);
-    else if (norm_mode == 1)
-        DQ_LAUNCH_QV(1, true);
+                       packed_dev, packed_worker_stride_bytes, norms_out)
+    if (norm_mode == 1)
+        DQ_LAUNCH_QV(1, true, false);
+    else if (norm_mode == 2)
+        DQ_LAUNCH_QV(2, true, false);
+    else if (plan->many_whole && keep)
+        DQ_LAUNCH_QV(0, true, true);
+    else if (plan->many_whole)
+        DQ_LAUNCH_QV(0, true, false);
+    else if (keep)
+        DQ_LAUNCH_QV(0, false, true);
     else
-        DQ_LAUNCH_QV(2, true);
+        DQ_LAUNCH_QV(0, false, false);
 #undef DQ_LAUNCH_QV
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
