@@ -73,3 +73,94 @@ def test_levels_at_the_edges_of_the_rounding(dq, oracle, layout):
                         a, z = np.asarray(a), np.asarray(z)
                         assert np.array_equal(a[~odd[w]], z[~odd[w]]), (b, above, table is None, w)
     plan.close()
+
+
+def _edge_values(oracle, plan, seg_len, M, b, share, rng):
+    """Values whose a (for a norm of s = 2^b - 1) is an edge of the rounding for `share` of them and uniform elsewhere.
+    Every tensor's first value is s, so that s is its max norm; pads are NaN.  Some products of the others pass s for a
+    norm one step below."""
+    dp, s, inf = plan.padded_elems, np.float32((1 << b) - 1), np.float32(np.inf)
+    u = _random(oracle, dp, M)
+    whole = rng.integers(0, int(s) + 1, size=(M, dp)).astype(np.float32)
+    on = (whole + u).astype(np.float32)
+    kinds = [whole, on, np.nextafter(on, inf), np.nextafter(on, np.float32(0)), u, np.nextafter(u, np.float32(0)),
+             np.nextafter(whole, np.float32(0)), np.full_like(u, 1e-45), np.zeros_like(u), np.full_like(u, s)]
+    edges = np.choose(rng.integers(0, len(kinds), size=(M, dp)), kinds)
+    g = np.where(rng.random((M, dp)) < share, edges, rng.random((M, dp)) * s).astype(np.float32)
+    g = np.minimum(g, s) * rng.choice(np.array([-1, 1], dtype=np.float32), size=(M, dp))
+    pad = np.ones(dp, dtype=bool)
+    start = 0
+    for n in seg_len:
+        if n:
+            g[:, start] = s
+        pad[start:start + n] = False
+        start += -(-n // 128) * 128
+    g[:, pad] = np.nan
+    return g, s
+
+
+# tensors of two granules; a chunk of one tensor, then tensors that share one: all inside their chunks
+LOCAL = [[256] * 19, [4096, 77, 0, 500, 1, 129, 3000]]
+
+
+@pytest.mark.parametrize("layout", range(len(LOCAL)))
+def test_kernels_that_compute_the_norms_themselves(dq, oracle, layout):
+    seg_len, M = LOCAL[layout], 2
+    plan = dq.Plan(seg_len)
+    rng = np.random.default_rng(10 + layout)
+    want_norm = np.array([0 if n == 0 else 1 for n in seg_len], dtype=np.float32)
+    for b in range(1, 9):
+        g, s = _edge_values(oracle, plan, seg_len, M, b, 0.9, rng)
+        gd = torch.from_numpy(g).cuda()
+        want = oracle.quantize_pack(seg_len, g, np.tile(want_norm * s, (M, 1)), b, SEED, STEP)
+        for table in (None, dq.Widths(plan, [b] * len(seg_len))):
+            norms = torch.full((M, len(seg_len)), float("nan"), device="cuda")
+            packed = torch.zeros((M, plan.packed_bytes(b)), dtype=torch.uint8, device="cuda")
+            if table is None:
+                dq.norm_quantize_pack(plan, gd, b, SEED, STEP, norms, packed, linf=True)
+            else:
+                dq.norm_quantize_pack_v(plan, table, gd, SEED, STEP, norms, packed, linf=True)
+            assert np.array_equal(norms.cpu().numpy(), np.tile(want_norm * s, (M, 1)))
+            assert np.array_equal(packed.cpu().numpy(), want), (b, table is None)
+    plan.close()
+
+
+# chunks inside a tensor that goes on beyond them, its tail with others, and a chunk of several
+CROSSING = [[2 * 4096 + 640], [300, 2 * 4096, 500, 129, 5000]]
+
+
+@pytest.mark.parametrize("share", [0.9, 0.008])
+@pytest.mark.parametrize("layout", range(len(CROSSING)))
+def test_both_looks_of_the_bracketed_kernels(dq, oracle, layout, share):
+    """Brackets of one step to either side of the norm, so that the elements left open are those on an edge: more than a
+    chunk can record (quantized again), or about thirty a chunk (recorded and settled); and a bracket that is the norm."""
+    seg_len, M = CROSSING[layout], 2
+    plan = dq.Plan(seg_len)
+    rng = np.random.default_rng(20 + layout)
+    ws = torch.empty(dq.bracketed_workspace_bytes(plan, M), dtype=torch.uint8, device="cuda")
+    for b in range(1, 9):
+        g, s = _edge_values(oracle, plan, seg_len, M, b, share, rng)
+        gd = torch.from_numpy(g).cuda()
+        norm = np.full((M, len(seg_len)), s, dtype=np.float32)
+        want = oracle.quantize_pack(seg_len, g, norm, b, SEED, STEP)
+        for exact in (False, True):
+            lo = norm if exact else np.nextafter(norm, np.float32(0))
+            hi = norm if exact else np.nextafter(norm, np.float32(np.inf))
+            lo, hi = torch.from_numpy(lo.copy()).cuda(), torch.from_numpy(hi.copy()).cuda()
+            for table in (None, dq.Widths(plan, [b] * len(seg_len))):
+                norms = torch.full((M, len(seg_len)), float("nan"), device="cuda")
+                packed = torch.zeros((M, plan.packed_bytes(b)), dtype=torch.uint8, device="cuda")
+                stats = torch.zeros(2, dtype=torch.int64, device="cuda")
+                if table is None:
+                    dq.norm_quantize_pack_bracketed(plan, gd, lo, hi, b, SEED, STEP, norms, packed, ws, stats=stats, linf=True)
+                else:
+                    dq.norm_quantize_pack_bracketed_v(plan, table, gd, lo, hi, SEED, STEP, norms, packed, ws, stats=stats,
+                                                      linf=True)
+                assert np.array_equal(norms.cpu().numpy(), norm)
+                assert np.array_equal(packed.cpu().numpy(), want), (b, exact, table is None)
+                settled, redone = (int(v) for v in stats.cpu())
+                if exact:
+                    assert settled == 0 and redone == 0
+                else:
+                    assert (redone > 0) if share > 0.5 else (settled > 0 and redone == 0)
+    plan.close()
