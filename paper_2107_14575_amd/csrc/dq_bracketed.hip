@@ -79,8 +79,10 @@ __device__ __forceinline__ void record_open(uint32_t open, const float4 x, const
 // A chunk that lies in one tensor which goes on beyond it -- nearly every chunk of a gradient of large
 // tensors: one bracket for all of it (two scalar loads and two divisions), nothing to mask.  The squares
 // are added from the values as they were loaded, the lanes quantize the two quads they loaded and the
-// codes change places, and no wavefront waits for another: row totals and counts meet in LDS, and the
-// wavefront that finishes last (a ticket in LDS) writes the chunk's partial sum and block header.
+// codes change places.  Row totals and counts meet in LDS, and the wavefront that finishes last (a ticket in
+// LDS) writes the chunk's partial sum and block header: no wavefront waits for another where the chunk's bytes of the
+// message start on cache lines; elsewhere there is one barrier ahead of their stores (qp_store_chunk), so all of the
+// workgroup has to come here.
 // What bounds it: the vector ALU.  Measured against the general route below for every chunk: a lagged
 // iteration of 2^26 values, 16 workers, b = 4 from the widths table 1172 -> 1081 us, of the ResNet-18 shape,
 // 8 workers, b = 3 141 -> 132 us.

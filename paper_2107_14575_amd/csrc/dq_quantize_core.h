@@ -69,8 +69,9 @@ __device__ __forceinline__ void stage_bytes_v(uint8_t* dst, uint64_t v, int b)
 // addition (a quad's first needs no fma), sign; with minimum (and the canonicalising maximum ahead of it), v_fract, two
 // conversions, compare, add with carry and shift they were 12.5, and 8.5 in a form for wavefronts whose products are all
 // below 1.  Fma and addition also issue twice as fast as those (2.4 against 4.3 cycles by themselves, less of a
-// difference in a mixture).  Norms and messages in one pass, 16.8 M values in buckets of 512, M = 8: b = 4 137 -> 120 us,
-// b = 8 141 -> 123, b = 2 (products below 1) 125 -> 120.
+// difference in a mixture).  Norms and messages in one pass, 16.8 M values in buckets of 512, M = 8, no input in a cache: b = 2
+// (products below 1) 122.5 -> 117.6 us, b = 3 128.8 -> 120.1, b = 4 138.1 -> 118.9, b = 7 144.8 -> 128.6, b = 8 140.8 -> 121.6.
+// The smallest calls pay for it at b = 1 and 2: one chunk, norms given, 2.3 -> 2.4 us.
 // ---------------------------------------------------------------------------------------------
 
 // s|g|/N of the lane's eight elements, one rounding each, and what the wavefront can conclude from the largest:
@@ -395,7 +396,8 @@ __device__ __forceinline__ bool qp_on_lines(const uint8_t* sign, const uint8_t* 
     return ((reinterpret_cast<uintptr_t>(sign) | reinterpret_cast<uintptr_t>(level)) & 127u) == 0;
 }
 
-// The chunk's staged bytes leave: by wavefronts (each after its own staging) or together (see qp_on_lines).
+// The chunk's staged bytes leave: by wavefronts (each after its own staging) or together after a barrier (see qp_on_lines),
+// so all of the workgroup has to come here.
 // n_elems: the chunk's elements; sign and level: where its stretches start; b: its width.
 template <bool KEEP = false>
 __device__ __forceinline__ void qp_store_chunk(uint8_t* sign, uint8_t* level, const uint8_t* lds_sign, const uint8_t* lds_level,
@@ -416,7 +418,7 @@ __device__ __forceinline__ void qp_store_chunk(uint8_t* sign, uint8_t* level, co
 }
 
 // What bounds it: the memory system's rate at 4 bytes read to (B+1)/8 written (about 6.1-6.2 TB/s, what a
-// kernel with the same accesses and no arithmetic reaches), with the vector ALU at 80 % beside it.  A chunk
+// kernel with the same accesses and no arithmetic reaches), with the vector ALU at 89 % beside it (b = 4).  A chunk
 // that lies in one tensor (nearly all of a gradient of large tensors) takes the first route: two scalar
 // loads and one division per wavefront in place of the granule table, LDS and a barrier, and the codes
 // change places between the lanes instead of the values.  Measured at D = 2^28, M = 16 against the table
@@ -729,7 +731,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
             }
             lds_sign[e >> 3] = static_cast<uint8_t>(sign);
             // b bytes at an offset that is a multiple of b past a 16-byte boundary (every tensor's
-            // stretch of a chunk starts on one), so the naturally aligned stores of stage_bytes apply
+            // stretch of a chunk starts on one); stage_bytes takes any
             stage_bytes_v(&lds_level[lds_level_base[local] + static_cast<int32_t>(e >> 3) * b], level, b);
         }
     }
