@@ -169,6 +169,32 @@ __device__ __forceinline__ void dq_store_stream(float4* dst, const float4& v)
     const dq_v4f t = { v.x, v.y, v.z, v.w };
     __builtin_nontemporal_store(t, reinterpret_cast<dq_v4f*>(dst));
 }
+// A buffer over `bytes` bytes at an address that is the same for the whole wavefront.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t dq_bytes_buffer(const void* at, uint32_t bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(at);
+    const uint64_t uniform = (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32)))) << 32) |
+                             static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a)));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform), 0, static_cast<int>(bytes), 0x00020000);
+}
+// Stores of data that passes through once carry the streaming hint (STREAM); otherwise they go through the XCD's own cache
+// to the last-level one, where the next kernel finds the data.  A plain store leaves its line dirty in the XCD's cache instead; the
+// next kernel then waits for up to 32 MB of such lines to be written back, or fetches them from another XCD one by one.
+// Past the buffer's end nothing is stored, and loads give zero.
+template <bool STREAM>
+__device__ __forceinline__ void dq_store_buffer(const __amdgpu_buffer_rsrc_t buffer, uint32_t byte, const uint4& v)
+{
+    constexpr int NON_TEMPORAL = 2, DEVICE_SCOPE = 16; // nt, sc1
+    const dq_v4u t = { v.x, v.y, v.z, v.w };
+    __builtin_amdgcn_raw_buffer_store_b128(t, buffer, static_cast<int>(byte), 0, STREAM ? NON_TEMPORAL : DEVICE_SCOPE);
+}
+template <bool STREAM>
+__device__ __forceinline__ float4 dq_load_buffer(const __amdgpu_buffer_rsrc_t buffer, uint32_t byte)
+{
+    constexpr int NON_TEMPORAL = 2;
+    const dq_v4u t = __builtin_amdgcn_raw_buffer_load_b128(buffer, static_cast<int>(byte), 0, STREAM ? NON_TEMPORAL : 0);
+    return make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
+}
 __device__ __forceinline__ float4 dq_load_stream(const float4* src)
 {
     const dq_v4f t = __builtin_nontemporal_load(reinterpret_cast<const dq_v4f*>(src));
@@ -217,18 +243,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t dq_elems_buffer(const float* g
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g), 0, static_cast<int>(n_elems * 4u), 0x00020000);
 }
-__device__ __forceinline__ float4 dq_load_stream(const __amdgpu_buffer_rsrc_t buffer, uint32_t byte)
-{
-    constexpr int STREAM = 2; // the non-temporal bit
-    const dq_v4u t = __builtin_amdgcn_raw_buffer_load_b128(buffer, static_cast<int>(byte), 0, STREAM);
-    return make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
-}
 __device__ __forceinline__ void dq_load_wave_tile(const __amdgpu_buffer_rsrc_t buffer, uint32_t base, uint32_t lane,
                                                   float4& lo, float4& hi)
 {
     const uint32_t at = (base + (lane & 31u) * 8u + (lane >> 5) * 4u) * 4u;
-    lo = dq_load_stream(buffer, at);
-    hi = dq_load_stream(buffer, at + 1024u);
+    lo = dq_load_buffer<true>(buffer, at);
+    hi = dq_load_buffer<true>(buffer, at + 1024u);
 }
 __device__ __forceinline__ void dq_swap_halves(float& a, float& b)
 {

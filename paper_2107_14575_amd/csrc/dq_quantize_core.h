@@ -355,23 +355,19 @@ __device__ __forceinline__ uint32_t qp_granule(uint32_t tid, int it, uint32_t n_
     return (e < n_elems ? e : n_elems - QP_PER_LANE) >> 7;
 }
 
-// One 16-byte piece of a message.  KEEP: it may stay in the caches; otherwise it carries the streaming hint.
-template <bool KEEP>
-__device__ __forceinline__ void qp_store_piece(uint4* dst, const uint4& v)
-{
-    if constexpr (KEEP)
-        *dst = v;
-    else
-        dq_store_stream(dst, v);
-}
-
-// A wavefront's staged bytes [0, bytes) (a multiple of 16) leave as 16-byte stores.
+// A wavefront's staged bytes [0, bytes) (a multiple of 16) leave as 16-byte stores; dst is the same for the whole wavefront.
+// KEEP: through to the last-level cache (dq_store_buffer); otherwise with the streaming hint.
 template <bool KEEP = false>
 __device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t lane)
 {
-    uint4* d = reinterpret_cast<uint4*>(dst);
     const uint4* f = reinterpret_cast<const uint4*>(src);
-    for (uint32_t i = lane; i < bytes / 16; i += 64) qp_store_piece<KEEP>(d + i, f[i]);
+    if constexpr (KEEP) {
+        const __amdgpu_buffer_rsrc_t buffer = dq_bytes_buffer(dst, bytes);
+        for (uint32_t i = lane; i < bytes / 16; i += 64) dq_store_buffer<false>(buffer, i * 16u, f[i]);
+    } else {
+        uint4* d = reinterpret_cast<uint4*>(dst);
+        for (uint32_t i = lane; i < bytes / 16; i += 64) dq_store_stream(d + i, f[i]);
+    }
 }
 
 // The workgroup's staged bytes [0, bytes) (a multiple of 16), after a barrier.  The lanes are counted from the start of
@@ -379,11 +375,17 @@ __device__ __forceinline__ void qp_store_wave(uint8_t* __restrict__ dst, const u
 template <bool KEEP = false>
 __device__ __forceinline__ void qp_store_block(uint8_t* __restrict__ dst, const uint8_t* src, uint32_t bytes, uint32_t tid)
 {
-    uint4* d = reinterpret_cast<uint4*>(dst);
     const uint4* f = reinterpret_cast<const uint4*>(src);
     const uint32_t skew = (static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst)) & 127u) >> 4;
-    for (uint32_t i = tid; i < bytes / 16 + skew; i += QP_THREADS)
-        if (i >= skew) qp_store_piece<KEEP>(d + (i - skew), f[i - skew]);
+    if constexpr (KEEP) {
+        const __amdgpu_buffer_rsrc_t buffer = dq_bytes_buffer(dst, bytes);
+        for (uint32_t i = tid; i < bytes / 16 + skew; i += QP_THREADS)
+            if (i >= skew) dq_store_buffer<false>(buffer, (i - skew) * 16u, f[i - skew]);
+    } else {
+        uint4* d = reinterpret_cast<uint4*>(dst);
+        for (uint32_t i = tid; i < bytes / 16 + skew; i += QP_THREADS)
+            if (i >= skew) dq_store_stream(d + (i - skew), f[i - skew]);
+    }
 }
 
 // Whether a chunk's two stretches of the message start on cache lines; each wavefront's part then does too (its tiles
@@ -429,7 +431,7 @@ __device__ __forceinline__ void qp_store_chunk(uint8_t* sign, uint8_t* level, co
 // values in tensors of 128, M = 8 b = 4 38.0 -> 36.6, 16.8 M in tensors of 512, M = 8 b = 6 121.8 -> 114.8 and, with a
 // widths table, b = 7 130.9 -> 122.4; 30.7 M in tensors of 1000, M = 4 b = 6 112.0 -> 104.5.
 //
-// KEEP: the message's stores go without the streaming hint (qp_keep_messages).
+// KEEP: the message's stores go through to the last-level cache (qp_keep_messages).
 // tid: threadIdx.x, or qp_tid_in_loop() where a workgroup takes several chunks.
 // NORM = 0: the norms are an input.  NORM = 1 (l2) or 2 (max): chunk-local plans only; the kernel
 // computes the norms of its chunk's tensors itself, writes them to norms_out and quantizes from

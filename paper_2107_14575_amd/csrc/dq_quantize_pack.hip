@@ -110,36 +110,22 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
     }
 }
 
-// Whether the messages are stored without the streaming hint: they are read next, by the same GPU's reduce or by whatever
-// sends them, and a model of moderate size leaves them room in the 256 MB last-level cache.  What quantizing saves the
-// reduce pays back in part (transformer shape, M = 16, widths per worker: 180 -> 159 us against 55 -> 69), so whole iterations
-// decide: norm, quantize, reduce on gradients not seen before, 15500 of them drawn over 4096 to 2^24 values, M = 1..64, one
-// tensor and ragged ones, with and without update, with the hint and without it (time with / time without, on average).
-//   One width, b >= 3, by the messages' bytes: up to 1 MB +3 %, 2 to 4 MB +0.5 %, 4 to 16 MB -2 % (b = 5 to 8; b = 3 and 4 -1 to
-// +2 %), 16 to 20 MB +1.5 %, 24 to 300 MB +2 to 4.5 %, beyond 320 MB -3 %.  2^20 values, M = 16 b = 4 36.1 -> 38.8 us, 2^22, M = 2
-// b = 8 25.6 -> 27.3; 2^24, M = 8 b = 4 221.4 -> 211.8, ResNet-18 shape, M = 16 b = 6 304.6 -> 289.3.  From 12 M values on, where
-// one worker's messages are that small, they gain 1 to 4 % too.  (Why some megabytes lose and fewer do not is not known:
-// the XCDs' own caches hold 32 MB, and lines are in part written back there only when another XCD reads them.)
-// b = 1 and 2 gain or lose 2 to 5 % at either end and keep the hint.
-//   Widths tables (b = 1..8 alike, unknown here): six to eighteen million values of two or more workers -0.3 % shared, -1.1 %
-// per worker, a single worker's +2 %; outside +1 to 3.5 %.  Transformer shape, M = 16 345.8 -> 331.4, per worker 342.9 -> 328.5.
-//   Up to 18 M elements: one width at 21 to 24 M gains or loses 1 to 3 %, 2^25, M = 16 b = 4 810.8 -> 823.4, 2^26, M = 16 b = 4
-// 1687 -> 1922; with a widths table 21 M, M = 16 b = 6 582 -> 633.
-constexpr int QP_KEEP_WIDTH = 3;
-constexpr int64_t QP_KEEP_ELEMS = 18 << 20, QP_KEEP_BYTES = 320 << 20;
-constexpr int64_t QP_KEEP_NOT_FROM = 4 << 20, QP_KEEP_NOT_BELOW = 16 << 20, QP_KEEP_NOT_ELEMS = 12 << 20;
+// Whether the messages go through to the last-level cache (dq_store_buffer) and not past it with the streaming hint: they are
+// read next, by the same GPU's reduce or by whatever sends them.  Whole iterations decide (norm, quantize, reduce on gradients
+// not seen before), 390 of them drawn over 2^17 to 2^28 values, M = 1..64, one tensor and ragged ones, all widths; time against the
+// hint: 0.92 to 1.0 up to 400 MB of messages whatever their number (2^24 values, M = 8 b = 2, 5, 8 0.955, 0.950, 0.971; 2^25, M = 2 b = 5
+// 0.925; transformer shape, M = 24 with update b = 7 0.966), still 0.97 to 0.98 at 400 to 670 MB for b <= 4; beyond that most of them
+// are gone from the 256 MB before they are read and the stores cost 1 to 5 % (2^28, M = 16 b = 4 6400 -> 6490 us).  Plain stores, which
+// leave the lines dirty in the XCDs' caches, were 1 to 2 % slower than this at the sizes where they gain, and lose at others.
+// With M > 32 and b >= 5, where the reduce reads them as if they came from memory, 144 to 280 MB gain 0 to 2 % and 360 to 400 lose 2 to 4.
+// Narrow calls of 4 to 13 MB gain or lose up to 2 %.
 inline bool qp_keep_messages(const dq_plan* plan, int M, int b)
 {
-    const int64_t bytes = M * dq_packed_bytes(plan, b);
-    return b >= QP_KEEP_WIDTH && plan->padded_elems <= QP_KEEP_ELEMS && bytes <= QP_KEEP_BYTES &&
-           (bytes < QP_KEEP_NOT_FROM || bytes >= QP_KEEP_NOT_BELOW || plan->padded_elems >= QP_KEEP_NOT_ELEMS);
+    const int64_t megabytes = b <= 4 ? 640 : M <= 32 ? 400 : 280;
+    return M * dq_packed_bytes(plan, b) <= megabytes << 20;
 }
-// The same where the widths may be known to the GPU only: eight bits everywhere is the most, six stand for the usual.
-inline bool qp_keep_messages_v(const dq_plan* plan, int M)
-{
-    return plan->padded_elems <= QP_KEEP_ELEMS && M * dq_packed_bytes(plan, 8) <= QP_KEEP_BYTES &&
-           (M == 1 || qp_keep_messages(plan, M, 6));
-}
+// Widths that may be known to the GPU only: six bits stand for the usual.
+inline bool qp_keep_messages_v(const dq_plan* plan, int M) { return qp_keep_messages(plan, M, 6); }
 
 template <int B, int NORM>
 int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M, const float* norms,
@@ -159,11 +145,11 @@ int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M
     } else {
         const bool keep = qp_keep_messages(plan, M, B);
         if (plan->many_whole && keep)
-            DQ_LAUNCH_Q(true, B >= QP_KEEP_WIDTH);
+            DQ_LAUNCH_Q(true, true);
         else if (plan->many_whole)
             DQ_LAUNCH_Q(true, false);
         else if (keep)
-            DQ_LAUNCH_Q(false, B >= QP_KEEP_WIDTH);
+            DQ_LAUNCH_Q(false, true);
         else
             DQ_LAUNCH_Q(false, false);
     }

@@ -287,9 +287,7 @@ struct block_total {
 // A lane's B level dwords of one worker, by the widest loads their size allows (a global load needs no
 // more than dword alignment).  Where one load takes them all (b <= 4), the lanes' loads cover whole cache lines
 // and the streaming hint pays at the largest sizes.  Where a line is met by several loads (5 to 7) it has to
-// stay when messages are all that is read: with the hint b = 7 took 236 instead of 226 us at D = 2^26, M = 16 and
-// 36.7 instead of 32.5 us on 11 M elements, M = 8.  With the model update it is the other way round (STREAM; see
-// UR_LAST_LEVEL_CACHE).
+// stay unless they are many (STREAM; see ur_stream): with the hint b = 7 took 36.7 instead of 32.5 us on 11 M elements, M = 8.
 typedef uint32_t ur_v4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t ur_v3u __attribute__((ext_vector_type(3), aligned(4)));
 typedef uint32_t ur_v2u __attribute__((ext_vector_type(2), aligned(4)));
@@ -453,10 +451,38 @@ __device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign
         prepare, unit, acc, slots);
 }
 
+// The model's elements [first, first + n) of a wavefront (first is the same for all its lanes), by their index from `first`.
+// What lies past the layout's end is read as zero and not written.
+// ONCE: it passes through with the streaming hint; otherwise it is left in the last-level cache for the next iteration.
+template <bool ONCE>
+struct ur_model {
+    __amdgpu_buffer_rsrc_t buffer;
+    ur_model() = default;
+    __device__ __forceinline__ ur_model(float* x, int64_t first, int n, int64_t padded_elems)
+        : buffer(dq_bytes_buffer(x + first, static_cast<uint32_t>(padded_elems - first < n ? padded_elems - first : n) * 4u))
+    {
+    }
+    __device__ __forceinline__ float4 load(int at) const { return dq_load_buffer<ONCE>(buffer, at * 4u); }
+    __device__ __forceinline__ void store(int at, const float4& v) const
+    {
+        dq_store_buffer<ONCE>(buffer, at * 4u, make_uint4(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)));
+    }
+};
+
+// x - eta * g_hat (pads: g_hat is +0, x unchanged)
+__device__ __forceinline__ float4 ur_step(float4 x, const float4& g, float eta)
+{
+    x.x = __builtin_fmaf(-eta, g.x, x.x);
+    x.y = __builtin_fmaf(-eta, g.y, x.y);
+    x.z = __builtin_fmaf(-eta, g.z, x.z);
+    x.w = __builtin_fmaf(-eta, g.w, x.w);
+    return x;
+}
+
 // Scales a lane's sums by 1/M (zero beyond the tensor's end), transposes the wavefront's 2048 elements
 // (from padded index wave0 on) through LDS and writes them out; with UPDATE it also applies the model update to x (and then
 // `out` may be null).
-template <bool UPDATE>
+template <bool UPDATE, bool ONCE = false>
 __device__ __forceinline__ void finish_tile(float (&acc)[UR_PER_LANE], bool active, int64_t n_valid, float inv_M,
                                             float4* lds_out, int tid, int64_t wave0, int64_t padded_elems,
                                             float* __restrict__ out, float* __restrict__ x, float eta)
@@ -468,15 +494,14 @@ __device__ __forceinline__ void finish_tile(float (&acc)[UR_PER_LANE], bool acti
     }
     // lane t of wave v holds elements [v*2048 + 32t, +32): slot (t, q) -> t*8 + (q ^ (t & 7))
     const int wave = tid >> 6, lane = tid & 63;
-    // the model's pieces, all eight in flight before the first is used (each load behind its own bounds
-    // check and the store before it cost a memory latency apiece); past the end: the last ones again
+    // the model's pieces, all eight in flight before the first is used (each load behind the store before it cost a
+    // memory latency apiece)
     float4 xv[8];
+    ur_model<ONCE> model;
     if constexpr (UPDATE) {
+        model = ur_model<ONCE>(x, wave0, UR_WAVE_ELEMS, padded_elems);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t P = wave0 + 256 * j + 4 * lane;
-            xv[j] = *reinterpret_cast<const float4*>(x + (P < padded_elems ? P : padded_elems - 4));
-        }
+        for (int j = 0; j < 8; ++j) xv[j] = model.load(256 * j + 4 * lane);
     }
     float4* wave_out = lds_out + wave * 512;
 #pragma unroll
@@ -504,23 +529,11 @@ __device__ __forceinline__ void finish_tile(float (&acc)[UR_PER_LANE], bool acti
         float4 v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = piece(j);
-        auto update = [&](int j) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
             const int64_t P = wave0 + 256 * j + 4 * lane;
-            if (out) dq_store_stream(reinterpret_cast<float4*>(out + P), v[j]);
-            float4 t = xv[j];
-            t.x = __builtin_fmaf(-eta, v[j].x, t.x);
-            t.y = __builtin_fmaf(-eta, v[j].y, t.y);
-            t.z = __builtin_fmaf(-eta, v[j].z, t.z);
-            t.w = __builtin_fmaf(-eta, v[j].w, t.w);
-            *reinterpret_cast<float4*>(x + P) = t;
-        };
-        if (wave0 + UR_WAVE_ELEMS <= padded_elems) { // the same for the whole wavefront
-#pragma unroll
-            for (int j = 0; j < 8; ++j) update(j);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (wave0 + 256 * j + 4 * lane < padded_elems) update(j);
+            if (out && P < padded_elems) dq_store_stream(reinterpret_cast<float4*>(out + P), v[j]);
+            model.store(256 * j + 4 * lane, ur_step(xv[j], v[j], eta));
         }
     }
 }
@@ -607,7 +620,8 @@ __device__ __forceinline__ const float* wave_table(const wave_span& span, int la
     return table + (c - first) * M;
 }
 
-template <int B, bool UPDATE, bool STREAM = false> // STREAM: the hint on level loads that would not have it
+// STREAM: the streaming hint on level loads that would not have it; ONCE: on the model (ur_stream, ur_model_once)
+template <int B, bool UPDATE, bool STREAM, bool ONCE>
 __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_reduce(
     const uint8_t* __restrict__ packed, int64_t packed_stride, int M, const float* __restrict__ norms,
     int32_t n_seg, const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
@@ -652,7 +666,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
             if constexpr (!ur_table_first(B)) make_table();
         },
         [&](int w) { return unit_ptr[w]; }, span.n_lanes, acc, slots_of(lds_out, tid));
-    finish_tile<UPDATE>(acc, active, n_valid, inv_M * ur_sum_scale(B), lds_out, tid, span.start, padded_elems, out, x, eta);
+    finish_tile<UPDATE, ONCE>(acc, active, n_valid, inv_M * ur_sum_scale(B), lds_out, tid, span.start, padded_elems, out, x, eta);
 }
 
 // Few tiles and many workers: the workgroup's four wavefronts share the 2048 elements of a span, each with `per_wave`
@@ -681,11 +695,12 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
     const int last = (M - 1) / (per_wave * UR_SUM_BLOCK); // the last wavefront with workers
 
     const auto piece_at = [&](int j) { return span.start + 256 * (wave * PIECES + j) + 4 * lane; };
-    float4 xv[PIECES]; // the model's pieces, in flight from the start; past the end: the last ones again
+    float4 xv[PIECES]; // the model's pieces, in flight from the start
+    ur_model<false> model;
     if constexpr (UPDATE) {
+        model = ur_model<false>(x, span.start, UR_WAVE_ELEMS, padded_elems);
 #pragma unroll
-        for (int j = 0; j < PIECES; ++j)
-            xv[j] = *reinterpret_cast<const float4*>(x + (piece_at(j) < padded_elems ? piece_at(j) : padded_elems - 4));
+        for (int j = 0; j < PIECES; ++j) xv[j] = model.load(256 * (wave * PIECES + j) + 4 * lane);
     }
 
     float acc[UR_PER_LANE];
@@ -740,14 +755,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
         const int src = 8 * (wave * PIECES + j) + (lane >> 3), q = lane & 7;
         const float4 v = sum[src * 8 + (q ^ (src & 7))];
         if (!UPDATE || out) dq_store_stream(reinterpret_cast<float4*>(out + P), v);
-        if constexpr (UPDATE) { // pads: the sum is +0, x unchanged
-            float4 t = xv[j];
-            t.x = __builtin_fmaf(-eta, v.x, t.x);
-            t.y = __builtin_fmaf(-eta, v.y, t.y);
-            t.z = __builtin_fmaf(-eta, v.z, t.z);
-            t.w = __builtin_fmaf(-eta, v.w, t.w);
-            *reinterpret_cast<float4*>(x + P) = t;
-        }
+        if constexpr (UPDATE) model.store(256 * (wave * PIECES + j) + 4 * lane, ur_step(xv[j], v, eta));
     }
 }
 
@@ -776,10 +784,11 @@ __global__ __launch_bounds__(UR_THREADS) void k_unpack_dequant_reduce_narrow(
     const int64_t P0 = span.start + lane * UR_NARROW_PER_LANE;
     const uint32_t own = lane < span.n_lanes ? lane : span.n_lanes - 1; // lanes past the end fetch the last one's bytes
     float4 xv[2];
+    ur_model<false> model;
     if constexpr (UPDATE) {
-        const float4* xp = reinterpret_cast<const float4*>(x + span.start) + own * 2u;
-        xv[0] = xp[0];
-        xv[1] = xp[1];
+        model = ur_model<false>(x, span.start, UR_NARROW_WAVE, padded_elems);
+        xv[0] = model.load(own * UR_NARROW_PER_LANE);
+        xv[1] = model.load(own * UR_NARROW_PER_LANE + 4);
     }
 
     const uint8_t* sign_wave = packed + (span.start >> 3);
@@ -849,21 +858,14 @@ __global__ __launch_bounds__(UR_THREADS) void k_unpack_dequant_reduce_narrow(
     for (int h = 0; h < 2; ++h) {
         const float4 v = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
         if (!UPDATE || out) *reinterpret_cast<float4*>(out + P0 + 4 * h) = v;
-        if constexpr (UPDATE) {
-            float4 t = xv[h];
-            t.x = __builtin_fmaf(-eta, v.x, t.x);
-            t.y = __builtin_fmaf(-eta, v.y, t.y);
-            t.z = __builtin_fmaf(-eta, v.z, t.z);
-            t.w = __builtin_fmaf(-eta, v.w, t.w);
-            *reinterpret_cast<float4*>(x + P0 + 4 * h) = t;
-        }
+        if constexpr (UPDATE) model.store(lane * UR_NARROW_PER_LANE + 4 * h, ur_step(xv[h], v, eta));
     }
 }
 
 // Per-tensor widths: a wavefront inside one tensor takes its b and the place of its level dwords from the
 // widths table (scalar) and runs the accumulation specialised for that b.  Elsewhere each lane does: its
 // 32 elements lie in one 128-element granule, hence in one segment.
-template <bool UPDATE>
+template <bool UPDATE, bool STREAM, bool ONCE> // as in k_unpack_dequant_reduce
 __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_reduce_v(
     const uint8_t* __restrict__ packed, int64_t packed_stride, int M, const float* __restrict__ norms,
     int32_t n_seg, const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
@@ -894,7 +896,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
         const float unit = lane < M ? ur_unit(norms[static_cast<int64_t>(lane) * n_seg + seg], b) : 0.0f;
         const uint8_t* level_wave = level_plane + e.level_start + ((span.start - e.seg_start) >> 3) * b;
         dq_with_width(b, [&](auto width) {
-            accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value), false>(
+            accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value), STREAM>(
                 packed + (span.start >> 3), [&](int w) { return level_wave + static_cast<int64_t>(w) * packed_stride; },
                 packed_stride, M, [] {}, [&](int w) { return lane_value(unit, w); }, span.n_lanes, acc, slots_of(lds_out, tid));
         });
@@ -921,7 +923,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
             });
         }
     }
-    finish_tile<UPDATE>(acc, active, n_valid, inv_M * ur_sum_scale(b), lds_out, tid, span.start, padded_elems, out, x, eta);
+    finish_tile<UPDATE, ONCE>(acc, active, n_valid, inv_M * ur_sum_scale(b), lds_out, tid, span.start, padded_elems, out, x, eta);
 }
 
 // Per-worker widths: every worker's message has its own layout.  Workers' gradients of one tensor are alike,
@@ -935,7 +937,7 @@ struct worker_entry { // what a lane needs to decode one worker's tensor: 16 byt
     int64_t level_base; // level-plane byte offset of padded index P is level_base + (P >> 3) * b
 };
 
-template <bool UPDATE>
+template <bool UPDATE, bool STREAM, bool ONCE> // as in k_unpack_dequant_reduce
 __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_reduce_w(
     const uint8_t* __restrict__ packed, int64_t packed_stride, int M, const float* __restrict__ norms,
     int32_t n_seg, int32_t n_cseg, const int32_t* __restrict__ granule_cseg, const int32_t* __restrict__ cseg_seg,
@@ -969,7 +971,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
             const uint32_t at_lo = static_cast<uint32_t>(at), at_hi = static_cast<uint32_t>(static_cast<uint64_t>(at) >> 32);
             const float unit = ur_unit(N, b);
             dq_with_width(b, [&](auto width) {
-                accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value), false>(
+                accumulate_wave<decltype(width)::value, ur_group(decltype(width)::value), STREAM>(
                     packed + (span.start >> 3),
                     [&](int w) {
                         const uint64_t off = (static_cast<uint64_t>(__builtin_amdgcn_readlane(at_hi, w)) << 32) |
@@ -982,7 +984,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
             // and the general one paid: widths mixed, 4.2 M ragged elements, M = 64 152 us before there were two routes,
             // 206 joined, 137 now; one width in buckets of 512, M = 8, b = 2 33, 42, 31; this route, ResNet-18 shape, M = 8, b = 4
             // 24.0 joined, 21.2 now.
-            finish_tile<UPDATE>(acc, active, n_valid, inv_M * ur_sum_scale(b), lds_out, tid, span.start, padded_elems, out, x, eta);
+            finish_tile<UPDATE, ONCE>(acc, active, n_valid, inv_M * ur_sum_scale(b), lds_out, tid, span.start, padded_elems, out, x, eta);
             return;
         }
     }
@@ -1038,7 +1040,7 @@ __global__ __launch_bounds__(UR_THREADS, UR_MIN_WAVES) void k_unpack_dequant_red
         }
         total.finish(acc);
     }
-    finish_tile<UPDATE>(acc, active, n_valid, inv_M * UR_FP16_SCALE, lds_out, tid, span.start, padded_elems, out, x, eta);
+    finish_tile<UPDATE, ONCE>(acc, active, n_valid, inv_M * UR_FP16_SCALE, lds_out, tid, span.start, padded_elems, out, x, eta);
 }
 
 // acc[k] += sgn_k * scale for a lane's 32 elements: the scale with its sign flipped where the bit is set.
@@ -1184,16 +1186,38 @@ __global__ __launch_bounds__(UR_THREADS) void k_sign_reduce_count(
 
 constexpr size_t UR_LDS_THREE_PER_CU = 41 * 1024; // of 160 KiB
 
-// With the model update, messages and model that do not fit the last-level cache together: the level loads of
-// widths 5 to 7 carry the streaming hint too, so that the messages do not push the model out.  Measured without
-// and with it, in us (inputs in no cache): 2^26 elements, M = 8 b = 6 183 -> 153, M = 16 b = 5 244 -> 214, M = 32 b = 7 499 -> 488;
-// 2^24, M = 16 b = 7 80 -> 68 (all of them 3 to 12 % above what they took when every load had the hint, and below it
-// now).  Smaller inputs that were just written are still in the cache, as in an iteration that simulates all workers,
-// and are better off without: 12.5 M elements, M = 16 b = 6 42.6 -> 48.4, ResNet-18 shape, M = 8 28.8 -> 30.1; from
-// elsewhere they would gain (54.0 -> 48.9, 34.0 -> 31.4).  Beyond 32 workers (three workgroups per CU, the vector ALU as
-// much as the loads) it gives nothing: 4.2 M ragged elements, M = 64 b = 5 55.6 -> 62.0.
+// Whether the level loads of widths 5 to 7 carry the streaming hint although several of them meet a cache line: with the
+// update, where messages and model together are more than half of the last-level cache, so that the messages do not push the model
+// out.  Measured over 1 to 270 M values, M = 1..31: the reduce alone, messages from memory, 16.8 M, M = 16 b = 5 65 -> 55 us, 20 M,
+// M = 4 b = 7 44.5 -> 40.2; whole iterations (norm, quantize, reduce) 11.2 M, M = 16 b = 7 315 -> 303; below, where an iteration's
+// messages are still in the cache, it costs (ResNet-18 shape, M = 8 28.8 -> 30.1).  Without update it gains 3 to 7 % of iterations with 200
+// to 400 MB of messages and loses up to 9 % where they come from memory.  With more than 32 workers (three workgroups per CU, the
+// vector ALU as much as the loads) it loses there too: 4.2 M ragged elements, M = 64 b = 5 56 -> 62, transformer shape, M = 62 b = 5 113 -> 128.
 constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20;
 constexpr bool ur_may_stream(int b) { return b >= 5 && b <= 7; }
+inline bool ur_stream(const dq_plan* plan, int M, int b)
+{
+    return ur_may_stream(b) && M <= 32 && M * dq_packed_bytes(plan, b) + plan->padded_elems * 4 > UR_LAST_LEVEL_CACHE / 2;
+}
+// Whether the model passes through with the hint: a large one would not be in the cache when it is next read, and takes the
+// messages' place.  Iterations with b = 2 and 8, us, model left in the cache / passing through: 2^24, M = 2 73 / 77, M = 8 (b = 8) 233 / 230;
+// 21 M, M = 2 92 / 95, M = 32 969 / 929; 2^25, M = 2 149 / 141, M = 32 1500 / 1474; 2^26, M = 2 288 / 271.  The reduce alone: 22 M, M = 16 b = 8
+// 91 / 97, 28 M 134 / 125.  Left plainly, in the XCDs' own caches, models up to 2^24 took 1 to 5 % of an iteration longer.
+constexpr int64_t UR_ONCE_ELEMS = 24 << 20;
+inline bool ur_model_once(const dq_plan* plan) { return plan->padded_elems > UR_ONCE_ELEMS; }
+
+// Runs f(STREAM, ONCE) with the two as compile-time constants.
+template <bool MAY_STREAM, typename F>
+inline void ur_with_policy(bool stream, bool once, F&& f)
+{
+    using yes = std::true_type;
+    using no = std::false_type;
+    using streamed = std::integral_constant<bool, MAY_STREAM>;
+    if (stream && once) f(streamed{}, yes{});
+    else if (stream) f(streamed{}, no{});
+    else if (once) f(no{}, yes{});
+    else f(no{}, no{});
+}
 
 // Up to how many tiles the workers are divided over wavefronts (k_unpack_dequant_reduce_split), measured with update against
 // the undivided kernel for M = 28..64, 64..600 tiles, all widths, messages in no cache and read before (time undivided / time
@@ -1266,19 +1290,16 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
     const bool three = B >= 4 && M >= 8 && (x ? !ur_may_stream(B) && n_tiles >= 8192 : n_tiles >= 4096);
     if (three && lds_bytes < UR_LDS_THREE_PER_CU) lds_bytes = UR_LDS_THREE_PER_CU;
     const dim3 grid(static_cast<unsigned>(n_tiles)), block(UR_THREADS);
-    const bool fits_cache = plan->padded_elems * (M * (B + 1) + 32) / 8 <= UR_LAST_LEVEL_CACHE; // messages and model
-    if (x && ur_may_stream(B) && !fits_cache && M <= 32)
-        hipLaunchKernelGGL((k_unpack_dequant_reduce<B, true, ur_may_stream(B)>), grid, block, lds_bytes, stream, packed,
-                           packed_stride, M, norms, plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg,
-                           plan->d_cseg_valid_end, plan->padded_elems, inv_M, out, x, eta);
-    else if (x)
-        hipLaunchKernelGGL((k_unpack_dequant_reduce<B, true>), grid, block, lds_bytes, stream, packed, packed_stride, M,
-                           norms, plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end,
-                           plan->padded_elems, inv_M, out, x, eta);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, stream, packed, packed_stride, M, norms, plan->n_seg, plan->d_granule_cseg,
+                           plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, inv_M, out, x, eta);
+    };
+    if (x)
+        ur_with_policy<ur_may_stream(B)>(ur_stream(plan, M, B), ur_model_once(plan), [&](auto s, auto once) {
+            go(k_unpack_dequant_reduce<B, true, decltype(s)::value, decltype(once)::value>);
+        });
     else
-        hipLaunchKernelGGL((k_unpack_dequant_reduce<B, false>), grid, block, lds_bytes, stream, packed, packed_stride, M,
-                           norms, plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end,
-                           plan->padded_elems, inv_M, out, x, eta);
+        go(k_unpack_dequant_reduce<B, false, false, false>);
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
 
@@ -1335,43 +1356,50 @@ int reduce_entry_v(const dq_plan_t* plan, const dq_widths_t* widths, const uint8
     const dim3 grid(static_cast<unsigned>(n_tiles)), block(UR_THREADS);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const float inv_M = 1.0f / static_cast<float>(M);
+    const bool hint = ur_stream(plan, M, 6), once = ur_model_once(plan); // six bits stand for widths that the GPU may have set
     if (widths->n_workers != 1) {
         const size_t lds_w = UR_TILE * sizeof(float) + static_cast<size_t>(UR_MAX_LOCAL_SEG) * M * sizeof(worker_entry);
-        // beyond 64 KiB of LDS per workgroup (M > 32) the kernel has to be told, and the GPU has to have it
+        int max_lds = 64 * 1024;
         if (lds_w > 64 * 1024) {
-            int max_lds = 0;
             if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, plan->device) != hipSuccess)
                 return DQ_ERR_HIP;
             if (lds_w > static_cast<size_t>(max_lds)) return DQ_ERR_INVALID_ARG;
-            const void* fn = x_dev ? reinterpret_cast<const void*>(&k_unpack_dequant_reduce_w<true>)
-                                   : reinterpret_cast<const void*>(&k_unpack_dequant_reduce_w<false>);
-            if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_w)) != hipSuccess) {
-                (void)hipGetLastError();
-                return DQ_ERR_HIP;
-            }
         }
+        bool refused = false;
+        auto go = [&](auto kernel) {
+            // beyond 64 KiB of LDS per workgroup (M > 32) the kernel has to be told
+            if (lds_w > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                         static_cast<int>(lds_w)) != hipSuccess) {
+                refused = true;
+                return;
+            }
+            hipLaunchKernelGGL(kernel, grid, block, lds_w, stream, packed_dev, packed_worker_stride_bytes, M, norms_dev, plan->n_seg,
+                               plan->n_cseg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table,
+                               plan->padded_elems, inv_M, out_dev, x_dev, eta);
+        };
         if (x_dev)
-            hipLaunchKernelGGL(k_unpack_dequant_reduce_w<true>, grid, block, lds_w, stream, packed_dev,
-                               packed_worker_stride_bytes, M, norms_dev, plan->n_seg, plan->n_cseg,
-                               plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table,
-                               plan->padded_elems, inv_M, out_dev, x_dev, eta);
+            ur_with_policy<true>(hint, once, [&](auto s, auto o) {
+                go(k_unpack_dequant_reduce_w<true, decltype(s)::value, decltype(o)::value>);
+            });
         else
-            hipLaunchKernelGGL(k_unpack_dequant_reduce_w<false>, grid, block, lds_w, stream, packed_dev,
-                               packed_worker_stride_bytes, M, norms_dev, plan->n_seg, plan->n_cseg,
-                               plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table,
-                               plan->padded_elems, inv_M, out_dev, x_dev, eta);
+            go(k_unpack_dequant_reduce_w<false, false, false>);
+        if (refused) {
+            (void)hipGetLastError();
+            return DQ_ERR_HIP;
+        }
         return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
     }
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, stream, packed_dev, packed_worker_stride_bytes, M, norms_dev, plan->n_seg,
+                           plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, plan->padded_elems, inv_M,
+                           out_dev, x_dev, eta);
+    };
     if (x_dev)
-        hipLaunchKernelGGL(k_unpack_dequant_reduce_v<true>, grid, block, lds_bytes, stream, packed_dev,
-                           packed_worker_stride_bytes, M, norms_dev, plan->n_seg, plan->d_granule_cseg,
-                           plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, plan->padded_elems, inv_M,
-                           out_dev, x_dev, eta);
+        ur_with_policy<true>(hint, once, [&](auto s, auto o) {
+            go(k_unpack_dequant_reduce_v<true, decltype(s)::value, decltype(o)::value>);
+        });
     else
-        hipLaunchKernelGGL(k_unpack_dequant_reduce_v<false>, grid, block, lds_bytes, stream, packed_dev,
-                           packed_worker_stride_bytes, M, norms_dev, plan->n_seg, plan->d_granule_cseg,
-                           plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, plan->padded_elems, inv_M,
-                           out_dev, x_dev, eta);
+        go(k_unpack_dequant_reduce_v<false, false, false>);
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
 
