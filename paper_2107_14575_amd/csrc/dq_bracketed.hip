@@ -24,7 +24,8 @@
 //       gradient (the only case that reads it twice); a few thousand workgroups walk the map, so
 //       an empty map costs next to nothing.
 //   k_bracket_settle_redo      both in one launch for up to 2^16 (worker, chunk) pairs: one wavefront per
-//       chunk and a lane per record; a chunk to be quantized again is taken by its workgroup.
+//       chunk and a lane per record; a chunk to be quantized again is taken by its workgroup.  Up to 6144 pairs it
+//       takes k_bracket_norm_finish's work too.
 // The messages are exactly those of dq_quantize_pack for the norms this path computes.
 #include "dq_quantize_core.h"
 
@@ -662,60 +663,167 @@ __device__ __forceinline__ bool chunk_needs_redo(uint32_t count, uint32_t flags,
 // its block instead of by granule, record and tensor in turn, and the quantizer's lane arithmetic stays inside the loop
 // (66 to 72 registers, were 82 to 98): ResNet-18 shape, M = 8, b = 2 18.9 -> 14.7 us, b = 3 20.4 -> 15.4, b = 5 30.3 -> 25.1.
 // Two chunks to a wavefront: 12.1, 14.7, but 32.6 where a fifth are taken again (a workgroup takes its chunks in turn).
-template <int B>
+// FOLD: k_bracket_norm_finish is not launched; a wavefront adds the partial sums of its chunk's tensors itself (up to two of them
+// go on beyond the chunk), and the one with a tensor's first chunk writes the norm.  That reads a tensor's sums once per chunk and
+// worker, a few KB from the L2, in place of a launch.  Lagged iterations, us, up to the line (one round of the
+// kernel's wavefronts): 4197 elements, M = 2 b = 2 25.2 -> 21.0, 2^20, M = 4 25.1 -> 21.2, 0.5 M ragged, M = 8 24.7 -> 21.4, 2^22, M = 4 31.4 -> 30.1;
+// beyond it every further round pays for the sums: 2^22, M = 8 45.6 -> 46.0, M = 16 77.0 -> 79.0, ResNet-18 shape, M = 8 b = 3 114.4 -> 118.4.
+constexpr int SETTLE_FOLD_CHUNKS = 1024; // 16 sums a lane
+constexpr int64_t SETTLE_FOLD_PAIRS = 6144; // (worker, chunk) pairs
+struct bracket_finish { // what k_bracket_norm_finish takes
+    const double* partials;
+    int64_t n_slots;
+    const int64_t* cseg_start;
+    const float* norm_lo;
+    const float* norm_hi;
+    float* norms;
+    int linf;
+};
+
+// The sum (or maximum) of a tensor's n <= SETTLE_FOLD_CHUNKS slots, in every lane: the additions of k_bracket_norm_finish in its
+// order (four lanes of its 256 to one here), so the same bits.
+template <bool LINF>
+__device__ __forceinline__ double bracket_slots_total(const double* __restrict__ p, int n, int lane)
+{
+    double part[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        double v[4] = { 0.0, 0.0, 0.0, 0.0 };
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = lane + 64 * q + 256 * k;
+            if (i < n) v[k] = p[i];
+        }
+        part[q] = dq_chunk_combine<LINF>(dq_chunk_combine<LINF>(v[0], v[1]), dq_chunk_combine<LINF>(v[2], v[3]));
+    }
+    double total = dq_chunk_combine<LINF>(dq_chunk_combine<LINF>(part[0], part[2]), dq_chunk_combine<LINF>(part[1], part[3]));
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) total = dq_chunk_combine<LINF>(total, __shfl_down(total, off, 64));
+    return __longlong_as_double(static_cast<long long>(
+        (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint64_t>(__double_as_longlong(total)) >> 32)))) << 32) |
+        static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint64_t>(__double_as_longlong(total)))))));
+}
+
+// Norms that a wavefront has worked out: of segment seg[k], N[k] (seg -1: none).
+struct bracket_norms {
+    int32_t seg[2];
+    float N[2];
+    __device__ __forceinline__ float operator()(const float* row, int32_t s) const
+    {
+        return s == seg[0] ? N[0] : s == seg[1] ? N[1] : row[s];
+    }
+};
+
+// Tensor c (the same for the whole wavefront) of worker w, if it goes on beyond the chunk at chunk0: its norm as entry k of `out`,
+// written to the caller's norms if this is its first chunk.  Returns whether the norm lies inside its bracket (true for a tensor
+// that lies wholly inside the chunk: the first kernel has finished and used its norm).
+__device__ __forceinline__ bool bracket_finish_tensor(const bracket_finish& f, int32_t c, uint32_t w, int64_t chunk0, int32_t n_seg,
+                                                      const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
+                                                      int lane, int k, bracket_norms& out)
+{
+    const int64_t start = f.cseg_start[c], end = cseg_valid_end[c];
+    const int32_t seg = cseg_seg[c];
+    const int64_t first = start / DQ_CHUNK, n = (end - 1) / DQ_CHUNK - first + 1;
+    out.seg[k] = -1;
+    if (n == 1) return true;
+    const double* p = f.partials + static_cast<int64_t>(w) * f.n_slots + first + c;
+    const int64_t at = static_cast<int64_t>(w) * n_seg + seg;
+    const float lo = f.norm_lo[at], hi = f.norm_hi[at];
+    const float N = f.linf ? static_cast<float>(bracket_slots_total<true>(p, static_cast<int>(n), lane))
+                           : static_cast<float>(sqrt(bracket_slots_total<false>(p, static_cast<int>(n), lane)));
+    out.seg[k] = seg;
+    out.N[k] = N;
+    if (first * DQ_CHUNK + DQ_CHUNK > chunk0 && lane == 0) f.norms[at] = N;
+    return N >= lo && N <= hi;
+}
+
+template <int B, bool FOLD>
 __global__ __launch_bounds__(QP_THREADS) void k_bracket_settle_redo(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     int32_t n_cseg, const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems, uint32_t key0,
     uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed, int64_t packed_stride,
     dq_bracket_block* __restrict__ blocks, int64_t n_chunks, const uint8_t* __restrict__ inside,
-    const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride)
+    const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride, const bracket_finish finish)
 {
-    __shared__ int lds_again[QP_THREADS / 64];
+    constexpr int WAVES = QP_THREADS / 64;
+    __shared__ int lds_again[WAVES];
+    __shared__ bracket_norms lds_norms[FOLD ? WAVES : 1];
     const dq_cseg_width* __restrict__ widths = widths_table + static_cast<int64_t>(blockIdx.y) * widths_worker_stride;
     const uint32_t w = blockIdx.y;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t chunk_first = static_cast<int64_t>(blockIdx.x) * (QP_THREADS / 64), chunk = chunk_first + wave;
+    const int64_t chunk_first = static_cast<int64_t>(blockIdx.x) * WAVES, chunk = chunk_first + wave;
     // all that the wavefront needs, in flight together; past the last chunk it is the last one's, and not used
     const int64_t own = chunk < n_chunks ? chunk : n_chunks - 1;
     dq_bracket_block* blk = blocks + static_cast<int64_t>(w) * n_chunks + own;
     const dq_chunk_tensor owner = dq_load_chunk_tensor(chunk_tensor, own);
     const uint2 rec = blk->rec[lane < DQ_BRACKET_CAP ? lane : 0];
     const uint32_t count = blk->count, flags = blk->flags;
-    // the chunk's only tensor, if it has one: its norm, and whether that lies inside its bracket
-    const float N = norms[static_cast<int64_t>(w) * n_seg + owner.seg];
-    const uint32_t in = inside[static_cast<int64_t>(w) * n_cseg + (owner.cseg >= 0 ? owner.cseg : 0)];
+    const float* row = norms + static_cast<int64_t>(w) * n_seg;
     const int64_t chunk0 = chunk * DQ_CHUNK;
     bool again = false;
+    bracket_norms own_norms = { { -1, -1 }, { 0.0f, 0.0f } };
+    float N = 0.0f;     // of the chunk's only tensor, if it has one,
+    uint32_t in = 0;    // and whether it lies inside its bracket
+    if constexpr (!FOLD) {
+        N = row[owner.seg];
+        in = inside[static_cast<int64_t>(w) * n_cseg + (owner.cseg >= 0 ? owner.cseg : 0)];
+    }
     if (chunk < n_chunks) { // the same for the whole wavefront
-        if (owner.cseg >= 0)
-            again = flags != 0 || count > DQ_BRACKET_CAP || in == 0;
-        else
+        again = flags != 0 || count > DQ_BRACKET_CAP;
+        if constexpr (FOLD) {
+            if (owner.cseg >= 0) {
+                again = !bracket_finish_tensor(finish, owner.cseg, w, chunk0, n_seg, cseg_seg, cseg_valid_end, lane, 0, own_norms) || again;
+                N = own_norms.N[0]; // a tensor of this one chunk has no records
+            } else {
+                const int64_t last_granule = ((chunk0 + DQ_CHUNK < padded_elems ? chunk0 + DQ_CHUNK : padded_elems) - 1) >> 7;
+                const int32_t c_first = granule_cseg[chunk0 >> 7], c_last = granule_cseg[last_granule];
+                again = !bracket_finish_tensor(finish, c_first, w, chunk0, n_seg, cseg_seg, cseg_valid_end, lane, 0, own_norms) || again;
+                if (c_last != c_first)
+                    again = !bracket_finish_tensor(finish, c_last, w, chunk0, n_seg, cseg_seg, cseg_valid_end, lane, 1, own_norms) || again;
+            }
+        } else if (owner.cseg >= 0) {
+            again = again || in == 0;
+        } else {
             again = chunk_needs_redo(count, flags, chunk0, padded_elems, w, n_cseg, granule_cseg, inside);
+        }
         if (again) {
             if (lane == 0) blk->flags = flags | 2u;
         } else if (lane < count) {
             uint32_t* plane = reinterpret_cast<uint32_t*>(packed + static_cast<int64_t>(w) * packed_stride + (padded_elems >> 3));
-            if (owner.cseg >= 0)
+            if (owner.cseg >= 0) {
                 settle_element<B>(rec, chunk0, owner.cseg, N, key0, key1, step, worker_base + w, plane, widths);
-            else
+            } else if constexpr (FOLD) { // the record's tensor first (rec.x < 4096 and inside the layout: the first kernel wrote it)
+                const int32_t c = granule_cseg[(chunk0 >> 7) + (rec.x >> 7)];
+                settle_element<B>(rec, chunk0, c, own_norms(row, cseg_seg[c]), key0, key1, step, worker_base + w, plane, widths);
+            } else {
                 settle_record<B>(rec, chunk0, w, norms, n_seg, granule_cseg, cseg_seg, key0, key1, step, worker_base + w, plane,
                                  widths);
+            }
         }
     }
-    if (lane == 0) lds_again[wave] = again ? 1 : 0;
+    if (lane == 0) {
+        lds_again[wave] = again ? 1 : 0;
+        if constexpr (FOLD) lds_norms[wave] = own_norms;
+    }
     __syncthreads();
-    for (int k = 0; k < QP_THREADS / 64; ++k) {
+    for (int k = 0; k < WAVES; ++k) {
         if (__builtin_amdgcn_readfirstlane(lds_again[k]) == 0) continue; // the same for the whole workgroup
         const uint32_t c = static_cast<uint32_t>(chunk_first) + k;
-        if constexpr (B == 0)
-            quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
-                                        widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
-                                        packed, packed_stride, nullptr, c, qp_tid_in_loop());
+        auto redo = [&](auto norm_of) {
+            if constexpr (B == 0)
+                quantize_pack_chunk_v<2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg, cseg_valid_end,
+                                            widths_table, widths_worker_stride, padded_elems, key0, key1, step, worker_base,
+                                            packed, packed_stride, nullptr, c, qp_tid_in_loop(), norm_of);
+            else
+                quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg,
+                                             cseg_valid_end, padded_elems, key0, key1, step, worker_base, packed, packed_stride,
+                                             nullptr, c, qp_tid_in_loop(), norm_of);
+        };
+        if constexpr (FOLD)
+            redo(lds_norms[k]);
         else
-            quantize_pack_chunk<B, 2, 0>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg,
-                                         cseg_valid_end, padded_elems, key0, key1, step, worker_base, packed, packed_stride,
-                                         nullptr, c, qp_tid_in_loop());
+            redo(qp_norm_given{});
         __syncthreads(); // the chunk's staging in LDS is reused by the next one
     }
 }
@@ -862,15 +970,24 @@ int launch_bracketed(const dq_plan* plan, const float* grads, int64_t worker_str
                            norm_lo, norm_hi, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_start,
                            plan->d_cseg_valid_end, plan->padded_elems, key0, key1, step, worker_base, packed,
                            packed_stride, partials, L.n_slots, blocks, L.n_chunks, norms, inside, plan->n_cseg);
-    if (plan->n_span > 0)
+    const bool wide = static_cast<int64_t>(M) * L.n_chunks <= SETTLE_WIDE_MAX;
+    const bool fold = static_cast<int64_t>(M) * L.n_chunks <= SETTLE_FOLD_PAIRS && plan->n_span > 0 && plan->span_chunks <= SETTLE_FOLD_CHUNKS;
+    if (plan->n_span > 0 && !fold)
         hipLaunchKernelGGL(k_bracket_norm_finish<LINF>, dim3(plan->n_span, M), dim3(256), 0, stream, partials, L.n_slots,
                            plan->d_cseg_start, plan->d_cseg_valid_end, plan->d_cseg_seg, plan->d_span_cseg, plan->n_seg,
                            plan->n_cseg, norm_lo, norm_hi, norms, inside);
-    if (static_cast<int64_t>(M) * L.n_chunks <= SETTLE_WIDE_MAX) {
-        hipLaunchKernelGGL(k_bracket_settle_redo<B>, dim3(static_cast<unsigned>((L.n_chunks + 3) / 4), M), block, 0, stream,
-                           grads, worker_stride, norms, plan->n_seg, plan->n_cseg, plan->d_chunk_tensor,
-                           plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, key0, key1,
-                           step, worker_base, packed, packed_stride, blocks, L.n_chunks, inside, widths_table, widths_row);
+    if (wide) {
+        const bracket_finish finish = { partials, L.n_slots, plan->d_cseg_start, norm_lo, norm_hi, norms, LINF ? 1 : 0 };
+        auto settle = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((L.n_chunks + 3) / 4), M), block, 0, stream, grads, worker_stride,
+                               norms, plan->n_seg, plan->n_cseg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,
+                               plan->d_cseg_valid_end, plan->padded_elems, key0, key1, step, worker_base, packed, packed_stride, blocks,
+                               L.n_chunks, inside, widths_table, widths_row, finish);
+        };
+        if (fold)
+            settle(k_bracket_settle_redo<B, true>);
+        else
+            settle(k_bracket_settle_redo<B, false>);
     } else {
         hipLaunchKernelGGL(k_bracket_settle<B>, dim3(static_cast<unsigned>((L.n_chunks + 255) / 256), M), dim3(256), 0,
                            stream, norms, plan->n_seg, plan->n_cseg, plan->d_granule_cseg, plan->d_cseg_seg,

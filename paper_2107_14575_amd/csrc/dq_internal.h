@@ -56,6 +56,7 @@ struct dq_plan {
     int64_t* d_cseg_start;         // [n_nonempty] P_l
     int32_t* d_span_cseg;          // [n_span] compact indices of the tensors that cross a multiple of 4096
     int32_t n_span;                //          padded elements (all others lie inside one chunk)
+    int64_t span_chunks;           // the most chunks that one of them touches
     dq_norm_item* d_items;         // [n_items]
     int32_t* d_seg_item_begin;     // [n_seg + 1] items of segment l are [begin[l], begin[l+1])
     int32_t* d_finish_seg;         // [n_finish] segments whose norm needs the finishing kernel: all but

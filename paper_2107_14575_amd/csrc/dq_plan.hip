@@ -108,7 +108,9 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
                 cseg_seg.push_back(l);
                 cseg_valid_end.push_back(p->seg_start[l] + p->seg_len[l]);
                 cseg_start.push_back(p->seg_start[l]);
-                if (p->seg_start[l] / 4096 != (p->seg_start[l] + p->seg_len[l] - 1) / 4096) span_cseg.push_back(c);
+                const int64_t chunks = (p->seg_start[l] + p->seg_len[l] - 1) / 4096 - p->seg_start[l] / 4096 + 1;
+                if (chunks > 1) span_cseg.push_back(c);
+                if (chunks > p->span_chunks) p->span_chunks = chunks;
                 // the chunks that begin inside this tensor (padding included: tensors begin at multiples of 128)
                 for (int64_t k = (p->seg_start[l] + 4095) / 4096; k * 4096 < p->seg_start[l + 1]; ++k)
                     chunk_tensor[static_cast<size_t>(k)] =

@@ -419,6 +419,12 @@ __device__ __forceinline__ void qp_store_chunk(uint8_t* sign, uint8_t* level, co
     }
 }
 
+// The norm of a chunk's tensor (segment seg) for one worker: at[seg] of what the caller gave.  A kernel that works norms out
+// itself has a form of its own (k_bracket_settle_redo).
+struct qp_norm_given {
+    __device__ __forceinline__ float operator()(const float* row, int32_t seg) const { return row[seg]; }
+};
+
 // What bounds it: the memory system's rate at 4 bytes read to (B+1)/8 written (about 6.1-6.2 TB/s, what a
 // kernel with the same accesses and no arithmetic reaches), with the vector ALU at 89 % beside it (b = 4).  A chunk
 // that lies in one tensor (nearly all of a gradient of large tensors) takes the first route: two scalar
@@ -436,13 +442,13 @@ __device__ __forceinline__ void qp_store_chunk(uint8_t* sign, uint8_t* level, co
 // NORM = 0: the norms are an input.  NORM = 1 (l2) or 2 (max): chunk-local plans only; the kernel
 // computes the norms of its chunk's tensors itself, writes them to norms_out and quantizes from
 // the registers it already holds -- one read of the gradient instead of two.
-template <int B, int TILES, int NORM, bool WHOLE = true, bool KEEP = false>
+template <int B, int TILES, int NORM, bool WHOLE = true, bool KEEP = false, typename NormOf = qp_norm_given>
 __device__ __forceinline__ void quantize_pack_chunk(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x, NormOf norm_of = {})
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -479,7 +485,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
 
     if constexpr (NORM == 0 && WHOLE) {
         const dq_chunk_tensor whole = dq_load_chunk_tensor(chunk_tensor, chunk0 / DQ_CHUNK);
-        const float N = norms[static_cast<int64_t>(w) * n_seg + whole.seg]; // issued whatever cseg is: one wait less
+        const float N = norm_of(norms + static_cast<int64_t>(w) * n_seg, whole.seg); // issued whatever cseg is: one wait less
         if (whole.cseg >= 0) { // 4096 elements of one tensor: one scale, nothing to mask, no table, no barrier
             const float scale = N >= DQ_MIN_NORM ? S / N : 0.0f;
 #pragma unroll
@@ -507,7 +513,7 @@ __device__ __forceinline__ void quantize_pack_chunk(
     const int32_t seg_last = gseg[(n_elems - 1) >> 7];
     if constexpr (NORM == 0) {
         if (static_cast<int32_t>(tid) <= seg_last - seg_first) {
-            const float N = norms[static_cast<int64_t>(w) * n_seg + cseg_seg[seg_first + tid]];
+            const float N = norm_of(norms + static_cast<int64_t>(w) * n_seg, cseg_seg[seg_first + tid]);
             lds_scale[tid] = N >= DQ_MIN_NORM ? S / N : 0.0f; // zero, tiny or NaN norm: every level 0
             const int64_t rel = cseg_valid_end[seg_first + tid] - chunk0;
             lds_valid_end[tid] = rel < CHUNK ? static_cast<int32_t>(rel) : CHUNK;
@@ -589,14 +595,14 @@ __device__ __forceinline__ void quantize_pack_chunk(
 // still one contiguous stretch of the message (every segment's stretch is a whole number of
 // 16-byte pieces per granule), so they are staged and stored the same way.
 // ---------------------------------------------------------------------------------------------
-template <int TILES, int NORM, bool WHOLE = true, bool KEEP = false> // as in quantize_pack_chunk
+template <int TILES, int NORM, bool WHOLE = true, bool KEEP = false, typename NormOf = qp_norm_given> // as in quantize_pack_chunk
 __device__ __forceinline__ void quantize_pack_chunk_v(
     const float* __restrict__ grads, int64_t worker_stride, const float* __restrict__ norms, int32_t n_seg,
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
     const dq_cseg_width* __restrict__ widths_table, int32_t widths_worker_stride, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x)
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x, NormOf norm_of = {})
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -635,7 +641,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
 
     if constexpr (NORM == 0 && WHOLE) { // one tensor: as in quantize_pack_chunk, its width from one (scalar) table entry
         const dq_chunk_tensor whole = dq_load_chunk_tensor(chunk_tensor, chunk0 / DQ_CHUNK);
-        const float N = norms[static_cast<int64_t>(w) * n_seg + whole.seg];
+        const float N = norm_of(norms + static_cast<int64_t>(w) * n_seg, whole.seg);
         if (whole.cseg >= 0) {
             const dq_cseg_width e = widths[whole.cseg];
             const float S = static_cast<float>((1 << e.b) - 1);
@@ -670,7 +676,7 @@ __device__ __forceinline__ void quantize_pack_chunk_v(
         const float S = static_cast<float>((1 << e.b) - 1);
         const int32_t own_seg = cseg_seg[seg_first + tid];
         if constexpr (NORM == 0) {
-            const float N = norms[static_cast<int64_t>(w) * n_seg + own_seg];
+            const float N = norm_of(norms + static_cast<int64_t>(w) * n_seg, own_seg);
             lds_scale[tid] = N >= DQ_MIN_NORM ? S / N : 0.0f;
         } else {
             lds_seg[tid] = own_seg;

@@ -277,3 +277,32 @@ def test_between_the_two_settle_forms(dq):
         n_pairs = M * ((plan.padded_elems + 4095) // 4096)
         assert (int(stats[1]) == n_pairs) if all_again else (int(stats[1]) == 0 and int(stats[0]) > 0)
     plan.close()
+
+
+@pytest.mark.parametrize("linf", [False, True])
+@pytest.mark.parametrize("chunks", [2, 5, 64, 256, 257, 1023, 1024, 1025])
+def test_norms_finished_beside_the_settling(dq, oracle, chunks, linf):
+    """Up to 6144 (worker, chunk) pairs, no tensor over more than 1024 chunks, the settling kernel adds the partial sums itself:
+    tensors that end and begin inside one chunk beside whole ones, their norms inside their brackets and outside, and the same
+    norms bit for bit as from the kernel that adds them for more workers."""
+    seg_len = [chunks * 4096 - 300, 150, 500, 4096 + 77, 0, 60, 2 * 4096 - 900]
+    gen = torch.Generator().manual_seed(chunks)
+    padded = sum((n + 127) // 128 * 128 for n in seg_len)
+    grads = torch.randn((2, padded), generator=gen) * 1e-2
+    for b, lo, hi in ((3, 0.97, 1.03), (6, 4.0, 8.0)):
+        settled, redone, total = _run(dq, oracle, seg_len, grads, b, lo, hi, linf=linf)
+        assert total <= 6144 and (redone > 0 or lo < 1.0)
+    plan = dq.Plan(seg_len)
+    many = min(64, 6144 // ((plan.padded_elems + 4095) // 4096) + 1)
+    ref = gpu_norm(dq, plan, grads.cuda(), linf)
+    got = []
+    for M in (1, many):
+        g = grads[:1].expand(M, -1).contiguous().cuda()
+        lo, hi = (ref[:1] * 0.9).expand(M, -1).contiguous(), (ref[:1] * 1.1).expand(M, -1).contiguous()
+        norms = torch.full((M, plan.n_seg), float("nan"), device="cuda")
+        packed = torch.zeros((M, plan.packed_bytes(2)), dtype=torch.uint8, device="cuda")
+        ws = torch.full((dq.bracketed_workspace_bytes(plan, M),), 0xEE, dtype=torch.uint8, device="cuda")
+        dq.norm_quantize_pack_bracketed(plan, g, lo, hi, 2, SEED, 1, norms, packed, ws, linf=linf)
+        got.append(norms.cpu().numpy().view(np.uint32))
+    assert np.array_equal(np.broadcast_to(got[0], got[1].shape), got[1])
+    plan.close()
