@@ -1,15 +1,19 @@
-"""Thin ctypes binding of libdq.so.  Argument marshalling only: pointers, sizes and the current
+"""Thin binding of libdq.so.  Argument marshalling only: pointers, sizes and the current
 torch stream go straight to the C ABI (``include/dq.h``); no arithmetic of the method happens here
-and there is no fallback -- without the built library every call raises."""
+and there is no fallback -- without the built library every call raises.  What an iteration calls goes through
+a CPython module (``csrc/dq_python.cpp``), the rest through ctypes."""
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 
 import numpy as np
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libdq.so")
+_CALL_PATH = os.path.join(_PKG, "_dqcall.so")
 
 DQ_OK = 0
 GRANULE = 128
@@ -43,6 +47,7 @@ class DQError(RuntimeError):
 
 
 _lib = None
+_call = None  # the module of csrc/dq_python.cpp
 
 
 def library_path() -> str:
@@ -51,12 +56,13 @@ def library_path() -> str:
 
 def load_library():
     """dlopen the in-tree libdq.so; raises if it has not been built."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
+    missing = [path for path in (_LIB_PATH, _CALL_PATH) if not os.path.exists(path)]
+    if missing:
         raise ImportError(
-            f"{_LIB_PATH} is missing: build it with `python -m paper_2107_14575_amd.build` "
+            f"{missing[0]} is missing: build it with `python -m paper_2107_14575_amd.build` "
             "(or __graft_entry__.build()); there is no fallback path")
     L = C.CDLL(_LIB_PATH)
     vp, i64, i32, f32p = C.c_void_p, C.c_int64, C.c_int32, C.POINTER(C.c_float)
@@ -158,8 +164,20 @@ def load_library():
     L.dq_comm_cost_bits.restype = i64
     L.dq_status_string.argtypes = [C.c_int]
     L.dq_status_string.restype = C.c_char_p
+    spec = importlib.util.spec_from_file_location(
+        "_dqcall", _CALL_PATH, loader=importlib.machinery.ExtensionFileLoader("_dqcall", _CALL_PATH))
+    call = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(call)
+    _call = call
     _lib = L
     return L
+
+
+def _calls():
+    """The per-iteration calls, for a function that has no plan (whose making loads them)."""
+    if _call is None:
+        load_library()
+    return _call
 
 
 def _check(what: str, status: int) -> None:
@@ -176,7 +194,8 @@ def _torch_stream_lookup():
     raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     if raw is None:
         return lambda: int(torch.cuda.current_stream().cuda_stream)
-    current_device = torch.cuda.current_device  # initialises the GPU if nothing has yet
+    torch.cuda.current_device()  # initialises the GPU if nothing has yet
+    current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
     return lambda: raw(current_device())
 
 
@@ -203,12 +222,13 @@ class Plan:
         _check("dq_plan_create",
                L.dq_plan_create(lens.ctypes.data_as(C.POINTER(C.c_int64)), lens.size, C.byref(handle)))
         self._h = handle
+        self._ptr = handle.value  # what the calls are given
         self.seg_len = lens
 
     def close(self) -> None:
         if getattr(self, "_h", None) is not None and self._h.value:
             load_library().dq_plan_destroy(self._h)
-            self._h = None
+            self._h = self._ptr = None
 
     def __del__(self):
         try:
@@ -242,7 +262,7 @@ class Plan:
         return int(load_library().dq_plan_segment_start(self.handle, l))
 
     def packed_bytes(self, b: int) -> int:
-        return int(load_library().dq_packed_bytes(self.handle, b))
+        return _call.packed_bytes(self._ptr or self.handle, b)
 
     def workspace_bytes(self, M: int) -> int:
         return int(load_library().dq_workspace_bytes(self.handle, M))
@@ -251,18 +271,12 @@ class Plan:
 def norm(plan: Plan, grads, norms_out, workspace, stream=None) -> None:
     """grads: float32 CUDA tensor [M][stride]; norms_out: float32 CUDA [M][n_seg];
     workspace: CUDA byte tensor of plan.workspace_bytes(M)."""
-    M, stride = int(grads.shape[0]), int(grads.stride(0))
-    _check("dq_norm", load_library().dq_norm(plan.handle, grads.data_ptr(), stride, M,
-                                             norms_out.data_ptr(), workspace.data_ptr(),
-                                             _stream_handle(stream)))
+    _check("dq_norm", _call.norm(plan._ptr or plan.handle, grads, norms_out, workspace, 0, _stream_handle(stream)))
 
 
 def norm_linf(plan: Plan, grads, norms_out, workspace, stream=None) -> None:
     """As norm, with the max norm (p = infinity)."""
-    M, stride = int(grads.shape[0]), int(grads.stride(0))
-    _check("dq_norm_linf", load_library().dq_norm_linf(plan.handle, grads.data_ptr(), stride, M,
-                                                       norms_out.data_ptr(), workspace.data_ptr(),
-                                                       _stream_handle(stream)))
+    _check("dq_norm_linf", _call.norm(plan._ptr or plan.handle, grads, norms_out, workspace, 1, _stream_handle(stream)))
 
 
 def norm_static_scratch(plan: Plan, grads, norms_out, linf: bool = False, stream=None) -> None:
@@ -278,37 +292,31 @@ def norm_static_scratch_max_bytes() -> int:
     return int(load_library().dq_norm_static_scratch_max_bytes())
 
 
-def _select_bits(name, norms_host, t, T, eps_hat_q, alpha, b_min, b_max):
+def _select_bits(name, norms_host, t, T, eps_hat_q, alpha, b_min, b_max, linf):
     n = np.ascontiguousarray(norms_host, dtype=np.float32)
     if n.ndim != 2:
         raise ValueError("norms must be [M][n_seg]")
-    b = C.c_int(0)
-    gbar = C.c_double(0.0)
-    fn = getattr(load_library(), name)
-    # the address as a plain integer: a typed ctypes pointer took 3 of the call's 7.6 us
-    _check(name, fn(n.__array_interface__["data"][0], n.shape[0], n.shape[1],
-                    t, T, eps_hat_q, alpha, b_min, b_max, C.byref(b), C.byref(gbar)))
-    return b.value, gbar.value
+    status, b, gbar = _calls().select_bits(n, t, T, eps_hat_q, alpha, b_min, b_max, linf)
+    _check(name, status)
+    return b, gbar
 
 
 def select_bits(norms_host, t: int, T: int, eps_hat_q: float, alpha: float, b_min: int, b_max: int):
     """norms_host: host float32 array [M][n_seg] -> (b, Gbar)."""
-    return _select_bits("dq_select_bits", norms_host, t, T, eps_hat_q, alpha, b_min, b_max)
+    return _select_bits("dq_select_bits", norms_host, t, T, eps_hat_q, alpha, b_min, b_max, 0)
 
 
 def select_bits_linf(norms_host, t: int, T: int, eps_hat_q: float, alpha: float, b_min: int, b_max: int):
     """select_bits for norms from norm_linf."""
-    return _select_bits("dq_select_bits_linf", norms_host, t, T, eps_hat_q, alpha, b_min, b_max)
+    return _select_bits("dq_select_bits_linf", norms_host, t, T, eps_hat_q, alpha, b_min, b_max, 1)
 
 
 def norm_quantize_pack(plan: Plan, grads, b: int, seed: int, step: int, norms_out, packed_out,
                        worker_base: int = 0, linf: bool = False, stream=None) -> None:
     """One pass over the gradient for chunk-local plans: norms (written to norms_out) and messages."""
-    M, stride = int(grads.shape[0]), int(grads.stride(0))
     _check("dq_norm_quantize_pack",
-           load_library().dq_norm_quantize_pack(plan.handle, grads.data_ptr(), stride, M, 1 if linf else 0, b, seed,
-                                                step, worker_base, norms_out.data_ptr(), packed_out.data_ptr(),
-                                                int(packed_out.stride(0)), _stream_handle(stream)))
+           _call.norm_quantize_pack(plan._ptr or plan.handle, grads, b, seed, step, worker_base, norms_out, packed_out,
+                                    1 if linf else 0, _stream_handle(stream)))
 
 
 def norm_bracket(norms, margin: float, lo_out, hi_out, stream=None) -> None:
@@ -317,8 +325,7 @@ def norm_bracket(norms, margin: float, lo_out, hi_out, stream=None) -> None:
         raise ValueError("contiguous tensors")
     if lo_out.numel() != norms.numel() or hi_out.numel() != norms.numel():
         raise ValueError("one bracket per norm")
-    _check("dq_norm_bracket", load_library().dq_norm_bracket(norms.data_ptr(), norms.numel(), margin, lo_out.data_ptr(),
-                                                             hi_out.data_ptr(), _stream_handle(stream)))
+    _check("dq_norm_bracket", _calls().norm_bracket(norms, norms.numel(), margin, lo_out, hi_out, _stream_handle(stream)))
 
 
 def bracketed_workspace_bytes(plan: Plan, M: int) -> int:
@@ -332,43 +339,31 @@ def norm_quantize_pack_bracketed(plan: Plan, grads, norm_lo, norm_hi, b: int, se
     [M][n_seg]) for every norm: norms (written to norms_out) and the messages of quantize_pack for
     them.  workspace: uint8 CUDA tensor of bracketed_workspace_bytes(plan, M); stats: optional CUDA
     int64 [2] (elements settled afterwards, chunks quantized again)."""
-    M, stride = int(grads.shape[0]), int(grads.stride(0))
-    if workspace.numel() * workspace.element_size() < bracketed_workspace_bytes(plan, M):
+    if workspace.numel() * workspace.element_size() < bracketed_workspace_bytes(plan, int(grads.shape[0])):
         raise ValueError("workspace too small: see bracketed_workspace_bytes")
     _check("dq_norm_quantize_pack_bracketed",
-           load_library().dq_norm_quantize_pack_bracketed(
-               plan.handle, grads.data_ptr(), stride, M, 1 if linf else 0, norm_lo.data_ptr(), norm_hi.data_ptr(), b,
-               seed, step,
-               worker_base, norms_out.data_ptr(), packed_out.data_ptr(), int(packed_out.stride(0)),
-               workspace.data_ptr(), stats.data_ptr() if stats is not None else None, _stream_handle(stream)))
+           _call.bracketed(plan._ptr or plan.handle, 0, grads, norm_lo, norm_hi, b, seed, step, worker_base, norms_out,
+                           packed_out, workspace, stats, 1 if linf else 0, _stream_handle(stream)))
 
 
 def quantize_pack(plan: Plan, grads, norms, b: int, seed: int, step: int, packed_out,
                   worker_base: int = 0, stream=None) -> None:
     """packed_out: uint8 CUDA tensor [M][stride_bytes], written in full per message."""
-    M, stride = int(grads.shape[0]), int(grads.stride(0))
     _check("dq_quantize_pack",
-           load_library().dq_quantize_pack(plan.handle, grads.data_ptr(), stride, M, norms.data_ptr(), b,
-                                           seed, step, worker_base, packed_out.data_ptr(),
-                                           int(packed_out.stride(0)), _stream_handle(stream)))
+           _call.quantize_pack(plan._ptr or plan.handle, grads, norms, b, seed, step, worker_base, packed_out,
+                               _stream_handle(stream)))
 
 
 def unpack_dequant_reduce(plan: Plan, packed, norms, b: int, out, stream=None) -> None:
     """packed: uint8 CUDA [M][stride_bytes]; out: float32 CUDA [D']."""
-    M = int(packed.shape[0])
     _check("dq_unpack_dequant_reduce",
-           load_library().dq_unpack_dequant_reduce(plan.handle, packed.data_ptr(), int(packed.stride(0)), M,
-                                                   norms.data_ptr(), b, out.data_ptr(),
-                                                   _stream_handle(stream)))
+           _call.reduce(plan._ptr or plan.handle, packed, norms, b, out, _stream_handle(stream)))
 
 
 def unpack_dequant_reduce_update(plan: Plan, packed, norms, b: int, eta: float, x, ghat=None, stream=None) -> None:
     """x: float32 CUDA [D'], updated in place to x - eta * g_hat; ghat (optional) receives g_hat."""
-    M = int(packed.shape[0])
     _check("dq_unpack_dequant_reduce_update",
-           load_library().dq_unpack_dequant_reduce_update(
-               plan.handle, packed.data_ptr(), int(packed.stride(0)), M, norms.data_ptr(), b, eta,
-               x.data_ptr(), None if ghat is None else ghat.data_ptr(), _stream_handle(stream)))
+           _call.reduce_update(plan._ptr or plan.handle, packed, norms, b, eta, x, ghat, _stream_handle(stream)))
 
 
 def alpha_est(F_t: float, F_0: float, t: int) -> float:
@@ -435,6 +430,7 @@ class Widths:
             _check("dq_widths_create_per_worker",
                    load_library().dq_widths_create_per_worker(plan.handle, int(workers), C.byref(handle)))
         self._h = handle
+        self._ptr = handle.value
         self.plan = plan
         self.workers = workers
         if b_seg is not None:
@@ -464,7 +460,7 @@ class Widths:
     def close(self) -> None:
         if getattr(self, "_h", None) is not None and self._h.value:
             load_library().dq_widths_destroy(self._h)
-            self._h = None
+            self._h = self._ptr = None
 
     def __del__(self):
         try:
@@ -507,24 +503,18 @@ def norm_quantize_pack_bracketed_v(plan: Plan, widths: Widths, grads, norm_lo, n
                                    packed_out, workspace, worker_base: int = 0, stats=None, linf: bool = False,
                                    stream=None) -> None:
     """norm_quantize_pack_bracketed with the widths of `widths` (per tensor, shared or one row per worker)."""
-    M, stride = int(grads.shape[0]), int(grads.stride(0))
-    if workspace.numel() * workspace.element_size() < bracketed_workspace_bytes(plan, M):
+    if workspace.numel() * workspace.element_size() < bracketed_workspace_bytes(plan, int(grads.shape[0])):
         raise ValueError("workspace too small: see bracketed_workspace_bytes")
     _check("dq_norm_quantize_pack_bracketed_v",
-           load_library().dq_norm_quantize_pack_bracketed_v(
-               plan.handle, widths.handle, grads.data_ptr(), stride, M, 1 if linf else 0, norm_lo.data_ptr(),
-               norm_hi.data_ptr(), seed, step, worker_base, norms_out.data_ptr(), packed_out.data_ptr(),
-               int(packed_out.stride(0)), workspace.data_ptr(), stats.data_ptr() if stats is not None else None,
-               _stream_handle(stream)))
+           _call.bracketed(plan._ptr or plan.handle, widths._ptr or widths.handle, grads, norm_lo, norm_hi, 0, seed, step,
+                           worker_base, norms_out, packed_out, workspace, stats, 1 if linf else 0, _stream_handle(stream)))
 
 
 def quantize_pack_v(plan: Plan, widths: Widths, grads, norms, seed: int, step: int, packed_out,
                     worker_base: int = 0, stream=None) -> None:
-    M, stride = int(grads.shape[0]), int(grads.stride(0))
     _check("dq_quantize_pack_v",
-           load_library().dq_quantize_pack_v(plan.handle, widths.handle, grads.data_ptr(), stride, M,
-                                             norms.data_ptr(), seed, step, worker_base, packed_out.data_ptr(),
-                                             int(packed_out.stride(0)), _stream_handle(stream)))
+           _call.quantize_pack_v(plan._ptr or plan.handle, widths._ptr or widths.handle, grads, norms, seed, step, worker_base,
+                                 packed_out, _stream_handle(stream)))
 
 
 def norm_quantize_pack_v(plan: Plan, widths: Widths, grads, seed: int, step: int, norms_out, packed_out,
@@ -539,41 +529,26 @@ def norm_quantize_pack_v(plan: Plan, widths: Widths, grads, seed: int, step: int
 
 
 def unpack_dequant_reduce_v(plan: Plan, widths: Widths, packed, norms, out, stream=None) -> None:
-    M = int(packed.shape[0])
     _check("dq_unpack_dequant_reduce_v",
-           load_library().dq_unpack_dequant_reduce_v(plan.handle, widths.handle, packed.data_ptr(),
-                                                     int(packed.stride(0)), M, norms.data_ptr(), out.data_ptr(),
-                                                     _stream_handle(stream)))
+           _call.reduce_v(plan._ptr or plan.handle, widths._ptr or widths.handle, packed, norms, out, _stream_handle(stream)))
 
 
 def unpack_dequant_reduce_update_v(plan: Plan, widths: Widths, packed, norms, eta: float, x, ghat=None,
                                    stream=None) -> None:
-    M = int(packed.shape[0])
     _check("dq_unpack_dequant_reduce_update_v",
-           load_library().dq_unpack_dequant_reduce_update_v(plan.handle, widths.handle, packed.data_ptr(),
-                                                            int(packed.stride(0)), M, norms.data_ptr(), eta,
-                                                            x.data_ptr(), ghat.data_ptr() if ghat is not None else None,
-                                                            _stream_handle(stream)))
+           _call.reduce_update_v(plan._ptr or plan.handle, widths._ptr or widths.handle, packed, norms, eta, x, ghat,
+                                 _stream_handle(stream)))
 
 
 # ------------------------------------------------------------------------- sign-only messages
 def sign_pack(plan: Plan, grads, packed_out, stream=None) -> None:
     """packed_out: uint8 CUDA [M][>= D'/8]: every worker's sign plane."""
-    M, stride = int(grads.shape[0]), int(grads.stride(0))
-    _check("dq_sign_pack", load_library().dq_sign_pack(plan.handle, grads.data_ptr(), stride, M,
-                                                       packed_out.data_ptr(), int(packed_out.stride(0)),
-                                                       _stream_handle(stream)))
+    _check("dq_sign_pack", _call.sign_pack(plan._ptr or plan.handle, grads, packed_out, _stream_handle(stream)))
 
 
 def sign_reduce(plan: Plan, packed, out, scales=None, stream=None) -> None:
-    M = int(packed.shape[0])
-    _check("dq_sign_reduce", load_library().dq_sign_reduce(plan.handle, packed.data_ptr(), int(packed.stride(0)), M,
-                                                           scales.data_ptr() if scales is not None else None,
-                                                           out.data_ptr(), _stream_handle(stream)))
+    _check("dq_sign_reduce", _call.sign_reduce(plan._ptr or plan.handle, packed, scales, out, 0, _stream_handle(stream)))
 
 
 def sign_majority(plan: Plan, packed, out, stream=None) -> None:
-    M = int(packed.shape[0])
-    _check("dq_sign_majority", load_library().dq_sign_majority(plan.handle, packed.data_ptr(),
-                                                               int(packed.stride(0)), M, out.data_ptr(),
-                                                               _stream_handle(stream)))
+    _check("dq_sign_majority", _call.sign_reduce(plan._ptr or plan.handle, packed, None, out, 1, _stream_handle(stream)))

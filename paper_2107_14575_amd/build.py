@@ -1,14 +1,16 @@
-"""Builds libdq.so (the C-ABI HIP library) in-tree with hipcc for gfx950."""
+"""Builds libdq.so (the C-ABI HIP library, hipcc for gfx950) and _dqcall.so (its calls from Python, g++) in-tree."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
+import sysconfig
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
 CSRC = os.path.join(_PKG, "csrc")
 LIB_PATH = os.path.join(_PKG, "libdq.so")
+CALL_PATH = os.path.join(_PKG, "_dqcall.so")
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
@@ -24,8 +26,21 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def build_calls(verbose: bool = False) -> str:
+    """Compile the CPython module beside libdq.so (which it is linked to by its place)."""
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(_ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], "-o", CALL_PATH, os.path.join(CSRC, "dq_python.cpp"), "-L", _PKG, "-l:libdq.so",
+           "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout)
+    return CALL_PATH
+
+
 def build_library(verbose: bool = False) -> str:
-    """Compile every HIP source into libdq.so; always compiles."""
+    """Compile every HIP source into libdq.so, and the calls from Python; always compiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(_ROOT, "include"), "-I", CSRC, "-o", LIB_PATH, *sources()]
     if verbose:
@@ -37,6 +52,7 @@ def build_library(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
         print(out, flush=True)
+    build_calls(verbose)
     return LIB_PATH
 
 

@@ -1,0 +1,400 @@
+// The Python side of the per-iteration entry points: takes the tensors' addresses, strides and row counts and calls the C
+// functions of dq.h, without the GIL.  Arguments are converted as ctypes converts them (whole numbers by Python int only, cut to
+// the C type; ctypes.ArgumentError otherwise).  Returns the status; binding.py has the names, defaults and checks.
+//
+// A small call is its launch (2.6 us of HIP) and what leads there.  Through ctypes, with the attributes read in Python:
+// quantize_pack 5.5 us, norm 4.8, select_bits 2.0; here 4.6, 4.1, 0.4.  An iteration of 4096 values, M = 8, 33.8 -> 28.9 us, of 2^20, M = 4,
+// 35.9 -> 31.9.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <stdint.h>
+
+#include "dq.h"
+
+namespace {
+
+PyObject* g_argument_error = nullptr; // ctypes.ArgumentError
+PyObject *s_data_ptr = nullptr, *s_stride = nullptr, *s_size = nullptr, *s_zero = nullptr;
+
+// One call's arguments, taken one after the other; `ok` goes false with a Python exception set.
+struct taker {
+    PyObject* const* args;
+    Py_ssize_t n, at = 0;
+    bool ok = true;
+
+    taker(PyObject* const* a, Py_ssize_t have, Py_ssize_t want) : args(a), n(have)
+    {
+        if (have != want) {
+            PyErr_Format(PyExc_TypeError, "%zd arguments, not %zd", want, have);
+            ok = false;
+        }
+    }
+    uint64_t bits_of(PyObject* o)
+    {
+        if (!PyLong_Check(o)) {
+            PyErr_Format(g_argument_error, "int expected instead of %s instance", Py_TYPE(o)->tp_name);
+            ok = false;
+            return 0;
+        }
+        return PyLong_AsUnsignedLongLongMask(o); // no error: an int
+    }
+    uint64_t result_of(PyObject* o) // of a tensor's method; takes the reference
+    {
+        if (!o) {
+            ok = false;
+            return 0;
+        }
+        const uint64_t v = PyLong_AsUnsignedLongLongMask(o);
+        if (v == static_cast<uint64_t>(-1) && PyErr_Occurred()) ok = false;
+        Py_DECREF(o);
+        return v;
+    }
+    uint64_t whole() { return ok ? bits_of(args[at++]) : 0; }
+    int as_int() { return static_cast<int>(whole()); }
+    uint32_t as_u32() { return static_cast<uint32_t>(whole()); }
+    int64_t as_i64() { return static_cast<int64_t>(whole()); }
+    void* address() { return reinterpret_cast<void*>(whole()); } // a handle or stream, an int
+    double real()
+    {
+        if (!ok) return 0.0;
+        const double v = PyFloat_AsDouble(args[at++]);
+        if (v == -1.0 && PyErr_Occurred()) {
+            PyErr_Clear();
+            PyErr_SetString(g_argument_error, "a number expected");
+            ok = false;
+        }
+        return v;
+    }
+    PyObject* object() { return ok ? args[at++] : nullptr; }
+    template <typename T>
+    T* data_of(PyObject* t) // NULL for None
+    {
+        if (!ok || t == Py_None) return nullptr;
+        return reinterpret_cast<T*>(result_of(PyObject_CallMethodNoArgs(t, s_data_ptr)));
+    }
+    template <typename T>
+    T* data()
+    {
+        PyObject* t = object();
+        if (ok && t == Py_None) { // as None.data_ptr()
+            PyErr_SetString(PyExc_AttributeError, "'NoneType' object has no attribute 'data_ptr'");
+            ok = false;
+        }
+        return data_of<T>(t);
+    }
+    template <typename T>
+    T* data_or_null()
+    {
+        return data_of<T>(object());
+    }
+    int64_t stride0(PyObject* t) { return ok ? static_cast<int64_t>(result_of(PyObject_CallMethodOneArg(t, s_stride, s_zero))) : 0; }
+    int rows(PyObject* t) { return ok ? static_cast<int>(result_of(PyObject_CallMethodOneArg(t, s_size, s_zero))) : 0; }
+};
+
+template <typename F>
+PyObject* status_of(const taker& a, F&& call)
+{
+    if (!a.ok) return nullptr;
+    int status;
+    Py_BEGIN_ALLOW_THREADS;
+    status = call();
+    Py_END_ALLOW_THREADS;
+    return PyLong_FromLong(status);
+}
+
+template <typename T>
+struct matrix { // a tensor of one row per worker
+    T* data;
+    int64_t stride;
+    int rows;
+};
+template <typename T>
+matrix<T> take_matrix(taker& a)
+{
+    PyObject* t = a.object();
+    matrix<T> m = {};
+    if (!a.ok) return m;
+    m.rows = a.rows(t);
+    m.stride = a.stride0(t);
+    m.data = a.data_of<T>(t);
+    return m;
+}
+
+using args_t = PyObject* const*;
+
+// (plan, grads, norms, workspace, linf, stream)
+PyObject* py_norm(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 6);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto grads = take_matrix<const float>(a);
+    float* norms = a.data<float>();
+    void* workspace = a.data<void>();
+    const int linf = a.as_int();
+    void* stream = a.address();
+    return status_of(a, [&] {
+        return linf ? dq_norm_linf(plan, grads.data, grads.stride, grads.rows, norms, workspace, stream)
+                    : dq_norm(plan, grads.data, grads.stride, grads.rows, norms, workspace, stream);
+    });
+}
+
+// (plan, grads, norms, b, seed, step, worker_base, packed, stream)
+PyObject* py_quantize_pack(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 9);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto grads = take_matrix<const float>(a);
+    const float* norms = a.data<const float>();
+    const int b = a.as_int();
+    const uint64_t seed = a.whole();
+    const uint32_t step = a.as_u32(), worker_base = a.as_u32();
+    PyObject* out = a.object();
+    uint8_t* packed = a.data_of<uint8_t>(out);
+    const int64_t stride = a.stride0(out);
+    void* stream = a.address();
+    return status_of(a, [&] {
+        return dq_quantize_pack(plan, grads.data, grads.stride, grads.rows, norms, b, seed, step, worker_base, packed, stride, stream);
+    });
+}
+
+// (plan, widths, grads, norms, seed, step, worker_base, packed, stream)
+PyObject* py_quantize_pack_v(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 9);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto* widths = static_cast<const dq_widths_t*>(a.address());
+    const auto grads = take_matrix<const float>(a);
+    const float* norms = a.data<const float>();
+    const uint64_t seed = a.whole();
+    const uint32_t step = a.as_u32(), worker_base = a.as_u32();
+    PyObject* out = a.object();
+    uint8_t* packed = a.data_of<uint8_t>(out);
+    const int64_t stride = a.stride0(out);
+    void* stream = a.address();
+    return status_of(a, [&] {
+        return dq_quantize_pack_v(plan, widths, grads.data, grads.stride, grads.rows, norms, seed, step, worker_base, packed, stride,
+                                  stream);
+    });
+}
+
+// (plan, grads, b, seed, step, worker_base, norms, packed, linf, stream)
+PyObject* py_norm_quantize_pack(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 10);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto grads = take_matrix<const float>(a);
+    const int b = a.as_int();
+    const uint64_t seed = a.whole();
+    const uint32_t step = a.as_u32(), worker_base = a.as_u32();
+    float* norms = a.data<float>();
+    PyObject* out = a.object();
+    uint8_t* packed = a.data_of<uint8_t>(out);
+    const int64_t stride = a.stride0(out);
+    const int linf = a.as_int();
+    void* stream = a.address();
+    return status_of(a, [&] {
+        return dq_norm_quantize_pack(plan, grads.data, grads.stride, grads.rows, linf, b, seed, step, worker_base, norms, packed, stride,
+                                     stream);
+    });
+}
+
+// (norms, numel, margin, lo, hi, stream)
+PyObject* py_norm_bracket(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 6);
+    const float* norms = a.data<const float>();
+    const int64_t count = a.as_i64();
+    const float margin = static_cast<float>(a.real());
+    float *lo = a.data<float>(), *hi = a.data<float>();
+    void* stream = a.address();
+    return status_of(a, [&] { return dq_norm_bracket(norms, count, margin, lo, hi, stream); });
+}
+
+// (plan, widths or 0, grads, lo, hi, b, seed, step, worker_base, norms, packed, workspace, stats, linf, stream)
+PyObject* py_bracketed(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 15);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto* widths = static_cast<const dq_widths_t*>(a.address());
+    const auto grads = take_matrix<const float>(a);
+    const float *lo = a.data<const float>(), *hi = a.data<const float>();
+    const int b = a.as_int();
+    const uint64_t seed = a.whole();
+    const uint32_t step = a.as_u32(), worker_base = a.as_u32();
+    float* norms = a.data<float>();
+    PyObject* out = a.object();
+    uint8_t* packed = a.data_of<uint8_t>(out);
+    const int64_t stride = a.stride0(out);
+    void* workspace = a.data<void>();
+    auto* stats = a.data_or_null<int64_t>();
+    const int linf = a.as_int();
+    void* stream = a.address();
+    return status_of(a, [&] {
+        return widths ? dq_norm_quantize_pack_bracketed_v(plan, widths, grads.data, grads.stride, grads.rows, linf, lo, hi, seed, step,
+                                                          worker_base, norms, packed, stride, workspace, stats, stream)
+                      : dq_norm_quantize_pack_bracketed(plan, grads.data, grads.stride, grads.rows, linf, lo, hi, b, seed, step,
+                                                        worker_base, norms, packed, stride, workspace, stats, stream);
+    });
+}
+
+// (plan, packed, norms, b, out, stream)
+PyObject* py_reduce(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 6);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto packed = take_matrix<const uint8_t>(a);
+    const float* norms = a.data<const float>();
+    const int b = a.as_int();
+    float* out = a.data<float>();
+    void* stream = a.address();
+    return status_of(a, [&] { return dq_unpack_dequant_reduce(plan, packed.data, packed.stride, packed.rows, norms, b, out, stream); });
+}
+
+// (plan, packed, norms, b, eta, x, ghat, stream)
+PyObject* py_reduce_update(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 8);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto packed = take_matrix<const uint8_t>(a);
+    const float* norms = a.data<const float>();
+    const int b = a.as_int();
+    const float eta = static_cast<float>(a.real());
+    float *x = a.data<float>(), *ghat = a.data_or_null<float>();
+    void* stream = a.address();
+    return status_of(a, [&] {
+        return dq_unpack_dequant_reduce_update(plan, packed.data, packed.stride, packed.rows, norms, b, eta, x, ghat, stream);
+    });
+}
+
+// (plan, widths, packed, norms, out, stream)
+PyObject* py_reduce_v(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 6);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto* widths = static_cast<const dq_widths_t*>(a.address());
+    const auto packed = take_matrix<const uint8_t>(a);
+    const float* norms = a.data<const float>();
+    float* out = a.data<float>();
+    void* stream = a.address();
+    return status_of(a, [&] { return dq_unpack_dequant_reduce_v(plan, widths, packed.data, packed.stride, packed.rows, norms, out, stream); });
+}
+
+// (plan, widths, packed, norms, eta, x, ghat, stream)
+PyObject* py_reduce_update_v(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 8);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto* widths = static_cast<const dq_widths_t*>(a.address());
+    const auto packed = take_matrix<const uint8_t>(a);
+    const float* norms = a.data<const float>();
+    const float eta = static_cast<float>(a.real());
+    float *x = a.data<float>(), *ghat = a.data_or_null<float>();
+    void* stream = a.address();
+    return status_of(a, [&] {
+        return dq_unpack_dequant_reduce_update_v(plan, widths, packed.data, packed.stride, packed.rows, norms, eta, x, ghat, stream);
+    });
+}
+
+// (plan, grads, packed, stream)
+PyObject* py_sign_pack(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 4);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto grads = take_matrix<const float>(a);
+    PyObject* out = a.object();
+    uint8_t* packed = a.data_of<uint8_t>(out);
+    const int64_t stride = a.stride0(out);
+    void* stream = a.address();
+    return status_of(a, [&] { return dq_sign_pack(plan, grads.data, grads.stride, grads.rows, packed, stride, stream); });
+}
+
+// (plan, packed, scales, out, majority, stream)
+PyObject* py_sign_reduce(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 6);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const auto packed = take_matrix<const uint8_t>(a);
+    const float* scales = a.data_or_null<const float>();
+    float* out = a.data<float>();
+    const int majority = a.as_int();
+    void* stream = a.address();
+    return status_of(a, [&] {
+        return majority ? dq_sign_majority(plan, packed.data, packed.stride, packed.rows, out, stream)
+                        : dq_sign_reduce(plan, packed.data, packed.stride, packed.rows, scales, out, stream);
+    });
+}
+
+// (norms: C-contiguous float32 [M][n_seg], t, T, eps_hat_q, alpha, b_min, b_max, linf) -> (status, b, Gbar)
+PyObject* py_select_bits(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 8);
+    PyObject* array = a.object();
+    const int64_t t = a.as_i64(), T = a.as_i64();
+    const double eps = a.real(), alpha = a.real();
+    const int b_min = a.as_int(), b_max = a.as_int(), linf = a.as_int();
+    if (!a.ok) return nullptr;
+    Py_buffer view;
+    if (PyObject_GetBuffer(array, &view, PyBUF_C_CONTIGUOUS) != 0) return nullptr;
+    if (view.ndim != 2 || view.itemsize != 4 || view.shape[0] > INT32_MAX || view.shape[1] > INT32_MAX) {
+        PyBuffer_Release(&view);
+        PyErr_SetString(PyExc_ValueError, "norms must be [M][n_seg]");
+        return nullptr;
+    }
+    int b = 0, status;
+    double gbar = 0.0;
+    const auto* norms = static_cast<const float*>(view.buf);
+    const int M = static_cast<int>(view.shape[0]), n_seg = static_cast<int>(view.shape[1]);
+    Py_BEGIN_ALLOW_THREADS;
+    status = linf ? dq_select_bits_linf(norms, M, n_seg, t, T, eps, alpha, b_min, b_max, &b, &gbar)
+                  : dq_select_bits(norms, M, n_seg, t, T, eps, alpha, b_min, b_max, &b, &gbar);
+    Py_END_ALLOW_THREADS;
+    PyBuffer_Release(&view);
+    return Py_BuildValue("iid", status, b, gbar);
+}
+
+// (plan, b) -> bytes
+PyObject* py_packed_bytes(PyObject*, args_t args, Py_ssize_t n)
+{
+    taker a(args, n, 2);
+    const auto* plan = static_cast<const dq_plan_t*>(a.address());
+    const int b = a.as_int();
+    if (!a.ok) return nullptr;
+    return PyLong_FromLongLong(dq_packed_bytes(plan, b));
+}
+
+#define DQ_METHOD(name, fn) { name, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(fn)), METH_FASTCALL, nullptr }
+PyMethodDef methods[] = {
+    DQ_METHOD("norm", py_norm),
+    DQ_METHOD("quantize_pack", py_quantize_pack),
+    DQ_METHOD("quantize_pack_v", py_quantize_pack_v),
+    DQ_METHOD("norm_quantize_pack", py_norm_quantize_pack),
+    DQ_METHOD("norm_bracket", py_norm_bracket),
+    DQ_METHOD("bracketed", py_bracketed),
+    DQ_METHOD("reduce", py_reduce),
+    DQ_METHOD("reduce_update", py_reduce_update),
+    DQ_METHOD("reduce_v", py_reduce_v),
+    DQ_METHOD("reduce_update_v", py_reduce_update_v),
+    DQ_METHOD("sign_pack", py_sign_pack),
+    DQ_METHOD("sign_reduce", py_sign_reduce),
+    DQ_METHOD("select_bits", py_select_bits),
+    DQ_METHOD("packed_bytes", py_packed_bytes),
+    { nullptr, nullptr, 0, nullptr },
+};
+PyModuleDef module = { PyModuleDef_HEAD_INIT, "_dqcall", "Calls of libdq.so's per-iteration entry points.", -1, methods, nullptr, nullptr, nullptr, nullptr };
+
+} // namespace
+
+PyMODINIT_FUNC PyInit__dqcall(void)
+{
+    PyObject* ctypes = PyImport_ImportModule("ctypes");
+    if (!ctypes) return nullptr;
+    g_argument_error = PyObject_GetAttrString(ctypes, "ArgumentError");
+    Py_DECREF(ctypes);
+    s_data_ptr = PyUnicode_InternFromString("data_ptr");
+    s_stride = PyUnicode_InternFromString("stride");
+    s_size = PyUnicode_InternFromString("size");
+    s_zero = PyLong_FromLong(0);
+    if (!g_argument_error || !s_data_ptr || !s_stride || !s_size || !s_zero) return nullptr;
+    return PyModule_Create(&module);
+}

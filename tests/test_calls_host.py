@@ -1,0 +1,57 @@
+"""The CPython module that makes the per-iteration calls (csrc/dq_python.cpp), as far as no GPU is needed: the same results and the
+same refusals as the C functions through ctypes."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+
+@pytest.fixture(scope="module")
+def dq():
+    import paper_2107_14575_amd as dq
+    dq.load_library()
+    return dq
+
+
+def test_rule_as_through_ctypes(dq):
+    lib = dq.load_library()
+    rng = np.random.default_rng(3)
+    for linf, call, fn in ((0, dq.select_bits, lib.dq_select_bits), (1, dq.select_bits_linf, lib.dq_select_bits_linf)):
+        for M, n_seg in ((1, 1), (8, 1), (3, 62), (64, 7)):
+            norms = rng.random((M, n_seg)).astype(np.float32)
+            b, gbar = C.c_int(0), C.c_double(0.0)
+            assert fn(norms.ctypes.data, M, n_seg, 5, 20, 0.5, 0.97, 1, 8, C.byref(b), C.byref(gbar)) == 0
+            assert call(norms, 5, 20, 0.5, 0.97, 1, 8) == (b.value, gbar.value)
+            assert call(np.asfortranarray(norms.astype(np.float64)), 5, 20, 0.5, 0.97, 1, 8) == (b.value, gbar.value)
+    with pytest.raises(ValueError):
+        dq.select_bits(np.ones(4, np.float32), 5, 20, 0.5, 0.97, 1, 8)
+    from paper_2107_14575_amd.binding import DQError
+    with pytest.raises(DQError):
+        dq.select_bits(np.ones((2, 2), np.float32), 20, 20, 0.5, 0.97, 1, 8)
+
+
+def test_refusals(dq):
+    """A status other than DQ_OK raises DQError, a wrong type ctypes.ArgumentError, a closed plan ValueError; None is not an array."""
+    from paper_2107_14575_amd import binding
+    plan = dq.Plan([5, 300])
+    grads = torch.zeros((2, plan.padded_elems))
+    norms = torch.zeros((2, 2))
+    packed = torch.zeros((2, plan.packed_bytes(8)), dtype=torch.uint8)
+    call, stream = binding._calls().quantize_pack, 0
+    with pytest.raises(C.ArgumentError):
+        call(plan.handle.value, grads, norms, 2.0, 1, 0, 0, packed, stream)
+    with pytest.raises(C.ArgumentError):
+        call(plan.handle.value, grads, norms, np.int64(2), 1, 0, 0, packed, stream)
+    with pytest.raises(AttributeError):
+        call(plan.handle.value, grads, None, 2, 1, 0, 0, packed, stream)
+    with pytest.raises(TypeError):
+        call(plan.handle.value, grads)
+    invalid = -1
+    assert call(plan.handle.value, grads, norms, 9, 1, 0, 0, packed, stream) == invalid
+    assert call(plan.handle.value, grads[:, :4].contiguous(), norms, 2, 1 << 80, 0, 0, packed, stream) == invalid
+    with pytest.raises(TypeError):
+        binding.quantize_pack(plan, grads, norms, 2, 1, 0)
+    plan.close()
+    with pytest.raises(ValueError):
+        plan.packed_bytes(2)
