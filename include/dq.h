@@ -59,7 +59,7 @@ typedef enum dq_status {
 #define DQ_MAX_WORKERS 64   /* largest M one call accepts                                         */
 #define DQ_MIN_NORM 0x1p-100f /* a norm that is not >= this (zero, tiny, NaN) quantizes to zeros   */
 
-typedef struct dq_plan dq_plan_t; /* opaque, immutable after creation, bound to one GPU */
+typedef struct dq_plan dq_plan_t; /* opaque, bound to one GPU; no call changes what another one sees of it */
 
 /* Builds the layout of n_seg tensors of seg_len_host[l] >= 0 elements and uploads its tables to
  * the current HIP device.  Without a usable device the plan is still created for the host-side

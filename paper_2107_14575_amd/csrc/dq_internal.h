@@ -33,6 +33,8 @@ __device__ __forceinline__ dq_chunk_tensor dq_load_chunk_tensor(const dq_chunk_t
     return dq_chunk_tensor{ static_cast<int32_t>(static_cast<uint32_t>(v)), static_cast<int32_t>(v >> 32) };
 }
 
+constexpr int DQ_ARRIVED_SEGS = 512;
+
 struct dq_plan {
     int32_t n_seg;
     int64_t padded_elems; // D'
@@ -61,6 +63,11 @@ struct dq_plan {
     int32_t* d_seg_item_begin;     // [n_seg + 1] items of segment l are [begin[l], begin[l+1])
     int32_t* d_finish_seg;         // [n_finish] segments whose norm needs the finishing kernel: all but
     int32_t n_finish;              //            those of exactly one item (the first kernel finishes these)
+    int32_t most_items;            // the most items of one segment
+    // [DQ_MAX_WORKERS][n_seg] items of a segment that have arrived, zero between calls; null for more than DQ_ARRIVED_SEGS
+    // segments.  The one part of a plan that a kernel writes: only for calls on the default stream, which run one after the other
+    // whatever thread makes them and cannot be captured (see dq_norm.hip).
+    uint32_t* d_arrived;
 };
 
 // Per-tensor bit-widths (dq_widths_*): one entry per non-empty segment, indexed like the plan's
