@@ -5,6 +5,8 @@ import glob
 import os
 import subprocess
 import sysconfig
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
@@ -42,16 +44,26 @@ def build_calls(verbose: bool = False) -> str:
 def build_library(verbose: bool = False) -> str:
     """Compile every HIP source into libdq.so, and the calls from Python; always compiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(_ROOT, "include"), "-I", CSRC, "-o", LIB_PATH, *sources()]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    out = "\n".join(l for l in res.stdout.splitlines()
-                    if "packed-fp32-ops" not in l or "error" in l)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
-    if verbose and out.strip():
-        print(out, flush=True)
+    include = ["-I", os.path.join(_ROOT, "include"), "-I", CSRC]
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        out = "\n".join(l for l in res.stdout.splitlines()
+                        if "packed-fp32-ops" not in l or "error" in l)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + out)
+        if verbose and out.strip():
+            print(out, flush=True)
+
+    # the sources side by side: one of them holds most of the kernels
+    with tempfile.TemporaryDirectory() as objects:
+        jobs = [(src, os.path.join(objects, os.path.basename(src) + ".o")) for src in sources()]
+        flags = [f for f in HIPCC_FLAGS if f != "-shared"]
+        with ThreadPoolExecutor(len(jobs)) as pool:
+            list(pool.map(lambda job: run([hipcc, *flags, *include, "-c", job[0], "-o", job[1]]), jobs))
+        run([hipcc, *HIPCC_FLAGS, "-o", LIB_PATH, *(obj for _, obj in jobs)])
     build_calls(verbose)
     return LIB_PATH
 
