@@ -114,15 +114,16 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
 // Whether the messages go through to the last-level cache (dq_store_buffer) and not past it with the streaming hint: they are
 // read next, by the same GPU's reduce or by whatever sends them.  Whole iterations decide (norm, quantize, reduce on gradients
 // not seen before), 390 of them drawn over 2^17 to 2^28 values, M = 1..64, one tensor and ragged ones, all widths; time against the
-// hint: 0.92 to 1.0 up to 400 MB of messages whatever their number (2^24 values, M = 8 b = 2, 5, 8 0.955, 0.950, 0.971; 2^25, M = 2 b = 5
+// hint: 0.92 to 1.0 up to 190 to 400 MB of messages whatever their number (2^24 values, M = 8 b = 2, 5, 8 0.955, 0.950, 0.971; 2^25, M = 2 b = 5
 // 0.925; transformer shape, M = 24 with update b = 7 0.966), still 0.97 to 0.98 at 400 to 670 MB for b <= 4; beyond that most of them
 // are gone from the 256 MB before they are read and the stores cost 1 to 5 % (2^28, M = 16 b = 4 6400 -> 6490 us).  Plain stores, which
 // leave the lines dirty in the XCDs' caches, were 1 to 2 % slower than this at the sizes where they gain, and lose at others.
-// With M > 32 and b >= 5, where the reduce reads them as if they came from memory, 144 to 280 MB gain 0 to 2 % and 360 to 400 lose 2 to 4.
+// With b = 5 to 7, whose level loads carry no hint without update, and with M > 32 they gain up to 190 MB; 200 to 400 MB gain 3 to 4 % with
+// update and lose 1 to 4 % without (34 M, M = 13 b = 6 753 -> 772, 30 M, M = 9 b = 5 454 -> 465).
 // Narrow calls of 4 to 13 MB gain or lose up to 2 %.
 inline bool qp_keep_messages(const dq_plan* plan, int M, int b)
 {
-    const int64_t megabytes = b <= 4 ? 640 : M <= 32 ? 400 : 280;
+    const int64_t megabytes = b <= 4 ? 640 : b == 8 && M <= 32 ? 400 : 190;
     return M * dq_packed_bytes(plan, b) <= megabytes << 20;
 }
 // Widths that may be known to the GPU only: six bits stand for the usual.
