@@ -7,8 +7,8 @@
 // workgroup per (segment, worker) adds that segment's item partials in a fixed order and takes
 // the square root.  A segment of a single item (at most 4096 elements) is finished by pass 1
 // itself -- the same value, since its sum has one term -- so a gradient cut into many small
-// tensors costs no second-pass workgroups.  HBM traffic: 4 bytes read per element, plus 8 bytes
-// per 4096 elements.
+// tensors costs no second-pass workgroups.  Small calls on the default stream leave pass 2 out altogether (ARRIVE).
+// HBM traffic: 4 bytes read per element, plus 8 bytes per 4096 elements.
 // The max norm takes the same two passes with binary32 maxima in place of the binary64 sums (a
 // maximum does not depend on the order; a NaN element never wins a comparison).
 //

@@ -19,7 +19,7 @@
 // after: 2^26 x 16 b = 5 199 -> 183 us, b = 6 214 -> 203, b = 8 255 -> 249; 4.2 M ragged elements with
 // update, M = 64, b = 5 66.9 -> 52 us, b = 8 76.6 -> 66; ResNet-18 shape with update, M = 8, b = 6
 // 35.4 -> 28.4 us.  Narrow widths are where they were before those changes or below: 2^28 x 16 b = 1 402 -> 380,
-// b = 2 466 -> 447, b = 3 538 -> 532, b = 4 594 -> 588 and with update 875 -> 820; ResNet-18 shape, M = 8, b = 1, 2, 3
+// b = 2 466 -> 447, b = 3 538 -> 532, b = 4 594 -> 588 and with update 875 -> 768; ResNet-18 shape, M = 8, b = 1, 2, 3
 // 15.0, 15.4, 16.9 -> 14.6, 15.3, 16.7 (see ur_table_first).
 //
 // The 32 results of a lane are consecutive in memory, so storing them directly would be 16-byte
