@@ -168,6 +168,8 @@ def load_library():
         "_dqcall", _CALL_PATH, loader=importlib.machinery.ExtensionFileLoader("_dqcall", _CALL_PATH))
     call = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(call)
+    # the functions of the library just opened, whatever other libdq.so there is
+    call.bind({name: C.cast(getattr(L, name), C.c_void_p).value for name in call.functions})
     _call = call
     _lib = L
     return L

@@ -29,10 +29,9 @@ def sources():
 
 
 def build_calls(verbose: bool = False) -> str:
-    """Compile the CPython module beside libdq.so (which it is linked to by its place)."""
+    """Compile the CPython module.  It is not linked to libdq.so: binding.py binds it to the one that it opens."""
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(_ROOT, "include"),
-           "-I", sysconfig.get_paths()["include"], "-o", CALL_PATH, os.path.join(CSRC, "dq_python.cpp"), "-L", _PKG, "-l:libdq.so",
-           "-Wl,-rpath,$ORIGIN"]
+           "-I", sysconfig.get_paths()["include"], "-o", CALL_PATH, os.path.join(CSRC, "dq_python.cpp")]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

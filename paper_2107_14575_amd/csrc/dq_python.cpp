@@ -1,5 +1,7 @@
 // The Python side of the per-iteration entry points: takes the tensors' addresses, strides and row counts and calls the C
-// functions of dq.h, without the GIL.  Arguments are converted as ctypes converts them (whole numbers by Python int only, cut to
+// functions of dq.h, without the GIL.  The functions are those of the library that binding.py has opened, which hands their addresses over
+// (bind): the module itself needs no libdq.so, so it cannot come by another one on the loader's search path or of another copy of the
+// package, whose plans have another form.  Arguments are converted as ctypes converts them (whole numbers by Python int only, cut to
 // the C type; ctypes.ArgumentError otherwise).  Returns the status; binding.py has the names, defaults and checks.
 //
 // A small call is its launch (2.6 us of HIP) and what leads there.  Through ctypes, with the attributes read in Python:
@@ -14,18 +16,36 @@
 
 namespace {
 
-PyObject* g_argument_error = nullptr; // ctypes.ArgumentError
-PyObject *s_data_ptr = nullptr, *s_stride = nullptr, *s_size = nullptr, *s_zero = nullptr;
+#define DQ_FUNCTIONS(X) \
+    X(dq_norm) X(dq_norm_linf) X(dq_quantize_pack) X(dq_quantize_pack_v) X(dq_norm_quantize_pack) X(dq_norm_bracket) \
+    X(dq_norm_quantize_pack_bracketed) X(dq_norm_quantize_pack_bracketed_v) X(dq_unpack_dequant_reduce) X(dq_unpack_dequant_reduce_v) \
+    X(dq_unpack_dequant_reduce_update) X(dq_unpack_dequant_reduce_update_v) X(dq_sign_pack) X(dq_sign_reduce) X(dq_sign_majority) \
+    X(dq_select_bits) X(dq_select_bits_linf) X(dq_packed_bytes)
+
+// Of one module object: copies of the package that share this file are bound each to their own library.
+struct state {
+#define X(fn) decltype(&::fn) fn;
+    DQ_FUNCTIONS(X)
+#undef X
+    bool bound;
+    PyObject* argument_error; // ctypes.ArgumentError
+    PyObject *data_ptr, *stride, *size, *zero;
+};
+state* state_of(PyObject* module) { return static_cast<state*>(PyModule_GetState(module)); }
 
 // One call's arguments, taken one after the other; `ok` goes false with a Python exception set.
 struct taker {
+    const state* lib;
     PyObject* const* args;
-    Py_ssize_t n, at = 0;
+    Py_ssize_t at = 0;
     bool ok = true;
 
-    taker(PyObject* const* a, Py_ssize_t have, Py_ssize_t want) : args(a), n(have)
+    taker(PyObject* module, PyObject* const* a, Py_ssize_t have, Py_ssize_t want) : lib(state_of(module)), args(a)
     {
-        if (have != want) {
+        if (!lib->bound) {
+            PyErr_SetString(PyExc_RuntimeError, "no library bound");
+            ok = false;
+        } else if (have != want) {
             PyErr_Format(PyExc_TypeError, "%zd arguments, not %zd", want, have);
             ok = false;
         }
@@ -33,7 +53,7 @@ struct taker {
     uint64_t bits_of(PyObject* o)
     {
         if (!PyLong_Check(o)) {
-            PyErr_Format(g_argument_error, "int expected instead of %s instance", Py_TYPE(o)->tp_name);
+            PyErr_Format(lib->argument_error, "int expected instead of %s instance", Py_TYPE(o)->tp_name);
             ok = false;
             return 0;
         }
@@ -61,7 +81,7 @@ struct taker {
         const double v = PyFloat_AsDouble(args[at++]);
         if (v == -1.0 && PyErr_Occurred()) {
             PyErr_Clear();
-            PyErr_SetString(g_argument_error, "a number expected");
+            PyErr_SetString(lib->argument_error, "a number expected");
             ok = false;
         }
         return v;
@@ -71,7 +91,7 @@ struct taker {
     T* data_of(PyObject* t) // NULL for None
     {
         if (!ok || t == Py_None) return nullptr;
-        return reinterpret_cast<T*>(result_of(PyObject_CallMethodNoArgs(t, s_data_ptr)));
+        return reinterpret_cast<T*>(result_of(PyObject_CallMethodNoArgs(t, lib->data_ptr)));
     }
     template <typename T>
     T* data()
@@ -88,8 +108,8 @@ struct taker {
     {
         return data_of<T>(object());
     }
-    int64_t stride0(PyObject* t) { return ok ? static_cast<int64_t>(result_of(PyObject_CallMethodOneArg(t, s_stride, s_zero))) : 0; }
-    int rows(PyObject* t) { return ok ? static_cast<int>(result_of(PyObject_CallMethodOneArg(t, s_size, s_zero))) : 0; }
+    int64_t stride0(PyObject* t) { return ok ? static_cast<int64_t>(result_of(PyObject_CallMethodOneArg(t, lib->stride, lib->zero))) : 0; }
+    int rows(PyObject* t) { return ok ? static_cast<int>(result_of(PyObject_CallMethodOneArg(t, lib->size, lib->zero))) : 0; }
 };
 
 template <typename F>
@@ -124,9 +144,9 @@ matrix<T> take_matrix(taker& a)
 using args_t = PyObject* const*;
 
 // (plan, grads, norms, workspace, linf, stream)
-PyObject* py_norm(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_norm(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 6);
+    taker a(module, args, n, 6);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto grads = take_matrix<const float>(a);
     float* norms = a.data<float>();
@@ -134,15 +154,15 @@ PyObject* py_norm(PyObject*, args_t args, Py_ssize_t n)
     const int linf = a.as_int();
     void* stream = a.address();
     return status_of(a, [&] {
-        return linf ? dq_norm_linf(plan, grads.data, grads.stride, grads.rows, norms, workspace, stream)
-                    : dq_norm(plan, grads.data, grads.stride, grads.rows, norms, workspace, stream);
+        return linf ? a.lib->dq_norm_linf(plan, grads.data, grads.stride, grads.rows, norms, workspace, stream)
+                    : a.lib->dq_norm(plan, grads.data, grads.stride, grads.rows, norms, workspace, stream);
     });
 }
 
 // (plan, grads, norms, b, seed, step, worker_base, packed, stream)
-PyObject* py_quantize_pack(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_quantize_pack(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 9);
+    taker a(module, args, n, 9);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto grads = take_matrix<const float>(a);
     const float* norms = a.data<const float>();
@@ -154,14 +174,14 @@ PyObject* py_quantize_pack(PyObject*, args_t args, Py_ssize_t n)
     const int64_t stride = a.stride0(out);
     void* stream = a.address();
     return status_of(a, [&] {
-        return dq_quantize_pack(plan, grads.data, grads.stride, grads.rows, norms, b, seed, step, worker_base, packed, stride, stream);
+        return a.lib->dq_quantize_pack(plan, grads.data, grads.stride, grads.rows, norms, b, seed, step, worker_base, packed, stride, stream);
     });
 }
 
 // (plan, widths, grads, norms, seed, step, worker_base, packed, stream)
-PyObject* py_quantize_pack_v(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_quantize_pack_v(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 9);
+    taker a(module, args, n, 9);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto* widths = static_cast<const dq_widths_t*>(a.address());
     const auto grads = take_matrix<const float>(a);
@@ -173,15 +193,15 @@ PyObject* py_quantize_pack_v(PyObject*, args_t args, Py_ssize_t n)
     const int64_t stride = a.stride0(out);
     void* stream = a.address();
     return status_of(a, [&] {
-        return dq_quantize_pack_v(plan, widths, grads.data, grads.stride, grads.rows, norms, seed, step, worker_base, packed, stride,
+        return a.lib->dq_quantize_pack_v(plan, widths, grads.data, grads.stride, grads.rows, norms, seed, step, worker_base, packed, stride,
                                   stream);
     });
 }
 
 // (plan, grads, b, seed, step, worker_base, norms, packed, linf, stream)
-PyObject* py_norm_quantize_pack(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_norm_quantize_pack(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 10);
+    taker a(module, args, n, 10);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto grads = take_matrix<const float>(a);
     const int b = a.as_int();
@@ -194,27 +214,27 @@ PyObject* py_norm_quantize_pack(PyObject*, args_t args, Py_ssize_t n)
     const int linf = a.as_int();
     void* stream = a.address();
     return status_of(a, [&] {
-        return dq_norm_quantize_pack(plan, grads.data, grads.stride, grads.rows, linf, b, seed, step, worker_base, norms, packed, stride,
+        return a.lib->dq_norm_quantize_pack(plan, grads.data, grads.stride, grads.rows, linf, b, seed, step, worker_base, norms, packed, stride,
                                      stream);
     });
 }
 
 // (norms, numel, margin, lo, hi, stream)
-PyObject* py_norm_bracket(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_norm_bracket(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 6);
+    taker a(module, args, n, 6);
     const float* norms = a.data<const float>();
     const int64_t count = a.as_i64();
     const float margin = static_cast<float>(a.real());
     float *lo = a.data<float>(), *hi = a.data<float>();
     void* stream = a.address();
-    return status_of(a, [&] { return dq_norm_bracket(norms, count, margin, lo, hi, stream); });
+    return status_of(a, [&] { return a.lib->dq_norm_bracket(norms, count, margin, lo, hi, stream); });
 }
 
 // (plan, widths or 0, grads, lo, hi, b, seed, step, worker_base, norms, packed, workspace, stats, linf, stream)
-PyObject* py_bracketed(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_bracketed(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 15);
+    taker a(module, args, n, 15);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto* widths = static_cast<const dq_widths_t*>(a.address());
     const auto grads = take_matrix<const float>(a);
@@ -231,30 +251,30 @@ PyObject* py_bracketed(PyObject*, args_t args, Py_ssize_t n)
     const int linf = a.as_int();
     void* stream = a.address();
     return status_of(a, [&] {
-        return widths ? dq_norm_quantize_pack_bracketed_v(plan, widths, grads.data, grads.stride, grads.rows, linf, lo, hi, seed, step,
+        return widths ? a.lib->dq_norm_quantize_pack_bracketed_v(plan, widths, grads.data, grads.stride, grads.rows, linf, lo, hi, seed, step,
                                                           worker_base, norms, packed, stride, workspace, stats, stream)
-                      : dq_norm_quantize_pack_bracketed(plan, grads.data, grads.stride, grads.rows, linf, lo, hi, b, seed, step,
+                      : a.lib->dq_norm_quantize_pack_bracketed(plan, grads.data, grads.stride, grads.rows, linf, lo, hi, b, seed, step,
                                                         worker_base, norms, packed, stride, workspace, stats, stream);
     });
 }
 
 // (plan, packed, norms, b, out, stream)
-PyObject* py_reduce(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_reduce(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 6);
+    taker a(module, args, n, 6);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto packed = take_matrix<const uint8_t>(a);
     const float* norms = a.data<const float>();
     const int b = a.as_int();
     float* out = a.data<float>();
     void* stream = a.address();
-    return status_of(a, [&] { return dq_unpack_dequant_reduce(plan, packed.data, packed.stride, packed.rows, norms, b, out, stream); });
+    return status_of(a, [&] { return a.lib->dq_unpack_dequant_reduce(plan, packed.data, packed.stride, packed.rows, norms, b, out, stream); });
 }
 
 // (plan, packed, norms, b, eta, x, ghat, stream)
-PyObject* py_reduce_update(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_reduce_update(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 8);
+    taker a(module, args, n, 8);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto packed = take_matrix<const uint8_t>(a);
     const float* norms = a.data<const float>();
@@ -263,27 +283,27 @@ PyObject* py_reduce_update(PyObject*, args_t args, Py_ssize_t n)
     float *x = a.data<float>(), *ghat = a.data_or_null<float>();
     void* stream = a.address();
     return status_of(a, [&] {
-        return dq_unpack_dequant_reduce_update(plan, packed.data, packed.stride, packed.rows, norms, b, eta, x, ghat, stream);
+        return a.lib->dq_unpack_dequant_reduce_update(plan, packed.data, packed.stride, packed.rows, norms, b, eta, x, ghat, stream);
     });
 }
 
 // (plan, widths, packed, norms, out, stream)
-PyObject* py_reduce_v(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_reduce_v(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 6);
+    taker a(module, args, n, 6);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto* widths = static_cast<const dq_widths_t*>(a.address());
     const auto packed = take_matrix<const uint8_t>(a);
     const float* norms = a.data<const float>();
     float* out = a.data<float>();
     void* stream = a.address();
-    return status_of(a, [&] { return dq_unpack_dequant_reduce_v(plan, widths, packed.data, packed.stride, packed.rows, norms, out, stream); });
+    return status_of(a, [&] { return a.lib->dq_unpack_dequant_reduce_v(plan, widths, packed.data, packed.stride, packed.rows, norms, out, stream); });
 }
 
 // (plan, widths, packed, norms, eta, x, ghat, stream)
-PyObject* py_reduce_update_v(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_reduce_update_v(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 8);
+    taker a(module, args, n, 8);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto* widths = static_cast<const dq_widths_t*>(a.address());
     const auto packed = take_matrix<const uint8_t>(a);
@@ -292,27 +312,27 @@ PyObject* py_reduce_update_v(PyObject*, args_t args, Py_ssize_t n)
     float *x = a.data<float>(), *ghat = a.data_or_null<float>();
     void* stream = a.address();
     return status_of(a, [&] {
-        return dq_unpack_dequant_reduce_update_v(plan, widths, packed.data, packed.stride, packed.rows, norms, eta, x, ghat, stream);
+        return a.lib->dq_unpack_dequant_reduce_update_v(plan, widths, packed.data, packed.stride, packed.rows, norms, eta, x, ghat, stream);
     });
 }
 
 // (plan, grads, packed, stream)
-PyObject* py_sign_pack(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_sign_pack(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 4);
+    taker a(module, args, n, 4);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto grads = take_matrix<const float>(a);
     PyObject* out = a.object();
     uint8_t* packed = a.data_of<uint8_t>(out);
     const int64_t stride = a.stride0(out);
     void* stream = a.address();
-    return status_of(a, [&] { return dq_sign_pack(plan, grads.data, grads.stride, grads.rows, packed, stride, stream); });
+    return status_of(a, [&] { return a.lib->dq_sign_pack(plan, grads.data, grads.stride, grads.rows, packed, stride, stream); });
 }
 
 // (plan, packed, scales, out, majority, stream)
-PyObject* py_sign_reduce(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_sign_reduce(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 6);
+    taker a(module, args, n, 6);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto packed = take_matrix<const uint8_t>(a);
     const float* scales = a.data_or_null<const float>();
@@ -320,15 +340,15 @@ PyObject* py_sign_reduce(PyObject*, args_t args, Py_ssize_t n)
     const int majority = a.as_int();
     void* stream = a.address();
     return status_of(a, [&] {
-        return majority ? dq_sign_majority(plan, packed.data, packed.stride, packed.rows, out, stream)
-                        : dq_sign_reduce(plan, packed.data, packed.stride, packed.rows, scales, out, stream);
+        return majority ? a.lib->dq_sign_majority(plan, packed.data, packed.stride, packed.rows, out, stream)
+                        : a.lib->dq_sign_reduce(plan, packed.data, packed.stride, packed.rows, scales, out, stream);
     });
 }
 
 // (norms: C-contiguous float32 [M][n_seg], t, T, eps_hat_q, alpha, b_min, b_max, linf) -> (status, b, Gbar)
-PyObject* py_select_bits(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_select_bits(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 8);
+    taker a(module, args, n, 8);
     PyObject* array = a.object();
     const int64_t t = a.as_i64(), T = a.as_i64();
     const double eps = a.real(), alpha = a.real();
@@ -346,25 +366,50 @@ PyObject* py_select_bits(PyObject*, args_t args, Py_ssize_t n)
     const auto* norms = static_cast<const float*>(view.buf);
     const int M = static_cast<int>(view.shape[0]), n_seg = static_cast<int>(view.shape[1]);
     Py_BEGIN_ALLOW_THREADS;
-    status = linf ? dq_select_bits_linf(norms, M, n_seg, t, T, eps, alpha, b_min, b_max, &b, &gbar)
-                  : dq_select_bits(norms, M, n_seg, t, T, eps, alpha, b_min, b_max, &b, &gbar);
+    status = linf ? a.lib->dq_select_bits_linf(norms, M, n_seg, t, T, eps, alpha, b_min, b_max, &b, &gbar)
+                  : a.lib->dq_select_bits(norms, M, n_seg, t, T, eps, alpha, b_min, b_max, &b, &gbar);
     Py_END_ALLOW_THREADS;
     PyBuffer_Release(&view);
     return Py_BuildValue("iid", status, b, gbar);
 }
 
 // (plan, b) -> bytes
-PyObject* py_packed_bytes(PyObject*, args_t args, Py_ssize_t n)
+PyObject* py_packed_bytes(PyObject* module, args_t args, Py_ssize_t n)
 {
-    taker a(args, n, 2);
+    taker a(module, args, n, 2);
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const int b = a.as_int();
     if (!a.ok) return nullptr;
-    return PyLong_FromLongLong(dq_packed_bytes(plan, b));
+    return PyLong_FromLongLong(a.lib->dq_packed_bytes(plan, b));
+}
+
+// ({name: address} of `functions`): the library that the other calls go to.
+PyObject* py_bind(PyObject* module, PyObject* addresses)
+{
+    state* lib = state_of(module);
+    if (!PyDict_Check(addresses)) {
+        PyErr_SetString(PyExc_TypeError, "a dict of addresses");
+        return nullptr;
+    }
+    lib->bound = false;
+    const auto take = [&](const char* name) -> void* {
+        PyObject* at = PyDict_GetItemString(addresses, name); // borrowed
+        void* fn = at ? PyLong_AsVoidPtr(at) : nullptr;
+        if (!fn && !PyErr_Occurred()) PyErr_Format(PyExc_ImportError, "%s: not in this library", name);
+        return fn;
+    };
+#define X(fn)                                               \
+    lib->fn = reinterpret_cast<decltype(&::fn)>(take(#fn)); \
+    if (!lib->fn) return nullptr;
+    DQ_FUNCTIONS(X)
+#undef X
+    lib->bound = true;
+    Py_RETURN_NONE;
 }
 
 #define DQ_METHOD(name, fn) { name, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(fn)), METH_FASTCALL, nullptr }
 PyMethodDef methods[] = {
+    { "bind", py_bind, METH_O, nullptr },
     DQ_METHOD("norm", py_norm),
     DQ_METHOD("quantize_pack", py_quantize_pack),
     DQ_METHOD("quantize_pack_v", py_quantize_pack_v),
@@ -381,20 +426,64 @@ PyMethodDef methods[] = {
     DQ_METHOD("packed_bytes", py_packed_bytes),
     { nullptr, nullptr, 0, nullptr },
 };
-PyModuleDef module = { PyModuleDef_HEAD_INIT, "_dqcall", "Calls of libdq.so's per-iteration entry points.", -1, methods, nullptr, nullptr, nullptr, nullptr };
+
+int fill(PyObject* module)
+{
+    state* lib = state_of(module);
+    PyObject* ctypes = PyImport_ImportModule("ctypes");
+    if (!ctypes) return -1;
+    lib->argument_error = PyObject_GetAttrString(ctypes, "ArgumentError");
+    Py_DECREF(ctypes);
+    lib->data_ptr = PyUnicode_InternFromString("data_ptr");
+    lib->stride = PyUnicode_InternFromString("stride");
+    lib->size = PyUnicode_InternFromString("size");
+    lib->zero = PyLong_FromLong(0);
+    if (!lib->argument_error || !lib->data_ptr || !lib->stride || !lib->size || !lib->zero) return -1;
+    static const char* const functions[] = {
+#define X(fn) #fn,
+        DQ_FUNCTIONS(X)
+#undef X
+    };
+    PyObject* names = PyList_New(0);
+    if (!names) return -1;
+    for (const char* function : functions) {
+        PyObject* name = PyUnicode_FromString(function);
+        const bool added = name && PyList_Append(names, name) == 0;
+        Py_XDECREF(name);
+        if (!added) {
+            Py_DECREF(names);
+            return -1;
+        }
+    }
+    if (PyModule_AddObject(module, "functions", names) != 0) {
+        Py_DECREF(names);
+        return -1;
+    }
+    return 0;
+}
+
+int visit_state(PyObject* module, visitproc visit, void* arg)
+{
+    if (state* lib = state_of(module)) Py_VISIT(lib->argument_error);
+    return 0;
+}
+int clear_state(PyObject* module)
+{
+    if (state* lib = state_of(module)) {
+        Py_CLEAR(lib->argument_error);
+        Py_CLEAR(lib->data_ptr);
+        Py_CLEAR(lib->stride);
+        Py_CLEAR(lib->size);
+        Py_CLEAR(lib->zero);
+        lib->bound = false;
+    }
+    return 0;
+}
+void free_state(void* module) { clear_state(static_cast<PyObject*>(module)); }
+
+PyModuleDef_Slot slots[] = { { Py_mod_exec, reinterpret_cast<void*>(fill) }, { 0, nullptr } };
+PyModuleDef definition = { PyModuleDef_HEAD_INIT, "_dqcall", "Calls of libdq.so's per-iteration entry points.", sizeof(state), methods, slots, visit_state, clear_state, free_state };
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__dqcall(void)
-{
-    PyObject* ctypes = PyImport_ImportModule("ctypes");
-    if (!ctypes) return nullptr;
-    g_argument_error = PyObject_GetAttrString(ctypes, "ArgumentError");
-    Py_DECREF(ctypes);
-    s_data_ptr = PyUnicode_InternFromString("data_ptr");
-    s_stride = PyUnicode_InternFromString("stride");
-    s_size = PyUnicode_InternFromString("size");
-    s_zero = PyLong_FromLong(0);
-    if (!g_argument_error || !s_data_ptr || !s_stride || !s_size || !s_zero) return nullptr;
-    return PyModule_Create(&module);
-}
+PyMODINIT_FUNC PyInit__dqcall(void) { return PyModuleDef_Init(&definition); }

@@ -1,10 +1,18 @@
 """The CPython module that makes the per-iteration calls (csrc/dq_python.cpp), as far as no GPU is needed: the same results and the
 same refusals as the C functions through ctypes."""
 import ctypes as C
+import os
+import pathlib
+import re
+import shutil
+import subprocess
+import sys
 
 import numpy as np
 import pytest
 import torch
+
+ROOT = pathlib.Path(__file__).resolve().parent.parent
 
 
 @pytest.fixture(scope="module")
@@ -55,3 +63,36 @@ def test_refusals(dq):
     plan.close()
     with pytest.raises(ValueError):
         plan.packed_bytes(2)
+
+
+def _stub_library(path):
+    """A libdq.so of another build: every function of the header, each returning 7."""
+    header = re.sub(r"/\*.*?\*/", "", (ROOT / "include" / "dq.h").read_text(), flags=re.S)
+    names = sorted(set(re.findall(r"\b(dq_[a-z_0-9]+)\s*\(", header)))
+    source = path.with_suffix(".c")
+    source.write_text("\n".join(f"long {name}(void) {{ return 7; }}" for name in names))
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(path), str(source)], check=True)
+
+
+@pytest.mark.parametrize("how", ["search path", "two copies", "one module, two libraries"])
+def test_calls_go_to_the_library_that_made_the_plan(dq, tmp_path, how):
+    """Another libdq.so within the loader's reach -- on its search path, or of a second copy of the package in the process -- is
+    not the one that is called."""
+    package, other = ROOT / "paper_2107_14575_amd", tmp_path / "other"
+    env = dict(os.environ, PYTHONPATH=os.pathsep.join([str(ROOT), str(tmp_path)]))
+    use = "import paper_2107_14575_amd as dq; plan = dq.Plan([5, 300]); print(plan.packed_bytes(4))"
+    if how == "search path":
+        other.mkdir()
+        _stub_library(other / "libdq.so")
+        env["LD_LIBRARY_PATH"] = os.pathsep.join([str(other), os.environ.get("LD_LIBRARY_PATH", "")])
+    else:
+        shutil.copytree(package, other, ignore=shutil.ignore_patterns("libdq.so", "_dqcall.so", "__pycache__"))
+        _stub_library(other / "libdq.so")
+        (shutil.copy if how == "two copies" else os.symlink)(package / "_dqcall.so", other / "_dqcall.so")
+        use = ("import other; other.load_library(); from other import binding; assert binding._call.packed_bytes(1, 4) == 7; " + use +
+               "; assert binding._call.packed_bytes(1, 4) == 7")
+    want = dq.Plan([5, 300]).packed_bytes(4)
+    assert want > 7
+    out = subprocess.run([sys.executable, "-c", use], env=env, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr[-2000:]
+    assert int(out.stdout) == want
