@@ -1,8 +1,9 @@
 // The Python side of the per-iteration entry points: takes the tensors' addresses, strides and row counts and calls the C
 // functions of dq.h, without the GIL.  The functions are those of the library that binding.py has opened, which hands their addresses over
 // (bind): the module itself needs no libdq.so, so it cannot come by another one on the loader's search path or of another copy of the
-// package, whose plans have another form.  Arguments are converted as ctypes converts them (whole numbers by Python int only, cut to
-// the C type; ctypes.ArgumentError otherwise).  Returns the status; binding.py has the names, defaults and checks.
+// package, whose plans have another form.  Arguments are converted as ctypes
+// converts them: plain numbers here, and whatever else it takes (numpy's and torch's numbers, instances of the C types, objects with
+// _as_parameter_) or refuses (ctypes.ArgumentError) by ctypes itself.  Returns the status; binding.py has the names, defaults and checks.
 //
 // A small call is its launch (2.6 us of HIP) and what leads there.  Through ctypes, with the attributes read in Python:
 // quantize_pack 5.5 us, norm 4.8, select_bits 2.0; here 4.6, 4.1, 0.4.  An iteration of 4096 values, M = 8, 33.8 -> 28.9 us, of 2^20, M = 4,
@@ -22,14 +23,16 @@ namespace {
     X(dq_unpack_dequant_reduce_update) X(dq_unpack_dequant_reduce_update_v) X(dq_sign_pack) X(dq_sign_reduce) X(dq_sign_majority) \
     X(dq_select_bits) X(dq_select_bits_linf) X(dq_packed_bytes)
 
+enum { INT32, UINT32, INT64, UINT64, ADDRESS, FLOAT32, FLOAT64, N_KINDS };
+
 // Of one module object: copies of the package that share this file are bound each to their own library.
 struct state {
 #define X(fn) decltype(&::fn) fn;
     DQ_FUNCTIONS(X)
 #undef X
     bool bound;
-    PyObject* argument_error; // ctypes.ArgumentError
-    PyObject *data_ptr, *stride, *size, *zero;
+    PyObject* convert[N_KINDS]; // ctypes functions of one argument, which they return
+    PyObject *data_ptr, *stride, *size, *shape, *zero;
 };
 state* state_of(PyObject* module) { return static_cast<state*>(PyModule_GetState(module)); }
 
@@ -50,48 +53,68 @@ struct taker {
             ok = false;
         }
     }
-    uint64_t bits_of(PyObject* o)
+    PyObject* converted(int kind, PyObject* o) // as ctypes passes it; a new reference
     {
-        if (!PyLong_Check(o)) {
-            PyErr_Format(lib->argument_error, "int expected instead of %s instance", Py_TYPE(o)->tp_name);
-            ok = false;
-            return 0;
-        }
-        return PyLong_AsUnsignedLongLongMask(o); // no error: an int
+        PyObject* value = PyObject_CallOneArg(lib->convert[kind], o);
+        if (!value) ok = false;
+        return value;
     }
-    uint64_t result_of(PyObject* o) // of a tensor's method; takes the reference
+    uint64_t bits_of(int kind, PyObject* o)
     {
+        if (PyLong_Check(o)) return PyLong_AsUnsignedLongLongMask(o); // no error: an int
+        PyObject* value = converted(kind, o);
+        if (!value) return 0;
+        const uint64_t v = PyLong_AsUnsignedLongLongMask(value);
+        Py_DECREF(value);
+        return v;
+    }
+    int64_t int_of(PyObject* o) // int(o); takes the reference
+    {
+        if (o && !PyLong_Check(o)) {
+            PyObject* value = PyNumber_Long(o);
+            Py_DECREF(o);
+            o = value;
+        }
         if (!o) {
             ok = false;
             return 0;
         }
         const uint64_t v = PyLong_AsUnsignedLongLongMask(o);
-        if (v == static_cast<uint64_t>(-1) && PyErr_Occurred()) ok = false;
         Py_DECREF(o);
-        return v;
+        return static_cast<int64_t>(v);
     }
-    uint64_t whole() { return ok ? bits_of(args[at++]) : 0; }
-    int as_int() { return static_cast<int>(whole()); }
-    uint32_t as_u32() { return static_cast<uint32_t>(whole()); }
-    int64_t as_i64() { return static_cast<int64_t>(whole()); }
-    void* address() { return reinterpret_cast<void*>(whole()); } // a handle or stream, an int
-    double real()
+    uint64_t whole(int kind) { return ok ? bits_of(kind, args[at++]) : 0; }
+    int as_int() { return static_cast<int>(whole(INT32)); }
+    uint32_t as_u32() { return static_cast<uint32_t>(whole(UINT32)); }
+    int64_t as_i64() { return static_cast<int64_t>(whole(INT64)); }
+    uint64_t as_u64() { return whole(UINT64); }
+    void* address() { return reinterpret_cast<void*>(whole(ADDRESS)); } // a handle or stream
+    double real(int kind)
     {
         if (!ok) return 0.0;
-        const double v = PyFloat_AsDouble(args[at++]);
-        if (v == -1.0 && PyErr_Occurred()) {
-            PyErr_Clear();
-            PyErr_SetString(lib->argument_error, "a number expected");
-            ok = false;
-        }
+        PyObject* o = args[at++];
+        if (PyFloat_Check(o)) return PyFloat_AS_DOUBLE(o);
+        PyObject* value = converted(kind, o);
+        if (!value) return 0.0;
+        const double v = PyFloat_AsDouble(value);
+        Py_DECREF(value);
         return v;
     }
+    float as_float() { return static_cast<float>(real(FLOAT32)); }
+    double as_double() { return real(FLOAT64); }
     PyObject* object() { return ok ? args[at++] : nullptr; }
     template <typename T>
     T* data_of(PyObject* t) // NULL for None
     {
         if (!ok || t == Py_None) return nullptr;
-        return reinterpret_cast<T*>(result_of(PyObject_CallMethodNoArgs(t, lib->data_ptr)));
+        PyObject* at_address = PyObject_CallMethodNoArgs(t, lib->data_ptr);
+        if (!at_address) {
+            ok = false;
+            return nullptr;
+        }
+        const uint64_t v = bits_of(ADDRESS, at_address);
+        Py_DECREF(at_address);
+        return reinterpret_cast<T*>(v);
     }
     template <typename T>
     T* data()
@@ -108,8 +131,21 @@ struct taker {
     {
         return data_of<T>(object());
     }
-    int64_t stride0(PyObject* t) { return ok ? static_cast<int64_t>(result_of(PyObject_CallMethodOneArg(t, lib->stride, lib->zero))) : 0; }
-    int rows(PyObject* t) { return ok ? static_cast<int>(result_of(PyObject_CallMethodOneArg(t, lib->size, lib->zero))) : 0; }
+    int64_t stride0(PyObject* t) { return ok ? int_of(PyObject_CallMethodOneArg(t, lib->stride, lib->zero)) : 0; }
+    int rows(PyObject* t)
+    {
+        if (!ok) return 0;
+        if (PyObject* size = PyObject_CallMethodOneArg(t, lib->size, lib->zero)) return static_cast<int>(int_of(size));
+        if (!PyErr_ExceptionMatches(PyExc_Exception)) {
+            ok = false;
+            return 0;
+        }
+        PyErr_Clear(); // no size(0), as a tensor has: shape[0]
+        PyObject* shape = PyObject_GetAttr(t, lib->shape);
+        PyObject* first = shape ? PyObject_GetItem(shape, lib->zero) : nullptr;
+        Py_XDECREF(shape);
+        return static_cast<int>(int_of(first));
+    }
 };
 
 template <typename F>
@@ -167,7 +203,7 @@ PyObject* py_quantize_pack(PyObject* module, args_t args, Py_ssize_t n)
     const auto grads = take_matrix<const float>(a);
     const float* norms = a.data<const float>();
     const int b = a.as_int();
-    const uint64_t seed = a.whole();
+    const uint64_t seed = a.as_u64();
     const uint32_t step = a.as_u32(), worker_base = a.as_u32();
     PyObject* out = a.object();
     uint8_t* packed = a.data_of<uint8_t>(out);
@@ -186,7 +222,7 @@ PyObject* py_quantize_pack_v(PyObject* module, args_t args, Py_ssize_t n)
     const auto* widths = static_cast<const dq_widths_t*>(a.address());
     const auto grads = take_matrix<const float>(a);
     const float* norms = a.data<const float>();
-    const uint64_t seed = a.whole();
+    const uint64_t seed = a.as_u64();
     const uint32_t step = a.as_u32(), worker_base = a.as_u32();
     PyObject* out = a.object();
     uint8_t* packed = a.data_of<uint8_t>(out);
@@ -205,7 +241,7 @@ PyObject* py_norm_quantize_pack(PyObject* module, args_t args, Py_ssize_t n)
     const auto* plan = static_cast<const dq_plan_t*>(a.address());
     const auto grads = take_matrix<const float>(a);
     const int b = a.as_int();
-    const uint64_t seed = a.whole();
+    const uint64_t seed = a.as_u64();
     const uint32_t step = a.as_u32(), worker_base = a.as_u32();
     float* norms = a.data<float>();
     PyObject* out = a.object();
@@ -225,7 +261,7 @@ PyObject* py_norm_bracket(PyObject* module, args_t args, Py_ssize_t n)
     taker a(module, args, n, 6);
     const float* norms = a.data<const float>();
     const int64_t count = a.as_i64();
-    const float margin = static_cast<float>(a.real());
+    const float margin = a.as_float();
     float *lo = a.data<float>(), *hi = a.data<float>();
     void* stream = a.address();
     return status_of(a, [&] { return a.lib->dq_norm_bracket(norms, count, margin, lo, hi, stream); });
@@ -240,7 +276,7 @@ PyObject* py_bracketed(PyObject* module, args_t args, Py_ssize_t n)
     const auto grads = take_matrix<const float>(a);
     const float *lo = a.data<const float>(), *hi = a.data<const float>();
     const int b = a.as_int();
-    const uint64_t seed = a.whole();
+    const uint64_t seed = a.as_u64();
     const uint32_t step = a.as_u32(), worker_base = a.as_u32();
     float* norms = a.data<float>();
     PyObject* out = a.object();
@@ -279,7 +315,7 @@ PyObject* py_reduce_update(PyObject* module, args_t args, Py_ssize_t n)
     const auto packed = take_matrix<const uint8_t>(a);
     const float* norms = a.data<const float>();
     const int b = a.as_int();
-    const float eta = static_cast<float>(a.real());
+    const float eta = a.as_float();
     float *x = a.data<float>(), *ghat = a.data_or_null<float>();
     void* stream = a.address();
     return status_of(a, [&] {
@@ -308,7 +344,7 @@ PyObject* py_reduce_update_v(PyObject* module, args_t args, Py_ssize_t n)
     const auto* widths = static_cast<const dq_widths_t*>(a.address());
     const auto packed = take_matrix<const uint8_t>(a);
     const float* norms = a.data<const float>();
-    const float eta = static_cast<float>(a.real());
+    const float eta = a.as_float();
     float *x = a.data<float>(), *ghat = a.data_or_null<float>();
     void* stream = a.address();
     return status_of(a, [&] {
@@ -351,7 +387,7 @@ PyObject* py_select_bits(PyObject* module, args_t args, Py_ssize_t n)
     taker a(module, args, n, 8);
     PyObject* array = a.object();
     const int64_t t = a.as_i64(), T = a.as_i64();
-    const double eps = a.real(), alpha = a.real();
+    const double eps = a.as_double(), alpha = a.as_double();
     const int b_min = a.as_int(), b_max = a.as_int(), linf = a.as_int();
     if (!a.ok) return nullptr;
     Py_buffer view;
@@ -427,18 +463,49 @@ PyMethodDef methods[] = {
     { nullptr, nullptr, 0, nullptr },
 };
 
+template <typename T>
+T same(T value)
+{
+    return value;
+}
+uint64_t number(void* address) { return reinterpret_cast<uint64_t>(address); }
+
+// ctypes.PYFUNCTYPE(result, argument)(fn); nullptr, with an exception set, if that fails or one is set already
+template <typename F>
+PyObject* returning(PyObject* ctypes, const char* result, const char* argument, F* fn)
+{
+    if (PyErr_Occurred()) return nullptr;
+    PyObject* result_type = PyObject_GetAttrString(ctypes, result);
+    PyObject* argument_type = result_type ? PyObject_GetAttrString(ctypes, argument) : nullptr;
+    PyObject* type = argument_type ? PyObject_CallMethod(ctypes, "PYFUNCTYPE", "OO", result_type, argument_type) : nullptr;
+    PyObject* made = type ? PyObject_CallFunction(type, "K", static_cast<unsigned long long>(reinterpret_cast<uintptr_t>(fn))) : nullptr;
+    Py_XDECREF(type);
+    Py_XDECREF(argument_type);
+    Py_XDECREF(result_type);
+    return made;
+}
+
 int fill(PyObject* module)
 {
     state* lib = state_of(module);
     PyObject* ctypes = PyImport_ImportModule("ctypes");
     if (!ctypes) return -1;
-    lib->argument_error = PyObject_GetAttrString(ctypes, "ArgumentError");
+    lib->convert[INT32] = returning(ctypes, "c_int32", "c_int32", &same<int32_t>);
+    lib->convert[UINT32] = returning(ctypes, "c_uint32", "c_uint32", &same<uint32_t>);
+    lib->convert[INT64] = returning(ctypes, "c_int64", "c_int64", &same<int64_t>);
+    lib->convert[UINT64] = returning(ctypes, "c_uint64", "c_uint64", &same<uint64_t>);
+    lib->convert[ADDRESS] = returning(ctypes, "c_uint64", "c_void_p", &number);
+    lib->convert[FLOAT32] = returning(ctypes, "c_float", "c_float", &same<float>);
+    lib->convert[FLOAT64] = returning(ctypes, "c_double", "c_double", &same<double>);
     Py_DECREF(ctypes);
+    for (const PyObject* convert : lib->convert)
+        if (!convert) return -1;
     lib->data_ptr = PyUnicode_InternFromString("data_ptr");
     lib->stride = PyUnicode_InternFromString("stride");
     lib->size = PyUnicode_InternFromString("size");
+    lib->shape = PyUnicode_InternFromString("shape");
     lib->zero = PyLong_FromLong(0);
-    if (!lib->argument_error || !lib->data_ptr || !lib->stride || !lib->size || !lib->zero) return -1;
+    if (!lib->data_ptr || !lib->stride || !lib->size || !lib->shape || !lib->zero) return -1;
     static const char* const functions[] = {
 #define X(fn) #fn,
         DQ_FUNCTIONS(X)
@@ -464,16 +531,18 @@ int fill(PyObject* module)
 
 int visit_state(PyObject* module, visitproc visit, void* arg)
 {
-    if (state* lib = state_of(module)) Py_VISIT(lib->argument_error);
+    if (state* lib = state_of(module))
+        for (PyObject* convert : lib->convert) Py_VISIT(convert);
     return 0;
 }
 int clear_state(PyObject* module)
 {
     if (state* lib = state_of(module)) {
-        Py_CLEAR(lib->argument_error);
+        for (PyObject*& convert : lib->convert) Py_CLEAR(convert);
         Py_CLEAR(lib->data_ptr);
         Py_CLEAR(lib->stride);
         Py_CLEAR(lib->size);
+        Py_CLEAR(lib->shape);
         Py_CLEAR(lib->zero);
         lib->bound = false;
     }

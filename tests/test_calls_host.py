@@ -50,7 +50,7 @@ def test_refusals(dq):
     with pytest.raises(C.ArgumentError):
         call(plan.handle.value, grads, norms, 2.0, 1, 0, 0, packed, stream)
     with pytest.raises(C.ArgumentError):
-        call(plan.handle.value, grads, norms, np.int64(2), 1, 0, 0, packed, stream)
+        call(plan.handle.value, grads, norms, "2", 1, 0, 0, packed, stream)
     with pytest.raises(AttributeError):
         call(plan.handle.value, grads, None, 2, 1, 0, 0, packed, stream)
     with pytest.raises(TypeError):
@@ -96,3 +96,66 @@ def test_calls_go_to_the_library_that_made_the_plan(dq, tmp_path, how):
     out = subprocess.run([sys.executable, "-c", use], env=env, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300)
     assert out.returncode == 0, out.stderr[-2000:]
     assert int(out.stdout) == want
+
+
+class _Parameter:
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+class _Rows:
+    """A matrix that is no torch tensor: data_ptr(), stride() and shape."""
+
+    def __init__(self, tensor):
+        self._tensor, self.shape = tensor, tensor.shape
+
+    def data_ptr(self):
+        return C.c_void_p(self._tensor.data_ptr())
+
+    def stride(self, dim):
+        return self._tensor.stride(dim)
+
+
+@pytest.mark.parametrize("form", [lambda v: v, _Parameter, lambda v: _Parameter(_Parameter(v))])
+def test_arguments_as_ctypes_takes_them(dq, form):
+    """Beside plain numbers: instances of the C types, numpy's and torch's numbers, and objects that stand for one.  Every other type is refused as it is by the
+    function called through ctypes."""
+    lib, plan = dq.load_library(), dq.Plan([5, 300])
+    wanted = plan.packed_bytes(4)
+    assert wanted == lib.dq_packed_bytes(plan.handle, 4)
+    for b in (4, C.c_int(4), C.c_int32(4), 4 + (1 << 32), np.int64(4), np.uint8(4), np.array(4), torch.tensor(4)):
+        assert plan.packed_bytes(form(b)) == wanted == lib.dq_packed_bytes(plan.handle, form(b))
+    for b in (4.0, "4", b"4", None, C.c_uint64(4), C.c_float(4.0), np.float32(4), np.array(4.0), [4]):
+        for call in (plan.packed_bytes, lambda v: lib.dq_packed_bytes(plan.handle, v)):
+            with pytest.raises(C.ArgumentError):
+                call(form(b))
+    norms = np.linspace(0.1, 1.0, 6, dtype=np.float32).reshape(2, 3)
+    rule = dq.select_bits(norms, 5, 20, 0.5, 0.97, 1, 8)
+    assert dq.select_bits(norms, form(C.c_int64(5)), form(20), form(C.c_double(0.5)), form(np.float64(0.97)), form(C.c_int(1)), form(np.int32(8))) == rule
+    for one in (1, np.float32(1), np.int64(1), np.array(1.0), torch.tensor(1.0)):
+        assert dq.select_bits(norms, 5, 20, form(one), 0.97, 1, 8) == dq.select_bits(norms, 5, 20, 1.0, 0.97, 1, 8)
+    for eps in ("0.5", None, C.c_float(0.5), 1 << 2000):
+        with pytest.raises(C.ArgumentError):
+            dq.select_bits(norms, 5, 20, form(eps), 0.97, 1, 8)
+    plan.close()
+
+
+def test_other_matrices_and_addresses(dq):
+    """What only has data_ptr(), stride() and shape is a matrix; a NULL plan or stream is None, a handle may be a c_void_p."""
+    from paper_2107_14575_amd import binding
+    plan = dq.Plan([5, 300])
+    invalid = -1
+    grads = _Rows(torch.zeros((2, plan.padded_elems)))
+    packed = _Rows(torch.zeros((2, plan.packed_bytes(8)), dtype=torch.uint8))
+    norms = _Rows(torch.zeros((2, 2)))
+    call = binding._calls()
+    for handle in (None, plan.handle, _Parameter(plan.handle)):
+        assert call.quantize_pack(handle, grads, norms, C.c_int(9), C.c_uint64(1), C.c_uint32(0), 0, packed, None) == invalid
+        assert call.quantize_pack(handle, grads, norms, np.int64(9), np.uint64(1 << 63), np.int64(-1), torch.tensor(0), packed, None) == invalid
+        assert call.reduce_update(handle, packed, norms, 9, C.c_float(0.1), norms, None, C.c_void_p(0)) == invalid
+    assert call.packed_bytes(plan.handle, 4) == plan.packed_bytes(4)
+    with pytest.raises(AttributeError):
+        call.quantize_pack(plan.handle, torch.zeros(3).numpy(), norms, 9, 1, 0, 0, packed, None)
+    with pytest.raises(C.ArgumentError):
+        call.quantize_pack(plan.handle, grads, norms, 9, C.c_uint32(1), 0, 0, packed, None)
+    plan.close()
