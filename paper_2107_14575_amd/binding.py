@@ -63,7 +63,7 @@ def load_library():
     if missing:
         raise ImportError(
             f"{missing[0]} is missing: build it with `python -m paper_2107_14575_amd.build` "
-            "(or __graft_entry__.build()); there is no fallback path")
+            "(or __graft_entry__.build()); _dqcall.so takes a C++ compiler and Python's headers; there is no fallback path")
     L = C.CDLL(_LIB_PATH)
     vp, i64, i32, f32p = C.c_void_p, C.c_int64, C.c_int32, C.POINTER(C.c_float)
     L.dq_plan_create.argtypes = [C.POINTER(i64), i32, C.POINTER(vp)]

@@ -6,6 +6,7 @@ import os
 import subprocess
 import sysconfig
 import tempfile
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -34,14 +35,17 @@ def build_calls(verbose: bool = False) -> str:
            "-I", sysconfig.get_paths()["include"], "-o", CALL_PATH, os.path.join(CSRC, "dq_python.cpp")]
     if verbose:
         print(" ".join(cmd), flush=True)
+    if os.path.exists(CALL_PATH):
+        os.remove(CALL_PATH)  # never one of an earlier build beside a new library
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if res.returncode != 0:
-        raise RuntimeError("g++ failed:\n" + res.stdout)
+        raise RuntimeError(f"{cmd[0]} failed:\n{res.stdout}")
     return CALL_PATH
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile every HIP source into libdq.so, and the calls from Python; always compiles."""
+    """Compile every HIP source into libdq.so, and the calls from Python; always compiles.  The C library stands by itself: if the
+    calls cannot be compiled (they take a C++ compiler and Python's headers), that is a warning, and importing them an error."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     include = ["-I", os.path.join(_ROOT, "include"), "-I", CSRC]
 
@@ -63,7 +67,10 @@ def build_library(verbose: bool = False) -> str:
         with ThreadPoolExecutor(len(jobs)) as pool:
             list(pool.map(lambda job: run([hipcc, *flags, *include, "-c", job[0], "-o", job[1]]), jobs))
         run([hipcc, *HIPCC_FLAGS, "-o", LIB_PATH, *(obj for _, obj in jobs)])
-    build_calls(verbose)
+    try:
+        build_calls(verbose)
+    except (RuntimeError, OSError) as e:
+        warnings.warn(f"no {os.path.basename(CALL_PATH)}, so no calls from Python: {e}", RuntimeWarning, stacklevel=2)
     return LIB_PATH
 
 

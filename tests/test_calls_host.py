@@ -159,3 +159,24 @@ def test_other_matrices_and_addresses(dq):
     with pytest.raises(C.ArgumentError):
         call.quantize_pack(plan.handle, grads, norms, 9, C.c_uint32(1), 0, 0, packed, None)
     plan.close()
+
+
+def test_library_builds_without_what_its_python_calls_need(tmp_path, monkeypatch):
+    """The C library needs hipcc alone.  Without a C++ compiler or Python's headers it is built all the same, with a warning, and no
+    module of an earlier build is left beside it."""
+    from paper_2107_14575_amd import build
+    source = tmp_path / "one.hip"
+    source.write_text('extern "C" int dq_one(void) { return 1; }\n')
+    monkeypatch.setattr(build, "sources", lambda: [str(source)])
+    monkeypatch.setattr(build, "LIB_PATH", str(tmp_path / "libdq.so"))
+    monkeypatch.setattr(build, "CALL_PATH", str(tmp_path / "_dqcall.so"))
+    for compiler in (str(tmp_path / "no-such-compiler"), "false"):
+        monkeypatch.setenv("CXX", compiler)
+        (tmp_path / "_dqcall.so").write_bytes(b"of an earlier build")
+        with pytest.warns(RuntimeWarning, match="_dqcall.so"):
+            assert build.build_library() == str(tmp_path / "libdq.so")
+        assert C.CDLL(str(tmp_path / "libdq.so")).dq_one() == 1
+        assert not (tmp_path / "_dqcall.so").exists()
+        with pytest.raises((RuntimeError, OSError)):
+            build.build_calls()
+        (tmp_path / "libdq.so").unlink()
