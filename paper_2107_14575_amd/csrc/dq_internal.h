@@ -33,7 +33,11 @@ __device__ __forceinline__ dq_chunk_tensor dq_load_chunk_tensor(const dq_chunk_t
     return dq_chunk_tensor{ static_cast<int32_t>(static_cast<uint32_t>(v)), static_cast<int32_t>(v >> 32) };
 }
 
-constexpr int DQ_ARRIVED_SEGS = 512;
+// Up to this many workgroups the norms take one launch (k_norm_partial<., true>): a small call is its launches.  Norms, quantize and
+// reduce, us: 5000 values, M = 4 16.7 -> 13.3 (100 000, 100 workgroups 16.8 -> 13.2; 2^19, M = 1, 128 of them 16.7 -> 13.2), with the rule on the
+// device 22.8 -> 19.4, with it on the host 32.2 -> 29.9.  Every arrival writes its XCD's cache back, one after the other, some
+// 50 ns each: 200 workgroups 16.5 -> 15.4, 400 16.8 -> 19.8, 1024 16.5 -> 36.
+constexpr int DQ_ARRIVE_WORKGROUPS = 160;
 
 struct dq_plan {
     int32_t n_seg;
@@ -63,9 +67,9 @@ struct dq_plan {
     int32_t* d_seg_item_begin;     // [n_seg + 1] items of segment l are [begin[l], begin[l+1])
     int32_t* d_finish_seg;         // [n_finish] segments whose norm needs the finishing kernel: all but
     int32_t n_finish;              //            those of exactly one item (the first kernel finishes these)
-    int32_t most_items;            // the most items of one segment
-    // [DQ_MAX_WORKERS][n_seg] items of a segment that have arrived, zero between calls; null for more than DQ_ARRIVED_SEGS
-    // segments.  The one part of a plan that a kernel writes: only for calls on the default stream, which run one after the other
+    // [DQ_ARRIVE_WORKGROUPS], of which [M][n_seg] are used: items of a segment that have arrived, zero between calls; null where one
+    // worker has more items than that or a segment none (every segment having one, M * n_seg counters are no more than M * n_items).
+    // The one part of a plan that a kernel writes: only for calls on the default stream, which run one after the other
     // whatever thread makes them and cannot be captured (see dq_norm.hip).
     uint32_t* d_arrived;
 };

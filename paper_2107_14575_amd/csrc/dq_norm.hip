@@ -70,11 +70,12 @@ __device__ __forceinline__ float larger(float m, float x)
 }
 
 // ARRIVE: no second pass.  The workgroup that finds itself the last of its segment's (a counter in the plan, put back to zero by it)
-// adds the partials: lane l of its first wavefront stands for lanes l, l + 64, ... of k_norm_finish's, the wave sums and their
-// total in the same order, so the same bits.  The counter is released and acquired at device scope: an XCD's cache is not another's.
-// The default stream only, where no two calls of a plan overlap.
+// adds the n <= DQ_ARRIVE_WORKGROUPS partials: its first wavefront stands for each of k_norm_finish's first three in turn (the others
+// have nothing to add there), the wave sums and their total in the same order, so the same bits.  The counter is released and
+// acquired at device scope: an XCD's cache is not another's.  The default stream only, where no two calls of a plan overlap.
 constexpr int FINISH_THREADS = 1024;
-constexpr int ARRIVE_ITEMS = 2 * FINISH_THREADS; // of one segment
+constexpr int ARRIVE_WAVES = (DQ_ARRIVE_WORKGROUPS + 63) / 64;
+static_assert(DQ_ARRIVE_WORKGROUPS <= FINISH_THREADS, "one partial to a lane of k_norm_finish");
 template <bool LINF>
 __device__ __forceinline__ void norm_arrive(double total, void* partials, int64_t row, int item_id, int begin, int n, int lane,
                                             uint32_t* arrived, float* __restrict__ norm)
@@ -90,25 +91,16 @@ __device__ __forceinline__ void norm_arrive(double total, void* partials, int64_
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     p += begin;
     T sum = 0;
-    for (int v = 0; v < FINISH_THREADS / 64 && 64 * v < n; v += 4) {
-        T acc[4];
+    T a[ARRIVE_WAVES];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = 64 * (v + k) + lane;
-            const T a = i < n ? p[i] : T(0), b = i + FINISH_THREADS < n ? p[i + FINISH_THREADS] : T(0);
-            if constexpr (LINF)
-                acc[k] = b > a ? b : a;
-            else
-                acc[k] = a + b;
-        }
+    for (int k = 0; k < ARRIVE_WAVES; ++k) a[k] = 64 * k + lane < n ? p[64 * k + lane] : T(0);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if constexpr (LINF) {
-                const float m = wave_max(acc[k]);
-                sum = m > sum ? m : sum;
-            } else {
-                sum += wave_sum(acc[k]);
-            }
+    for (int k = 0; k < ARRIVE_WAVES; ++k) {
+        if constexpr (LINF) {
+            const float m = wave_max(a[k]);
+            sum = m > sum ? m : sum;
+        } else {
+            sum += wave_sum(a[k]);
         }
     }
     if (lane == 0) {
@@ -382,12 +374,6 @@ extern "C" int dq_norm_static_scratch(const dq_plan_t* plan, const float* grads_
 
 namespace {
 
-// Up to this many workgroups the norms take one launch (k_norm_partial<., true>): a small call is its launches.  Norms, quantize and
-// reduce, us: 5000 values, M = 4 16.7 -> 13.3 (100 000, 100 workgroups 16.8 -> 13.2; 2^19, M = 1, 128 of them 16.7 -> 13.2), with the rule on the
-// device 22.8 -> 19.4, with it on the host 32.2 -> 29.9.  Every arrival writes its XCD's cache back, one after the other, some
-// 50 ns each: 200 workgroups 16.5 -> 15.4, 400 16.8 -> 19.8, 1024 16.5 -> 36.
-constexpr int64_t ARRIVE_WORKGROUPS = 160;
-
 int norm_entry(bool linf, const dq_plan_t* plan, const float* grads_dev, int64_t worker_stride_elems, int M,
                float* norms_dev, void* workspace_dev, void* hip_stream)
 {
@@ -425,9 +411,8 @@ int norm_entry(bool linf, const dq_plan_t* plan, const float* grads_dev, int64_t
         hipLaunchKernelGGL(kernel, grid_items, dim3(256), 0, stream, grads_dev, worker_stride_elems, plan->d_items, plan->n_items,
                            workspace_dev, plan->d_seg_item_begin, plan->n_seg, norms_dev, plan->d_arrived);
     };
-    // segments without elements have no items: the second pass writes their zeros
-    const bool arrive = stream == nullptr && plan->d_arrived && plan->n_cseg == plan->n_seg && plan->most_items <= ARRIVE_ITEMS &&
-                        static_cast<int64_t>(M) * plan->n_items <= ARRIVE_WORKGROUPS;
+    // (a segment without elements has no items: the second pass writes its zero, and such plans have no counters)
+    const bool arrive = stream == nullptr && plan->d_arrived && static_cast<int64_t>(M) * plan->n_items <= DQ_ARRIVE_WORKGROUPS;
     if (arrive) {
         if (linf)
             partial(k_norm_partial<true, true>);

@@ -96,6 +96,7 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
     std::vector<int32_t> finish_seg;
     table_stage stage;
     size_t at[10] = {};
+    bool counted = false;
     try {
         // every allocation of the host tables happens in here: std::bad_alloc never leaves the call
         granule_cseg.resize(static_cast<size_t>(total / DQ_GRANULE));
@@ -143,10 +144,8 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
         at[6] = stage.add(items);
         at[7] = stage.add(item_begin);
         at[8] = stage.add(finish_seg);
-        for (int32_t l = 0; l < n_seg; ++l)
-            if (item_begin[l + 1] - item_begin[l] > p->most_items) p->most_items = item_begin[l + 1] - item_begin[l];
-        if (n_seg <= DQ_ARRIVED_SEGS)
-            at[9] = stage.add(std::vector<uint32_t>(static_cast<size_t>(n_seg) * DQ_MAX_WORKERS, 0u));
+        counted = cseg_seg.size() == static_cast<size_t>(n_seg) && items.size() <= DQ_ARRIVE_WORKGROUPS;
+        if (counted) at[9] = stage.add(std::vector<uint32_t>(DQ_ARRIVE_WORKGROUPS, 0u));
     } catch (const std::bad_alloc&) {
         dq_plan_destroy(p);
         return DQ_ERR_ALLOC;
@@ -174,7 +173,7 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
     p->d_items = reinterpret_cast<dq_norm_item*>(base + at[6]);
     p->d_seg_item_begin = reinterpret_cast<int32_t*>(base + at[7]);
     p->d_finish_seg = reinterpret_cast<int32_t*>(base + at[8]);
-    if (n_seg <= DQ_ARRIVED_SEGS) p->d_arrived = reinterpret_cast<uint32_t*>(base + at[9]);
+    if (counted) p->d_arrived = reinterpret_cast<uint32_t*>(base + at[9]);
     p->device = dev;
     dq_norm_static_scratch_prepare(dev); // set-up time: the allocation-free entry point then only launches
     p->n_cseg = static_cast<int32_t>(cseg_seg.size());
