@@ -80,6 +80,23 @@ def test_transformer_layout_full_size(dq, oracle):
     _sign_step(dq, oracle, seg_len, grads, None)
 
 
+MI = 1 << 20
+
+
+@pytest.mark.parametrize("seg_len,M", [([12 * MI - 128], 2), ([12 * MI - 51], 2), ([12 * MI, 77], 1),
+                                       ([20 * MI - 300, 300], 2), ([20 * MI - 300, 128, 77], 2),
+                                       ([20 * MI - 300, 300, 5], 2),
+                                       ([MI + 77, 300, 2 * MI - 384, 5, MI // 2 - 256 - 51], 32),
+                                       ([MI + 77, 300, 2 * MI - 384, 5, MI // 2 - 256 - 179], 32)])
+def test_messages_on_both_sides_of_the_lines(dq, oracle, seg_len, M):
+    """Written through to the last-level cache up to 20 * 2^20 elements, from 12 * 2^20 on or from 14 MB of messages; with the
+    streaming hint otherwise.  Ends of a layout that leave the last tile part empty, canaries behind every message."""
+    gen = torch.Generator().manual_seed(len(seg_len) + M)
+    grads = torch.randn((M, sum((n + 127) // 128 * 128 for n in seg_len)), generator=gen)
+    scales = torch.rand((M, len(seg_len)), generator=gen).numpy()
+    _sign_step(dq, oracle, seg_len, grads, scales)
+
+
 def test_argument_checks(dq):
     plan = dq.Plan([1000])
     g = torch.zeros((2, plan.padded_elems), dtype=torch.float32, device="cuda")
