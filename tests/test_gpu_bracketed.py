@@ -285,7 +285,8 @@ def test_norms_finished_beside_the_settling(dq, oracle, chunks, linf):
     """Up to 6144 (worker, chunk) pairs, no tensor over more than 1024 chunks, the settling kernel adds the partial sums itself:
     tensors that end and begin inside one chunk beside whole ones, their norms inside their brackets and outside, and the same
     norms bit for bit as from the kernel that adds them for more workers."""
-    seg_len = [chunks * 4096 - 300, 150, 500, 4096 + 77, 0, 60, 2 * 4096 - 900]
+    # the last tensor is there so that 64 workers have more than 6144 pairs with the shortest of the others too
+    seg_len = [chunks * 4096 - 300, 150, 500, 4096 + 77, 0, 60, 2 * 4096 - 900, 97 * 4096]
     gen = torch.Generator().manual_seed(chunks)
     padded = sum((n + 127) // 128 * 128 for n in seg_len)
     grads = torch.randn((2, padded), generator=gen) * 1e-2
@@ -293,7 +294,9 @@ def test_norms_finished_beside_the_settling(dq, oracle, chunks, linf):
         settled, redone, total = _run(dq, oracle, seg_len, grads, b, lo, hi, linf=linf)
         assert total <= 6144 and (redone > 0 or lo < 1.0)
     plan = dq.Plan(seg_len)
-    many = min(64, 6144 // ((plan.padded_elems + 4095) // 4096) + 1)
+    n_chunks = (plan.padded_elems + 4095) // 4096
+    many = min(64, 6144 // n_chunks + 1)
+    assert n_chunks <= 6144 < many * n_chunks  # one form for one worker (but for 1025 chunks), the other for many
     ref = gpu_norm(dq, plan, grads.cuda(), linf)
     got = []
     for M in (1, many):
