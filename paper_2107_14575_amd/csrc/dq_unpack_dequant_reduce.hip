@@ -1202,7 +1202,9 @@ inline bool ur_stream(const dq_plan* plan, int M, int b)
 // Whether the model passes through with the hint: a large one would not be in the cache when it is next read, and takes the
 // messages' place.  Iterations with b = 2 and 8, us, model left in the cache / passing through: 2^24, M = 2 73 / 77, M = 8 (b = 8) 233 / 230;
 // 21 M, M = 2 92 / 95, M = 32 969 / 929; 2^25, M = 2 149 / 141, M = 32 1500 / 1474; 2^26, M = 2 288 / 271.  The reduce alone: 22 M, M = 16 b = 8
-// 91 / 97, 28 M 134 / 125.  Left plainly, in the XCDs' own caches, models up to 2^24 took 1 to 5 % of an iteration longer.
+// 91 / 97, 28 M 134 / 125.  Where the line lies depends on the workers too (with 32 of them passing through gains from 21 M on already); by
+// elements alone it lies where few and many are even.  Left plainly, in the XCDs' own caches, models of 14 to 24 M took 1 to 9 % of an
+// iteration longer (21 M, b = 2, M = 2 113 us against 105, M = 32 969 against 946).
 constexpr int64_t UR_ONCE_ELEMS = 24 << 20;
 inline bool ur_model_once(const dq_plan* plan) { return plan->padded_elems > UR_ONCE_ELEMS; }
 
