@@ -39,6 +39,13 @@ __device__ __forceinline__ dq_chunk_tensor dq_load_chunk_tensor(const dq_chunk_t
 // 50 ns each: 200 workgroups 16.5 -> 15.4, 400 16.8 -> 19.8, 1024 16.5 -> 36.
 constexpr int DQ_ARRIVE_WORKGROUPS = 160;
 
+// Kernels that stream the gradient keep more requests in flight than the memory needs when all the workgroups that fit a CU are resident, and
+// lose some of its rate.  A launch of many rounds of workgroups asks for so much LDS that fewer are: DQ_LDS_PER_CU / n less what rounding takes.
+constexpr int64_t DQ_LDS_PER_CU = 160 * 1024;
+// Four rounds of 2048: iterations with 8192 workgroups a pass 73.6 -> 73.2 us, with 16 000 to 82 000 1 to 2.5 % less, with 4300 0.8 % more.
+constexpr int64_t DQ_MANY_WORKGROUPS = 8192;
+inline constexpr size_t dq_lds_for(int per_cu) { return static_cast<size_t>(DQ_LDS_PER_CU / per_cu - 512); }
+
 struct dq_plan {
     int32_t n_seg;
     int64_t padded_elems; // D'

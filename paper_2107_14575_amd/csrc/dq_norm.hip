@@ -69,6 +69,17 @@ __device__ __forceinline__ float larger(float m, float x)
     return a > m ? a : m;
 }
 
+// A partial goes through the XCD's own cache to the last-level one (THROUGH): neighbours come from other XCDs, and a plain store leaves the
+// same line dirty, in part, in several of them.  2^26 values, M = 16 633 -> 610 us for such a pass, 22 000 and 50 000 workgroups the same either way.
+template <bool THROUGH, typename T>
+__device__ __forceinline__ void store_partial(T* at, T v)
+{
+    if constexpr (THROUGH)
+        __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        *at = v;
+}
+
 // ARRIVE: no second pass.  The workgroup that finds itself the last of its segment's (a counter in the plan, put back to zero by it)
 // adds the n <= DQ_ARRIVE_WORKGROUPS partials: its first wavefront stands for each of k_norm_finish's first three in turn (the others
 // have nothing to add there), the wave sums and their total in the same order, so the same bits.  The counter is released and
@@ -109,7 +120,7 @@ __device__ __forceinline__ void norm_arrive(double total, void* partials, int64_
     }
 }
 
-template <bool LINF, bool ARRIVE>
+template <bool LINF, bool ARRIVE, bool THROUGH>
 __global__ __launch_bounds__(256) void k_norm_partial(const float* __restrict__ grads,
                                                       int64_t worker_stride,
                                                       const dq_norm_item* __restrict__ items,
@@ -163,7 +174,7 @@ __global__ __launch_bounds__(256) void k_norm_partial(const float* __restrict__ 
             if (seg_item_begin[item.seg + 1] - seg_item_begin[item.seg] == 1)
                 norms[static_cast<int64_t>(w) * n_seg + item.seg] = top;
             else
-                static_cast<float*>(partial_out)[static_cast<int64_t>(w) * n_items + item_id] = top;
+                store_partial<THROUGH>(static_cast<float*>(partial_out) + static_cast<int64_t>(w) * n_items + item_id, top);
         }
         return;
     }
@@ -199,7 +210,7 @@ __global__ __launch_bounds__(256) void k_norm_partial(const float* __restrict__ 
         if (seg_item_begin[item.seg + 1] - seg_item_begin[item.seg] == 1)
             norms[static_cast<int64_t>(w) * n_seg + item.seg] = static_cast<float>(sqrt(total));
         else
-            partial[static_cast<int64_t>(w) * n_items + item_id] = total;
+            store_partial<THROUGH>(partial + static_cast<int64_t>(w) * n_items + item_id, total);
     }
 }
 
@@ -407,25 +418,35 @@ int norm_entry(bool linf, const dq_plan_t* plan, const float* grads_dev, int64_t
         return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
     }
     const dim3 grid_items(plan->n_items, M), grid_segs(plan->n_finish, M);
-    auto partial = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid_items, dim3(256), 0, stream, grads_dev, worker_stride_elems, plan->d_items, plan->n_items,
+    auto partial = [&](auto kernel, size_t lds = 0) {
+        hipLaunchKernelGGL(kernel, grid_items, dim3(256), lds, stream, grads_dev, worker_stride_elems, plan->d_items, plan->n_items,
                            workspace_dev, plan->d_seg_item_begin, plan->n_seg, norms_dev, plan->d_arrived);
     };
     // (a segment without elements has no items: the second pass writes its zero, and such plans have no counters)
     const bool arrive = stream == nullptr && plan->d_arrived && static_cast<int64_t>(M) * plan->n_items <= DQ_ARRIVE_WORKGROUPS;
+    // Six workgroups per CU where eight fit: norm, rule, quantize and reduce, ResNet-18 shape, M = 8 174.9 -> 174.1 us, transformer shape, M = 16 345.3 -> 343.4;
+    // five lose 3 to 4 %, and calls of few rounds lose by six (3 M values, M = 5 33.1 -> 33.3).
+    const bool many = static_cast<int64_t>(M) * plan->n_items >= DQ_MANY_WORKGROUPS;
+    const size_t six = dq_lds_for(6);
     if (arrive) {
         if (linf)
-            partial(k_norm_partial<true, true>);
+            partial(k_norm_partial<true, true, false>);
         else
-            partial(k_norm_partial<false, true>);
+            partial(k_norm_partial<false, true, false>);
     } else if (linf) {
-        if (plan->n_items > 0) partial(k_norm_partial<true, false>);
+        if (many)
+            partial(k_norm_partial<true, false, true>, six);
+        else if (plan->n_items > 0)
+            partial(k_norm_partial<true, false, false>);
         if (plan->n_finish > 0)
             hipLaunchKernelGGL(k_norm_linf_finish, grid_segs, dim3(FINISH_THREADS), 0, stream,
                                static_cast<const float*>(workspace_dev), plan->n_items, plan->d_seg_item_begin,
                                plan->d_finish_seg, plan->n_seg, norms_dev);
     } else {
-        if (plan->n_items > 0) partial(k_norm_partial<false, false>);
+        if (many)
+            partial(k_norm_partial<false, false, true>, six);
+        else if (plan->n_items > 0)
+            partial(k_norm_partial<false, false, false>);
         if (plan->n_finish > 0)
             hipLaunchKernelGGL(k_norm_finish, grid_segs, dim3(FINISH_THREADS), 0, stream,
                                static_cast<const double*>(workspace_dev), plan->n_items, plan->d_seg_item_begin,
