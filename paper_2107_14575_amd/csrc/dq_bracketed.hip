@@ -57,14 +57,20 @@ __device__ __forceinline__ uint32_t level_of_s(float v, float scale, float S, ui
 // eight elements the kernels needed 85 to 88 registers for the random numbers kept across the second look (five wavefronts
 // per SIMD); so they need 70 to 72 (seven): 2^24 values, M = 16, b = 2 254 -> 245 us, ResNet-18 shape, M = 8, b = 3
 // 105 -> 97.
+// B: the width, 0 where it is a value.
+template <int B>
 __device__ __forceinline__ void record_open(uint32_t open, const float4 x, const int b, const uint32_t e, uint32_t* count,
                                             dq_bracket_block* __restrict__ blk, uint32_t& lv)
 {
     const uint32_t field = (1u << b) - 1u;
-    open &= static_cast<uint32_t>((static_cast<uint64_t>(1) << (4 * b)) - 1u); // each turn clears one of four fields: at most four turns
+    open &= quad_fields<B>(b); // each turn clears one of four fields: at most four turns
     while (open != 0) {
         const int bit = __builtin_ctz(open);
-        const uint32_t k = (bit >= b ? 1u : 0u) + (bit >= 2 * b ? 1u : 0u) + (bit >= 3 * b ? 1u : 0u);
+        uint32_t k; // bit / b, for bits below 32
+        if constexpr (B > 0)
+            k = static_cast<uint32_t>(bit) * ((256 + (B > 0 ? B : 1) - 1) / (B > 0 ? B : 1)) >> 8;
+        else
+            k = (bit >= b ? 1u : 0u) + (bit >= 2 * b ? 1u : 0u) + (bit >= 3 * b ? 1u : 0u);
         const uint32_t keep = ~(field << (k * b));
         const float lo = (k & 1u) ? x.y : x.x, hi = (k & 1u) ? x.w : x.z;
         const uint32_t slot = atomicAdd(count, 1u);
@@ -145,7 +151,10 @@ __device__ __forceinline__ void bracketed_one_tensor(const float4 (&x)[2][2], fl
     // the zero path (norm below DQ_MIN_NORM) is not monotone against the rest: no bracket across it
     const bool usable = lo >= DQ_MIN_NORM && hi >= lo && hi <= 3.0e38f; // false for NaN; the same for all lanes
     if (usable) {
-        const float scale_hi = S / lo, scale_lo = S / hi;
+        // both in one division, a half of the wavefront each
+        const float scales = S / (lane < 32u ? lo : hi);
+        const float scale_hi = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scales), 0));
+        const float scale_lo = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scales), 32));
         const uint32_t quad_lo0 = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 2);
         const uint32_t quad_hi = static_cast<uint32_t>(static_cast<uint64_t>(chunk0) >> 34);
         const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * 2);
@@ -154,19 +163,19 @@ __device__ __forceinline__ void bracketed_one_tensor(const float4 (&x)[2][2], fl
             const uint32_t tile0 = wave0 + it * QP_WAVE_TILE;
             const uint32_t e0 = tile0 + (lane & 31u) * 8u + (lane >> 5) * 4u; // elements e0.. and e0 + 256..
             const uint32_t quad = quad_lo0 + (e0 >> 2);
-            uint32_t sg[2], lv[2], sign;
+            uint32_t lv[2], sign;
             uint64_t level;
             float t[8];
             // levels at the low end of the bracket: the largest any norm inside it can give
             const qp_range range = quantize_quads<B>(x[it][0], x[it][1], scale_hi, 0.0f, 0, quad, quad + 64u, quad_hi, worker,
-                                                     step, key0, key1, sg, lv, t);
-            if (__any((lv[0] | lv[1]) != 0)) { // a zero at the low end is a zero everywhere in the bracket
+                                                     step, key0, key1, lv, t);
+            if (__any(((lv[0] | lv[1]) & quad_fields<B>(B)) != 0)) { // a zero at the low end is a zero everywhere in the bracket
                 uint32_t lv_lo[2];
                 quantize_again<B>(range, x[it][0], x[it][1], scale_lo, 0.0f, 0, t, lv_lo);
-                record_open(lv[0] ^ lv_lo[0], x[it][0], B, e0, &state->count, blk, lv[0]);
-                record_open(lv[1] ^ lv_lo[1], x[it][1], B, e0 + 256, &state->count, blk, lv[1]);
+                record_open<B>(lv[0] ^ lv_lo[0], x[it][0], B, e0, &state->count, blk, lv[0]);
+                record_open<B>(lv[1] ^ lv_lo[1], x[it][1], B, e0 + 256, &state->count, blk, lv[1]);
             }
-            quantize_exchange<B>(sg, lv, 0, sign, level);
+            quantize_exchange<B>(x[it][0], x[it][1], lv, 0, sign, level);
             const uint32_t at = (tile0 >> 3) + lane;
             lds_sign[at] = static_cast<uint8_t>(sign);
             stage_bytes<B>(&lds_level[at * B], level);
@@ -212,7 +221,7 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
     constexpr int TILES = 2;
     constexpr int CHUNK = DQ_CHUNK;
     constexpr float S = static_cast<float>((1 << B) - 1);
-    constexpr uint32_t quad_fields = static_cast<uint32_t>((static_cast<uint64_t>(1) << (4 * B)) - 1u);
+    constexpr uint32_t FIELDS = quad_fields<B>(B);
 
     __shared__ float lds_scale_hi[DQ_CHUNK_GRANULES]; // s / lo: the larger scale
     __shared__ float lds_scale_lo[DQ_CHUNK_GRANULES]; // s / hi
@@ -324,16 +333,18 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
         if (e < n_elems) {
             const uint32_t quad = quad_lo0 + (e >> 2);
             // levels at the low end of the bracket: the largest any norm inside it can give
-            uint32_t sg[2], lv[2];
+            uint32_t lv[2];
             float t[8];
             const qp_range range = quantize_quads<B>(x[it][0], x[it][1], lds_scale_hi[local[it]], 0.0f, 0, quad, quad + 1u,
-                                                     quad_hi, worker, step, key0, key1, sg, lv, t);
+                                                     quad_hi, worker, step, key0, key1, lv, t);
+            lv[0] &= FIELDS;
+            lv[1] &= FIELDS;
             const int nv = valid[it] >= QP_PER_LANE ? QP_PER_LANE : (valid[it] > 0 ? valid[it] : 0);
-            uint32_t sign = quantize_sign_byte(sg[0], sg[1]);
+            uint32_t sign = quantize_sign_byte(x[it][0], x[it][1]);
             if (nv < QP_PER_LANE) { // the tensor ends inside (or before) this lane's eight elements
                 sign &= (1u << nv) - 1u;
                 const uint64_t fields = (static_cast<uint64_t>(1) << (nv * B)) - 1u;
-                lv[0] &= static_cast<uint32_t>(fields) & quad_fields;
+                lv[0] &= static_cast<uint32_t>(fields);
                 lv[1] &= static_cast<uint32_t>(fields >> (4 * B));
             }
             if ((lv[0] | lv[1]) != 0) { // a zero at the low end is a zero everywhere in the bracket
@@ -341,8 +352,8 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_bracketed(
                 quantize_again<B>(range, x[it][0], x[it][1], lds_scale_lo[local[it]], 0.0f, 0, t, lv_lo);
                 // (lv is zero past the tensor's end, so is what lv_lo has there once masked)
                 const uint64_t fields = nv < QP_PER_LANE ? (static_cast<uint64_t>(1) << (nv * B)) - 1u : ~static_cast<uint64_t>(0);
-                record_open(lv[0] ^ (lv_lo[0] & static_cast<uint32_t>(fields) & quad_fields), x[it][0], B, e, &lds_count, blk, lv[0]);
-                record_open(lv[1] ^ (lv_lo[1] & static_cast<uint32_t>(fields >> (4 * B))), x[it][1], B, e + 4u, &lds_count, blk, lv[1]);
+                record_open<B>(lv[0] ^ (lv_lo[0] & static_cast<uint32_t>(fields) & FIELDS), x[it][0], B, e, &lds_count, blk, lv[0]);
+                record_open<B>(lv[1] ^ (lv_lo[1] & static_cast<uint32_t>(fields >> (4 * B)) & FIELDS), x[it][1], B, e + 4u, &lds_count, blk, lv[1]);
             }
             const uint64_t level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * B));
             lds_sign[e >> 3] = static_cast<uint8_t>(sign);
@@ -502,19 +513,19 @@ __global__ __launch_bounds__(QP_THREADS, 7) void k_quantize_pack_bracketed_v(
         if (e < n_elems) {
             const float S = lds_levels[local[it]];
             const int b = lds_b[local[it]];
-            const uint32_t quad_fields = static_cast<uint32_t>((static_cast<uint64_t>(1) << (4 * b)) - 1u);
+            const uint32_t FIELDS = quad_fields<0>(b);
             const uint32_t quad = quad_lo0 + (e >> 2);
-            uint32_t sg[2], lv[2];
+            uint32_t lv[2];
             float t[8];
             const qp_range range = quantize_quads<0>(x[it][0], x[it][1], lds_scale_hi[local[it]], S, b, quad, quad + 1u,
-                                                     quad_hi, worker, step, key0, key1, sg, lv, t);
+                                                     quad_hi, worker, step, key0, key1, lv, t);
             const int left = lds_valid_end[local[it]] - static_cast<int32_t>(e); // read again: seven wavefronts leave no register for it
             const int nv = left >= QP_PER_LANE ? QP_PER_LANE : (left > 0 ? left : 0);
-            uint32_t sign = quantize_sign_byte(sg[0], sg[1]);
+            uint32_t sign = quantize_sign_byte(x[it][0], x[it][1]);
             if (nv < QP_PER_LANE) { // the tensor ends inside (or before) this lane's eight elements
                 sign &= (1u << nv) - 1u;
                 const uint64_t fields = (static_cast<uint64_t>(1) << (nv * b)) - 1u;
-                lv[0] &= static_cast<uint32_t>(fields) & quad_fields;
+                lv[0] &= static_cast<uint32_t>(fields) & FIELDS;
                 lv[1] &= static_cast<uint32_t>(fields >> (4 * b));
             }
             if ((lv[0] | lv[1]) != 0) { // a zero at the low end is a zero everywhere in the bracket
@@ -522,8 +533,8 @@ __global__ __launch_bounds__(QP_THREADS, 7) void k_quantize_pack_bracketed_v(
                 quantize_again<0>(range, x[it][0], x[it][1], lds_scale_lo[local[it]], S, b, t, lv_lo);
                 // (lv is zero past the tensor's end, so is what lv_lo has there once masked)
                 const uint64_t fields = nv < QP_PER_LANE ? (static_cast<uint64_t>(1) << (nv * b)) - 1u : ~static_cast<uint64_t>(0);
-                record_open(lv[0] ^ (lv_lo[0] & static_cast<uint32_t>(fields) & quad_fields), x[it][0], b, e, &lds_count, blk, lv[0]);
-                record_open(lv[1] ^ (lv_lo[1] & static_cast<uint32_t>(fields >> (4 * b))), x[it][1], b, e + 4u, &lds_count, blk, lv[1]);
+                record_open<0>(lv[0] ^ (lv_lo[0] & static_cast<uint32_t>(fields) & FIELDS), x[it][0], b, e, &lds_count, blk, lv[0]);
+                record_open<0>(lv[1] ^ (lv_lo[1] & static_cast<uint32_t>(fields >> (4 * b))), x[it][1], b, e + 4u, &lds_count, blk, lv[1]);
             }
             const uint64_t level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * b));
             lds_sign[e >> 3] = static_cast<uint8_t>(sign);

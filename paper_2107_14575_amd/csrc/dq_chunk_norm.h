@@ -33,6 +33,31 @@ __device__ __forceinline__ double dq_row_ror(double v)
     return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
 }
 
+// value of the lane that DPP control CTRL names, in the same row
+template <int CTRL>
+__device__ __forceinline__ double dq_dpp(double v)
+{
+    const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint32_t lo = static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(bits)), CTRL, 0xF, 0xF, true));
+    const uint32_t hi = static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(bits >> 32)), CTRL, 0xF, 0xF, true));
+    return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+
+// The row totals of two values a lane, in the first and the ninth lane of every 16-lane row: the halves of the row take a value each after
+// the first step.  Additions in pairs (l, l + 8), (l, l + 4), (l, l + 2), (l, l + 1), as four rotate-and-add steps of either value have
+// them in every lane, for two thirds of their instructions.
+__device__ __forceinline__ double dq_row_sums_of_two(double a, double b, int lane)
+{
+    const bool second = (lane & 8) != 0;
+    double v = (second ? b : a) + dq_row_ror<8>(second ? a : b);
+    v += dq_dpp<0x104>(v); // row_shl:4, the lane four places further on
+    v += dq_dpp<0x102>(v);
+    v += dq_dpp<0x101>(v);
+    return v;
+}
+
 // Step 1 (every lane): x[it][h] are the lane's float4 halves of tile it; valid[it] says how many
 // of the lane's eight elements of tile `it` belong to their tensor (<= 0: none, >= 8: all);
 // local[it] is the index of that tensor among the chunk's tensors and granule[it] the lane's granule
@@ -101,12 +126,11 @@ __device__ __forceinline__ int dq_chunk_granule_sums(const float4 (&x)[2][2], co
         }
         return 16;
     }
+    if constexpr (LINF) { // maxima are exact in binary32
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w,
-                             x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
-        double sum;
-        if constexpr (LINF) { // maxima are exact in binary32
+        for (int it = 0; it < 2; ++it) {
+            const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w,
+                                 x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
             float m = 0.0f;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
@@ -118,30 +142,36 @@ __device__ __forceinline__ int dq_chunk_granule_sums(const float4 (&x)[2][2], co
             o = dq_row_ror<4>(m); m = o > m ? o : m;
             o = dq_row_ror<2>(m); m = o > m ? o : m;
             o = dq_row_ror<1>(m); m = o > m ? o : m;
-            sum = static_cast<double>(m);
-        } else {
-            double acc = 0.0;
+            if ((tid & 15) == 0) {
+                lds_gsum[granule[it]] = static_cast<double>(m);
+                lds_glocal[granule[it]] = local[it];
+            }
+        }
+    } else {
+        double sum[2];
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w,
+                                 x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
+            sum[it] = 0.0;
             if (valid[it] >= 8) { // all eight belong to the tensor (almost every lane): no masking
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     const double e = static_cast<double>(v[k]);
-                    acc = __builtin_fma(e, e, acc);
+                    sum[it] = __builtin_fma(e, e, sum[it]);
                 }
             } else {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     const double e = static_cast<double>(k < valid[it] ? v[k] : 0.0f);
-                    acc = __builtin_fma(e, e, acc);
+                    sum[it] = __builtin_fma(e, e, sum[it]);
                 }
             }
-            acc += dq_row_ror<8>(acc);
-            acc += dq_row_ror<4>(acc);
-            acc += dq_row_ror<2>(acc);
-            acc += dq_row_ror<1>(acc);
-            sum = acc; // every lane of the row now has all sixteen terms; the first lane's order is the one used
         }
-        if ((tid & 15) == 0) {
-            lds_gsum[granule[it]] = sum;
+        const double row = dq_row_sums_of_two(sum[0], sum[1], tid);
+        if ((tid & 7) == 0) {
+            const int it = (tid >> 3) & 1;
+            lds_gsum[granule[it]] = row;
             lds_glocal[granule[it]] = local[it];
         }
     }

@@ -65,8 +65,8 @@ __device__ __forceinline__ void stage_bytes_v(uint8_t* dst, uint64_t v, int b)
 // also holds the levels packed before it (times 2^b by one exact fma).
 //
 // What bounds it: vector issue, where the norms are computed in the same pass; the plain pass is bound by memory.  Per
-// element and beside the 9.3 instructions of Philox, 7.4 are issued: multiply, half a max3, shift, convert, fma, fma and
-// addition (a quad's first needs no fma), sign; with minimum (and the canonicalising maximum ahead of it), v_fract, two
+// element and beside the 9.3 instructions of Philox, 6.4 are issued: multiply, half a max3, shift, convert, fma, fma and
+// addition (a quad's first needs no fma), half a sign (see quantize_exchange); with minimum (and the canonicalising maximum ahead of it), v_fract, two
 // conversions, compare, add with carry and shift they were 12.5, and 8.5 in a form for wavefronts whose products are all
 // below 1.  Fma and addition also issue twice as fast as those (2.4 against 4.3 cycles by themselves, less of a
 // difference in a mixture).  Norms and messages in one pass, 16.8 M values in buckets of 512, M = 8, no input in a cache: b = 2
@@ -120,7 +120,8 @@ __device__ __forceinline__ void quantize_random(const uint32_t quad0, const uint
     for (int k = 0; k < 8; ++k) t[k] = static_cast<float>(r[k >> 2][k & 3] >> 8);
 }
 
-// The two quads' levels, four fields of b bits each in lv[h], from the clamped products and the random numbers.
+// The two quads' levels, four fields of b bits each in the low 4 b bits of lv[h], from the clamped products and the random numbers.  Above
+// the fields lv holds what the sum leaves there (B = 1 to 5; zero otherwise): whoever takes the fields masks them or drops the rest.
 // The rounding mode is set and put back inside the one asm statement, so no other operation runs under it.
 // Results are marked as written early: without that an operand still to be read may be given the register of a result
 // that has the same value to begin with.
@@ -163,8 +164,8 @@ __device__ __forceinline__ void quantize_levels(const float (&a)[8], const float
             : "+&v"(c[0]), "+&v"(c[1]), "+&v"(c[2]), "+&v"(c[3]), "+&v"(c[4]), "+&v"(c[5]), "+&v"(c[6]), "+&v"(c[7])
             : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "s"(0x1p-24f),
               "s"(0x1.8p23f), "s"(pw), "v"(back));
-        lv[0] = __float_as_uint(c[3]) - MAGIC;
-        lv[1] = __float_as_uint(c[7]) - MAGIC;
+        lv[0] = __float_as_uint(c[3]);
+        lv[1] = __float_as_uint(c[7]);
     } else {
         asm("s_nop 1\n\t"
             "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 1\n\t"
@@ -200,32 +201,36 @@ __device__ __forceinline__ void quantize_levels(const float (&a)[8], const float
     }
 }
 
-// The sign bits of a quad in bits 28..31 (element 0 in bit 28); the bits below are not cleared.
-__device__ __forceinline__ uint32_t quantize_signs(const float4 x)
+// w moved up by four bits and a quad's sign bits below it (element 0 in bit 0): one instruction an element.
+__device__ __forceinline__ uint32_t quantize_signs_below(uint32_t w, const float4 x)
 {
-    // bitop3 0xCA: a ? b : c, bit by bit
-    const uint32_t hi = __builtin_amdgcn_bitop3_b32(0x80000000u, __float_as_uint(x.w), __float_as_uint(x.z) >> 1, 0xCA);
-    const uint32_t lo = __builtin_amdgcn_bitop3_b32(0x80000000u, __float_as_uint(x.y), __float_as_uint(x.x) >> 1, 0xCA);
-    return __builtin_amdgcn_bitop3_b32(0xC0000000u, hi, lo >> 2, 0xCA);
+    w = __builtin_amdgcn_alignbit(w, __float_as_uint(x.w), 31);
+    w = __builtin_amdgcn_alignbit(w, __float_as_uint(x.z), 31);
+    w = __builtin_amdgcn_alignbit(w, __float_as_uint(x.y), 31);
+    return __builtin_amdgcn_alignbit(w, __float_as_uint(x.x), 31);
 }
-// the sign byte of eight elements from the words of their two quads (bits 28..31 count)
-__device__ __forceinline__ uint32_t quantize_sign_byte(const uint32_t sg0, const uint32_t sg1)
+// the sign byte of a lane's eight consecutive elements
+__device__ __forceinline__ uint32_t quantize_sign_byte(const float4 x0, const float4 x1)
 {
-    return (sg0 >> 28) | ((sg1 >> 24) & 0xF0u);
+    return quantize_signs_below(quantize_signs_below(0u, x1), x0);
+}
+// the fields of a quad, four of b bits
+template <int B>
+__device__ __forceinline__ constexpr uint32_t quad_fields(int b)
+{
+    return static_cast<uint32_t>((static_cast<uint64_t>(1) << (4 * (B > 0 ? B : b))) - 1u);
 }
 
-// Both quads: the words of quantize_signs and the levels.  The random numbers are left in t for a caller that
+// Both quads: the levels.  The random numbers are left in t for a caller that
 // quantizes the same elements again (QP_ALL_ZERO: none were drawn, every level is 0 for any smaller scale too).
 template <int B>
 __device__ __forceinline__ qp_range quantize_quads(const float4 x0, const float4 x1, const float scale, const float S,
                                                    const int b, const uint32_t quad0, const uint32_t quad1,
                                                    const uint32_t quad_hi, const uint32_t worker, const uint32_t step,
-                                                   const uint32_t key0, const uint32_t key1, uint32_t (&sign)[2],
-                                                   uint32_t (&lv)[2], float (&t)[8])
+                                                   const uint32_t key0, const uint32_t key1, uint32_t (&lv)[2],
+                                                   float (&t)[8])
 {
     float a[8];
-    sign[0] = quantize_signs(x0);
-    sign[1] = quantize_signs(x1);
     lv[0] = lv[1] = 0u;
     const qp_range range = quantize_products<B>(x0, x1, scale, S, a);
     if (range != QP_ALL_ZERO) {
@@ -256,31 +261,30 @@ __device__ __forceinline__ qp_range quantize8(const float4 x_lo, const float4 x_
                                               const uint32_t worker, const uint32_t step, const uint32_t key0,
                                               const uint32_t key1, uint32_t& sign, uint64_t& level, float (&t)[8])
 {
-    uint32_t sg[2], lv[2];
-    const qp_range range = quantize_quads<B>(x_lo, x_hi, scale, S, b, quad, quad + 1u, quad_hi, worker, step, key0, key1,
-                                             sg, lv, t);
-    sign = quantize_sign_byte(sg[0], sg[1]);
-    level = static_cast<uint64_t>(lv[0]) | (static_cast<uint64_t>(lv[1]) << (4 * (B > 0 ? B : b)));
+    uint32_t lv[2];
+    const qp_range range = quantize_quads<B>(x_lo, x_hi, scale, S, b, quad, quad + 1u, quad_hi, worker, step, key0, key1, lv, t);
+    sign = quantize_sign_byte(x_lo, x_hi);
+    level = static_cast<uint64_t>(lv[0] & quad_fields<B>(b)) | (static_cast<uint64_t>(lv[1] & quad_fields<B>(b)) << (4 * (B > 0 ? B : b)));
     return range;
 }
 
-// The codes of the two quads a lane loaded (dq_load_wave_tile, not arranged) change places between the halves of
-// the wavefront, so that the lane has its eight consecutive elements' sign byte and level bits.  Up to seven bits
-// the signs travel in the top four bits of the levels' words.
+// The codes of the two quads x0 and x1 that a lane loaded (dq_load_wave_tile, not arranged) change places between the halves of
+// the wavefront, so that the lane has its eight consecutive elements' sign byte (in the low eight bits of `sign`) and level bits (in
+// the low 8 b bits of `level`).  Up to seven bits the signs travel below the levels in one word: with a word of signs made by masks and
+// merged above the levels, a tile took 8 instructions more: with that and what dq_row_sums_of_two saves, norms and messages in one pass, 16.8 M values in
+// buckets of 4096, M = 8, b = 5 with the reduce 149.2 -> 143.3 us; of 512, b = 2 132.4 -> 128.9; bracketed 2^26, M = 16, b = 4 1053 -> 1039.
 template <int B>
-__device__ __forceinline__ void quantize_exchange(const uint32_t (&sg)[2], const uint32_t (&lv)[2], const int b,
+__device__ __forceinline__ void quantize_exchange(const float4 x0, const float4 x1, const uint32_t (&lv)[2], const int b,
                                                   uint32_t& sign, uint64_t& level)
 {
     if constexpr (B >= 1 && B <= 7) {
-        constexpr uint32_t FIELDS = (1u << (4 * (B >= 1 && B <= 7 ? B : 1))) - 1u;
-        const auto w = __builtin_amdgcn_permlane32_swap(__builtin_amdgcn_bitop3_b32(0xF0000000u, sg[0], lv[0], 0xCA),
-                                                        __builtin_amdgcn_bitop3_b32(0xF0000000u, sg[1], lv[1], 0xCA), false, false);
-        sign = quantize_sign_byte(w[0], w[1]);
-        level = static_cast<uint64_t>(w[0] & FIELDS) | (static_cast<uint64_t>(w[1] & FIELDS) << (4 * B));
+        const auto w = __builtin_amdgcn_permlane32_swap(quantize_signs_below(lv[0], x0), quantize_signs_below(lv[1], x1), false, false);
+        sign = __builtin_amdgcn_bitop3_b32(0xFu, w[0], w[1] << 4, 0xCA); // a ? b : c, bit by bit
+        level = static_cast<uint64_t>((w[0] >> 4) & quad_fields<B>(B)) | (static_cast<uint64_t>((w[1] >> 4) & quad_fields<B>(B)) << (4 * B));
     } else {
-        const auto s = __builtin_amdgcn_permlane32_swap(sg[0], sg[1], false, false);
+        const auto s = __builtin_amdgcn_permlane32_swap(quantize_signs_below(0u, x0), quantize_signs_below(0u, x1), false, false);
         const auto l = __builtin_amdgcn_permlane32_swap(lv[0], lv[1], false, false);
-        sign = quantize_sign_byte(s[0], s[1]);
+        sign = s[0] | (s[1] << 4);
         level = static_cast<uint64_t>(l[0]) | (static_cast<uint64_t>(l[1]) << (4 * (B > 0 ? B : b)));
     }
 }
@@ -294,11 +298,11 @@ __device__ __forceinline__ void quantize_wave_tile(const float4 lo, const float4
                                                    const uint32_t quad_hi, const uint32_t worker, const uint32_t step,
                                                    const uint32_t key0, const uint32_t key1, uint32_t& sign, uint64_t& level)
 {
-    uint32_t sg[2], lv[2];
+    uint32_t lv[2];
     float t[8];
     const uint32_t quad = quad_tile + (lane & 31u) * 2u + (lane >> 5);
-    quantize_quads<B>(lo, hi, scale, S, b, quad, quad + 64u, quad_hi, worker, step, key0, key1, sg, lv, t);
-    quantize_exchange<B>(sg, lv, b, sign, level);
+    quantize_quads<B>(lo, hi, scale, S, b, quad, quad + 64u, quad_hi, worker, step, key0, key1, lv, t);
+    quantize_exchange<B>(lo, hi, lv, b, sign, level);
 }
 
 // threadIdx.x for the body of a loop over chunks: what follows from it is not worked out ahead of the loop and held in
@@ -432,7 +436,8 @@ struct qp_norm_given {
 // change places between the lanes instead of the values.  Measured at D = 2^28, M = 16 against the table
 // route alone: b = 2 3.36 -> 3.06 ms (6.1 TB/s), b = 4 3.39 -> 3.28 ms; ResNet-18 shape, M = 8, b = 2
 // 74.9 -> 66.9 us.  Chunks that hold a tensor's end or several tensors take the table.
-// WHOLE = false (NORM = 0 only): no such route, and the lanes' elements as qp_load_block has them, for layouts with
+// NORM != 0: WHOLE = with the route for buckets.
+// WHOLE = false, NORM = 0: no such route, and the lanes' elements as qp_load_block has them, for layouts with
 // few chunks of one tensor (dq_plan::many_whole).  Measured there against the form with the route, in us: 5.4 M
 // values in tensors of 128, M = 8 b = 4 38.0 -> 36.6, 16.8 M in tensors of 512, M = 8 b = 6 121.8 -> 114.8 and, with a
 // widths table, b = 7 130.9 -> 122.4; 30.7 M in tensors of 1000, M = 4 b = 6 112.0 -> 104.5.
@@ -504,6 +509,10 @@ __device__ __forceinline__ void quantize_pack_chunk(
         }
     }
 
+    // Buckets that a wavefront holds whole: no tables, and each wavefront goes its own way (one barrier, and only where the chunk's stretches are off the
+    // cache lines) in place of three barriers with two lookups ahead of the first.  16.8 M values, M = 8 with the reduce, buckets of 128, 256, 512, 1024,
+    // b = 8 158 -> 152, 156 -> 151, 156 -> 151, 155 -> 151 us; 4 M, M = 3, b = 5 24.9 -> 22.4.  A root and a division for every wavefront are
+    // what it costs; buckets of 2048 and 4096 lie in several wavefronts and take the tables.
     int32_t seg[TILES];
 #pragma unroll
     for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES, BLOCK>(tid, it, n_elems)];
