@@ -49,19 +49,30 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
 
 // ---------------------------------------------------------------------------------------------
 // Sign-only messages (the one-bit baseline of the paper's Table 2): the sign plane alone.  Same
-// work split with four tiles per workgroup; no random numbers, no norms.
+// work split; no random numbers, no norms.
 // HBM traffic per element: 4 bytes read, 1/8 byte written.
+//
+// What bounds it: the memory system's rate for a read stream with a thirtieth of writes in it (a kernel with these accesses and no
+// arithmetic reaches 6.3 to 6.4 TB/s at 4 GiB, without its stores 7.1).  Wavefronts that are done sooner leave more requests in
+// flight than that takes and lose some of it: a chunk of one tensor needs no table (two serial lookups behind the loads), and that alone made large
+// calls 1 % slower, until fewer workgroups were resident.  Two tiles a wavefront and six workgroups per CU (by the size of the LDS request;
+// eight fit) against four tiles, all chunks by the table and eight, us, with the reduce: ResNet-18 shape, M = 8 73.0 -> 70.7, M = 40 306 -> 302;
+// transformer shape, M = 60 532 -> 524; 4 M values, M = 8 29.2 -> 27.3; 2^24, M = 64 725 -> 699.  Eight per CU: 72.0, 306, 532, 28.1, 706; five: 71.0,
+// 303, 534, 28.9, 718; four tiles and eight per CU 72.0, 309, 536, 28.1, -.
 // ---------------------------------------------------------------------------------------------
-constexpr int SP_TILES = 4;
+constexpr int SP_TILES = 2;
+constexpr size_t SP_LDS_SIX_PER_CU = dq_lds_for(6) - SP_TILES * QP_THREADS; // beside what the kernel declares
 
 template <bool KEEP> // as in k_quantize_pack (sign_keep_messages)
 __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restrict__ grads, int64_t worker_stride,
+                                                          const dq_chunk_tensor* __restrict__ chunk_tensor,
                                                           const int32_t* __restrict__ granule_cseg,
                                                           const int64_t* __restrict__ cseg_valid_end,
                                                           int64_t padded_elems, uint8_t* __restrict__ packed,
                                                           int64_t packed_stride)
 {
     constexpr int CHUNK = QP_TILE * SP_TILES;
+    static_assert(CHUNK == DQ_CHUNK, "a workgroup's elements are one entry of the chunk table");
     __shared__ __align__(16) uint8_t lds_sign[SP_TILES * QP_THREADS];
 
     const uint32_t tid = threadIdx.x;
@@ -85,29 +96,39 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
         x[it][0] = dq_load_stream(reinterpret_cast<const float4*>(at + e0 * 4u));
         x[it][1] = dq_load_stream(reinterpret_cast<const float4*>(at + e1 * 4u));
     }
+    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * SP_TILES);
+    const dq_chunk_tensor whole = dq_load_chunk_tensor(chunk_tensor, blockIdx.x);
+    if (whole.cseg >= 0) { // 4096 elements of one tensor, the same for the whole workgroup: nothing to mask, and the codes change places
 #pragma unroll
-    for (int it = 0; it < SP_TILES; ++it) valid_end[it] = cseg_valid_end[gseg[qp_granule<SP_TILES>(tid, it, n_elems)]];
+        for (int it = 0; it < SP_TILES; ++it) {
+            const auto w = __builtin_amdgcn_permlane32_swap(quantize_signs_below(0u, x[it][0]), quantize_signs_below(0u, x[it][1]), false, false);
+            lds_sign[((wave0 + it * QP_WAVE_TILE) >> 3) + (tid & 63u)] = static_cast<uint8_t>(w[0] | (w[1] << 4));
+        }
+    } else {
 #pragma unroll
-    for (int it = 0; it < SP_TILES; ++it) {
-        dq_arrange_wave_tile(x[it][0], x[it][1]);
-        const uint32_t e = qp_elem<SP_TILES>(tid, it);
-        if (e < n_elems) {
-            const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w,
-                                 x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
-            uint32_t sign = 0;
+        for (int it = 0; it < SP_TILES; ++it) valid_end[it] = cseg_valid_end[gseg[qp_granule<SP_TILES>(tid, it, n_elems)]];
 #pragma unroll
-            for (int k = 7; k >= 0; --k) sign = __builtin_amdgcn_alignbit(sign, __float_as_uint(v[k]), 31);
-            const int64_t n_valid = valid_end[it] - (chunk0 + e);
-            if (n_valid < QP_PER_LANE) sign &= (1u << (n_valid > 0 ? static_cast<int>(n_valid) : 0)) - 1u;
-            lds_sign[e >> 3] = static_cast<uint8_t>(sign);
+        for (int it = 0; it < SP_TILES; ++it) {
+            dq_arrange_wave_tile(x[it][0], x[it][1]);
+            const uint32_t e = qp_elem<SP_TILES>(tid, it);
+            if (e < n_elems) {
+                uint32_t sign = quantize_sign_byte(x[it][0], x[it][1]);
+                const int64_t n_valid = valid_end[it] - (chunk0 + e);
+                if (n_valid < QP_PER_LANE) sign &= (1u << (n_valid > 0 ? static_cast<int>(n_valid) : 0)) - 1u;
+                lds_sign[e >> 3] = static_cast<uint8_t>(sign);
+            }
         }
     }
-    dq_wave_sync();
-    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * SP_TILES);
-    if (wave0 < n_elems) {
-        const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * SP_TILES ? n_elems - wave0 : QP_WAVE_TILE * SP_TILES;
-        qp_store_wave<KEEP>(packed + static_cast<int64_t>(w) * packed_stride + ((chunk0 + wave0) >> 3), &lds_sign[wave0 >> 3],
-                            n_wave >> 3, tid & 63u);
+    uint8_t* dst = packed + static_cast<int64_t>(w) * packed_stride + (chunk0 >> 3);
+    if (qp_on_lines(dst, dst)) { // as in qp_store_chunk
+        dq_wave_sync();
+        if (wave0 < n_elems) {
+            const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * SP_TILES ? n_elems - wave0 : QP_WAVE_TILE * SP_TILES;
+            qp_store_wave<KEEP>(dst + (wave0 >> 3), &lds_sign[wave0 >> 3], n_wave >> 3, tid & 63u);
+        }
+    } else {
+        __syncthreads();
+        qp_store_block<KEEP>(dst, lds_sign, n_elems >> 3, tid);
     }
 }
 
@@ -129,14 +150,13 @@ inline bool qp_keep_messages(const dq_plan* plan, int M, int b)
 // Widths that may be known to the GPU only: six bits stand for the usual.
 inline bool qp_keep_messages_v(const dq_plan* plan, int M) { return qp_keep_messages(plan, M, 6); }
 
-// The same for sign messages, which are small.  Pack and scaled reduce / majority, us: 2^24 values, M = 2 38.7 -> 37.9 / 40.3 -> 38.0, M = 8
-// 103.5 -> 101.9 / 103.4 -> 100.5, M = 32 381 -> 372 / 390 -> 377; ResNet-18 shape, M = 32 260 -> 255 / 250 -> 247, 2^22, M = 32 97.3 -> 96.9 /
-// 93.7 -> 92.6.  Fewer bytes of smaller models gain or lose up to 3 % (ResNet-18 shape, M = 2 28.3 -> 29.2), and models of 2^25 and 2^26 with
-// eight workers lose 3 to 4 % (2^25 206.5 -> 212.8).
-constexpr int64_t SP_KEEP_ELEMS = 20 << 20, SP_KEEP_FROM_ELEMS = 12 << 20, SP_KEEP_FROM_BYTES = 14 << 20;
+// The same for sign messages, which are small: whatever their number, from 12 M elements or 14 MB on.  Pack and majority, us, with the hint / through: 2^25
+// values, M = 8 201 / 193, 2^26 401 / 385, M = 16 758 / 723, 2^28 - 333, M = 4 923 / 891; transformer and ResNet-18 shapes, M = 16 to 60 the same.
+// Fewer bytes of smaller models gain 1 % (4 M values, M = 8) or lose up to 3 % (ResNet-18 shape, M = 2 26.9 / 27.7).
+constexpr int64_t SP_KEEP_FROM_ELEMS = 12 << 20, SP_KEEP_FROM_BYTES = 14 << 20;
 inline bool sign_keep_messages(const dq_plan* plan, int M)
 {
-    return plan->padded_elems <= SP_KEEP_ELEMS && (plan->padded_elems >= SP_KEEP_FROM_ELEMS || M * (plan->padded_elems / 8) >= SP_KEEP_FROM_BYTES);
+    return plan->padded_elems >= SP_KEEP_FROM_ELEMS || M * (plan->padded_elems / 8) >= SP_KEEP_FROM_BYTES;
 }
 
 // Seven workgroups per CU in calls of many rounds (eight of the kernels of one width fit): norm, rule, quantize and reduce, ResNet-18 shape, M = 8
@@ -301,8 +321,8 @@ extern "C" int dq_sign_pack(const dq_plan_t* plan, const float* grads_dev, int64
     const int64_t n_chunks = (plan->padded_elems + CHUNK - 1) / CHUNK;
     if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_chunks), M), dim3(QP_THREADS), 0,
-                           static_cast<hipStream_t>(hip_stream), grads_dev, worker_stride_elems, plan->d_granule_cseg,
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_chunks), M), dim3(QP_THREADS), SP_LDS_SIX_PER_CU,
+                           static_cast<hipStream_t>(hip_stream), grads_dev, worker_stride_elems, plan->d_chunk_tensor, plan->d_granule_cseg,
                            plan->d_cseg_valid_end, plan->padded_elems, packed_dev, packed_worker_stride_bytes);
     };
     if (sign_keep_messages(plan, M))
