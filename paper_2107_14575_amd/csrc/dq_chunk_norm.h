@@ -232,6 +232,66 @@ __device__ __forceinline__ void dq_chunk_tensor_totals(int g, int n_granules, co
     if (used && (g == n_granules - 1 || lds_glocal[g + 1] + 1 != t)) emit(t - 1, v);
 }
 
+// sqrt(x) for a sum of squares of binary32 values: zero, or between 2^-298 and 2^296 (2^40 values), or infinite or NaN.  Goldschmidt's iteration
+// from the hardware's estimate and two corrections by the residual, which gives the correctly rounded root; the library function's scaling of
+// small and large arguments is left out.
+__device__ __forceinline__ double dq_root_of_squares(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double s = x * y, h = 0.5 * y;
+    const double r = __builtin_fma(-h, s, 0.5);
+    s = __builtin_fma(s, r, s);
+    h = __builtin_fma(h, r, h);
+    s = __builtin_fma(__builtin_fma(-s, s, x), h, s);
+    s = __builtin_fma(__builtin_fma(-s, s, x), h, s);
+    return x == 0.0 || x == __builtin_inf() ? x : s;
+}
+
+// Buckets of 128 << log values, log <= 3, all of them data: a wavefront's two tiles (eight granules) hold whole buckets, so it works
+// out their norms by itself.  x as in dq_chunk_granule_sums, gsum eight words of LDS of the wavefront's own.  Every lane l gets the norm of
+// the bucket that holds granule l & 7 of the eight.  The additions are those of the two steps above in the same order (both partners of
+// a pair add the same two terms), so the same bits.
+template <bool LINF>
+__device__ __forceinline__ float dq_wave_bucket_norms(const float4 (&x)[2][2], int lane, double* gsum, int log)
+{
+    double sum[2];
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const float v[8] = { x[it][0].x, x[it][0].y, x[it][0].z, x[it][0].w, x[it][1].x, x[it][1].y, x[it][1].z, x[it][1].w };
+        if constexpr (LINF) {
+            float m = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float a = fabsf(v[k]);
+                m = a > m ? a : m;
+            }
+            float o;
+            o = dq_row_ror<8>(m); m = o > m ? o : m;
+            o = dq_row_ror<4>(m); m = o > m ? o : m;
+            o = dq_row_ror<2>(m); m = o > m ? o : m;
+            o = dq_row_ror<1>(m); m = o > m ? o : m;
+            if ((lane & 15) == 0) gsum[it * 4 + (lane >> 4)] = static_cast<double>(m);
+        } else {
+            sum[it] = 0.0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const double e = static_cast<double>(v[k]);
+                sum[it] = __builtin_fma(e, e, sum[it]);
+            }
+        }
+    }
+    if constexpr (!LINF) {
+        const double row = dq_row_sums_of_two(sum[0], sum[1], lane);
+        if ((lane & 7) == 0) gsum[((lane >> 3) & 1) * 4 + (lane >> 4)] = row;
+    }
+    dq_wave_sync();
+    double v = gsum[lane & 7];
+    if (log >= 1) v = dq_chunk_combine<LINF>(v, dq_dpp<0xB1>(v));  // quad_perm 1, 0, 3, 2
+    if (log >= 2) v = dq_chunk_combine<LINF>(v, dq_dpp<0x4E>(v));  // quad_perm 2, 3, 0, 1
+    if (log >= 3) v = dq_chunk_combine<LINF>(v, dq_dpp<0x141>(v)); // row_half_mirror
+    return LINF ? static_cast<float>(v) : static_cast<float>(dq_root_of_squares(v));
+}
+
 // The same for chunk-local plans, where the chunk holds whole tensors: emit(local tensor index, norm).
 template <bool LINF, typename Emit>
 __device__ __forceinline__ void dq_chunk_tensor_norms(int g, int n_granules, const double* lds_gsum,

@@ -39,6 +39,13 @@ __device__ __forceinline__ dq_chunk_tensor dq_load_chunk_tensor(const dq_chunk_t
 // 50 ns each: 200 workgroups 16.5 -> 15.4, 400 16.8 -> 19.8, 1024 16.5 -> 36.
 constexpr int DQ_ARRIVE_WORKGROUPS = 160;
 
+// A gradient cut into buckets of 128 << log values, log <= 3: the first `chunks` chunks hold nothing but whole buckets, so that granule g
+// belongs to tensor g >> log and no table has to say so.  chunks = 0: another kind of plan.
+struct dq_buckets {
+    uint32_t chunks;
+    int32_t log;
+};
+
 // Kernels that stream the gradient keep more requests in flight than the memory needs when all the workgroups that fit a CU are resident, and
 // lose some of its rate.  A launch of many rounds of workgroups asks for so much LDS that fewer are: DQ_LDS_PER_CU / n less what rounding takes.
 constexpr int64_t DQ_LDS_PER_CU = 160 * 1024;
@@ -59,6 +66,7 @@ struct dq_plan {
     // quantize_pack_chunk).  Against the form that does not, b = 1, 4, 6 take 1.02, 1.0, 1.04 of its time with no such
     // chunk (tensors of 3000), 0.98, 0.96, 1.03 at 13 % (4700), 0.95, 0.94, 0.99 at 32 % (6000).
     bool many_whole;
+    dq_buckets buckets;
     void* d_tables;       // the one device allocation that holds all of the tables below
     // device tables.  Kernels address segments through a compact index c that counts only the
     // non-empty ones, so consecutive granules differ by at most one in c.

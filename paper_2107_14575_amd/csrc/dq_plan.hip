@@ -72,6 +72,12 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
         return DQ_ERR_INVALID_ARG;
     }
     p->n_items = static_cast<int32_t>(n_items);
+    for (int32_t log = 0; log <= 3; ++log) { // all of one length but a shorter last one?
+        const int64_t len = static_cast<int64_t>(DQ_GRANULE) << log;
+        int32_t full = 0;
+        while (full < n_seg && seg_len_host[full] == len) ++full;
+        if (full >= n_seg - 1 && full > 0) p->buckets = dq_buckets{ static_cast<uint32_t>(full * len / 4096), log };
+    }
 
     int n_dev = 0;
     if (hipGetDeviceCount(&n_dev) != hipSuccess || n_dev < 1) {

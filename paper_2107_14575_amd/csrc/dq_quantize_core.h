@@ -453,7 +453,8 @@ __device__ __forceinline__ void quantize_pack_chunk(
     const dq_chunk_tensor* __restrict__ chunk_tensor, const int32_t* __restrict__ granule_cseg,
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end, int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x, NormOf norm_of = {})
+    int64_t packed_stride, float* __restrict__ norms_out, uint32_t chunk_index, uint32_t tid = threadIdx.x, NormOf norm_of = {},
+    dq_buckets buckets = {})
 {
     constexpr int CHUNK = QP_TILE * TILES;
     constexpr int MAX_LOCAL_SEG = CHUNK / DQ_GRANULE;
@@ -513,6 +514,34 @@ __device__ __forceinline__ void quantize_pack_chunk(
     // cache lines) in place of three barriers with two lookups ahead of the first.  16.8 M values, M = 8 with the reduce, buckets of 128, 256, 512, 1024,
     // b = 8 158 -> 152, 156 -> 151, 156 -> 151, 155 -> 151 us; 4 M, M = 3, b = 5 24.9 -> 22.4.  A root and a division for every wavefront are
     // what it costs; buckets of 2048 and 4096 lie in several wavefronts and take the tables.
+    if constexpr (NORM != 0 && WHOLE) {
+        if (chunk_index < buckets.chunks) {
+            __shared__ double lds_bucket[DQ_CHUNK_GRANULES];
+            const uint32_t lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+            for (int it = 0; it < TILES; ++it) dq_arrange_wave_tile(x[it][0], x[it][1]);
+            const float N = dq_wave_bucket_norms<NORM == 2>(x, static_cast<int>(lane), lds_bucket + wave * 8, buckets.log);
+            const float scale_of = N >= DQ_MIN_NORM ? S / N : 0.0f;
+            if (lane < 8u && (lane & ((1u << buckets.log) - 1u)) == 0)
+                norms_out[static_cast<int64_t>(w) * n_seg + (((chunk0 >> 7) + wave * 8 + lane) >> buckets.log)] = N;
+#pragma unroll
+            for (int it = 0; it < TILES; ++it) {
+                const uint32_t tile0 = wave0 + it * QP_WAVE_TILE, at = (tile0 >> 3) + lane;
+                const float scale = __shfl(scale_of, it * 4 + (lane >> 4), 64);
+                uint32_t sign;
+                uint64_t level;
+                float t[8];
+                quantize8<B>(x[it][0], x[it][1], scale, 0.0f, 0, quad_lo0 + (tile0 >> 2) + 2u * lane, quad_hi, worker, step, key0, key1,
+                             sign, level, t);
+                lds_sign[at] = static_cast<uint8_t>(sign);
+                stage_bytes<B>(&lds_level[at * B], level);
+            }
+            qp_store_chunk<KEEP>(msg + (chunk0 >> 3), msg + (padded_elems >> 3) + (chunk0 >> 3) * B, lds_sign, lds_level, CHUNK, wave0,
+                                 B, tid);
+            return;
+        }
+    }
+
     int32_t seg[TILES];
 #pragma unroll
     for (int it = 0; it < TILES; ++it) seg[it] = gseg[qp_granule<TILES, BLOCK>(tid, it, n_elems)];

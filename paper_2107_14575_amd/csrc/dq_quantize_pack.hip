@@ -25,11 +25,11 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack(
     const int32_t* __restrict__ cseg_seg, const int64_t* __restrict__ cseg_valid_end,
     int64_t padded_elems,
     uint32_t key0, uint32_t key1, uint32_t step, uint32_t worker_base, uint8_t* __restrict__ packed,
-    int64_t packed_stride, float* __restrict__ norms_out)
+    int64_t packed_stride, float* __restrict__ norms_out, dq_buckets buckets)
 {
     quantize_pack_chunk<B, TILES, NORM, WHOLE, KEEP>(grads, worker_stride, norms, n_seg, chunk_tensor, granule_cseg, cseg_seg,
                                                      cseg_valid_end, padded_elems, key0, key1, step, worker_base, packed,
-                                                     packed_stride, norms_out, blockIdx.x);
+                                                     packed_stride, norms_out, blockIdx.x, threadIdx.x, {}, buckets);
 }
 
 template <int TILES, int NORM, bool WHOLE, bool KEEP> // as in k_quantize_pack
@@ -176,9 +176,12 @@ int launch(const dq_plan* plan, const float* grads, int64_t worker_stride, int M
     hipLaunchKernelGGL((k_quantize_pack<B, QP_TILES, NORM, WHOLE, KEEP>), grid, block, lds, stream, grads, worker_stride, \
                        norms, plan->n_seg, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_seg,                \
                        plan->d_cseg_valid_end, plan->padded_elems, static_cast<uint32_t>(seed),                         \
-                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out)
-    if constexpr (NORM != 0) { // a kernel that works out the norms has the one form only
-        DQ_LAUNCH_Q(true, false);
+                       static_cast<uint32_t>(seed >> 32), step, worker_base, packed, packed_stride, norms_out, plan->buckets)
+    if constexpr (NORM != 0) { // WHOLE: with the buckets' route
+        if (plan->buckets.chunks > 0)
+            DQ_LAUNCH_Q(true, false);
+        else
+            DQ_LAUNCH_Q(false, false);
     } else {
         const bool keep = qp_keep_messages(plan, M, B);
         if (plan->many_whole && keep)
