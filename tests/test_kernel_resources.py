@@ -45,3 +45,10 @@ def test_no_other_kernel_spills(tmp_path, source, least):
     told = {k: v for k, v in kernels.items() if "k_quantize_pack_bracketed_v" in k}
     assert all(v[1] >= 7 for v in told.values()), told
     assert bool(told) == (source == "dq_bracketed.hip")
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_no_reduce_kernel_with_a_table_spills(tmp_path):
+    kernels = _resources(tmp_path, "dq_reduce_widths.hip")
+    assert len(kernels) >= 20, sorted(kernels)
+    assert {k: v for k, v in kernels.items() if v[0] != 0} == {}
