@@ -51,6 +51,9 @@ template <int W> __host__ __device__ constexpr int ur_min_waves(int b) { return 
 // 29.3 -> 31.8.
 __host__ __device__ constexpr bool ur_table_first(int b) { return b <= 4; }
 
+// Widths whose level loads carry the streaming hint in some calls only (ur_stream).
+__host__ __device__ constexpr bool ur_may_stream(int b) { return b >= 5 && b <= 7; }
+
 // bytes of {hi, lo} picked by the four selector bytes of sel: 0..3 = bytes of lo, 4..7 = bytes of hi
 __device__ __forceinline__ uint32_t byte_perm(uint32_t hi, uint32_t lo, uint32_t sel)
 {
@@ -456,7 +459,7 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
             int64_t off = static_cast<int64_t>(w) * packed_stride; // scalar, for the reason given at scalar_address
             asm("" : "+s"(off));
             sg = load_sign<W>(global_address(sign_ptr + off));
-            load_levels<ur_raw<B, W>, W == 2 || B <= 4>(global_address(level_ptr + off), wd);
+            load_levels<ur_raw<B, W>, B <= 4 || (W == 2 && B == 8)>(global_address(level_ptr + off), wd);
         },
         [] {}, [&](int w) { return unit_ptr[w]; }, acc, slots);
 }
@@ -465,7 +468,8 @@ __device__ __forceinline__ void accumulate_lane(const uint8_t* __restrict__ sign
 // of the wavefront's first element and level_wave(w) worker w's level bytes of it, the same for all lanes,
 // so a worker's address is scalar arithmetic.  Lanes past the end (n_lanes, a multiple of 4 W, exist) fetch
 // the last ones' bytes.
-// W = 2: one load takes a worker's fields whatever the width, so the streaming hint stays on.
+// W = 2: one load takes a worker's fields whatever the width.  The streaming hint stays off at B = 5 to 7 all the same unless STREAM says otherwise: with it on,
+// reduces of messages in no cache gain 1 to 2 % and iterations whose messages are still there lose (2^25 to 2^26 values, M = 3 b = 7 without update 172 -> 186 us).
 // W = 1: at B = 8 a lane's dwords are two 16-byte pieces: each load instruction covers 1 KiB in full (lanes
 // 0..31 and 32..63 take the first and second pieces of 32 lanes) and swaps between the halves of the
 // wavefront put the pieces in place, so that the streaming hint can stay on.
@@ -494,7 +498,7 @@ __device__ __forceinline__ void accumulate_wave(const uint8_t* __restrict__ sign
                 wd[0] = a.x; wd[1] = a.y; wd[2] = a.z; wd[3] = a.w;
                 wd[4] = b.x; wd[5] = b.y; wd[6] = b.z; wd[7] = b.w;
             } else {
-                load_levels<ur_raw<B, W>, STREAM || W == 2 || B <= 4>(lp + at0, wd);
+                load_levels<ur_raw<B, W>, STREAM || !ur_may_stream(B)>(lp + at0, wd);
             }
         },
         prepare, unit, acc, slots);
@@ -671,13 +675,13 @@ __device__ __forceinline__ const float* wave_table(const wave_span& span, int la
 // out.  Measured over 1 to 270 M values, M = 1..31: the reduce alone, messages from memory, 16.8 M, M = 16 b = 5 65 -> 55 us, 20 M,
 // M = 4 b = 7 44.5 -> 40.2; whole iterations (norm, quantize, reduce) 11.2 M, M = 16 b = 7 315 -> 303; below, where an iteration's
 // messages are still in the cache, it costs (ResNet-18 shape, M = 8 28.8 -> 30.1).  Without update it gains 3 to 7 % of iterations with 200
-// to 400 MB of messages and loses up to 9 % where they come from memory.  With more than 32 workers (three workgroups per CU, the
-// vector ALU as much as the loads) it loses there too: 4.2 M ragged elements, M = 64 b = 5 56 -> 62, transformer shape, M = 62 b = 5 113 -> 128.
+// to 400 MB of messages and loses up to 9 % where they come from memory.  With more than 32 workers and W = 1 (three workgroups per CU, the
+// vector ALU as much as the loads) it loses there too: 4.2 M ragged elements, M = 64 b = 5 56 -> 62, transformer shape, M = 62 b = 5 113 -> 128; with W = 2
+// it gains: 11 to 20 M, M = 47 and 64 b = 5 to 7 1.0 -> 0.88 of the time with W = 1.
 constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20;
-constexpr bool ur_may_stream(int b) { return b >= 5 && b <= 7; }
-inline bool ur_stream(const dq_plan* plan, int M, int b)
+inline bool ur_stream(const dq_plan* plan, int M, int b, bool two)
 {
-    return ur_may_stream(b) && M <= 32 && M * dq_packed_bytes(plan, b) + plan->padded_elems * 4 > UR_LAST_LEVEL_CACHE / 2;
+    return ur_may_stream(b) && (two || M <= 32) && M * dq_packed_bytes(plan, b) + plan->padded_elems * 4 > UR_LAST_LEVEL_CACHE / 2;
 }
 // Whether the model passes through with the hint: a large one would not be in the cache when it is next read, and takes the
 // messages' place.  Iterations with b = 2 and 8, us, model left in the cache / passing through: 2^24, M = 2 73 / 77, M = 8 (b = 8) 233 / 230;
@@ -701,24 +705,41 @@ inline void ur_with_policy(bool stream, bool once, F&& f)
     else f(no{}, no{});
 }
 
-// Whether two workers share a decoded word (W = 2).  b = 0: widths that the host does not know.  Measured for M = 1 to 64, 64 to 10 000 tiles of 8192
-// elements, all widths, with and without update, messages in no cache (time with W = 2 / with W = 1): 0.78 to 0.95 up to 330 tiles; with
-// update 0.80 to 1.0 beyond (514 tiles, M = 64 b = 6 0.78; 1366, M = 8 b = 6 0.91; 10 000, M = 16 0.92 to 1.0), but 1.0 to 1.12 at b = 1 from 2500 tiles and 24
-// workers on; without, the same from five bits and three workers on (M = 1 and 2 at 800 tiles 1.13 to 1.17).  Narrower fields without update are bound by
-// the decoding, which W = 2 does twice for an odd worker and not in one load for three: M = 1 to 4 0.93 to 1.33, M = 6 to 64 b = 2 and 4 0.83 to 1.0, b = 3
-// 0.87 to 1.12 with fewer than twelve, b = 1 0.87 to 1.0 up to 1366 tiles and 1.0 to 1.15 beyond.  Between 385 and 512 tiles the fullest CU has as much to
-// do either way: M <= 8 0.93 to 1.17, b = 8 1.0 to 1.12.  The kernel with a widths table, which has no form for few tiles: 0.69 to 0.95 up to 200 tiles
-// (M = 64 on 4 M elements 0.78).
-inline bool ur_two_workers(const dq_plan* plan, int b, int M, bool update)
+// Whether two workers share a decoded word (W = 2).  b = 0: a widths table, which the GPU may have filled.  A tile is 8192 elements: one workgroup at W = 1,
+// two at W = 2.  Measured with 6 to 32 768 tiles, M = 1 to 64, all widths, messages in no cache (time with W = 2 / with W = 1):
+//   up to 384 tiles 0.76 to 1.04, all together 0.94;
+//   up to 1280 (five to a CU; tables with update 768) what counts is whether the fullest CU has less to do with half tiles, 2 n / 256 rounded up against n / 256: where it
+//   does (an odd number of 128 tiles) b >= 5 from four workers on and b <= 4 and tables from ten on 0.83 to 1.0; where it does not 0.96 to 1.16 (512 tiles, M = 16 b = 4
+//   1.16), b = 5 to 7 with update from six workers on 0.85 to 0.99.  With fewer workers the wavefronts' start and the decoding, twice for an odd one, decide: 0.98 to 1.36;
+//   beyond, without update b = 2 and b >= 4 for six to thirteen workers 0.93 to 1.0, the others 0.98 to 1.24 (b = 3, M = 1 1.24, M = 16 1.03; b = 4, M = 16 1.04);
+//   with update 0.85 to 1.0 for six to sixteen workers, with a table to 32, at b = 5 to 7 for one to 32; with more, whose messages are read in pieces of half the size,
+//   1.0 to 1.08, but b = 5 to 7 and tables 0.87 to 0.96 while the model stays in the cache; with fewer, or b = 1, 0.96 to 1.12 there and 0.93 to 0.99 where it passes through.
+// Whole iterations say the same, less sharply (b = 3, 2^26 to 2^28 values, M = 1 to 4, no update: 1.04 to 1.12 with W = 2).
+inline bool ur_two_workers(int64_t n_tiles, int b, int M, bool update, bool once)
+{
+    const bool halves = b >= 5 && b <= 7;
+    if (n_tiles <= 384) return true;
+    if (n_tiles <= (update && b == 0 ? 768 : 1280)) return (n_tiles + 127) / 128 % 2 != 0 ? M >= (b >= 5 ? 4 : 10) : halves && update && M >= 6;
+    if (!update) return M >= 6 && M <= 13 && (b == 2 || b >= 4);
+    if (!once && !halves && (M < 6 || b == 1)) return false;
+    return M <= (!halves && b != 0 ? 16 : once ? 32 : 64);
+}
+
+// The form that a call takes.  b as above.
+struct ur_form {
+    bool two;    // W = 2
+    bool stream; // with update: the hint on the level loads of widths 5 to 7
+    bool once;   // with update: the hint on the model
+};
+// rows: a widths table with a row per worker (W = 1 only)
+inline ur_form ur_form_of(const dq_plan* plan, int b, int M, bool update, bool rows = false)
 {
     const int64_t n_tiles = (plan->padded_elems + ur_tile<1> - 1) / ur_tile<1>;
-    if (n_tiles <= 256) return true;
-    if (n_tiles > 384 && n_tiles <= 512 && (M <= 8 || b == 8 || b == 0)) return false;
-    if (update) return !(b == 1 && M >= 24 && n_tiles >= 2000);
-    if (n_tiles <= 384) return true;
-    if (b >= 5) return M >= 3 || n_tiles <= 600;
-    if (b == 1) return M >= 6 && n_tiles <= 2000;
-    return M >= (b == 3 ? 12 : 6);
+    ur_form f;
+    f.once = update && ur_model_once(plan);
+    f.two = !rows && ur_two_workers(n_tiles, b, M, update, f.once);
+    f.stream = update && ur_stream(plan, M, b ? b : 6, f.two); // six bits stand for widths that the GPU may have set
+    return f;
 }
 
 } // namespace

@@ -351,11 +351,11 @@ int reduce_entry_v(const dq_plan_t* plan, const dq_widths_t* widths, const uint8
     // (16.8 M in buckets of 512, M = 16, b = 1 8 %).
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const float inv_M = 1.0f / static_cast<float>(M);
-    const bool hint = ur_stream(plan, M, 6), once = ur_model_once(plan); // six bits stand for widths that the GPU may have set
     const bool per_worker = widths->n_workers != 1;
+    const ur_form form = ur_form_of(plan, 0, M, x_dev != nullptr, per_worker);
     // (with a row of widths per worker iterations lost by two workers to a word, ResNet-18 shape, M = 8 170.2 -> 174.0 us, transformer shape, M = 16
     // 375.4 -> 376.8, 1.3 M ragged values, M = 43 148.6 -> 151.3, although the reduce alone gained)
-    const bool two = !per_worker && ur_two_workers(plan, 0, M, x_dev != nullptr);
+    const bool two = form.two;
     const dim3 grid(static_cast<unsigned>(two ? (plan->padded_elems + ur_tile<2> - 1) / ur_tile<2> : n_tiles)), block(UR_THREADS);
     const size_t tile_bytes = (two ? ur_tile<2> : ur_tile<1>) * sizeof(float);
     const size_t rows = static_cast<size_t>(two ? ur_max_local_seg<2> : ur_max_local_seg<1>) * M;
@@ -380,7 +380,7 @@ int reduce_entry_v(const dq_plan_t* plan, const dq_widths_t* widths, const uint8
                                plan->padded_elems, inv_M, out_dev, x_dev, eta);
         };
         if (x_dev)
-            ur_with_policy<true>(hint, once, [&](auto s, auto o) {
+            ur_with_policy<true>(form.stream, form.once, [&](auto s, auto o) {
                 go(k_unpack_dequant_reduce_w<true, decltype(s)::value, decltype(o)::value>);
             });
         else
@@ -396,18 +396,20 @@ int reduce_entry_v(const dq_plan_t* plan, const dq_widths_t* widths, const uint8
                            plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, plan->padded_elems, inv_M,
                            out_dev, x_dev, eta);
     };
-    if (two && !x_dev)
-        go(k_unpack_dequant_reduce_v<false, false, false, 2>);
-    else if (two && once)
-        go(k_unpack_dequant_reduce_v<true, false, true, 2>);
-    else if (two)
-        go(k_unpack_dequant_reduce_v<true, false, false, 2>);
-    else if (x_dev)
-        ur_with_policy<true>(hint, once, [&](auto s, auto o) {
-            go(k_unpack_dequant_reduce_v<true, decltype(s)::value, decltype(o)::value, 1>);
+    if (two && x_dev)
+        ur_with_policy<true>(form.stream, form.once, [&](auto s, auto o) {
+            go(k_unpack_dequant_reduce_v<true, decltype(s)::value, decltype(o)::value, 2>);
         });
-    else
+    else if (two)
+        go(k_unpack_dequant_reduce_v<false, false, false, 2>);
+    else if (!x_dev)
         go(k_unpack_dequant_reduce_v<false, false, false, 1>);
+    else if (form.stream) // (and not form.once: such calls take W = 2)
+        go(k_unpack_dequant_reduce_v<true, true, false, 1>);
+    else if (form.once)
+        go(k_unpack_dequant_reduce_v<true, false, true, 1>);
+    else
+        go(k_unpack_dequant_reduce_v<true, false, false, 1>);
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
 

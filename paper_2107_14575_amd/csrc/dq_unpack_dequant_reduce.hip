@@ -351,19 +351,20 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
 #undef DQ_LAUNCH_SPLIT
         return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
     }
-    if (ur_two_workers(plan, B, M, x != nullptr)) {
+    const ur_form form = ur_form_of(plan, B, M, x != nullptr);
+    if (form.two) {
         const dim3 grid(static_cast<unsigned>((plan->padded_elems + ur_tile<2> - 1) / ur_tile<2>)), block(UR_THREADS);
         const size_t lds = ur_tile<2> * sizeof(float) + static_cast<size_t>(ur_max_local_seg<2>) * M * sizeof(float);
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, block, lds, stream, packed, packed_stride, M, norms, plan->n_seg, plan->d_granule_cseg,
                                plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, inv_M, out, x, eta);
         };
-        if (!x)
-            go(k_unpack_dequant_reduce<B, false, false, false, 2>);
-        else if (ur_model_once(plan))
-            go(k_unpack_dequant_reduce<B, true, false, true, 2>);
+        if (x)
+            ur_with_policy<ur_may_stream(B)>(form.stream, form.once, [&](auto s, auto once) {
+                go(k_unpack_dequant_reduce<B, true, decltype(s)::value, decltype(once)::value, 2>);
+            });
         else
-            go(k_unpack_dequant_reduce<B, true, false, false, 2>);
+            go(k_unpack_dequant_reduce<B, false, false, false, 2>);
         return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
     }
     size_t lds_bytes = ur_tile<1> * sizeof(float) + static_cast<size_t>(ur_max_local_seg<1>) * M * sizeof(float);
@@ -381,12 +382,12 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
         hipLaunchKernelGGL(kernel, grid, block, lds_bytes, stream, packed, packed_stride, M, norms, plan->n_seg, plan->d_granule_cseg,
                            plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, inv_M, out, x, eta);
     };
-    if (x)
-        ur_with_policy<ur_may_stream(B)>(ur_stream(plan, M, B), ur_model_once(plan), [&](auto s, auto once) {
-            go(k_unpack_dequant_reduce<B, true, decltype(s)::value, decltype(once)::value, 1>);
-        });
-    else
+    if (!x)
         go(k_unpack_dequant_reduce<B, false, false, false, 1>);
+    else if (form.once) // (form.stream: such calls take W = 2)
+        go(k_unpack_dequant_reduce<B, true, false, true, 1>);
+    else
+        go(k_unpack_dequant_reduce<B, true, false, false, 1>);
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
 

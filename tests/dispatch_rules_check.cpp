@@ -1,0 +1,24 @@
+// Prints what the library's rules of dispatch choose (not part of libdq.so): built by tests/test_dispatch_rules.py and run on the CPU.
+// One line for every number of tiles, workers, width (0: a widths table; "rows": one with a row per worker)
+// and kind of reduce: what ur_form_of says.
+#include <cstdio>
+
+#include "dq_reduce_core.h"
+
+int main()
+{
+    const int64_t tiles[] = { 1, 100, 256, 300, 384, 385, 400, 470, 512, 513, 600, 650, 680, 720, 768, 769, 800, 1000, 1024, 1280, 1281, 1366, 1532, 2048, 2500, 3072, 3073, 3200, 4096, 6000, 8192, 16384, 32768 };
+    for (int64_t n : tiles)
+        for (int M = 1; M <= DQ_MAX_WORKERS; ++M)
+            for (int b = 0; b <= 8; ++b)
+                for (int update = 0; update < 2; ++update) {
+                    dq_plan plan{};
+                    plan.padded_elems = n * ur_tile<1>;
+                    const ur_form f = ur_form_of(&plan, b, M, update != 0);
+                    std::printf("reduce %lld %d %d %d %d %d %d\n", static_cast<long long>(n), M, b, update, f.two ? 2 : 1, f.stream, f.once);
+                    if (b != 0) continue;
+                    const ur_form r = ur_form_of(&plan, b, M, update != 0, true);
+                    std::printf("rows %lld %d %d %d %d %d %d\n", static_cast<long long>(n), M, b, update, r.two ? 2 : 1, r.stream, r.once);
+                }
+    return 0;
+}

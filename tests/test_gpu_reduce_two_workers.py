@@ -1,6 +1,6 @@
-"""The server average with a lane's 32 elements against the form in which two workers share a decoded word (a lane has 16), on layouts and
-calls where one entry point takes the one and the other the other: the same bits.  Per-worker widths, tensors alike and mixed, against the workers'
-messages decoded one by one, which the shared-width kernel does in the second form; scaled signs on both sides of their line."""
+"""The server average in its two forms -- a lane's 32 elements, or 16 with two workers to a decoded word -- on both sides of the lines between them, with
+and without update, one width and a shared table: the bits of the kernel with a row of widths per worker, which has the first form only.  Per-worker widths,
+tensors alike and mixed, against the workers' messages decoded one by one; scaled signs on both sides of their line."""
 import pytest
 import torch
 
@@ -9,35 +9,37 @@ from tests.test_gpu_parity import dq  # noqa: F401  (fixture)
 pytestmark = pytest.mark.gpu
 
 TILE = 8192
-# more than 600 tiles; ends inside a lane, a granule and a span, small tensors side by side, an empty one
-LAYOUTS = [[TILE * 601 - 5], [TILE * 300 + 77, 1, 0, 129, 4096, TILE * 302 - 1000] + [130] * 60]
+LINES = [(tiles, M) for tiles in (384, 385, 512, 513, 641, 768, 769, 1280, 1281) for M in (1, 3, 4, 5, 6, 9, 10, 13, 14, 16, 17, 32, 33, 64)]
 
 
-@pytest.mark.parametrize("layout", range(len(LAYOUTS)))
-@pytest.mark.parametrize("M,widths", [(1, range(1, 9)), (2, range(1, 9)), (3, range(1, 5)), (5, range(1, 5)), (8, [3]), (9, [3]), (11, [3])])
-def test_same_bits_with_and_without_update(dq, layout, M, widths):
-    seg_len = LAYOUTS[layout]
+# and beyond: the model passing through (from 3073 tiles on), fewer workgroups on a CU (4096 without and 8192 with update)
+@pytest.mark.parametrize("tiles,M", LINES + [(3072, 33), (3073, 1), (3073, 16), (3073, 17), (3073, 33), (4097, 14), (8192, 17)])
+def test_same_bits_as_with_a_row_of_widths_per_worker(dq, tiles, M):
+    # ends inside a lane, a granule and a span, small tensors side by side, an empty one
+    seg_len = [TILE * (tiles // 2) + 77, 1, 0, 129, 4096] + [130] * 60
+    seg_len.append(TILE * tiles - sum(-(-n // 128) * 128 for n in seg_len) - 1000)
     plan = dq.Plan(seg_len)
+    assert -(-plan.padded_elems // TILE) == tiles
     gen = torch.Generator(device="cuda")
-    gen.manual_seed(layout * 100 + M)
+    gen.manual_seed(tiles * 100 + M)
     norms = torch.rand((M, len(seg_len)), generator=gen, device="cuda") * 4 + 1e-3
     norms[M // 2, len(seg_len) // 2] = float("nan")
     norms[0, 0] = 0.0 if M > 1 else 2.0 ** -99
-    for b in widths:
+    for b in range(1, 9):
         packed = torch.randint(0, 256, (M, plan.packed_bytes(b)), dtype=torch.uint8, device="cuda", generator=gen)
-        want, got = (torch.full((plan.padded_elems,), float("nan"), device="cuda") for _ in range(2))
-        x = torch.zeros_like(want)
-        dq.unpack_dequant_reduce(plan, packed, norms, b, want)
-        dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.25, x, ghat=got)
-        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
-        assert torch.equal(x.view(torch.int32), (-0.25 * want + 0.0).view(torch.int32)), b
-        table = dq.Widths(plan, [b] * len(seg_len))
-        got.fill_(float("nan"))
-        dq.unpack_dequant_reduce_v(plan, table, packed, norms, got)
-        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
-        got.fill_(float("nan"))
-        dq.unpack_dequant_reduce_update_v(plan, table, packed, norms, 0.25, x, ghat=got)
-        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
+        want = torch.full((plan.padded_elems,), float("nan"), device="cuda")
+        table, rows = dq.Widths(plan, [b] * len(seg_len)), dq.Widths(plan, [[b] * len(seg_len)] * M, workers=M)
+        dq.unpack_dequant_reduce_v(plan, rows, packed, norms, want)
+        step = -0.25 * want + 0.0
+        for update, call in ((False, lambda out, x: dq.unpack_dequant_reduce(plan, packed, norms, b, out)),
+                             (False, lambda out, x: dq.unpack_dequant_reduce_v(plan, table, packed, norms, out)),
+                             (True, lambda out, x: dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.25, x, ghat=out)),
+                             (True, lambda out, x: dq.unpack_dequant_reduce_update_v(plan, table, packed, norms, 0.25, x, ghat=out))):
+            got, x = torch.full_like(want, float("nan")), torch.zeros_like(want)
+            call(got, x)
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
+            if update:
+                assert torch.equal(x.view(torch.int32), step.view(torch.int32)), b
     plan.close()
 
 
