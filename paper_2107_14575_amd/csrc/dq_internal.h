@@ -144,6 +144,15 @@ static inline dq_bracket_layout dq_bracket_layout_of(const dq_plan* plan, int M)
     return L;
 }
 
+// Whether the norm pass runs with fewer workgroups resident and its partial sums written through: many workgroups that stream, i.e. whose items
+// are nearly full.  Small tensors are an item each, and a workgroup with a few hundred values is latency and no stream: six workgroups per CU for
+// eight took 1.15 to 1.4 of the time there (129 000 tensors of 1 to 400 values, M = 32, max norm 2866 -> 4016 us), items of 2500 to 3000 values on average
+// 1.04 to 1.11, of 3500 0.97 to 1.04, of 3750 and more 0.91 to 1.02 (9000 to 40 000 items).
+static inline bool dq_norm_streams(int64_t workgroups, int64_t padded_elems, int64_t n_items)
+{
+    return workgroups >= DQ_MANY_WORKGROUPS && padded_elems >= n_items * (DQ_NORM_CHUNK / 8 * 7);
+}
+
 static inline bool dq_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // sum_l N_l^2 of one worker's row of norms in binary64: blocks of DQ_SUM_BLOCK tensors, each added

@@ -426,7 +426,7 @@ int norm_entry(bool linf, const dq_plan_t* plan, const float* grads_dev, int64_t
     const bool arrive = stream == nullptr && plan->d_arrived && static_cast<int64_t>(M) * plan->n_items <= DQ_ARRIVE_WORKGROUPS;
     // Six workgroups per CU where eight fit: norm, rule, quantize and reduce, ResNet-18 shape, M = 8 174.9 -> 174.1 us, transformer shape, M = 16 345.3 -> 343.4;
     // five lose 3 to 4 %, and calls of few rounds lose by six (3 M values, M = 5 33.1 -> 33.3).
-    const bool many = static_cast<int64_t>(M) * plan->n_items >= DQ_MANY_WORKGROUPS;
+    const bool many = dq_norm_streams(static_cast<int64_t>(M) * plan->n_items, plan->padded_elems, plan->n_items);
     const size_t six = dq_lds_for(6);
     if (arrive) {
         if (linf)

@@ -1,4 +1,5 @@
 // Prints what the library's rules of dispatch choose (not part of libdq.so): built by tests/test_dispatch_rules.py and run on the CPU.
+// "norm": workgroups, padded values and items of one worker's gradient, and whether the pass runs as a stream.
 // One line for every number of tiles, workers, width (0: a widths table; "rows": one with a row per worker)
 // and kind of reduce: what ur_form_of says.
 #include <cstdio>
@@ -20,5 +21,10 @@ int main()
                     const ur_form r = ur_form_of(&plan, b, M, update != 0, true);
                     std::printf("rows %lld %d %d %d %d %d %d\n", static_cast<long long>(n), M, b, update, r.two ? 2 : 1, r.stream, r.once);
                 }
+    const int64_t items[] = { 1000, 8191, 8192, 40000 };
+    for (int64_t n : items)
+        for (int64_t average : { 384, 1152, 2560, 3000, 3583, 3584, 4096 })
+            std::printf("norm %lld %lld %lld %d\n", static_cast<long long>(n), static_cast<long long>(n * average), static_cast<long long>(n),
+                        dq_norm_streams(n, n * average, n));
     return 0;
 }
