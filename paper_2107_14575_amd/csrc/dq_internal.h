@@ -66,6 +66,7 @@ struct dq_plan {
     // quantize_pack_chunk).  Against the form that does not, b = 1, 4, 6 take 1.02, 1.0, 1.04 of its time with no such
     // chunk (tensors of 3000), 0.98, 0.96, 1.03 at 13 % (4700), 0.95, 0.94, 0.99 at 32 % (6000).
     bool many_whole;
+    bool mostly_whole; // dq_mostly_whole
     dq_buckets buckets;
     void* d_tables;       // the one device allocation that holds all of the tables below
     // device tables.  Kernels address segments through a compact index c that counts only the
@@ -152,6 +153,9 @@ static inline bool dq_norm_streams(int64_t workgroups, int64_t padded_elems, int
 {
     return workgroups >= DQ_MANY_WORKGROUPS && padded_elems >= n_items * (DQ_NORM_CHUNK / 8 * 7);
 }
+
+// At least half of a layout's chunks are of one tensor: which form k_sign_pack has.
+static inline bool dq_mostly_whole(int64_t n_whole, int64_t n_chunks) { return 2 * n_whole >= n_chunks; }
 
 static inline bool dq_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

@@ -141,6 +141,7 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
         int64_t n_whole = 0;
         for (const dq_chunk_tensor& k : chunk_tensor) n_whole += k.cseg >= 0 ? 1 : 0;
         p->many_whole = 4 * n_whole >= static_cast<int64_t>(chunk_tensor.size());
+        p->mostly_whole = dq_mostly_whole(n_whole, static_cast<int64_t>(chunk_tensor.size()));
         at[0] = stage.add(chunk_tensor);
         at[1] = stage.add(granule_cseg);
         at[2] = stage.add(cseg_seg);

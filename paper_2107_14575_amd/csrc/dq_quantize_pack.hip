@@ -55,15 +55,18 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
 // What bounds it: the memory system's rate for a read stream with a thirtieth of writes in it (a kernel with these accesses and no
 // arithmetic reaches 6.3 to 6.4 TB/s at 4 GiB, without its stores 7.1).  Wavefronts that are done sooner leave more requests in
 // flight than that takes and lose some of it: a chunk of one tensor needs no table (two serial lookups behind the loads), and that alone made large
-// calls 1 % slower, until fewer workgroups were resident.  Two tiles a wavefront and six workgroups per CU (by the size of the LDS request;
+// calls 1 % slower, until fewer workgroups were resident.  WHOLE (layouts of large tensors): two tiles a wavefront and six workgroups per CU (by the size of the LDS request;
 // eight fit) against four tiles, all chunks by the table and eight, us, with the reduce: ResNet-18 shape, M = 8 73.0 -> 70.7, M = 40 306 -> 302;
 // transformer shape, M = 60 532 -> 524; 4 M values, M = 8 29.2 -> 27.3; 2^24, M = 64 725 -> 699.  Eight per CU: 72.0, 306, 532, 28.1, 706; five: 71.0,
 // 303, 534, 28.9, 718; four tiles and eight per CU 72.0, 309, 536, 28.1, -.
+// Otherwise (most chunks hold several tensors) the lookups are on every wavefront's way, and four tiles, all by the table, with eight per CU hide them:
+// 16.8 M values in tensors of 128, 300, 1000, M = 4, pack alone 12.9, 16.6, 13.7 us against 14.6, 18.9, 14.8 in the first form (13.5, 17.7, 14.4 with eight per CU).
+// The line is half of the chunks: tensors of 5000, 6000 and 8000 (18, 32 and 51 % of them) 0.97 to 1.05, 0.99 to 1.04 and 0.93 to 1.0 in the first form.
 // ---------------------------------------------------------------------------------------------
-constexpr int SP_TILES = 2;
-constexpr size_t SP_LDS_SIX_PER_CU = dq_lds_for(6) - SP_TILES * QP_THREADS; // beside what the kernel declares
+template <bool WHOLE> constexpr int SP_TILES = WHOLE ? 2 : 4;
+constexpr size_t SP_LDS_SIX_PER_CU = dq_lds_for(6) - SP_TILES<true> * QP_THREADS; // beside what the kernel declares
 
-template <bool KEEP> // as in k_quantize_pack (sign_keep_messages)
+template <bool WHOLE, bool KEEP> // KEEP: as in k_quantize_pack (sign_keep_messages)
 __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restrict__ grads, int64_t worker_stride,
                                                           const dq_chunk_tensor* __restrict__ chunk_tensor,
                                                           const int32_t* __restrict__ granule_cseg,
@@ -71,9 +74,9 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
                                                           int64_t padded_elems, uint8_t* __restrict__ packed,
                                                           int64_t packed_stride)
 {
-    constexpr int CHUNK = QP_TILE * SP_TILES;
-    static_assert(CHUNK == DQ_CHUNK, "a workgroup's elements are one entry of the chunk table");
-    __shared__ __align__(16) uint8_t lds_sign[SP_TILES * QP_THREADS];
+    constexpr int TILES = SP_TILES<WHOLE>, CHUNK = QP_TILE * TILES;
+    static_assert(!WHOLE || CHUNK == DQ_CHUNK, "a workgroup's elements are one entry of the chunk table");
+    __shared__ __align__(16) uint8_t lds_sign[TILES * QP_THREADS];
 
     const uint32_t tid = threadIdx.x;
     const uint32_t w = blockIdx.y;
@@ -82,13 +85,13 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
     const float* g = grads + static_cast<int64_t>(w) * worker_stride + chunk0;
     const int32_t* gseg = granule_cseg + (chunk0 >> 7);
 
-    float4 x[SP_TILES][2];
-    int64_t valid_end[SP_TILES];
+    float4 x[TILES][2];
+    int64_t valid_end[TILES];
     // Global loads with clamped offsets here: as buffer loads (qp_load) the eight of a lane stream 1 to 1.5 % slower (2^26
     // values, M = 16 687 -> 693 us, ResNet-18 shape, M = 35 261 -> 264), and there is no arithmetic to gain on.
 #pragma unroll
-    for (int it = 0; it < SP_TILES; ++it) {
-        const uint32_t base = (tid >> 6) * (QP_WAVE_TILE * SP_TILES) + it * QP_WAVE_TILE;
+    for (int it = 0; it < TILES; ++it) {
+        const uint32_t base = (tid >> 6) * (QP_WAVE_TILE * TILES) + it * QP_WAVE_TILE;
         uint32_t e0 = base + (tid & 31u) * 8u + ((tid >> 5) & 1u) * 4u, e1 = e0 + 256u;
         e0 = e0 < n_elems ? e0 : n_elems - 4u; // in bounds, and only lanes past the end receive it
         e1 = e1 < n_elems ? e1 : n_elems - 4u;
@@ -96,21 +99,22 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
         x[it][0] = dq_load_stream(reinterpret_cast<const float4*>(at + e0 * 4u));
         x[it][1] = dq_load_stream(reinterpret_cast<const float4*>(at + e1 * 4u));
     }
-    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * SP_TILES);
-    const dq_chunk_tensor whole = dq_load_chunk_tensor(chunk_tensor, blockIdx.x);
-    if (whole.cseg >= 0) { // 4096 elements of one tensor, the same for the whole workgroup: nothing to mask, and the codes change places
+    const uint32_t wave0 = (tid >> 6) * (QP_WAVE_TILE * TILES);
+    bool whole = false;
+    if constexpr (WHOLE) whole = dq_load_chunk_tensor(chunk_tensor, blockIdx.x).cseg >= 0;
+    if (whole) { // 4096 elements of one tensor, the same for the whole workgroup: nothing to mask, and the codes change places
 #pragma unroll
-        for (int it = 0; it < SP_TILES; ++it) {
+        for (int it = 0; it < TILES; ++it) {
             const auto w = __builtin_amdgcn_permlane32_swap(quantize_signs_below(0u, x[it][0]), quantize_signs_below(0u, x[it][1]), false, false);
             lds_sign[((wave0 + it * QP_WAVE_TILE) >> 3) + (tid & 63u)] = static_cast<uint8_t>(w[0] | (w[1] << 4));
         }
     } else {
 #pragma unroll
-        for (int it = 0; it < SP_TILES; ++it) valid_end[it] = cseg_valid_end[gseg[qp_granule<SP_TILES>(tid, it, n_elems)]];
+        for (int it = 0; it < TILES; ++it) valid_end[it] = cseg_valid_end[gseg[qp_granule<TILES>(tid, it, n_elems)]];
 #pragma unroll
-        for (int it = 0; it < SP_TILES; ++it) {
+        for (int it = 0; it < TILES; ++it) {
             dq_arrange_wave_tile(x[it][0], x[it][1]);
-            const uint32_t e = qp_elem<SP_TILES>(tid, it);
+            const uint32_t e = qp_elem<TILES>(tid, it);
             if (e < n_elems) {
                 uint32_t sign = quantize_sign_byte(x[it][0], x[it][1]);
                 const int64_t n_valid = valid_end[it] - (chunk0 + e);
@@ -123,7 +127,7 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
     if (qp_on_lines(dst, dst)) { // as in qp_store_chunk
         dq_wave_sync();
         if (wave0 < n_elems) {
-            const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * SP_TILES ? n_elems - wave0 : QP_WAVE_TILE * SP_TILES;
+            const uint32_t n_wave = n_elems - wave0 < QP_WAVE_TILE * TILES ? n_elems - wave0 : QP_WAVE_TILE * TILES;
             qp_store_wave<KEEP>(dst + (wave0 >> 3), &lds_sign[wave0 >> 3], n_wave >> 3, tid & 63u);
         }
     } else {
@@ -320,18 +324,19 @@ extern "C" int dq_sign_pack(const dq_plan_t* plan, const float* grads_dev, int64
     const int rc = dq_plan_check_device(plan);
     if (rc != DQ_OK) return rc;
     if (plan->padded_elems == 0) return DQ_OK;
-    constexpr int CHUNK = QP_TILE * SP_TILES;
-    const int64_t n_chunks = (plan->padded_elems + CHUNK - 1) / CHUNK;
-    if (n_chunks > INT32_MAX) return DQ_ERR_INVALID_ARG;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_chunks), M), dim3(QP_THREADS), SP_LDS_SIX_PER_CU,
-                           static_cast<hipStream_t>(hip_stream), grads_dev, worker_stride_elems, plan->d_chunk_tensor, plan->d_granule_cseg,
-                           plan->d_cseg_valid_end, plan->padded_elems, packed_dev, packed_worker_stride_bytes);
+    auto go = [&](auto kernel, int64_t chunk, size_t lds) {
+        const int64_t n_chunks = (plan->padded_elems + chunk - 1) / chunk;
+        if (n_chunks > INT32_MAX) return false;
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_chunks), M), dim3(QP_THREADS), lds, static_cast<hipStream_t>(hip_stream), grads_dev,
+                           worker_stride_elems, plan->d_chunk_tensor, plan->d_granule_cseg, plan->d_cseg_valid_end, plan->padded_elems, packed_dev,
+                           packed_worker_stride_bytes);
+        return true;
     };
-    if (sign_keep_messages(plan, M))
-        go(k_sign_pack<true>);
-    else
-        go(k_sign_pack<false>);
+    const bool keep = sign_keep_messages(plan, M);
+    constexpr int64_t CHUNK = QP_TILE * SP_TILES<true>, LARGE = QP_TILE * SP_TILES<false>;
+    const bool fits = plan->mostly_whole ? (keep ? go(k_sign_pack<true, true>, CHUNK, SP_LDS_SIX_PER_CU) : go(k_sign_pack<true, false>, CHUNK, SP_LDS_SIX_PER_CU))
+                                         : (keep ? go(k_sign_pack<false, true>, LARGE, 0) : go(k_sign_pack<false, false>, LARGE, 0));
+    if (!fits) return DQ_ERR_INVALID_ARG;
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
 

@@ -1,4 +1,5 @@
 // Prints what the library's rules of dispatch choose (not part of libdq.so): built by tests/test_dispatch_rules.py and run on the CPU.
+// "whole": chunks of one tensor, all chunks, and whether sign messages go chunk by chunk.
 // "norm": workgroups, padded values and items of one worker's gradient, and whether the pass runs as a stream.
 // One line for every number of tiles, workers, width (0: a widths table; "rows": one with a row per worker)
 // and kind of reduce: what ur_form_of says.
@@ -26,5 +27,7 @@ int main()
         for (int64_t average : { 384, 1152, 2560, 3000, 3583, 3584, 4096 })
             std::printf("norm %lld %lld %lld %d\n", static_cast<long long>(n), static_cast<long long>(n * average), static_cast<long long>(n),
                         dq_norm_streams(n, n * average, n));
+    for (int64_t whole : { 0, 18, 32, 49, 50, 51, 100 })
+        std::printf("whole %lld 100 %d\n", static_cast<long long>(whole), dq_mostly_whole(whole, 100));
     return 0;
 }

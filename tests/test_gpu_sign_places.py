@@ -16,7 +16,9 @@ def _signs(grads, lens, starts, padded):
 
 
 @pytest.mark.parametrize("skew", [0, 16, 112])
-@pytest.mark.parametrize("lens", [[1], [4096], [4095], [8192, 1], [5000, 0, 9000, 129], [128] * 40, [20000, 4096 * 3], [4096 * 9 - 127]])
+@pytest.mark.parametrize("lens", [[1], [4096], [4095], [8192, 1], [5000, 0, 9000, 129], [128] * 40, [20000, 4096 * 3], [4096 * 9 - 127],
+                                  # small tensors over several groups of four tiles; half of the chunks of one tensor, and one chunk less
+                                  [300] * 100, [1000] * 17 + [1], [8192, 3000, 3000], [8192, 3000, 3000, 3000]])
 def test_sign_messages(dq, lens, skew):
     M = 2
     plan = dq.Plan(lens)
