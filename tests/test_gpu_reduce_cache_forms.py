@@ -1,6 +1,7 @@
 """The reduce with update in its cache forms -- the model left in the last-level cache or passing through, the level loads with the
-streaming hint or without -- on both sides of the lines between them, with a ragged end: the average is that of the reduce without
-update bit for bit, the model is x - eta * average, and nothing past the layout's end is touched."""
+streaming hint or without -- on both sides of the lines between them, in the forms that such calls take (two workers to a decoded word; one with a
+row of widths per worker, and with 33 workers beyond 24 M elements), with a ragged end: the average is that of the reduce without update bit
+for bit, the model is x - eta * average, and nothing past the layout's end is touched."""
 import pytest
 import torch
 

@@ -1,7 +1,6 @@
-"""The server average on both sides of the lines between its three kernels (a lane's 32 elements, a lane's 8 elements
-for few tiles, workers divided over wavefronts): the same bits as the widths-table kernel, which has one form for every
-size, and that one is compared with the oracle elsewhere (test_gpu_reduce_routes).  Messages are random bytes, norms
-include unusable ones."""
+"""The server average on both sides of the lines between its kernels for few tiles (a lane's 8 elements, workers divided over wavefronts, two workers to a
+decoded word), one width and a shared table: the same bits as the kernel with a row of widths per worker, which has one form for every size (a lane's 32
+elements), and that one is compared with the oracle elsewhere (test_gpu_reduce_routes).  Messages are random bytes, norms include unusable ones."""
 import pytest
 import torch
 
@@ -19,7 +18,7 @@ LAYOUTS = [
 
 @pytest.mark.parametrize("M", [1, 4, 8, 9, 16, 24, 25, 32, 40, 41, 57, 64])
 @pytest.mark.parametrize("layout", range(len(LAYOUTS)))
-def test_same_bits_as_the_widths_table_kernel(dq, layout, M):
+def test_same_bits_as_with_a_row_of_widths_per_worker(dq, layout, M):
     seg_len = LAYOUTS[layout]
     plan = dq.Plan(seg_len)
     gen = torch.Generator(device="cuda")
@@ -31,14 +30,19 @@ def test_same_bits_as_the_widths_table_kernel(dq, layout, M):
     for b in range(1, 9):
         packed = torch.randint(0, 256, (M, plan.packed_bytes(b)), dtype=torch.uint8, device="cuda", generator=gen)
         want, got = torch.full_like(x0, float("nan")), torch.full_like(x0, float("nan"))
-        table = dq.Widths(plan, [b] * len(seg_len))
-        dq.unpack_dequant_reduce_v(plan, table, packed, norms, want)
+        table, rows = dq.Widths(plan, [b] * len(seg_len)), dq.Widths(plan, [[b] * len(seg_len)] * M, workers=M)
+        dq.unpack_dequant_reduce_v(plan, rows, packed, norms, want)
         dq.unpack_dequant_reduce(plan, packed, norms, b, got)
         assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
-        x, y, ghat = x0.clone(), x0.clone(), torch.full_like(x0, float("nan"))
-        dq.unpack_dequant_reduce_update_v(plan, table, packed, norms, 0.25, x)
+        got.fill_(float("nan"))
+        dq.unpack_dequant_reduce_v(plan, table, packed, norms, got)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
+        x, y, z, ghat = x0.clone(), x0.clone(), x0.clone(), torch.full_like(x0, float("nan"))
+        dq.unpack_dequant_reduce_update_v(plan, rows, packed, norms, 0.25, x)
         dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.25, y, ghat=ghat)
+        dq.unpack_dequant_reduce_update_v(plan, table, packed, norms, 0.25, z)
         assert torch.equal(y.view(torch.int32), x.view(torch.int32)), b
+        assert torch.equal(z.view(torch.int32), x.view(torch.int32)), b
         assert torch.equal(ghat.view(torch.int32), want.view(torch.int32)), b
     plan.close()
 
@@ -56,12 +60,15 @@ def test_same_bits_on_both_sides_of_the_farthest_lines(dq, seg_len, M):
     for b in range(1, 9):
         packed = torch.randint(0, 256, (M, plan.packed_bytes(b)), dtype=torch.uint8, device="cuda", generator=gen)
         want, got = torch.full_like(x0, float("nan")), torch.full_like(x0, float("nan"))
-        table = dq.Widths(plan, [b] * len(seg_len))
-        dq.unpack_dequant_reduce_v(plan, table, packed, norms, want)
+        table, rows = dq.Widths(plan, [b] * len(seg_len)), dq.Widths(plan, [[b] * len(seg_len)] * M, workers=M)
+        dq.unpack_dequant_reduce_v(plan, rows, packed, norms, want)
         dq.unpack_dequant_reduce(plan, packed, norms, b, got)
         assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
+        got.fill_(float("nan"))
+        dq.unpack_dequant_reduce_v(plan, table, packed, norms, got)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
         x, y = x0.clone(), x0.clone()
-        dq.unpack_dequant_reduce_update_v(plan, table, packed, norms, 0.25, x)
+        dq.unpack_dequant_reduce_update_v(plan, rows, packed, norms, 0.25, x)
         dq.unpack_dequant_reduce_update(plan, packed, norms, b, 0.25, y)
         assert torch.equal(y.view(torch.int32), x.view(torch.int32)), b
     plan.close()
@@ -71,7 +78,7 @@ def test_same_bits_on_both_sides_of_the_farthest_lines(dq, seg_len, M):
 @pytest.mark.parametrize("seg_len", [[200, 0, 7, 129, 511], [4096 + 640], [TILE * 64 - 900, 640], [TILE * 100, 5, TILE * 28 - 128]])
 def test_sum_beyond_the_largest_value_with_a_finite_average(dq, seg_len, M):
     """Every worker at the top level with one sign and a norm near the largest binary32 value: the sum over the workers
-    passes it, the average does not.  The same bits as the widths-table kernel, and N to the sum's rounding: at most
+    passes it, the average does not.  The same bits as with a row of widths per worker, and N to the sum's rounding: at most
     7 + ceil(M / 8) roundings of the sum, and three more (N / s, s products, 1 / M), of 2^-24 each."""
     plan = dq.Plan(seg_len)
     N = 3.0e38
@@ -81,9 +88,12 @@ def test_sum_beyond_the_largest_value_with_a_finite_average(dq, seg_len, M):
         packed = torch.full((M, plan.packed_bytes(b)), 255, dtype=torch.uint8, device="cuda")
         packed[:, :plan.padded_elems // 8] = 0  # the signs
         want, got = (torch.full((plan.padded_elems,), float("nan"), device="cuda") for _ in range(2))
-        table = dq.Widths(plan, [b] * len(seg_len))
-        dq.unpack_dequant_reduce_v(plan, table, packed, norms, want)
+        table, rows = dq.Widths(plan, [b] * len(seg_len)), dq.Widths(plan, [[b] * len(seg_len)] * M, workers=M)
+        dq.unpack_dequant_reduce_v(plan, rows, packed, norms, want)
         dq.unpack_dequant_reduce(plan, packed, norms, b, got)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
+        got.fill_(float("nan"))
+        dq.unpack_dequant_reduce_v(plan, table, packed, norms, got)
         assert torch.equal(got.view(torch.int32), want.view(torch.int32)), b
         data = got[got != 0].double()
         assert data.numel() == sum(seg_len) and torch.all((data / N - 1).abs() <= bound), b

@@ -140,7 +140,7 @@ def test_workers_of_mixed_widths(dq, oracle, M):
 @pytest.mark.parametrize("b", [1, 2, 3, 4])
 @pytest.mark.parametrize("M", [15, 16, 17, 31, 64])
 def test_groups_of_workers(dq, oracle, b, M):
-    """Widths 1 to 4 take up to sixteen workers' loads at once: full groups, and what is left of the next one,
+    """Several workers' loads go out at once (eight here, by the forms for few tiles): full groups, and what is left of the next one,
     on workgroups all of whose wavefronts hold data and on ones whose last wavefronts hold none."""
     for seg_len in ([8192 + 2048 + 1], [300, 2048, 129, 8192 * 2]):
         rng = np.random.default_rng(1000 * b + M)
