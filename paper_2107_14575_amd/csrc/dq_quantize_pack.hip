@@ -143,16 +143,18 @@ __global__ __launch_bounds__(QP_THREADS) void k_sign_pack(const float* __restric
 // 0.925; transformer shape, M = 24 with update b = 7 0.966), still 0.97 to 0.98 at 400 to 670 MB for b <= 4; beyond that most of them
 // are gone from the 256 MB before they are read and the stores cost 1 to 5 % (2^28, M = 16 b = 4 6400 -> 6490 us).  Plain stores, which
 // leave the lines dirty in the XCDs' caches, were 1 to 2 % slower than this at the sizes where they gain, and lose at others.
-// With b = 5 to 7, whose level loads carry no hint without update, and with M > 32 they gain up to 190 MB; 200 to 400 MB gain 3 to 4 % with
-// update and lose 1 to 4 % without (34 M, M = 13 b = 6 753 -> 772, 30 M, M = 9 b = 5 454 -> 465).
+// With b = 5 to 7, whose level loads carry no hint without update, the line lies at 320 MB: iterations of one tensor or many large ones, M = 1 to 32, time against the
+// hint without and with update at 195 to 260 MB 0.88 to 0.98 and 0.92 to 0.99, at 290 to 310 0.95 to 0.99 and 0.94 to 0.99, at 350 to 400 0.99 to 1.04 and 0.95 to
+// 0.97 (transformer shape, M = 16 b = 7, 192 MB: 333 -> 307 and 331 -> 327 us; 34 M, M = 13 b = 6, 369 MB: 708 -> 726 and 727 -> 700).  Layouts of small tensors, whose
+// workgroups store together, lose 0 to 3 % beyond 190 MB, and so more than 32 workers' messages at b >= 5 did when the lines were drawn.
 // Narrow calls of 4 to 13 MB gain or lose up to 2 %.
 inline bool qp_keep_messages(const dq_plan* plan, int M, int b)
 {
-    const int64_t megabytes = b <= 4 ? 640 : b == 8 && M <= 32 ? 400 : 190;
+    const int64_t megabytes = b <= 4 ? 640 : M > 32 ? 190 : b == 8 ? 400 : plan->many_whole ? 320 : 190;
     return M * dq_packed_bytes(plan, b) <= megabytes << 20;
 }
 // Widths that may be known to the GPU only: six bits stand for the usual.
-inline bool qp_keep_messages_v(const dq_plan* plan, int M) { return qp_keep_messages(plan, M, 6); }
+inline bool qp_keep_messages_v(const dq_plan* plan, int M) { return M * dq_packed_bytes(plan, 6) <= 190 << 20; }
 
 // The same for sign messages, which are small: whatever their number, from 12 M elements or 14 MB on.  Pack and majority, us, with the hint / through: 2^25
 // values, M = 8 201 / 193, 2^26 401 / 385, M = 16 758 / 723, 2^28 - 333, M = 4 923 / 891; transformer and ResNet-18 shapes, M = 16 to 60 the same.

@@ -1,5 +1,5 @@
 """Messages written through to the last-level cache and messages with the streaming hint, on both sides of the lines between the two
-(190, 400 and 640 MB of messages, by width and number of workers): the oracle's bytes.  Lengths that leave the planes on and off the
+(190 to 640 MB of messages, by width, number of workers and layout): the oracle's bytes.  Lengths that leave the planes on and off the
 cache lines, plans of large tensors and of small ones."""
 import numpy as np
 import pytest
@@ -40,14 +40,15 @@ def test_moderate_messages(dq, oracle, layout, b):
     plan.close()
 
 
-# (width, 0 for a widths table; workers; MB of messages up to which they are written through, a table's at six bits)
-LINES = [(1, 64, 640), (2, 64, 640), (4, 64, 640), (5, 64, 190), (6, 32, 190), (7, 64, 190), (8, 33, 190), (8, 32, 400), (0, 64, 190)]
+# (width, 0 for a widths table; workers; MB of messages up to which they are written through, a table's at six bits; the same for small tensors)
+LINES = [(1, 64, 640, 640), (2, 64, 640, 640), (4, 64, 640, 640), (5, 32, 320, 190), (5, 64, 190, 190), (6, 32, 320, 190), (7, 32, 320, 190), (7, 64, 190, 190),
+         (8, 33, 190, 190), (8, 32, 400, 400), (0, 32, 190, 190), (0, 64, 190, 190)]
 
 
 def _layout(line, small, beyond):
     """A layout whose messages are just up to the line, or one granule beyond it: one large tensor or many of 1000 elements, both
     with a ragged end."""
-    b, M, megabytes = line
+    b, M, megabytes = line[0], line[1], line[2 + small]
     granules = (megabytes << 20) // (16 * ((b or 6) + 1) * M) + beyond
     seg_len = [1000] * (granules // 8 - 1) if small else []
     return seg_len + [(granules - 8 * len(seg_len)) * 128 - 51]
@@ -58,7 +59,7 @@ def _layout(line, small, beyond):
 @pytest.mark.parametrize("line", LINES)
 def test_messages_on_both_sides_of_the_lines(dq, oracle, line, small, beyond):
     """All workers at once against eight at a time (always written through), and the last worker's against the oracle."""
-    b, workers, megabytes = line
+    b, workers, megabytes = line[0], line[1], line[2 + small]
     seg_len = _layout(line, small, beyond)
     plan = dq.Plan(seg_len)
     assert (workers * plan.packed_bytes(b or 6) > megabytes << 20) == bool(beyond)
