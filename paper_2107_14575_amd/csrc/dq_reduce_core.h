@@ -677,11 +677,13 @@ __device__ __forceinline__ const float* wave_table(const wave_span& span, int la
 // messages are still in the cache, it costs (ResNet-18 shape, M = 8 28.8 -> 30.1).  Without update it gains 3 to 7 % of iterations with 200
 // to 400 MB of messages and loses up to 9 % where they come from memory.  With more than 32 workers and W = 1 (three workgroups per CU, the
 // vector ALU as much as the loads) it loses there too: 4.2 M ragged elements, M = 64 b = 5 56 -> 62, transformer shape, M = 62 b = 5 113 -> 128; with W = 2
-// it gains: 11 to 20 M, M = 47 and 64 b = 5 to 7 1.0 -> 0.88 of the time with W = 1.
-constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20;
+// it gains: 11 to 20 M, M = 47 and 64 b = 5 to 7 1.0 -> 0.88 of the time with W = 1.  There the line lies at 100 MB: iterations in which neither model nor messages
+// are in the cache at the start take 1.0 to 1.04 of the time without the hint at 100 to 128 MB and 0.97 to 1.0 below, those in which both are from the last iteration
+// 0.96 to 0.99 at 60 to 128 MB and 0.99 to 1.04 below.
+constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20, UR_STREAM_FROM = 100 << 20;
 inline bool ur_stream(const dq_plan* plan, int M, int b, bool two)
 {
-    return ur_may_stream(b) && (two || M <= 32) && M * dq_packed_bytes(plan, b) + plan->padded_elems * 4 > UR_LAST_LEVEL_CACHE / 2;
+    return ur_may_stream(b) && (two || M <= 32) && M * dq_packed_bytes(plan, b) + plan->padded_elems * 4 > (two ? UR_STREAM_FROM : UR_LAST_LEVEL_CACHE / 2);
 }
 // Whether the model passes through with the hint: a large one would not be in the cache when it is next read, and takes the
 // messages' place.  Iterations with b = 2 and 8, us, model left in the cache / passing through: 2^24, M = 2 73 / 77, M = 8 (b = 8) 233 / 230;

@@ -396,10 +396,12 @@ int reduce_entry_v(const dq_plan_t* plan, const dq_widths_t* widths, const uint8
                            plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, plan->padded_elems, inv_M,
                            out_dev, x_dev, eta);
     };
-    if (two && x_dev)
-        ur_with_policy<true>(form.stream, form.once, [&](auto s, auto o) {
-            go(k_unpack_dequant_reduce_v<true, decltype(s)::value, decltype(o)::value, 2>);
-        });
+    if (two && form.once) // (a model of that size is most of what form.stream asks for: it is set)
+        go(k_unpack_dequant_reduce_v<true, true, true, 2>);
+    else if (two && form.stream)
+        go(k_unpack_dequant_reduce_v<true, true, false, 2>);
+    else if (two && x_dev)
+        go(k_unpack_dequant_reduce_v<true, false, false, 2>);
     else if (two)
         go(k_unpack_dequant_reduce_v<false, false, false, 2>);
     else if (!x_dev)

@@ -359,12 +359,14 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
             hipLaunchKernelGGL(kernel, grid, block, lds, stream, packed, packed_stride, M, norms, plan->n_seg, plan->d_granule_cseg,
                                plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, inv_M, out, x, eta);
         };
-        if (x)
-            ur_with_policy<ur_may_stream(B)>(form.stream, form.once, [&](auto s, auto once) {
-                go(k_unpack_dequant_reduce<B, true, decltype(s)::value, decltype(once)::value, 2>);
-            });
-        else
+        if (!x)
             go(k_unpack_dequant_reduce<B, false, false, false, 2>);
+        else if (form.once) // (a model of that size is most of what form.stream asks for: it is set at the widths that look)
+            go(k_unpack_dequant_reduce<B, true, ur_may_stream(B), true, 2>);
+        else if (form.stream)
+            go(k_unpack_dequant_reduce<B, true, ur_may_stream(B), false, 2>);
+        else
+            go(k_unpack_dequant_reduce<B, true, false, false, 2>);
         return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
     }
     size_t lds_bytes = ur_tile<1> * sizeof(float) + static_cast<size_t>(ur_max_local_seg<1>) * M * sizeof(float);

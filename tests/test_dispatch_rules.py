@@ -55,10 +55,10 @@ def test_reduces_take_the_form_that_was_measured_to_be_faster(form):
 
 
 def test_level_loads_are_streamed_with_update_only(form):
-    """Widths 5 to 7 (and tables): the hint only where messages and model together exceed half of the last-level cache, with W = 1 up to 32 workers."""
+    """Widths 5 to 7 (and tables): the hint only where messages and model together exceed 100 MB or, with W = 1 and up to 32 workers, 128 MB."""
     for (tiles, workers, width, update), (two, streamed, once) in form.items():
         size = tiles * 8192 * (workers * ((width or 6) + 1) / 8 + 4)
-        assert bool(streamed) == (bool(update) and (width or 6) in (5, 6, 7) and (two == 2 or workers <= 32) and size > 128 << 20)
+        assert bool(streamed) == (bool(update) and (width or 6) in (5, 6, 7) and (two == 2 or workers <= 32) and size > (100 if two == 2 else 128) << 20)
         assert bool(once) == (bool(update) and tiles * 8192 > 24 << 20)
 
 

@@ -38,7 +38,7 @@ def _check_update(plan, want, gen, update):
 
 
 @pytest.mark.parametrize("elems,M,b", [(ONCE, 2, 2), (ONCE + 77, 2, 2), (ONCE + 77, 1, 8), (ONCE + 3 * 4096 + 129, 2, 5), (ONCE, 2, 6),
-                                       (5_200_077, 32, 6), (2_600_077, 32, 7), (5_200_077, 33, 5)])
+                                       (11_000_077, 5, 6), (11_000_077, 8, 6), (5_200_077, 32, 6), (2_600_077, 32, 7), (5_200_077, 33, 5)])
 @pytest.mark.parametrize("table", [False, True])
 def test_update_as_average_and_step(dq, elems, M, b, table):
     plan = dq.Plan([elems])
