@@ -711,9 +711,11 @@ inline void ur_with_policy(bool stream, bool once, F&& f)
 // two at W = 2.  Measured with 6 to 32 768 tiles, M = 1 to 64, all widths, messages in no cache (time with W = 2 / with W = 1):
 //   up to 384 tiles 0.76 to 1.04, all together 0.94;
 //   up to 1280 (five to a CU; tables with update 768) what counts is whether the fullest CU has less to do with half tiles, 2 n / 256 rounded up against n / 256: where it
-//   does (an odd number of 128 tiles) b >= 5 from four workers on and b <= 4 and tables from ten on 0.83 to 1.0; where it does not 0.96 to 1.16 (512 tiles, M = 16 b = 4
+//   does (an odd number of 128 tiles) b >= 5 from four workers on (from six where one round of W = 1, 1024 tiles, takes all and one of W = 2, 768, does not: M = 4 and 5 1.03
+//   to 1.1 there) and b <= 4 and tables from ten on 0.83 to 1.0; where it does not 0.96 to 1.16 (512 tiles, M = 16 b = 4
 //   1.16), b = 5 to 7 with update from six workers on 0.85 to 0.99.  With fewer workers the wavefronts' start and the decoding, twice for an odd one, decide: 0.98 to 1.36;
-//   beyond, without update b = 2 and b >= 4 for six to thirteen workers 0.93 to 1.0, the others 0.98 to 1.24 (b = 3, M = 1 1.24, M = 16 1.03; b = 4, M = 16 1.04);
+//   beyond, without update b = 2 and b >= 4 for six to thirteen workers 0.93 to 1.0, b = 4 to 7 for sixteen 0.95 to 1.0 where the planes are on cache lines and 0.98 to
+//   1.04 where they are not, the others 0.98 to 1.24 (b = 3: M = 1 1.24, M = 16 1.03; b = 8, M = 16 0.99 to 1.03);
 //   with update 0.85 to 1.0 for six to sixteen workers, with a table to 32, at b = 5 to 7 for one to 32; with more, whose messages are read in pieces of half the size,
 //   1.0 to 1.08, but b = 5 to 7 and tables 0.87 to 0.96 while the model stays in the cache; with fewer, or b = 1, 0.96 to 1.12 there and 0.93 to 0.99 where it passes through.
 // Whole iterations say the same, less sharply (b = 3, 2^26 to 2^28 values, M = 1 to 4, no update: 1.04 to 1.12 with W = 2).
@@ -721,8 +723,12 @@ inline bool ur_two_workers(int64_t n_tiles, int b, int M, bool update, bool once
 {
     const bool halves = b >= 5 && b <= 7;
     if (n_tiles <= 384) return true;
-    if (n_tiles <= (update && b == 0 ? 768 : 1280)) return (n_tiles + 127) / 128 % 2 != 0 ? M >= (b >= 5 ? 4 : 10) : halves && update && M >= 6;
-    if (!update) return M >= 6 && M <= 13 && (b == 2 || b >= 4);
+    if (n_tiles <= (update && b == 0 ? 768 : 1280)) {
+        const bool less = (n_tiles + 127) / 128 % 2 != 0; // for the fullest CU with half tiles
+        if (!less) return halves && update && M >= 6;
+        return M >= (b < 5 ? 10 : n_tiles > 768 && n_tiles <= 1024 ? 6 : 4);
+    }
+    if (!update) return M >= 6 && M <= (b >= 4 && b != 8 ? 16 : 13) && (b == 2 || b >= 4);
     if (!once && !halves && (M < 6 || b == 1)) return false;
     return M <= (!halves && b != 0 ? 16 : once ? 32 : 64);
 }

@@ -44,8 +44,8 @@ def form(rules):
 # tiles, workers, width (0: a table), update: calls in which the other form took 1.03 to 1.3 of the time
 ONE_WORKER = [(800, 8, 1, 0), (600, 4, 3, 1), (600, 2, 4, 1), (800, 2, 1, 1), (512, 16, 4, 0), (680, 16, 2, 1), (1000, 10, 1, 0), (1366, 4, 1, 1),
               (800, 1, 6, 1), (8192, 1, 3, 0), (32768, 16, 3, 0), (32768, 16, 8, 0), (6000, 3, 7, 0), (4096, 32, 4, 0), (6000, 64, 2, 0), (8192, 64, 5, 1), (6000, 32, 1, 1),
-              (8192, 24, 1, 1), (600, 4, 0, 1), (800, 2, 0, 0), (470, 4, 0, 1), (680, 13, 0, 0), (680, 13, 0, 1), (720, 24, 7, 0), (650, 4, 7, 1), (6000, 64, 0, 1), (6000, 2, 0, 0)]
-TWO_WORKERS = [(513, 64, 5, 1), (1366, 8, 6, 1), (1532, 16, 8, 1), (300, 20, 2, 1), (384, 20, 5, 0), (3072, 47, 7, 1), (1000, 24, 0, 1), (6000, 8, 4, 1), (16384, 4, 5, 1),
+              (8192, 24, 1, 1), (600, 4, 0, 1), (800, 2, 0, 0), (470, 4, 0, 1), (680, 13, 0, 0), (680, 13, 0, 1), (720, 24, 7, 0), (650, 4, 7, 1), (800, 5, 7, 1), (800, 4, 6, 0), (6000, 64, 0, 1), (6000, 2, 0, 0)]
+TWO_WORKERS = [(513, 64, 5, 1), (1366, 8, 6, 1), (1532, 16, 8, 1), (300, 20, 2, 1), (384, 20, 5, 0), (32768, 16, 4, 0), (8192, 16, 7, 0), (3072, 47, 7, 1), (1000, 24, 0, 1), (6000, 8, 4, 1), (16384, 4, 5, 1),
                (800, 47, 0, 1), (1532, 16, 0, 1), (4096, 8, 0, 1), (300, 47, 0, 1)]
 
 
