@@ -680,10 +680,15 @@ __device__ __forceinline__ const float* wave_table(const wave_span& span, int la
 // it gains: 11 to 20 M, M = 47 and 64 b = 5 to 7 1.0 -> 0.88 of the time with W = 1.  There the line lies at 100 MB: iterations in which neither model nor messages
 // are in the cache at the start take 1.0 to 1.04 of the time without the hint at 100 to 128 MB and 0.97 to 1.0 below, those in which both are from the last iteration
 // 0.96 to 0.99 at 60 to 128 MB and 0.99 to 1.04 below.
-constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20, UR_STREAM_FROM = 100 << 20;
-inline bool ur_stream(const dq_plan* plan, int M, int b, bool two)
+// Without update and with W = 2 it is for messages of more than 640 MB, of which next to nothing is in the cache: 2^28 values, M = 16 b = 5, 6, 7 0.71, 0.82, 0.90 ->
+// 0.69, 0.80, 0.88 ms; iterations are the same with and without it from 400 MB on, and up to 260 MB they lose 1 to 10 % by it.
+constexpr int64_t UR_LAST_LEVEL_CACHE = 256 << 20, UR_STREAM_FROM = 100 << 20, UR_STREAM_MESSAGES_FROM = 640 << 20;
+inline bool ur_stream(const dq_plan* plan, int M, int b, bool two, bool update)
 {
-    return ur_may_stream(b) && (two || M <= 32) && M * dq_packed_bytes(plan, b) + plan->padded_elems * 4 > (two ? UR_STREAM_FROM : UR_LAST_LEVEL_CACHE / 2);
+    if (!ur_may_stream(b)) return false;
+    const int64_t messages = M * dq_packed_bytes(plan, b);
+    if (!update) return two && messages > UR_STREAM_MESSAGES_FROM;
+    return (two || M <= 32) && messages + plan->padded_elems * 4 > (two ? UR_STREAM_FROM : UR_LAST_LEVEL_CACHE / 2);
 }
 // Whether the model passes through with the hint: a large one would not be in the cache when it is next read, and takes the
 // messages' place.  Iterations with b = 2 and 8, us, model left in the cache / passing through: 2^24, M = 2 73 / 77, M = 8 (b = 8) 233 / 230;
@@ -715,8 +720,8 @@ inline void ur_with_policy(bool stream, bool once, F&& f)
 //   to 1.1 there) and b <= 4 and tables from ten on 0.83 to 1.0; where it does not 0.96 to 1.16 (512 tiles, M = 16 b = 4
 //   1.16), b = 5 to 7 with update from six workers on 0.85 to 0.99.  With fewer workers the wavefronts' start and the decoding, twice for an odd one, decide: 0.98 to 1.36;
 //   beyond, without update b = 2 and b >= 4 for six to thirteen workers 0.93 to 1.0, b = 4 to 7 for sixteen 0.95 to 1.0 where the planes are on cache lines and 0.98 to
-//   1.04 where they are not, the others 0.98 to 1.24 (b = 3: M = 1 1.24, M = 16 1.03; b = 8, M = 16 0.99 to 1.03);
-//   with update 0.85 to 1.0 for six to sixteen workers, with a table to 32, at b = 5 to 7 for one to 32; with more, whose messages are read in pieces of half the size,
+//   1.04 where they are not (tables with b = 2, 4, 6, 8 1.0 to 1.05, 0.96 to 1.02, 0.95 to 0.99, 0.97 to 1.0), the others 0.98 to 1.24 (b = 3: M = 1 1.24, M = 16 1.03; b = 8, M = 16 0.99 to 1.03);
+//   with update 0.85 to 1.0 for six to sixteen workers (b = 8 from three on), with a table for three to 32, at b = 5 to 7 for one to 32; with more, whose messages are read in pieces of half the size,
 //   1.0 to 1.08, but b = 5 to 7 and tables 0.87 to 0.96 while the model stays in the cache; with fewer, or b = 1, 0.96 to 1.12 there and 0.93 to 0.99 where it passes through.
 // Whole iterations say the same, less sharply (b = 3, 2^26 to 2^28 values, M = 1 to 4, no update: 1.04 to 1.12 with W = 2).
 inline bool ur_two_workers(int64_t n_tiles, int b, int M, bool update, bool once)
@@ -728,15 +733,15 @@ inline bool ur_two_workers(int64_t n_tiles, int b, int M, bool update, bool once
         if (!less) return halves && update && M >= 6;
         return M >= (b < 5 ? 10 : n_tiles > 768 && n_tiles <= 1024 ? 6 : 4);
     }
-    if (!update) return M >= 6 && M <= (b >= 4 && b != 8 ? 16 : 13) && (b == 2 || b >= 4);
-    if (!once && !halves && (M < 6 || b == 1)) return false;
+    if (!update) return M >= 6 && M <= (b == 2 || b == 8 ? 13 : 16) && b != 1 && b != 3;
+    if (!once && !halves && (M < (b == 0 || b == 8 ? 3 : 6) || b == 1)) return false;
     return M <= (!halves && b != 0 ? 16 : once ? 32 : 64);
 }
 
 // The form that a call takes.  b as above.
 struct ur_form {
     bool two;    // W = 2
-    bool stream; // with update: the hint on the level loads of widths 5 to 7
+    bool stream; // the hint on the level loads of widths 5 to 7
     bool once;   // with update: the hint on the model
 };
 // rows: a widths table with a row per worker (W = 1 only)
@@ -746,7 +751,7 @@ inline ur_form ur_form_of(const dq_plan* plan, int b, int M, bool update, bool r
     ur_form f;
     f.once = update && ur_model_once(plan);
     f.two = !rows && ur_two_workers(n_tiles, b, M, update, f.once);
-    f.stream = update && ur_stream(plan, M, b ? b : 6, f.two); // six bits stand for widths that the GPU may have set
+    f.stream = ur_stream(plan, M, b ? b : 6, f.two, update); // six bits stand for widths that the GPU may have set
     return f;
 }
 

@@ -396,22 +396,27 @@ int reduce_entry_v(const dq_plan_t* plan, const dq_widths_t* widths, const uint8
                            plan->n_seg, plan->d_granule_cseg, plan->d_cseg_seg, plan->d_cseg_valid_end, widths->d_table, plan->padded_elems, inv_M,
                            out_dev, x_dev, eta);
     };
-    if (two && form.once) // (a model of that size is most of what form.stream asks for: it is set)
-        go(k_unpack_dequant_reduce_v<true, true, true, 2>);
-    else if (two && form.stream)
-        go(k_unpack_dequant_reduce_v<true, true, false, 2>);
-    else if (two && x_dev)
-        go(k_unpack_dequant_reduce_v<true, false, false, 2>);
-    else if (two)
-        go(k_unpack_dequant_reduce_v<false, false, false, 2>);
-    else if (!x_dev)
-        go(k_unpack_dequant_reduce_v<false, false, false, 1>);
-    else if (form.stream) // (and not form.once: such calls take W = 2)
+    if (!x_dev) {
+        if (two && form.stream)
+            go(k_unpack_dequant_reduce_v<false, true, false, 2>);
+        else if (two)
+            go(k_unpack_dequant_reduce_v<false, false, false, 2>);
+        else
+            go(k_unpack_dequant_reduce_v<false, false, false, 1>);
+    } else if (two) {
+        if (form.once) // (a model of that size is most of what form.stream asks for: it is set)
+            go(k_unpack_dequant_reduce_v<true, true, true, 2>);
+        else if (form.stream)
+            go(k_unpack_dequant_reduce_v<true, true, false, 2>);
+        else
+            go(k_unpack_dequant_reduce_v<true, false, false, 2>);
+    } else if (form.stream) { // (and not form.once: such calls take W = 2)
         go(k_unpack_dequant_reduce_v<true, true, false, 1>);
-    else if (form.once)
+    } else if (form.once) {
         go(k_unpack_dequant_reduce_v<true, false, true, 1>);
-    else
+    } else {
         go(k_unpack_dequant_reduce_v<true, false, false, 1>);
+    }
     return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
 }
 

@@ -2,10 +2,9 @@
 //     out_P = (1/M) sum_i sgn_{i,P} * level_{i,P} * (N_{i,l} / s),
 // with every worker's message read exactly once.
 //
-// Work split.  One workgroup (256 lanes) owns 4096 consecutive padded elements; a lane owns 16 of
-// them, and the words that it decodes hold one worker's fields in one half and the next one's in the other
-// (W = 2, see ur_two_workers: most calls).  Or it owns 8192, a lane 32 of them, so that per worker it reads one sign dword and
-// B level dwords -- every load is dword aligned for every B -- and keeps 32 binary32 accumulators (W = 1).
+// Work split.  One workgroup (256 lanes) owns 8192 consecutive padded elements; a lane owns 32 of them, so that per worker it reads one sign dword
+// and B level dwords -- every load is dword aligned for every B -- and keeps 32 binary32 accumulators (W = 1).  Or it owns 4096, a lane 16 of
+// them, and the words that it decodes hold one worker's fields in one half and the next one's in the other (W = 2).  ur_two_workers says which calls take it.
 //
 // Arithmetic per (worker, element).  B <= 4: the level fields are spread one per byte word-wise
 // (byte permutes and a shift/mask per four elements), the four sign bits of the word's elements go
@@ -359,7 +358,9 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
             hipLaunchKernelGGL(kernel, grid, block, lds, stream, packed, packed_stride, M, norms, plan->n_seg, plan->d_granule_cseg,
                                plan->d_cseg_seg, plan->d_cseg_valid_end, plan->padded_elems, inv_M, out, x, eta);
         };
-        if (!x)
+        if (!x && form.stream)
+            go(k_unpack_dequant_reduce<B, false, ur_may_stream(B), false, 2>);
+        else if (!x)
             go(k_unpack_dequant_reduce<B, false, false, false, 2>);
         else if (form.once) // (a model of that size is most of what form.stream asks for: it is set at the widths that look)
             go(k_unpack_dequant_reduce<B, true, ur_may_stream(B), true, 2>);
@@ -370,7 +371,7 @@ int launch(const dq_plan* plan, const uint8_t* packed, int64_t packed_stride, in
         return hipGetLastError() == hipSuccess ? DQ_OK : DQ_ERR_HIP;
     }
     size_t lds_bytes = ur_tile<1> * sizeof(float) + static_cast<size_t>(ur_max_local_seg<1>) * M * sizeof(float);
-    // Where thousands of tiles stream wide messages, three workgroups per CU move more than four.  Measured for
+    // Where thousands of tiles stream wide messages, three workgroups per CU move more than four (W = 1; six to thirteen or sixteen workers without update take W = 2).  Measured for
     // M = 1..32, 2048..16384 tiles, b = 4..8, inputs in no cache and inputs read before, as a factor on the time:
     // M = 16 b = 4..8 0.98, 0.98, 0.97, 0.98, 0.99 at 4096 tiles and 0.95, 0.94, 0.95, 0.97, 0.99 at 16384; M = 8 0.98..1.0 at
     // 4096, 0.97..0.99 at 8192; M = 32 0.96..0.99 at 8192.  Below 4096 tiles or eight workers four are as good or better (M = 16

@@ -45,7 +45,7 @@ def form(rules):
 ONE_WORKER = [(800, 8, 1, 0), (600, 4, 3, 1), (600, 2, 4, 1), (800, 2, 1, 1), (512, 16, 4, 0), (680, 16, 2, 1), (1000, 10, 1, 0), (1366, 4, 1, 1),
               (800, 1, 6, 1), (8192, 1, 3, 0), (32768, 16, 3, 0), (32768, 16, 8, 0), (6000, 3, 7, 0), (4096, 32, 4, 0), (6000, 64, 2, 0), (8192, 64, 5, 1), (6000, 32, 1, 1),
               (8192, 24, 1, 1), (600, 4, 0, 1), (800, 2, 0, 0), (470, 4, 0, 1), (680, 13, 0, 0), (680, 13, 0, 1), (720, 24, 7, 0), (650, 4, 7, 1), (800, 5, 7, 1), (800, 4, 6, 0), (6000, 64, 0, 1), (6000, 2, 0, 0)]
-TWO_WORKERS = [(513, 64, 5, 1), (1366, 8, 6, 1), (1532, 16, 8, 1), (300, 20, 2, 1), (384, 20, 5, 0), (32768, 16, 4, 0), (8192, 16, 7, 0), (3072, 47, 7, 1), (1000, 24, 0, 1), (6000, 8, 4, 1), (16384, 4, 5, 1),
+TWO_WORKERS = [(513, 64, 5, 1), (1366, 8, 6, 1), (1532, 16, 8, 1), (300, 20, 2, 1), (384, 20, 5, 0), (32768, 16, 4, 0), (8192, 16, 7, 0), (32768, 16, 0, 0), (3072, 47, 7, 1), (1000, 24, 0, 1), (6000, 8, 4, 1), (16384, 4, 5, 1),
                (800, 47, 0, 1), (1532, 16, 0, 1), (4096, 8, 0, 1), (300, 47, 0, 1)]
 
 
@@ -54,11 +54,16 @@ def test_reduces_take_the_form_that_was_measured_to_be_faster(form):
     assert {c for c in TWO_WORKERS if form[c][0] != 2} == set()
 
 
-def test_level_loads_are_streamed_with_update_only(form):
-    """Widths 5 to 7 (and tables): the hint only where messages and model together exceed 100 MB or, with W = 1 and up to 32 workers, 128 MB."""
+def test_where_level_loads_are_streamed(form):
+    """Widths 5 to 7 (and tables): with update the hint where messages and model together exceed 100 MB or, with W = 1 and up to 32 workers, 128 MB; without,
+    with W = 2 only, where messages alone exceed 640 MB."""
     for (tiles, workers, width, update), (two, streamed, once) in form.items():
-        size = tiles * 8192 * (workers * ((width or 6) + 1) / 8 + 4)
-        assert bool(streamed) == (bool(update) and (width or 6) in (5, 6, 7) and (two == 2 or workers <= 32) and size > (100 if two == 2 else 128) << 20)
+        messages = tiles * 1024 * workers * ((width or 6) + 1)
+        if update:
+            want = (two == 2 or workers <= 32) and messages + tiles * 32768 > (100 if two == 2 else 128) << 20
+        else:
+            want = two == 2 and messages > 640 << 20
+        assert bool(streamed) == ((width or 6) in (5, 6, 7) and want)
         assert bool(once) == (bool(update) and tiles * 8192 > 24 << 20)
 
 

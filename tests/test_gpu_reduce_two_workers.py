@@ -12,8 +12,9 @@ TILE = 8192
 LINES = [(tiles, M) for tiles in (384, 385, 512, 513, 641, 768, 769, 1024, 1025, 1280, 1281) for M in (1, 3, 4, 5, 6, 9, 10, 13, 14, 16, 17, 32, 33, 64)]
 
 
-# and beyond: the model passing through (from 3073 tiles on), fewer workgroups on a CU (4096 without and 8192 with update)
-@pytest.mark.parametrize("tiles,M", LINES + [(3072, 33), (3073, 1), (3073, 16), (3073, 17), (3073, 33), (4097, 14), (4097, 17), (8192, 17)])
+# and beyond: the model passing through (from 3073 tiles on), fewer workgroups on a CU (4096 without and 8192 with update), messages
+# of more than 640 MB
+@pytest.mark.parametrize("tiles,M", LINES + [(3072, 33), (3073, 1), (3073, 16), (3073, 17), (3073, 33), (4097, 14), (4097, 17), (8192, 16), (8192, 17)])
 def test_same_bits_as_with_a_row_of_widths_per_worker(dq, tiles, M):
     # ends inside a lane, a granule and a span, small tensors side by side, an empty one
     seg_len = [TILE * (tiles // 2) + 77, 1, 0, 129, 4096] + [130] * 60
