@@ -233,8 +233,8 @@ __device__ __forceinline__ void dq_chunk_tensor_totals(int g, int n_granules, co
 }
 
 // sqrt(x) for a sum of squares of binary32 values: zero, or between 2^-298 and 2^296 (2^40 values), or infinite or NaN.  Goldschmidt's iteration
-// from the hardware's estimate and two corrections by the residual, which gives the correctly rounded root; the library function's scaling of
-// small and large arguments is left out.
+// from the hardware's estimate and two corrections by the residual (P. Markstein, "Software Division and Square Root Using Goldschmidt's
+// Algorithms", Real Numbers and Computers 2004), which gives the correctly rounded root.  No argument of that range needs to be scaled.
 __device__ __forceinline__ double dq_root_of_squares(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);

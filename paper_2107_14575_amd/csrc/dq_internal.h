@@ -39,8 +39,8 @@ __device__ __forceinline__ dq_chunk_tensor dq_load_chunk_tensor(const dq_chunk_t
 // 50 ns each: 200 workgroups 16.5 -> 15.4, 400 16.8 -> 19.8, 1024 16.5 -> 36.
 constexpr int DQ_ARRIVE_WORKGROUPS = 160;
 
-// A gradient cut into buckets of 128 << log values, log <= 3: the first `chunks` chunks hold nothing but whole buckets, so that granule g
-// belongs to tensor g >> log and no table has to say so.  chunks = 0: another kind of plan.
+// A gradient cut into buckets of 128 << log values, log <= 3, with a last tensor of any length: the first `chunks` chunks hold nothing but whole buckets, so
+// that granule g belongs to tensor g >> log and no table has to say so.  chunks = 0: another kind of plan.
 struct dq_buckets {
     uint32_t chunks;
     int32_t log;

@@ -72,7 +72,7 @@ extern "C" int dq_plan_create(const int64_t* seg_len_host, int32_t n_seg, dq_pla
         return DQ_ERR_INVALID_ARG;
     }
     p->n_items = static_cast<int32_t>(n_items);
-    for (int32_t log = 0; log <= 3; ++log) { // all of one length but a shorter last one?
+    for (int32_t log = 0; log <= 3; ++log) { // all of one length, whatever the last one's?
         const int64_t len = static_cast<int64_t>(DQ_GRANULE) << log;
         int32_t full = 0;
         while (full < n_seg && seg_len_host[full] == len) ++full;

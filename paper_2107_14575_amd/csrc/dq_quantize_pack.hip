@@ -56,9 +56,9 @@ __global__ __launch_bounds__(QP_THREADS) void k_quantize_pack_v(
 // arithmetic reaches 6.3 to 6.4 TB/s at 4 GiB, without its stores 7.1).  Wavefronts that are done sooner leave more requests in
 // flight than that takes and lose some of it: a chunk of one tensor needs no table (two serial lookups behind the loads), and that alone made large
 // calls 1 % slower, until fewer workgroups were resident.  WHOLE (layouts of large tensors): two tiles a wavefront and six workgroups per CU (by the size of the LDS request;
-// eight fit) against four tiles, all chunks by the table and eight, us, with the reduce: ResNet-18 shape, M = 8 73.0 -> 70.7, M = 40 306 -> 302;
-// transformer shape, M = 60 532 -> 524; 4 M values, M = 8 29.2 -> 27.3; 2^24, M = 64 725 -> 699.  Eight per CU: 72.0, 306, 532, 28.1, 706; five: 71.0,
-// 303, 534, 28.9, 718; four tiles and eight per CU 72.0, 309, 536, 28.1, -.
+// eight fit) against four tiles, all chunks by the table and eight, us, with the reduce: ResNet-18 shape, M = 8 72.9 -> 72.0, M = 40 306 -> 302;
+// transformer shape, M = 60 532 -> 524; 4 M values, M = 8 29.2 -> 27.3; 2^24, M = 64 725 -> 699.  Eight per CU: M = 40 306, 532, 28.1, 706; five
+// 303, 534, 28.9, 718; four tiles and eight per CU 309, 536, 28.1, -.
 // Otherwise (most chunks hold several tensors) the lookups are on every wavefront's way, and four tiles, all by the table, with eight per CU hide them:
 // 16.8 M values in tensors of 128, 300, 1000, M = 4, pack alone 12.9, 16.6, 13.7 us against 14.6, 18.9, 14.8 in the first form (13.5, 17.7, 14.4 with eight per CU).
 // The line is half of the chunks: tensors of 5000, 6000 and 8000 (18, 32 and 51 % of them) 0.97 to 1.05, 0.99 to 1.04 and 0.93 to 1.0 in the first form.

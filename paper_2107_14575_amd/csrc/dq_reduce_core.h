@@ -677,8 +677,8 @@ __device__ __forceinline__ const float* wave_table(const wave_span& span, int la
 // messages are still in the cache, it costs (ResNet-18 shape, M = 8 28.8 -> 30.1).  Without update it gains 3 to 7 % of iterations with 200
 // to 400 MB of messages and loses up to 9 % where they come from memory.  With more than 32 workers and W = 1 (three workgroups per CU, the
 // vector ALU as much as the loads) it loses there too: 4.2 M ragged elements, M = 64 b = 5 56 -> 62, transformer shape, M = 62 b = 5 113 -> 128; with W = 2
-// it gains: 11 to 20 M, M = 47 and 64 b = 5 to 7 1.0 -> 0.88 of the time with W = 1.  There the line lies at 100 MB: iterations in which neither model nor messages
-// are in the cache at the start take 1.0 to 1.04 of the time without the hint at 100 to 128 MB and 0.97 to 1.0 below, those in which both are from the last iteration
+// it gains: 11 to 20 M, M = 47 and 64 b = 5 to 7 1.0 -> 0.88 of the time with W = 1.  There the line lies at 100 MB: without the hint iterations in which neither model nor messages
+// are in the cache at the start take 1.0 to 1.04 of the time at 100 to 128 MB and 0.97 to 1.0 below, those in which both are from the last iteration
 // 0.96 to 0.99 at 60 to 128 MB and 0.99 to 1.04 below.
 // Without update and with W = 2 it is for messages of more than 640 MB, of which next to nothing is in the cache: 2^28 values, M = 16 b = 5, 6, 7 0.71, 0.82, 0.90 ->
 // 0.69, 0.80, 0.88 ms; iterations are the same with and without it from 400 MB on, and up to 260 MB they lose 1 to 10 % by it.
